@@ -41,7 +41,6 @@ constexpr int kMfmaRelBits = 25;      // the same for the matrix-core filter (tw
 constexpr uint32_t kMfmaRelMask = (1u << kMfmaRelBits) - 1;
 constexpr int64_t kMfmaMaxSliceLen = (int64_t)1 << kMfmaRelBits;
 constexpr int64_t kMfmaMinQueries = 9;  // fewer queries than this take the narrower xor/popcount tiles
-constexpr int kMfmaTableBytes = 256 * 8;  // the bits-to-elements table of the matrix-core filter
 constexpr int kSpinLimit = 1 << 22;   // bounded wait on a list lock (each turn sleeps)
 constexpr int kManySlices = 4;        // slices per query from which the lists exchange more than their k-th best
 
@@ -631,7 +630,7 @@ __device__ __forceinline__ void drain(const Lds<M, TQ> &s, const ScanArgs &a, co
         // entry = (b << kRelBits) | position of the lane's first code; b = c * TQ + (TQ - 1 - q)
         const uint32_t e = ring[lane];
         if constexpr (MFMA_BITS) {
-            const uint32_t idx = ~e >> kRelBits;  // 31 - (bit number): 4 * (16-code group) + row
+            const uint32_t idx = e >> kRelBits;  // bit number: 4 * (16-code group) + row
             q = (int)(4u * ((e >> kMfmaRelBits) & 3u) + (idx & 3u));
             rel = (e & kMfmaRelMask) + 16u * (idx >> 2);
         } else {
@@ -1150,33 +1149,42 @@ scan_kernel(ScanArgs a)
 
 // ---------------------------------------------------------------------------------------------
 // The fused scan with the Hamming test of Section 3.3 ("dual" in Section 4.2) on the matrix cores (64-bit codes, tiles
-// of 16 queries, flat and graph mode).  With every bit b written as the byte +1 (b = 0) or -1
-// (b = 1), the dot product of two codes is 64 - 2 * (Hamming distance), so
-//     distance <= ht   <=>   (2 * ht - 64) + dot >= 0,
-// and v_mfma_i32_16x16x64_i8 takes that sum for 16 queries x 16 codes at once when the constant
-// goes in as the accumulator: the sign bit of each of the 256 results is the verdict "farther
-// than ht".  Per pair that leaves 1/64 of a vector instruction to move the sign into the lane's
-// survivor mask, plus the code's share of turning bits into bytes, against five instructions
-// of xor / popcount; queue, ADC and lists are those of scan_kernel.
+// of 16 queries, flat and graph mode).  With the code's bits c_i in {0, 1}, the query's bits turned
+// into s_i = +1 (bit 0) or -1 (bit 1) and p the number of ones of the query,
+//     distance = p + sum_i s_i c_i,   so   f = (ht + 64 - p) - sum_i s_i c_i = ht + 64 - distance
+// lies in 0 .. 127 (ht <= 63) and its bit 6 says "within ht": a contraction whose small-integer
+// operands 4-bit floating point (E2M1) holds exactly, v_mfma_scale_f32_16x16x128_f8f6f4.
 //
-// Operand layout (wave64, lane l, col = l % 16, grp = l / 16): the A operand is row `col`
-// (query slot col), K positions of group grp; the B operand is column `col` (a code), K
-// positions of group grp; lane l receives results (row 4 * grp + r, column col), r = 0..3.
-// Both operands give group grp bits 16 * grp .. 16 * grp + 15 of their code, expanded through
-// a 256-entry table in LDS (byte -> 8 bytes of +-1): which K positions a group holds does not
-// matter as long as both sides agree.
+// Bits to operands costs one vector instruction per 8 bits and no table: E2M1 reads the nibbles
+// 0001, 0010, 0100 as 0.5, 1, 2, so `word & 0x11111111`, `& 0x22222222`, `& 0x44444444` (and the
+// word shifted right by one `& 0x44444444` for the top bit of each nibble) are operands already; the
+// query side carries 2, 1, 0.5 (0.5) in the same places, every product is 0 or +-1.
 //
-// A wave reads 64 codes with one 8-byte load per lane (lane l: code l of the block) and then
-// needs, for the four products of the block, the 16-bit part `grp` of codes col, 16 + col,
-// 32 + col, 48 + col: a 4 x 4 transpose of 16-bit parts between the four rows of 16 lanes,
-// done with one v_permlane32_swap, two v_perm and one v_permlane16_swap.
+// Two pairs to a result: the instruction's K = 128 positions hold the 64 bits of two codes (lanes
+// 0 .. 31 the halves of one, lanes 32 .. 63 of the other), and the per-lane block scales weigh
+// their sums 2^(s+1) and 2^(s+9), s = 0 .. 7.  With 2^23 added (through the accumulator, like the
+// constants) the result is a float32 in [2^23, 2^24) whose mantissa is the two fields side by side,
+// exact, bits 7 + s and 15 + s being the two verdicts.  s differs between the four result registers of
+// a product and between the two products of a pair, so one `(result & mask) | near` per register
+// puts sixteen verdicts into bits 7 .. 22 of one word: half a vector instruction per pair and lane.
 //
-// Survivor masks: bit 31 - (4 * t + r) of a lane's mask <=> (code 16 * t + col of the 128-code
-// block, query slot 4 * grp + r), t = 0..7.  Queue entries carry the bit number, grp and the
-// position of the block's code `col` (kMfmaRelBits bits).
+// Operand layout (wave64, lane l, col = l % 16, grp = l / 16): A = query slot col, B = a code of
+// column col, K positions 32 grp .. 32 grp + 31; the lane receives (query slots 4 grp + r, column
+// col), r = 0 .. 3.  A wave reads 64 codes with one 8-byte load per lane (lane l: code l); one
+// v_permlane16_swap of the two words leaves in one register the halves of the codes of lanes 0 .. 15
+// and 32 .. 47, in the other those of lanes 16 .. 31 and 48 .. 63, each half in its row of lanes.
+//
+// Survivor masks: bit 4 * t + r of a lane's mask <=> (code 16 * t + col of the 128-code block,
+// query slot 4 * grp + r), t = 0..7.  Queue entries carry the bit number, grp and the position of
+// the block's code `col` (kMfmaRelBits bits).
+//
+// What bounds it: vector instruction issue, about 45 per 2048 pairs for the test (22 to make
+// operands, the rest to collect verdicts) beside 4 products of 16 cycles.  Against bytes of +-1 from
+// a table in LDS and one int8 product per 16 codes (16 look-ups, 80 vector instructions), 1M x 1M
+// at ht = 20: 134.8 -> 106.3 ms; 10M x 10k at ht = 24, k = 100: 28.2 -> 24.6 ms on one box.
 // ---------------------------------------------------------------------------------------------
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+typedef float mfma_f32x4 __attribute__((ext_vector_type(4)));
 
 // (One 16-wave workgroup per compute unit = 4 waves per SIMD: telling the compiler so lets it
 //  spend registers on keeping the eight products of a block in flight together.)
@@ -1188,9 +1196,7 @@ scan_mfma_kernel(ScanArgs a)
     constexpr int M = 8, TQ = 16;
     constexpr int kBlock = 128;  // codes per wave and turn
     extern __shared__ __align__(16) unsigned char smem[];
-    // [256] byte -> eight bytes of +-1, at LDS address 0 so that a look-up address is just byte * 8
-    PSC_LDS u32x2 *xtab = (PSC_LDS u32x2 *)smem;
-    const Lds<M, TQ> s((PSC_LDS unsigned char *)smem + kMfmaTableBytes, a.kpad, NW);
+    const Lds<M, TQ> s((PSC_LDS unsigned char *)smem, a.kpad, NW);
     const int tid = (int)threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1216,9 +1222,9 @@ scan_mfma_kernel(ScanArgs a)
         slice_begin = ft.slice_begin;
         slice_end = ft.slice_end;
     }
-    // the look-ups below take the table to start at LDS address 0, the queue entries a position
-    // in kMfmaRelBits bits: flag the run instead of returning something wrong
-    if ((uint32_t)(uintptr_t)xtab != 0u || slice_end - slice_begin > kMfmaMaxSliceLen) {
+    // the queue entries take a position in kMfmaRelBits bits: flag the run instead of returning
+    // something wrong
+    if (slice_end - slice_begin > kMfmaMaxSliceLen) {
         if (tid == 0) atomicExch(a.status, 1);
         return;
     }
@@ -1234,12 +1240,6 @@ scan_mfma_kernel(ScanArgs a)
         s.lock[tid] = 0;
         s.gidx[tid] = gi;
         s.pslot[tid] = (IVF ? (gi >= 0 ? a.job_slot[q0 + tid] : 0) : slice) % a.pub_slots;
-    }
-    for (int v = tid; v < 256; v += NW * 64) {
-        uint32_t w[2] = {0u, 0u};
-#pragma unroll
-        for (int i = 0; i < 8; ++i) w[i >> 2] |= (((v >> i) & 1) ? 0xffu : 0x01u) << (8 * (i & 3));
-        xtab[v] = u32x2{w[0], w[1]};
     }
     if constexpr (IVF) {
         stage_list_tables<M, TQ, NW>(s, a, tile_list, q0, nvq);
@@ -1258,24 +1258,33 @@ scan_mfma_kernel(ScanArgs a)
         __syncthreads();
     }
 
-    // A operand: part grp of query slot col (slots past nvq: any code, their results are masked)
-    i32x4 qa;
-    {
-        uint32_t q16;
-        if constexpr (IVF)
-            q16 = ((const PSC_LDS uint16_t *)s.qcw)[(col < nvq ? col : 0) * 4 + grp];
-        else
-            q16 = ((const uint16_t *)a.qcodes)[(q0 + (col < nvq ? col : 0)) * 4 + grp];
-        const u32x2 lo = xtab[q16 & 0xffu], hi = xtab[q16 >> 8];
-        qa = i32x4{(int)lo.x, (int)lo.y, (int)hi.x, (int)hi.y};
-    }
+    // A operand: word grp % 2 of query slot col, its bits as signs (minus for a 0) on the magnitudes
+    // 2, 1, 0.5, 0.5; slots past nvq are all zero.
+    auto query_word = [&](int slot, int w) {
+        if constexpr (IVF) return (uint32_t)s.qcw[slot * 2 + w];
+        else return ((const uint32_t *)a.qcodes)[(q0 + slot) * 2 + w];
+    };
     const int ht = (int)(0x7fffffffu - a.bias);
-    const int c0 = 2 * ht - 64;
-    const i32x4 cinit = {c0, c0, c0, c0};
-    uint32_t valid_q = 0u;  // the lane's rows that are real queries, for all eight groups of codes
+    i32x8 qa = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (col < nvq) {
+        const uint32_t w = ~query_word(col, grp & 1);
+        qa[0] = (int)(((w & 0x11111111u) << 3) | 0x44444444u);
+        qa[1] = (int)((((w >> 1) & 0x11111111u) << 3) | 0x22222222u);
+        qa[2] = (int)((((w >> 2) & 0x11111111u) << 3) | 0x11111111u);
+        qa[3] = (int)((((w >> 3) & 0x11111111u) << 3) | 0x11111111u);
+    }
+    // block scales (biased exponents): the row's place s = row % 4 (+ 4 for the second product of a
+    // pair, on the other operand), eight bits higher for the second code
+    const int scale_q = 127 + 1 + (col & 3) + (grp >= 2 ? 8 : 0);
+    mfma_f32x4 cinit[2];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-        if (4 * grp + r < nvq) valid_q |= 0x11111111u << (3 - r);
+    for (int r = 0; r < 4; ++r) {
+        const int slot = 4 * grp + r;
+        float f = 0.f;  // (an empty slot's fields stay 0: never within ht)
+        if (slot < nvq) f = (float)(ht + 64 - __popc(query_word(slot, 0)) - __popc(query_word(slot, 1)));
+#pragma unroll
+        for (int t = 0; t < 2; ++t) cinit[t][r] = 8388608.f + f * (float)((1 << (r + 4 * t + 1)) + (1 << (r + 4 * t + 9)));
+    }
 
     lds_u32 *ring = s.queue + wave * kQueueCap;
     const uint32_t ring_base = (uint32_t)(uintptr_t)ring;
@@ -1324,53 +1333,36 @@ scan_mfma_kernel(ScanArgs a)
         }
     };
     auto filter_block = [&](auto whole, int64_t blk, const uint2 (&c)[2]) {
-        // In three phases kept apart for the scheduler (left alone it runs the eight products one
-        // after the other, each waiting for its table entries and then for its own result):
-        // all sixteen look-ups, the eight products, the thirty-two sign bits.
-        i32x4 cb[8];
+        mfma_f32x4 acc[4];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            // rows 0,1 get the low words of all four rows' codes, rows 2,3 the high words ...
-            const auto r32 = __builtin_amdgcn_permlane32_swap(c[h].x, c[h].y, false, false);
-            // ... sorted by 16-bit part ...
-            uint32_t pa = __builtin_amdgcn_perm(r32[1], r32[0], 0x05040100u);
-            uint32_t pb = __builtin_amdgcn_perm(r32[1], r32[0], 0x07060302u);
-            // ... and odd rows trade their even parts for the even rows' odd parts: row grp now
-            // holds part grp of the codes of rows 0 (pa low), 1 (pb low), 2 (pa high), 3 (pb high)
-            const auto r16 = __builtin_amdgcn_permlane16_swap(pa, pb, false, false);
-            pa = r16[0];
-            pb = r16[1];
+            const auto w = __builtin_amdgcn_permlane16_swap(c[h].x, c[h].y, false, false);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const uint32_t src = (t & 1) ? pb : pa;
-                const uint32_t c16 = (t & 2) ? (src >> 16) : (src & 0xffffu);
-                // (the table starts at LDS address 0: a look-up address is the byte times 8, which
-                //  the compiler then takes straight out of the word with a byte-select shift)
-                const u32x2 lo = *(PSC_LDS u32x2 *)(uintptr_t)((c16 & 0xffu) << 3);
-                const u32x2 hi = *(PSC_LDS u32x2 *)(uintptr_t)((c16 >> 8) << 3);
-                cb[4 * h + t] = i32x4{(int)lo.x, (int)lo.y, (int)hi.x, (int)hi.y};
+            for (int t = 0; t < 2; ++t) {
+                const i32x8 cb = {(int)(w[t] & 0x11111111u), (int)(w[t] & 0x22222222u), (int)(w[t] & 0x44444444u),
+                                  (int)((w[t] >> 1) & 0x44444444u), 0, 0, 0, 0};
+                acc[2 * h + t] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(qa, cb, cinit[t], 4, 4, 0, scale_q, 0,
+                                                                                  t ? 131 : 127);
             }
         }
-        __builtin_amdgcn_sched_barrier(0);
-        i32x4 acc[8];
+        uint32_t near[2] = {0u, 0u};
 #pragma unroll
-        for (int t = 0; t < 8; ++t) acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(qa, cb[t], cinit, 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        uint32_t far = 0u;
+        for (int h = 0; h < 2; ++h) {
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
+            for (int t = 0; t < 2; ++t) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) far = __builtin_amdgcn_alignbit(far, (uint32_t)acc[t][r], 31);
+                for (int r = 0; r < 4; ++r) near[h] |= __float_as_uint(acc[2 * h + t][r]) & (0x8080u << (r + 4 * t));
+            }
         }
-        uint32_t valid = valid_q;
+        uint32_t sv = (near[0] >> 7) | (near[1] << 9);
         if constexpr (!decltype(whole)::value) {  // ragged block: codes past the end do not count
             uint32_t in = 0u;
 #pragma unroll
             for (int t = 0; t < 8; ++t)
-                if (blk + 16 * t + col < slice_end) in |= 0xf0000000u >> (4 * t);
-            valid &= in;
+                if (blk + 16 * t + col < slice_end) in |= 0xfu << (4 * t);
+            sv &= in;
         }
-        queue_block(~far & valid, (uint32_t)(blk - slice_begin) + lane_bits);
+        queue_block(sv, (uint32_t)(blk - slice_begin) + lane_bits);
     };
     uint2 cur[2];
     int64_t blk = slice_begin + (int64_t)wave * kBlock;
@@ -2185,7 +2177,7 @@ int plan_scan(int m, int64_t nq, int64_t n, int k, int kind, ScanPlan *plan)
         const int t = options[o].tq, nw = options[o].nwaves;
         if (t > tq_cap) continue;
         const size_t need = (size_t)t * m * 256 * 4 + (size_t)t * p.kpad * 8 + (size_t)t * 16 + (size_t)t * m * 5 +
-                            (size_t)nw * (kQueueCap + 64) * 4 + (kind == kScanFusedMfma ? kMfmaTableBytes : 0);
+                            (size_t)nw * (kQueueCap + 64) * 4;
         if (need <= options[o].max_lds) {
             p.tq = t;
             p.nwaves = nw;
