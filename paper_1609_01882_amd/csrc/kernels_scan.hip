@@ -9,12 +9,13 @@
 //     lane) and compares each code with all TQ query codes: xor + popcount-accumulate per
 //     32-bit word, then one funnel shift that appends the "too far" bit to a 32-bit per-lane
 //     mask (one bit per (code, query)): 5 integer instructions per (query, 64-bit code) pair;
-//   * lanes that hold survivors append one (bit number, code position) entry per turn to a
-//     per-wave queue in LDS, positions assigned with ballot + prefix popcount, so that the
-//     expensive step runs on full wavefronts;
-//   * whenever the queue holds 64 entries the wave scores the newest 64: re-reads the codes,
-//     gathers m table entries each from LDS, sums them in float32 (j ascending) and compares
-//     with the query's current bound on its k-th best distance;
+//   * lanes that hold survivors append their mask and its position to a per-wave queue in LDS,
+//     places assigned with ballot + prefix popcount, so that the expensive step runs on full
+//     wavefronts;
+//   * whenever the queue holds 64 masks the wave scores one survivor of each of the newest 64:
+//     re-reads the codes, gathers m table entries each from LDS, sums them in float32 (j ascending)
+//     and compares with the query's current bound on its k-th best distance; masks with survivors
+//     left are appended again;
 //   * the few candidates that pass are spliced into the query's sorted list in LDS by the whole
 //     wave, under a per-query lock (waves of the workgroup share the lists); workgroups of one
 //     query tell each other how far their lists have come through a few words in global memory
@@ -33,11 +34,11 @@
 namespace psc {
 namespace {
 
-constexpr int kQueueCap = 128;        // ring entries per wave (power of two, >= 2*64)
-constexpr int kRelBits = 27;          // bits of a ring entry holding the position inside the slice
-constexpr uint32_t kRelMask = (1u << kRelBits) - 1;
-constexpr int64_t kMaxSliceLen = (int64_t)1 << kRelBits;
-constexpr int kMfmaRelBits = 25;      // the same for the matrix-core filter (two more bits name the lane's row group)
+constexpr int kQueueCap = 95;         // queue entries per wave (8 bytes each, and one to spare; see score_survivors)
+constexpr int kMfmaQueueCap = 111;    // the same for the matrix-core filter, whose blocks bring more of them
+constexpr int64_t kMaxSliceLen = (int64_t)1 << 27;
+constexpr int kMfmaRelBits = 25;      // bits of a queue entry of the matrix-core filter that hold the position inside
+                                      // the slice (two more name the lane's row group)
 constexpr uint32_t kMfmaRelMask = (1u << kMfmaRelBits) - 1;
 constexpr int64_t kMfmaMaxSliceLen = (int64_t)1 << kMfmaRelBits;
 constexpr int64_t kMfmaMinQueries = 9;  // fewer queries than this take the narrower xor/popcount tiles
@@ -173,6 +174,7 @@ typedef PSC_LDS volatile int lds_vi32;
 typedef PSC_LDS int lds_i32;
 
 typedef PSC_LDS volatile uint64_t lds_vu64;
+typedef PSC_LDS uint64_t lds_u64;
 
 // One list entry = (sortable distance key, id) packed in 64 bits, key in the high word, so that
 // the unsigned 64-bit order is the (distance, id) order.  The key is the usual order-preserving
@@ -205,9 +207,8 @@ struct Lds {
     lds_i32 *pslot;  // [TQ] word of the query's shared thresholds the slot's list publishes to
     lds_f32 *sterm;  // [TQ][M] inverted file: the per-job, per-sub-quantizer constant of the tables
     lds_u32 *qcw;    // [TQ][M/4] inverted file: the jobs' query codes
-    lds_u32 *queue;  // [nwaves][kQueueCap]; private to a wave: LDS keeps a wave's accesses in order
-    lds_u32 *dump;   // [nwaves][64] where lanes with nothing to queue write
-    __device__ __forceinline__ Lds(PSC_LDS unsigned char *base, int kpad, int nwaves)
+    lds_u64 *queue;  // [nwaves][entries]; private to a wave: LDS keeps a wave's accesses in order
+    __device__ __forceinline__ Lds(PSC_LDS unsigned char *base, int kpad)
     {
         lut = (lds_f32 *)base;
         top = (lds_vu64 *)(lut + TQ * M * 256);
@@ -217,8 +218,7 @@ struct Lds {
         pslot = gidx + TQ;
         sterm = (lds_f32 *)(pslot + TQ);
         qcw = (lds_u32 *)(sterm + TQ * M);
-        queue = qcw + TQ * M / 4;
-        dump = queue + nwaves * kQueueCap;
+        queue = (lds_u64 *)(qcw + TQ * M / 4);
     }
 };
 
@@ -582,83 +582,70 @@ struct SharedAsk {
     bool wanted = true;  // wave-uniform: the previous batch changed a list (or there was none yet)
 };
 
-// The queueing loop of the fused kernels, hand-scheduled (see the comment where it is used).
-// Operands: sv (survivor bits of the lane, consumed), fill (entries waiting, scalar), base (byte
-// address of queue slot `fill`, scalar), rel0 (low bits of the lane's entries), dump (address a
-// lane without a bit writes to); t0, t1 vector and n scalar temporaries.
-#define PSC_QUEUE_TURNS                                    \
-    "1:\n\t"                                               \
-    "v_cmp_ne_u32_e32 vcc, 0, %[sv]\n\t"                   \
-    "s_cbranch_vccz 2f\n\t"                                \
-    "v_mbcnt_lo_u32_b32 %[t0], vcc_lo, 0\n\t"              \
-    "v_mbcnt_hi_u32_b32 %[t0], vcc_hi, %[t0]\n\t"          \
-    "v_ffbl_b32_e32 %[t1], %[sv]\n\t"                      \
-    "v_lshl_add_u32 %[t0], %[t0], 2, %[base]\n\t"          \
-    "v_lshl_or_b32 %[t1], %[t1], 27, %[rel0]\n\t"          \
-    "v_cndmask_b32_e32 %[t0], %[dump], %[t0], vcc\n\t"     \
-    "ds_write_b32 %[t0], %[t1]\n\t"                        \
-    "s_bcnt1_i32_b64 %[n], vcc\n\t"                        \
-    "v_add_u32_e32 %[t0], -1, %[sv]\n\t"                   \
-    "s_lshl2_add_u32 %[base], %[n], %[base]\n\t"           \
-    "v_and_b32_e32 %[sv], %[sv], %[t0]\n\t"                \
-    "s_add_i32 %[fill], %[fill], %[n]\n\t"                 \
-    "s_cmp_lt_i32 %[fill], 64\n\t"                         \
-    "s_cbranch_scc1 1b\n\t"                                \
-    "2:"
-
-// Score `nvalid` (<= 64) entries of the wave's queue, starting at `ring`, and feed the ones that
-// beat the current threshold to the lists.  `slice_codes` = the codes of the tile's slice
-// (position 0 of the entries); `self0 + q` = the position query slot q must not return (graph
-// mode; a value no position can take otherwise).
-// MFMA_BITS: the entries come from the matrix-core filter (see scan_mfma_kernel for their layout).
-template <int M, int TQ, bool IVF, bool SHARE, bool MFMA_BITS = false>
-__device__ __forceinline__ void drain(const Lds<M, TQ> &s, const ScanArgs &a, const lds_u32 *ring, int nvalid,
-                                      const uint8_t *slice_codes, int64_t slice_begin, uint32_t self0,
-                                      SharedAsk &ask)
-{
-    const int lane = lane_id();
-    const bool act = lane < nvalid;
-    float d = __builtin_inff();
-    float thr = -__builtin_inff();
-    uint32_t rel = 0;
-    int q = 0;
-    uint32_t shared = kKeyInf;
-    if constexpr (SHARE) {
-        if (ask.wanted) shared = ask_shared_thresholds<M, TQ>(s, a);
+// A batch of survivors, one per lane, whose codes have been asked for: scored when the next batch is
+// taken, so that the trip to memory overlaps what the wave does in between.
+template <int M>
+struct Batch {
+    uint32_t w[M / 4];  // the code
+    uint32_t rel = 0;   // its position
+    int q = 0;          // query slot
+    int n = 0;          // lanes 0 .. n-1 have one (the same in every lane)
+    __device__ __forceinline__ Batch()
+    {
+#pragma unroll
+        for (int i = 0; i < M / 4; ++i) w[i] = 0u;
     }
-    if (act) {
-        // entry = (b << kRelBits) | position of the lane's first code; b = c * TQ + (TQ - 1 - q)
-        const uint32_t e = ring[lane];
-        if constexpr (MFMA_BITS) {
-            const uint32_t idx = e >> kRelBits;  // bit number: 4 * (16-code group) + row
-            q = (int)(4u * ((e >> kMfmaRelBits) & 3u) + (idx & 3u));
-            rel = (e & kMfmaRelMask) + 16u * (idx >> 2);
-        } else {
-            const uint32_t b = e >> kRelBits;
-            q = (int)((TQ - 1) - (b & (TQ - 1)));
-            rel = (e & kRelMask) + b / TQ;
-        }
-        const uint32_t *cw = (const uint32_t *)(slice_codes + (uint64_t)rel * M);
-        uint32_t w[M / 4];
-        if constexpr (M == 8) {
-            const uint2 v = *(const uint2 *)cw;
-            w[0] = v.x;
-            w[1] = v.y;
-        } else {
-            const uint4 v = *(const uint4 *)cw;
-            w[0] = v.x;
-            w[1] = v.y;
-            w[2] = v.z;
-            w[3] = v.w;
-        }
-        if constexpr (SHARE) {
-            if (ask.wanted) adopt_shared_thresholds<M, TQ>(s, shared);
-        }
+};
+
+// Take one survivor in each of the lanes 0 .. n-1: bit b of a mask that belongs to `rel0`.
+// `slice_codes` = the codes of the tile's slice (position 0).
+// MFMA_BITS: the mask comes from the matrix-core filter (see scan_mfma_kernel for its layout).
+template <int M, int TQ, bool MFMA_BITS>
+__device__ __forceinline__ void take_batch(Batch<M> &p, const int n, const uint32_t b, const uint32_t rel0,
+                                           const uint8_t *slice_codes)
+{
+    p.n = n;
+    if constexpr (MFMA_BITS) {  // b = 4 * (16-code group) + row; rel0 = position | row group << kMfmaRelBits
+        p.q = (int)(4u * ((rel0 >> kMfmaRelBits) & 3u) + (b & 3u));
+        p.rel = (rel0 & kMfmaRelMask) + 16u * (b >> 2);
+    } else {  // b = c * TQ + (TQ - 1 - q); rel0 = position of the lane's first code
+        p.q = (int)((TQ - 1) - (b & (TQ - 1)));
+        p.rel = rel0 + b / TQ;
+    }
+    if (n < 64 && lane_id() >= n) p.rel = 0u;  // (a position that exists)
+    const uint32_t *cw = (const uint32_t *)(slice_codes + (uint64_t)p.rel * M);
+    if constexpr (M == 8) {
+        const uint2 v = *(const uint2 *)cw;
+        p.w[0] = v.x;
+        p.w[1] = v.y;
+    } else {
+        const uint4 v = *(const uint4 *)cw;
+        p.w[0] = v.x;
+        p.w[1] = v.y;
+        p.w[2] = v.z;
+        p.w[3] = v.w;
+    }
+}
+
+// Score a batch and feed the survivors that beat the current threshold to the lists.  `self0 + q` =
+// the position query slot q must not return (graph mode; a value no position can take otherwise).
+template <int M, int TQ, bool IVF, bool SHARE>
+__device__ __forceinline__ void score_batch(const Lds<M, TQ> &s, const ScanArgs &a, const Batch<M> &p,
+                                            int64_t slice_begin, uint32_t self0, SharedAsk &ask)
+{
+    float d = __builtin_inff();
+    const int q = p.q;
+    const uint32_t rel = p.rel;
+    const uint32_t(&w)[M / 4] = p.w;
+    if constexpr (SHARE) {
+        if (ask.wanted) adopt_shared_thresholds<M, TQ>(s, ask_shared_thresholds<M, TQ>(s, a));
+    }
+    const float thr = s.thr[q];
+    {
         // The gathers are issued last sub-quantizer first and summed first sub-quantizer first:
         // LDS answers in order, so the first addition waits for all of them and the others for
         // nothing (one wait instruction instead of one per addition).
         const lds_f32 *t = s.lut + q * (M * 256);
-        thr = s.thr[q];
         if constexpr (IVF) {
             float tv[M];
 #pragma unroll
@@ -697,17 +684,13 @@ __device__ __forceinline__ void drain(const Lds<M, TQ> &s, const ScanArgs &a, co
                 d = acc;
             }
         }
-    } else {
-        if constexpr (SHARE) {
-            if (ask.wanted) adopt_shared_thresholds<M, TQ>(s, shared);
-        }
     }
-    bool pass = d <= thr;  // (lanes without an entry: +inf <= -inf)
+    bool pass = (d <= thr) & (lane_id() < p.n);
     uint32_t key = rel;    // what breaks distance ties: the position, or the stored id
     if constexpr (IVF) {
         if (pass) key = (uint32_t)a.ext_ids[slice_begin + rel];
     } else {
-        pass = pass && rel != self0 + (uint32_t)q;  // a vector is not its own neighbour
+        pass = pass & (rel != self0 + (uint32_t)q);  // a vector is not its own neighbour
     }
     uint64_t pm = ballot64(pass);
     ask.wanted = pm != 0;
@@ -717,6 +700,133 @@ __device__ __forceinline__ void drain(const Lds<M, TQ> &s, const ScanArgs &a, co
         const uint64_t mine = ballot64(pass && q == qcur);
         pm &= ~mine;
         insert_candidates<M, TQ, SHARE, SHARE && !IVF>(s, a, qcur, mine, d, key);
+    }
+}
+
+// The survivors of one block -- `sv`, a bit per (code, query) pair in every lane -- scored a full
+// wave at a time; what does not fill a wave yet waits in the wave's queue, places assigned with
+// ballot + prefix popcount.  `fill`: entries waiting, < 64 between calls.
+//
+// Flat scans queue whole masks: lanes with bits left append (mask, position); once 64 masks wait,
+// every lane takes one, scores its lowest bit and what is left of the masks is appended again.  Per
+// block that is one append whatever the number of bits, where queueing bit by bit takes a turn of
+// about 16 instructions per bit of the fullest lane (4 turns at 1 bit per lane).  What the queue
+// cannot take of a block's masks waits in its lanes.  1M x 1M at ht = 20 106.3 -> 95.1 ms, 10M x 10k at ht = 24 24.6 -> 20.6 (batches scored when
+// the next one is taken instead of waiting for their codes: 23.0 -> 20.6 of that).
+//
+// Inverted lists queue bits: a wave sees a block or two of a list, so nearly everything it queues is
+// left over when its list ends (10k x 64 probes of 10M vectors 4.46 -> 4.64 ms with masks whose bits
+// are spread over the lanes at the end), and a batch is scored as soon as it is taken.
+template <int M, int TQ, bool IVF, bool SHARE, bool MFMA_BITS, int CAP>
+__device__ __forceinline__ void score_survivors(const Lds<M, TQ> &s, const ScanArgs &a, lds_u64 *queue, int &fill,
+                                                Batch<M> &batch, uint32_t sv, uint32_t rel0, const uint8_t *slice_codes,
+                                                int64_t slice_begin, uint32_t self0, SharedAsk &ask)
+{
+    if constexpr (IVF) {
+        static_assert(2 * CAP >= 127, "fewer than 64 entries wait, at most 64 come");
+        lds_u32 *bits = (lds_u32 *)queue;
+        while (true) {
+            const uint64_t m = ballot64(sv != 0u);
+            if (m == 0) return;
+            int at = fill + prefix_count(m);
+            asm("" : "+v"(at));
+            bits[sv != 0u ? at : 2 * CAP] = ((uint32_t)__builtin_ctz(sv | 0x80000000u) << 27) | rel0;
+            sv &= sv - 1u;
+            fill += __builtin_popcountll(m);
+            if (fill < 64) continue;
+            __builtin_amdgcn_wave_barrier();
+            fill -= 64;
+            const uint32_t e = bits[fill + lane_id()];
+            __builtin_amdgcn_wave_barrier();
+            take_batch<M, TQ, MFMA_BITS>(batch, 64, e >> 27, e & ((1u << 27) - 1u), slice_codes);
+            score_batch<M, TQ, IVF, SHARE>(s, a, batch, slice_begin, self0, ask);
+        }
+    } else {
+        // (lanes without a bit write to the place behind the queue instead of being masked off)
+        uint64_t m = ballot64(sv != 0u);
+        int total = fill + __builtin_popcountll(m);
+        uint32_t at = (uint32_t)(fill + prefix_count(m));
+        asm("" : "+v"(at));  // (a select, not a branch around two instructions)
+        at = sv != 0u ? at : (uint32_t)CAP;
+        queue[at < (uint32_t)CAP ? at : (uint32_t)CAP] = ((uint64_t)rel0 << 32) | sv;
+        fill = total;
+        if (total < 64) return;
+        uint32_t rest = 0u;  // the block's masks the queue had no place for
+        if (__builtin_expect(total > CAP, 0)) {
+            rest = at >= (uint32_t)CAP ? sv : 0u;
+            fill = CAP;
+        }
+        auto round = [&]() {
+            __builtin_amdgcn_wave_barrier();
+            fill -= 64;  // the newest 64 masks go, the others stay where they are
+            const uint64_t e = queue[fill + lane_id()];
+            __builtin_amdgcn_wave_barrier();
+            score_batch<M, TQ, IVF, SHARE>(s, a, batch, slice_begin, self0, ask);
+            sv = (uint32_t)e;
+            take_batch<M, TQ, MFMA_BITS>(batch, 64, (uint32_t)__builtin_ctz(sv), (uint32_t)(e >> 32), slice_codes);
+            sv &= sv - 1u;
+            m = ballot64(sv != 0u);
+            at = (uint32_t)(fill + prefix_count(m));
+            asm("" : "+v"(at));
+            queue[sv != 0u ? at : (uint32_t)CAP] = (e >> 32 << 32) | sv;
+            fill += __builtin_popcountll(m);
+            if (__builtin_expect(total > CAP, 0)) {
+                m = ballot64(rest != 0u);
+                total = fill + __builtin_popcountll(m);
+                at = rest != 0u ? (uint32_t)(fill + prefix_count(m)) : (uint32_t)CAP;
+                queue[at < (uint32_t)CAP ? at : (uint32_t)CAP] = ((uint64_t)rel0 << 32) | rest;
+                rest = at >= (uint32_t)CAP ? rest : 0u;
+                fill = total < CAP ? total : CAP;
+            }
+        };
+        // The first round stands by itself: the batch it scores was asked for before the block's last
+        // loads, so it waits for that batch and not for them; in a round right after another one it
+        // is the youngest load, and the wait is for everything.
+        round();
+        while (fill >= 64) round();
+    }
+}
+// What waits when the wave has seen its last block: the batch taken last and fewer than 64 entries
+// (of masks, the bits are spread over the lanes first).
+template <int M, int TQ, bool IVF, bool SHARE, bool MFMA_BITS, int CAP>
+__device__ __forceinline__ void score_remaining(const Lds<M, TQ> &s, const ScanArgs &a, lds_u64 *queue, int fill,
+                                                Batch<M> &batch, const uint8_t *slice_codes, int64_t slice_begin,
+                                                uint32_t self0, SharedAsk &ask)
+{
+    __builtin_amdgcn_wave_barrier();
+    const int lane = lane_id();
+    lds_u32 *bits = (lds_u32 *)queue;  // entries of one bit each: (bit number, position)
+    if constexpr (IVF) {
+        if (fill == 0) return;
+        const uint32_t e = lane < fill ? bits[lane] : 0u;
+        take_batch<M, TQ, MFMA_BITS>(batch, fill, e >> 27, e & ((1u << 27) - 1u), slice_codes);
+        score_batch<M, TQ, IVF, SHARE>(s, a, batch, slice_begin, self0, ask);
+        return;
+    }
+    uint32_t sv = 0u, rel0 = 0u;
+    if (lane < fill) {
+        const uint64_t e = queue[lane];
+        sv = (uint32_t)e;
+        rel0 = (uint32_t)(e >> 32);
+    }
+    fill = 0;
+    __builtin_amdgcn_wave_barrier();
+    while (true) {
+        score_batch<M, TQ, IVF, SHARE>(s, a, batch, slice_begin, self0, ask);
+        while (fill < 64) {
+            const uint64_t m = ballot64(sv != 0u);
+            if (m == 0) break;
+            if (sv != 0u) bits[fill + prefix_count(m)] = ((uint32_t)__builtin_ctz(sv) << 27) | rel0;
+            sv &= sv - 1u;
+            fill += __builtin_popcountll(m);
+        }
+        if (fill == 0) return;
+        __builtin_amdgcn_wave_barrier();
+        const int n = fill < 64 ? fill : 64;
+        fill -= n;
+        const uint32_t e = lane < n ? bits[fill + lane] : 0u;
+        __builtin_amdgcn_wave_barrier();
+        take_batch<M, TQ, MFMA_BITS>(batch, n, e >> 27, e & ((1u << 27) - 1u), slice_codes);
     }
 }
 
@@ -820,7 +930,7 @@ __global__ void __launch_bounds__(NW * 64)
 scan_kernel(ScanArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    const Lds<M, TQ> s((PSC_LDS unsigned char *)smem, a.kpad, NW);
+    const Lds<M, TQ> s((PSC_LDS unsigned char *)smem, a.kpad);
     constexpr int WPC = M / 4;       // 32-bit words per code
     constexpr int CB = 32 / TQ;      // codes per lane and block: one survivor bit per (code, query)
     constexpr int NLD = CB * M / 16; // 16-byte loads per lane and block
@@ -918,9 +1028,9 @@ scan_kernel(ScanArgs a)
     uint32_t qmask_all = 0u;
 #pragma unroll
     for (int c = 0; c < CB; ++c) qmask_all |= qmask << (c * TQ);
-    lds_u32 *ring = s.queue + wave * kQueueCap;
-    const uint32_t ring_base = (uint32_t)(uintptr_t)ring;  // LDS byte address of the wave's queue
-    int fill = 0;  // wave-uniform: entries waiting in the queue (< 64 between turns)
+    lds_u64 *queue = s.queue + wave * (kQueueCap + 1);
+    Batch<M> batch;
+    int fill = 0;  // wave-uniform: masks waiting in the queue
     SharedAsk ask;
     const uint8_t *slice_codes = a.codes + slice_begin * M;
     // graph mode: slot q's own vector sits at position self0 + q of the slice (if it is in there)
@@ -983,9 +1093,6 @@ scan_kernel(ScanArgs a)
         const int64_t b = wave_first + u * stride;
         if (b < slice_end) load_block(lane_ptr + u * stride * M, b, b + 64 * CB <= slice_end, cur[u]);
     }
-    // Lanes without a survivor in a turn write to a private dump word instead of being masked
-    // off: cheaper than switching the execution mask twice per turn.
-    const uint32_t dump_addr = (uint32_t)(uintptr_t)(s.dump + wave * 64 + lane);
     // One super-block of the wave, starting at code `sb` of the database.  INSIDE: this
     // super-block and the next one lie entirely inside the scanned range, so no code needs masking
     // and the next loads need no bounds -- the form all but the first and last turns take.
@@ -1028,31 +1135,11 @@ scan_kernel(ScanArgs a)
                 if (b < slice_end) load_block(lane_ptr + u * stride * M, b, b + 64 * CB <= slice_end, cur[u]);
             }
         }
-        // ---- survivors -> queue (one entry per lane and turn), full wavefronts -> ADC
+        // ---- survivors -> queue, full wavefronts -> ADC
         uint32_t rel0 = (uint32_t)(sb - slice_begin) + (uint32_t)lane * CB;
         auto queue_block = [&](uint32_t sv) {
-            while (true) {
-                // Queue one survivor bit per lane and turn until no lane has bits left or 64 entries
-                // wait.  Hand-scheduled: the compiler's version of this loop spends more scalar
-                // instructions on loop control than vector instructions on the work, and every
-                // instruction of a wave costs an issue slot.  Per turn: the lanes with a bit are
-                // counted (vcc), each takes slot fill + (number of such lanes below it), writes
-                // (bit number << kRelBits) | position, and clears that bit; lanes without a bit
-                // write to their dump word.  `base` = byte address of queue slot `fill`.
-                fill = __builtin_amdgcn_readfirstlane(fill);  // (wave-uniform already; keeps it scalar)
-                uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)(ring_base + 4u * (uint32_t)fill)), t0, t1, n;
-                asm volatile(PSC_QUEUE_TURNS
-                             : [sv] "+v"(sv), [fill] "+s"(fill), [base] "+s"(base), [t0] "=&v"(t0), [t1] "=&v"(t1),
-                               [n] "=&s"(n)
-                             : [rel0] "v"(rel0), [dump] "v"(dump_addr)
-                             : "vcc", "scc", "memory");
-                static_assert(kRelBits == 27, "the shift in the queueing loop");
-                if (fill < 64) break;  // every lane is out of bits
-                __builtin_amdgcn_wave_barrier();
-                fill -= 64;  // the newest 64 entries go, the others stay where they are
-                drain<M, TQ, IVF, SHARE>(s, a, ring + fill, 64, slice_codes, slice_begin, self0, ask);
-                __builtin_amdgcn_wave_barrier();
-            }
+            score_survivors<M, TQ, IVF, SHARE, false, kQueueCap>(s, a, queue, fill, batch, sv, rel0, slice_codes,
+                                                                 slice_begin, self0, ask);
         };
         if constexpr (INSIDE) {  // the hot form: one copy of the queueing code per block, no loop around them
 #pragma unroll
@@ -1080,10 +1167,7 @@ scan_kernel(ScanArgs a)
     const int ninside = room >= 0 ? (int)(room / sstride) + 1 : 0;
     for (int i = 0; i < ninside; ++i, sb += sstride) superblock(std::true_type{}, sb);
     for (; sb < slice_end; sb += sstride) superblock(std::false_type{}, sb);
-    if (fill > 0) {
-        __builtin_amdgcn_wave_barrier();
-        drain<M, TQ, IVF, SHARE>(s, a, ring, fill, slice_codes, slice_begin, self0, ask);
-    }
+    score_remaining<M, TQ, IVF, SHARE, false, kQueueCap>(s, a, queue, fill, batch, slice_codes, slice_begin, self0, ask);
     __syncthreads();
 
     if (spread) {
@@ -1175,8 +1259,8 @@ scan_kernel(ScanArgs a)
 // and 32 .. 47, in the other those of lanes 16 .. 31 and 48 .. 63, each half in its row of lanes.
 //
 // Survivor masks: bit 4 * t + r of a lane's mask <=> (code 16 * t + col of the 128-code block,
-// query slot 4 * grp + r), t = 0..7.  Queue entries carry the bit number, grp and the position of
-// the block's code `col` (kMfmaRelBits bits).
+// query slot 4 * grp + r), t = 0..7.  Queue entries carry the mask, grp and the position of the
+// block's code `col` (kMfmaRelBits bits).
 //
 // What bounds it: vector instruction issue, about 45 per 2048 pairs for the test (22 to make
 // operands, the rest to collect verdicts) beside 4 products of 16 cycles.  Against bytes of +-1 from
@@ -1184,6 +1268,7 @@ scan_kernel(ScanArgs a)
 // at ht = 20: 134.8 -> 106.3 ms; 10M x 10k at ht = 24, k = 100: 28.2 -> 24.6 ms on one box.
 // ---------------------------------------------------------------------------------------------
 typedef int i32x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float mfma_f32x4 __attribute__((ext_vector_type(4)));
 
 // (One 16-wave workgroup per compute unit = 4 waves per SIMD: telling the compiler so lets it
@@ -1196,7 +1281,7 @@ scan_mfma_kernel(ScanArgs a)
     constexpr int M = 8, TQ = 16;
     constexpr int kBlock = 128;  // codes per wave and turn
     extern __shared__ __align__(16) unsigned char smem[];
-    const Lds<M, TQ> s((PSC_LDS unsigned char *)smem, a.kpad, NW);
+    const Lds<M, TQ> s((PSC_LDS unsigned char *)smem, a.kpad);
     const int tid = (int)threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1286,9 +1371,8 @@ scan_mfma_kernel(ScanArgs a)
         for (int t = 0; t < 2; ++t) cinit[t][r] = 8388608.f + f * (float)((1 << (r + 4 * t + 1)) + (1 << (r + 4 * t + 9)));
     }
 
-    lds_u32 *ring = s.queue + wave * kQueueCap;
-    const uint32_t ring_base = (uint32_t)(uintptr_t)ring;
-    const uint32_t dump_addr = (uint32_t)(uintptr_t)(s.dump + wave * 64 + lane);
+    lds_u64 *queue = s.queue + wave * (kMfmaQueueCap + 1);
+    Batch<M> batch;
     int fill = 0;
     SharedAsk ask;
     const uint8_t *slice_codes = a.codes + slice_begin * M;
@@ -1298,94 +1382,76 @@ scan_mfma_kernel(ScanArgs a)
         if (at > -64 && at < kMfmaMaxSliceLen) self0 = (uint32_t)at;
     }
     const uint32_t lane_bits = (uint32_t)col | ((uint32_t)grp << kMfmaRelBits);
+    uint32_t m1 = 0x11111111u, m2 = 0x22222222u, m4 = 0x44444444u;
+    asm("" : "+s"(m1), "+s"(m2), "+s"(m4));  // (in scalar registers: half the code size of literals)
 
-    auto queue_block = [&](uint32_t sv, const uint32_t rel0) {
-        while (true) {
-            fill = __builtin_amdgcn_readfirstlane(fill);
-            uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)(ring_base + 4u * (uint32_t)fill)), t0, t1, n;
-            asm volatile(PSC_QUEUE_TURNS
-                         : [sv] "+v"(sv), [fill] "+s"(fill), [base] "+s"(base), [t0] "=&v"(t0), [t1] "=&v"(t1),
-                           [n] "=&s"(n)
-                         : [rel0] "v"(rel0), [dump] "v"(dump_addr)
-                         : "vcc", "scc", "memory");
-            if (fill < 64) break;
-            __builtin_amdgcn_wave_barrier();
-            fill -= 64;
-            drain<M, TQ, IVF, SHARE, true>(s, a, ring + fill, 64, slice_codes, slice_begin, self0, ask);
-            __builtin_amdgcn_wave_barrier();
-        }
-    };
-
-    // The wave's blocks: wave, wave + NW, ... of the slice's 128-code blocks; the next block's
-    // codes are asked for before the current one is worked on.  WHOLE: the block lies entirely
-    // inside the slice (all but the last turn or two of a wave).
-    const int64_t stride = (int64_t)NW * kBlock;
-    auto load_block = [&](auto whole, int64_t blk, uint2 (&c)[2]) {
+    // The wave's blocks: wave, wave + NW, ... of the slice's 128-code blocks, positions counted from
+    // the slice's start (at most 2^25).  Two register sets in turn: a block's next-but-one is asked
+    // for as soon as its codes have become operands.  Past the slice's end the buffer's range check
+    // answers zero (and the bits are masked below).
+    const int len = (int)(slice_end - slice_begin);
+    constexpr int stride = NW * kBlock;
+    const uint32_t lane_off = (uint32_t)lane * M;
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc((void *)slice_codes, 0, len * M, 0x00020000);
+    auto load_block = [&](int blk, u32x2 (&c)[2]) {
+        const uint32_t at = (uint32_t)blk * (uint32_t)M + lane_off;  // (below 2^31: blk < len + 2 * stride)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int64_t p = blk + 64 * h + lane;
-            if constexpr (decltype(whole)::value) {
-                c[h] = *(const uint2 *)(a.codes + p * M);
-            } else {
-                c[h] = make_uint2(0u, 0u);
-                if (p < slice_end) c[h] = *(const uint2 *)(a.codes + p * M);
-            }
-        }
+        for (int h = 0; h < 2; ++h) c[h] = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)(at + 64u * M * h), 0, 0);
     };
-    auto filter_block = [&](auto whole, int64_t blk, const uint2 (&c)[2]) {
-        mfma_f32x4 acc[4];
+    auto scan_block = [&](int blk, u32x2 (&c)[2]) {
+        // (the pairs stay pairs up to here: split earlier, their halves are copied at the loop's end,
+        //  which waits for the loads just issued)
+        asm volatile("" : "+v"(c[0]), "+v"(c[1]));
+        i32x8 cb[4];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const auto w = __builtin_amdgcn_permlane16_swap(c[h].x, c[h].y, false, false);
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const i32x8 cb = {(int)(w[t] & 0x11111111u), (int)(w[t] & 0x22222222u), (int)(w[t] & 0x44444444u),
-                                  (int)((w[t] >> 1) & 0x44444444u), 0, 0, 0, 0};
-                acc[2 * h + t] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(qa, cb, cinit[t], 4, 4, 0, scale_q, 0,
-                                                                                  t ? 131 : 127);
-            }
+            for (int t = 0; t < 2; ++t)
+                cb[2 * h + t] = i32x8{(int)(w[t] & m1), (int)(w[t] & m2), (int)(w[t] & m4), (int)((w[t] >> 1) & m4), 0, 0, 0, 0};
         }
+        load_block(blk + 2 * stride, c);
+        mfma_f32x4 acc[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            acc[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(qa, cb[i], cinit[i & 1], 4, 4, 0, scale_q, 0,
+                                                                      (i & 1) ? 131 : 127);
         uint32_t near[2] = {0u, 0u};
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) near[h] |= __float_as_uint(acc[2 * h + t][r]) & (0x8080u << (r + 4 * t));
+                for (int r = 0; r < 4; ++r) {
+                    near[h] |= __float_as_uint(acc[2 * h + t][r]) & (0x8080u << (r + 4 * t));
+                    asm("" : "+v"(near[h]));  // (one and-or per register: left alone the compiler takes 1.5)
+                }
             }
         }
         uint32_t sv = (near[0] >> 7) | (near[1] << 9);
-        if constexpr (!decltype(whole)::value) {  // ragged block: codes past the end do not count
+        if (blk + kBlock > len) {  // ragged block: codes past the end do not count
             uint32_t in = 0u;
 #pragma unroll
             for (int t = 0; t < 8; ++t)
-                if (blk + 16 * t + col < slice_end) in |= 0xfu << (4 * t);
+                if (blk + 16 * t + col < len) in |= 0xfu << (4 * t);
             sv &= in;
         }
-        queue_block(sv, (uint32_t)(blk - slice_begin) + lane_bits);
+        score_survivors<M, TQ, IVF, SHARE, true, kMfmaQueueCap>(s, a, queue, fill, batch, sv, (uint32_t)blk + lane_bits,
+                                                                slice_codes, slice_begin, self0, ask);
     };
-    uint2 cur[2];
-    int64_t blk = slice_begin + (int64_t)wave * kBlock;
-    if (blk < slice_end) load_block(std::false_type{}, blk, cur);
-    while (blk + stride + kBlock <= slice_end) {  // this block and the next are whole
-        uint2 nxt[2];
-        load_block(std::true_type{}, blk + stride, nxt);
-        filter_block(std::true_type{}, blk, cur);
-        cur[0] = nxt[0];
-        cur[1] = nxt[1];
-        blk += stride;
+    u32x2 even[2], odd[2];
+    int blk = wave * kBlock;
+    load_block(blk, even);
+    __builtin_amdgcn_sched_barrier(0);  // (waits are counted: the order of the loads matters)
+    load_block(blk + stride, odd);
+    while (blk < len) {  // (an odd block past the end is all masked; a way out between the two would cost
+                         //  the waits their exact counts)
+        scan_block(blk, even);
+        scan_block(blk + stride, odd);
+        blk += 2 * stride;
     }
-    for (; blk < slice_end; blk += stride) {
-        uint2 nxt[2] = {make_uint2(0u, 0u), make_uint2(0u, 0u)};
-        if (blk + stride < slice_end) load_block(std::false_type{}, blk + stride, nxt);
-        filter_block(std::false_type{}, blk, cur);
-        cur[0] = nxt[0];
-        cur[1] = nxt[1];
-    }
-    if (fill > 0) {
-        __builtin_amdgcn_wave_barrier();
-        drain<M, TQ, IVF, SHARE, true>(s, a, ring, fill, slice_codes, slice_begin, self0, ask);
-    }
+    score_remaining<M, TQ, IVF, SHARE, true, kMfmaQueueCap>(s, a, queue, fill, batch, slice_codes, slice_begin, self0, ask);
     __syncthreads();
 
     for (int e = tid; e < nvq * a.k; e += NW * 64) {
@@ -1427,7 +1493,7 @@ adc_kernel(ScanArgs a)
 {
     static_assert(TQ % 4 == 0, "four queries per table entry");
     extern __shared__ __align__(16) unsigned char smem[];
-    const Lds<M, TQ> s((PSC_LDS unsigned char *)smem, a.kpad, NW);
+    const Lds<M, TQ> s((PSC_LDS unsigned char *)smem, a.kpad);
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     constexpr int G = TQ / 4;
     constexpr int WPC = M / 4;
@@ -2177,7 +2243,7 @@ int plan_scan(int m, int64_t nq, int64_t n, int k, int kind, ScanPlan *plan)
         const int t = options[o].tq, nw = options[o].nwaves;
         if (t > tq_cap) continue;
         const size_t need = (size_t)t * m * 256 * 4 + (size_t)t * p.kpad * 8 + (size_t)t * 16 + (size_t)t * m * 5 +
-                            (size_t)nw * (kQueueCap + 64) * 4;
+                            (size_t)nw * ((kind == kScanFusedMfma ? kMfmaQueueCap : kQueueCap) + 1) * 8;
         if (need <= options[o].max_lds) {
             p.tq = t;
             p.nwaves = nw;
