@@ -199,8 +199,8 @@ int psc_threshold_for_rate(const int64_t *hist_host, int nbits, double max_keep_
  * the scan rejects a survivor as soon as the sum over its first sub-quantizers exceeds the
  * query's current k-th best distance.
  * The Hamming test is exact on every route the library takes: xor / popcount on the vector
- * units, or (64-bit codes, 9 queries or more, selective thresholds) an int8 dot product of
- * +-1 expansions on the matrix cores, whose sign gives the same verdict.
+ * units, or (9 queries or more) a dot product of the bits as 4-bit floating point on the matrix
+ * cores, whose exact result holds the same verdict in one of its bits.
  * psc_set_filter_route forces one of the two where both apply (process-wide; a measurement aid,
  * results do not depend on it); psc_last_scan_route names the kernel, tile shape, database
  * slices and workgroup count the calling thread's last scan launched, e.g.

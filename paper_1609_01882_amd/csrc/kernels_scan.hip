@@ -41,7 +41,9 @@ constexpr int kMfmaRelBits = 25;      // bits of a queue entry of the matrix-cor
                                       // the slice (two more name the lane's row group)
 constexpr uint32_t kMfmaRelMask = (1u << kMfmaRelBits) - 1;
 constexpr int64_t kMfmaMaxSliceLen = (int64_t)1 << kMfmaRelBits;
-constexpr int64_t kMfmaMinQueries = 9;  // fewer queries than this take the narrower xor/popcount tiles
+// Fewer queries than this take the narrower xor/popcount tiles (those scans are bound by memory; 128
+// bits, 50M codes, 5 and 8 queries, k = 100: 0.18 to 0.24 ms at ht = 0 .. 48 with either filter).
+constexpr int64_t kMfmaMinQueries = 9;
 constexpr int kSpinLimit = 1 << 22;   // bounded wait on a list lock (each turn sleeps)
 constexpr int kManySlices = 4;        // slices per query from which the lists exchange more than their k-th best
 
@@ -605,9 +607,9 @@ __device__ __forceinline__ void take_batch(Batch<M> &p, const int n, const uint3
                                            const uint8_t *slice_codes)
 {
     p.n = n;
-    if constexpr (MFMA_BITS) {  // b = 4 * (16-code group) + row; rel0 = position | row group << kMfmaRelBits
+    if constexpr (MFMA_BITS) {  // b = 4 * (16-code group; 128 bits: 32) + row; rel0 = position | row group << kMfmaRelBits
         p.q = (int)(4u * ((rel0 >> kMfmaRelBits) & 3u) + (b & 3u));
-        p.rel = (rel0 & kMfmaRelMask) + 16u * (b >> 2);
+        p.rel = (rel0 & kMfmaRelMask) + (M == 8 ? 16u : 32u) * (b >> 2);
     } else {  // b = c * TQ + (TQ - 1 - q); rel0 = position of the lane's first code
         p.q = (int)((TQ - 1) - (b & (TQ - 1)));
         p.rel = rel0 + b / TQ;
@@ -1232,17 +1234,18 @@ scan_kernel(ScanArgs a)
 }
 
 // ---------------------------------------------------------------------------------------------
-// The fused scan with the Hamming test of Section 3.3 ("dual" in Section 4.2) on the matrix cores (64-bit codes, tiles
-// of 16 queries, flat and graph mode).  With the code's bits c_i in {0, 1}, the query's bits turned
+// The fused scan with the Hamming test of Section 3.3 ("dual" in Section 4.2) on the matrix cores (tiles of 16 queries
+// at 64 bits, of 8 at 128; the description is for 64 bits up to the last paragraph).  With the code's bits c_i in {0, 1}, the query's bits turned
 // into s_i = +1 (bit 0) or -1 (bit 1) and p the number of ones of the query,
 //     distance = p + sum_i s_i c_i,   so   f = (ht + 64 - p) - sum_i s_i c_i = ht + 64 - distance
 // lies in 0 .. 127 (ht <= 63) and its bit 6 says "within ht": a contraction whose small-integer
 // operands 4-bit floating point (E2M1) holds exactly, v_mfma_scale_f32_16x16x128_f8f6f4.
 //
 // Bits to operands costs one vector instruction per 8 bits and no table: E2M1 reads the nibbles
-// 0001, 0010, 0100 as 0.5, 1, 2, so `word & 0x11111111`, `& 0x22222222`, `& 0x44444444` (and the
-// word shifted right by one `& 0x44444444` for the top bit of each nibble) are operands already; the
-// query side carries 2, 1, 0.5 (0.5) in the same places, every product is 0 or +-1.
+// 0001, 0010, 0100 as 0.5, 1, 2, so `word & 0x11111111`, `& 0x22222222` and `& 0x44444444` are operands
+// already; the query side carries 2, 1, 0.5 in the same places, every product is 0 or +-1.  The top
+// bit of a nibble is the sign: `(word & 0x88888888) | 0x22222222` is 1 - 2 c, and with
+// s c = s / 2 - s (1 - 2 c) / 2 it meets +-0.5 on the query side and a constant.
 //
 // Two pairs to a result: the instruction's K = 128 positions hold the 64 bits of two codes (lanes
 // 0 .. 31 the halves of one, lanes 32 .. 63 of the other), and the per-lane block scales weigh
@@ -1262,6 +1265,14 @@ scan_kernel(ScanArgs a)
 // query slot 4 * grp + r), t = 0..7.  Queue entries carry the mask, grp and the position of the
 // block's code `col` (kMfmaRelBits bits).
 //
+// 128 bits: one product takes words 0 and 2 of its two codes (lanes read 8 bytes: row 0 of lanes the
+// first half of a code, row 1 the second, rows 2 and 3 those of the code 64 on), the next, into the
+// same result, words 1 and 3; no word changes lanes.  8 queries fill half of the rows, so two such
+// pairs serve one result, the first with the queries in rows 0 .. 7 (the others zero), the second,
+// with the next 16 codes, in rows 8 .. 15.  The fields are ht + 128 - distance, 8 bits, their bit 7 at
+// 7 + s and 15 + s.  Bit 4 * t + r of a mask is code 32 * t + 16 * (grp / 2) + col of a 256-code
+// block and query slot 4 * (grp % 2) + r.
+//
 // What bounds it: vector instruction issue, about 45 per 2048 pairs for the test (22 to make
 // operands, the rest to collect verdicts) beside 4 products of 16 cycles.  Against bytes of +-1 from
 // a table in LDS and one int8 product per 16 codes (16 look-ups, 80 vector instructions), 1M x 1M
@@ -1274,12 +1285,15 @@ typedef float mfma_f32x4 __attribute__((ext_vector_type(4)));
 // (One 16-wave workgroup per compute unit = 4 waves per SIMD: telling the compiler so lets it
 //  spend registers on keeping the eight products of a block in flight together.)
 // IVF: tiles are (inverted list, up to 16 of its jobs), as in scan_kernel.
-template <int NW, bool SHARE, bool IVF = false>
+template <int M, int NW, bool SHARE, bool IVF = false>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
 scan_mfma_kernel(ScanArgs a)
 {
-    constexpr int M = 8, TQ = 16;
-    constexpr int kBlock = 128;  // codes per wave and turn
+    static_assert(M == 8 || !IVF, "inverted lists of 128-bit codes take scan_kernel");
+    constexpr int TQ = M == 8 ? 16 : 8;
+    constexpr int WPC = M / 4;                  // 32-bit words per code
+    constexpr int kBlock = M == 8 ? 128 : 256;  // codes per wave and turn
+    constexpr int NLD = kBlock * M / 512;       // 8-byte loads per lane and turn
     extern __shared__ __align__(16) unsigned char smem[];
     const Lds<M, TQ> s((PSC_LDS unsigned char *)smem, a.kpad);
     const int tid = (int)threadIdx.x;
@@ -1343,32 +1357,49 @@ scan_mfma_kernel(ScanArgs a)
         __syncthreads();
     }
 
-    // A operand: word grp % 2 of query slot col, its bits as signs (minus for a 0) on the magnitudes
-    // 2, 1, 0.5, 0.5; slots past nvq are all zero.
+    // A operand: one word of query slot col % TQ as signs on the magnitudes 2, 1, 0.5 (minus for a 0)
+    // and 0.5 (minus for a 1: the database's fourth bits are signs, see above); slots past nvq are all
+    // zero.  64 bits: word grp % 2.  128 bits: qa[h][i] holds word 2 * (grp % 2) + i, in rows
+    // 8 h .. 8 h + 7, the other rows being zero.
     auto query_word = [&](int slot, int w) {
-        if constexpr (IVF) return (uint32_t)s.qcw[slot * 2 + w];
-        else return ((const uint32_t *)a.qcodes)[(q0 + slot) * 2 + w];
+        if constexpr (IVF) return (uint32_t)s.qcw[slot * WPC + w];
+        else return ((const uint32_t *)a.qcodes)[(q0 + slot) * WPC + w];
     };
     const int ht = (int)(0x7fffffffu - a.bias);
-    i32x8 qa = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (col < nvq) {
-        const uint32_t w = ~query_word(col, grp & 1);
-        qa[0] = (int)(((w & 0x11111111u) << 3) | 0x44444444u);
-        qa[1] = (int)((((w >> 1) & 0x11111111u) << 3) | 0x22222222u);
-        qa[2] = (int)((((w >> 2) & 0x11111111u) << 3) | 0x11111111u);
-        qa[3] = (int)((((w >> 3) & 0x11111111u) << 3) | 0x11111111u);
+    i32x8 qa[16 / TQ][WPC / 2];
+#pragma unroll
+    for (int i = 0; i < WPC / 2; ++i) {
+        const bool real = col % TQ < nvq;
+        const uint32_t w = real ? query_word(col % TQ, (WPC / 2) * (grp & 1) + i) : 0u;
+        const int v[4] = {(int)(((~w & 0x11111111u) << 3) | 0x44444444u), (int)(((~w & 0x22222222u) << 2) | 0x22222222u),
+                          (int)(((~w & 0x44444444u) << 1) | 0x11111111u), (int)((w & 0x88888888u) | 0x11111111u)};
+#pragma unroll
+        for (int h = 0; h < 16 / TQ; ++h) {
+            qa[h][i] = i32x8{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) qa[h][i][j] = real && col / TQ == h ? v[j] : 0;
+        }
     }
     // block scales (biased exponents): the row's place s = row % 4 (+ 4 for the second product of a
     // pair, on the other operand), eight bits higher for the second code
-    const int scale_q = 127 + 1 + (col & 3) + (grp >= 2 ? 8 : 0);
+    constexpr int kLow = M == 8 ? 1 : 0;  // place of a field's lowest bit at s = 0
+    const int scale_q = 127 + kLow + (col & 3) + (grp >= 2 ? 8 : 0);
     mfma_f32x4 cinit[2];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int slot = 4 * grp + r;
+        const int slot = (4 * grp + r) % TQ;
         float f = 0.f;  // (an empty slot's fields stay 0: never within ht)
-        if (slot < nvq) f = (float)(ht + 64 - __popc(query_word(slot, 0)) - __popc(query_word(slot, 1)));
+        if (slot < nvq) {
+            int ones = M;  // ones of the query, the sign bits' constant (M - ones among the fourth bits) with them
 #pragma unroll
-        for (int t = 0; t < 2; ++t) cinit[t][r] = 8388608.f + f * (float)((1 << (r + 4 * t + 1)) + (1 << (r + 4 * t + 9)));
+            for (int w = 0; w < WPC; ++w) ones += __popc(query_word(slot, w) & 0x77777777u);
+            f = (float)(ht + 8 * M - ones);
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int low = kLow + r + 4 * t;
+            cinit[t][r] = 8388608.f + f * (float)((1 << low) + (1 << (low + 8)));
+        }
     }
 
     lds_u64 *queue = s.queue + wave * (kMfmaQueueCap + 1);
@@ -1381,9 +1412,13 @@ scan_mfma_kernel(ScanArgs a)
         const int64_t at = a.skip_first + q0 - slice_begin;
         if (at > -64 && at < kMfmaMaxSliceLen) self0 = (uint32_t)at;
     }
-    const uint32_t lane_bits = (uint32_t)col | ((uint32_t)grp << kMfmaRelBits);
-    uint32_t m1 = 0x11111111u, m2 = 0x22222222u, m4 = 0x44444444u;
-    asm("" : "+s"(m1), "+s"(m2), "+s"(m4));  // (in scalar registers: half the code size of literals)
+    // what a queue entry adds to the block's position: the place of the mask's first code in the block
+    // and, above kMfmaRelBits, the lane's group of query slots
+    const uint32_t lane_code = (uint32_t)(M == 8 ? col : col + 16 * (grp >> 1));
+    const uint32_t lane_bits = lane_code | ((uint32_t)(M == 8 ? grp : grp & 1) << kMfmaRelBits);
+    constexpr int kStep = M == 8 ? 16 : 32;  // codes from one group of four mask bits to the next
+    uint32_t m1 = 0x11111111u, m2 = 0x22222222u, m4 = 0x44444444u, m8 = 0x88888888u, ones = 0x22222222u;
+    asm("" : "+s"(m1), "+s"(m2), "+s"(m4), "+s"(m8), "+v"(ones));  // (in registers: half the code size of literals)
 
     // The wave's blocks: wave, wave + NW, ... of the slice's 128-code blocks, positions counted from
     // the slice's start (at most 2^25).  Two register sets in turn: a block's next-but-one is asked
@@ -1391,32 +1426,58 @@ scan_mfma_kernel(ScanArgs a)
     // answers zero (and the bits are masked below).
     const int len = (int)(slice_end - slice_begin);
     constexpr int stride = NW * kBlock;
-    const uint32_t lane_off = (uint32_t)lane * M;
+    // (128 bits: rows 0, 1 of lanes read the halves of 16 codes, rows 2, 3 those of the 16 codes 64 on)
+    const uint32_t lane_off = M == 8 ? (uint32_t)lane * 8u : (uint32_t)(64 * (grp >> 1) + col) * 16u + 8u * (grp & 1);
     const __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc((void *)slice_codes, 0, len * M, 0x00020000);
-    auto load_block = [&](int blk, u32x2 (&c)[2]) {
-        const uint32_t at = (uint32_t)blk * (uint32_t)M + lane_off;  // (below 2^31: blk < len + 2 * stride)
+    auto load_block = [&](int blk, u32x2 (&c)[NLD]) {
+        const uint32_t at = (uint32_t)blk * (uint32_t)M + lane_off;  // (below 2^31: blk < len + 3 * stride)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) c[h] = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)(at + 64u * M * h), 0, 0);
+        for (int l = 0; l < NLD; ++l) {
+            // 64 bits: 64 codes in a row; 128 bits: two runs of 16, l = 4 p + 2 t + h as used below
+            const uint32_t first = M == 8 ? 64 * l : 128 * (l >> 2) + 16 * (l & 3);
+            c[l] = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)(at + first * M), 0, 0);
+        }
     };
-    auto scan_block = [&](int blk, u32x2 (&c)[2]) {
+    auto scan_block = [&](int blk, u32x2 (&c)[NLD]) {
         // (the pairs stay pairs up to here: split earlier, their halves are copied at the loop's end,
         //  which waits for the loads just issued)
-        asm volatile("" : "+v"(c[0]), "+v"(c[1]));
-        i32x8 cb[4];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const auto w = __builtin_amdgcn_permlane16_swap(c[h].x, c[h].y, false, false);
+        for (int l = 0; l < NLD; ++l) asm volatile("" : "+v"(c[l]));
+        auto operand = [&](uint32_t w) {
+            return i32x8{(int)(w & m1), (int)(w & m2), (int)(w & m4), (int)((w & m8) | ones), 0, 0, 0, 0};
+        };
+        i32x8 cb[2 * NLD];
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
-                cb[2 * h + t] = i32x8{(int)(w[t] & m1), (int)(w[t] & m2), (int)(w[t] & m4), (int)((w[t] >> 1) & m4), 0, 0, 0, 0};
+        for (int l = 0; l < NLD; ++l) {
+            uint32_t w0 = c[l][0], w1 = c[l][1];
+            if constexpr (M == 8) {
+                const auto w = __builtin_amdgcn_permlane16_swap(w0, w1, false, false);
+                w0 = w[0];
+                w1 = w[1];
+            }
+            cb[2 * l] = operand(w0);
+            cb[2 * l + 1] = operand(w1);
         }
         load_block(blk + 2 * stride, c);
         mfma_f32x4 acc[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            acc[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(qa, cb[i], cinit[i & 1], 4, 4, 0, scale_q, 0,
-                                                                      (i & 1) ? 131 : 127);
+        for (int i = 0; i < 4; ++i) {
+            const int t = i & 1, scale_t = 127 + 4 * t;
+            acc[i] = cinit[t];
+            if constexpr (M == 8) {
+                acc[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(qa[0][0], cb[i], acc[i], 4, 4, 0, scale_q, 0, scale_t);
+            } else {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                    for (int w = 0; w < 2; ++w)
+                        acc[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+                            qa[16 / TQ - 1 < h ? 0 : h][WPC / 2 - 1 < w ? 0 : w], cb[NLD < 8 ? 0 : 4 * i + 2 * h + w], acc[i],
+                            4, 4, 0, scale_q, 0, scale_t);
+                }
+            }
+        }
         uint32_t near[2] = {0u, 0u};
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -1434,13 +1495,13 @@ scan_mfma_kernel(ScanArgs a)
             uint32_t in = 0u;
 #pragma unroll
             for (int t = 0; t < 8; ++t)
-                if (blk + 16 * t + col < len) in |= 0xfu << (4 * t);
+                if (blk + kStep * t + (int)lane_code < len) in |= 0xfu << (4 * t);
             sv &= in;
         }
         score_survivors<M, TQ, IVF, SHARE, true, kMfmaQueueCap>(s, a, queue, fill, batch, sv, (uint32_t)blk + lane_bits,
                                                                 slice_codes, slice_begin, self0, ask);
     };
-    u32x2 even[2], odd[2];
+    u32x2 even[NLD], odd[NLD];
     int blk = wave * kBlock;
     load_block(blk, even);
     __builtin_amdgcn_sched_barrier(0);  // (waits are counted: the order of the loads matters)
@@ -2087,16 +2148,16 @@ int run_scan(const ScanArgs &a, int64_t ntiles, size_t lds, hipStream_t s)
     return PSC_OK;
 }
 
-template <int NW, bool SHARE, bool IVF = false>
+template <int M, int NW, bool SHARE, bool IVF = false>
 int run_scan_mfma(const ScanArgs &a, int64_t ntiles, size_t lds, hipStream_t s)
 {
     static bool configured = false;
     if (!configured) {
-        PSC_HIP_TRY(hipFuncSetAttribute((const void *)scan_mfma_kernel<NW, SHARE, IVF>,
+        PSC_HIP_TRY(hipFuncSetAttribute((const void *)scan_mfma_kernel<M, NW, SHARE, IVF>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
         configured = true;
     }
-    hipLaunchKernelGGL((scan_mfma_kernel<NW, SHARE, IVF>), dim3((unsigned)ntiles), dim3(NW * 64), lds, s, a);
+    hipLaunchKernelGGL((scan_mfma_kernel<M, NW, SHARE, IVF>), dim3((unsigned)ntiles), dim3(NW * 64), lds, s, a);
     PSC_HIP_TRY(hipGetLastError());
     return PSC_OK;
 }
@@ -2193,8 +2254,8 @@ void note_scan_route(const char *text) { snprintf(g_route, sizeof g_route, "%s",
 //    stages its tables or waits on a list lock while the other filters; fewer waves per list
 //    lock) -- measured 4% (clustered codes) to 11% (random codes) ahead of 16 x 16 at ht=24;
 //    falls back to 16 x 16, 8 x 16, 4 x 16 as k grows (the lists share LDS with the tables);
-//  * fused scan with the matrix-core filter (64-bit codes, 9 queries or more, few survivors):
-//    16 x 16, the only shape of scan_mfma_kernel (k up to 136);
+//  * fused scan with the matrix-core filter (9 queries or more): 16 x 16 (k up to 136) at 64 bits, 8 x 16
+//    at 128, the only shapes of scan_mfma_kernel;
 //  * up to 4 / 8 / 16 queries: no more query slots than queries (every slot costs filter work),
 //    which keeps a one-pass scan of few queries bound by memory bandwidth;
 //  * grouped inverted-file jobs: 4 x 8, three workgroups per compute unit (tiles are short, so
@@ -2225,11 +2286,11 @@ int plan_scan(int m, int64_t nq, int64_t n, int k, int kind, ScanPlan *plan)
     Shape options[5];
     int nopt = 0;
     if (kind == kScanFusedMfma) {
-        if (m != 8 || nq < kMfmaMinQueries) {
-            set_error("the matrix-core filter takes 64-bit codes and at least %d queries", (int)kMfmaMinQueries);
+        if (nq < kMfmaMinQueries) {
+            set_error("the matrix-core filter takes at least %d queries", (int)kMfmaMinQueries);
             return PSC_EINVAL;
         }
-        options[nopt++] = Shape{16, 16, kLdsBudget};
+        options[nopt++] = Shape{m == 8 ? 16 : 8, 16, kLdsBudget};
     } else {
         if (m == 8 && kind == kScanLists) options[nopt++] = Shape{4, 8, kLdsBudget / 2};
         if (m == 8 && kind == kScanFused && nq > 16)
@@ -2352,7 +2413,7 @@ size_t flat_scan_workspace_bytes(int m, int64_t nq, int64_t n, int k)
         bytes = std::max(bytes, p.total_bytes);
     }
     ScanPlan p;  // the matrix-core route where it applies (it has shapes and slices of its own)
-    if (m == 8 && nq >= kMfmaMinQueries && plan_scan(m, nq, n, k, kScanFusedMfma, &p) == PSC_OK)
+    if (nq >= kMfmaMinQueries && plan_scan(m, nq, n, k, kScanFusedMfma, &p) == PSC_OK)
         bytes = std::max(bytes, p.total_bytes);
     return bytes;
 }
@@ -2383,14 +2444,15 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
     const bool dense = ht >= 8 * m || random_code_survival(8 * m, ht) >= dense_from;
     ScanPlan p;
     int rc = PSC_EINVAL;
-    // Matrix-core filter: 64-bit codes, more than one tile of queries, k small enough for its
-    // 16-query tile, and few survivors (beyond about one pair in ten the queue and the lists
-    // decide the time and the two filters tie: measured equal at ht = 26, behind at ht = 28).
+    // Matrix-core filter: 9 queries or more and k small enough for its tile of 16 (128 bits: 8).  Ahead
+    // at every threshold that is not the dense route's (10M random codes, 2000 queries, k = 100,
+    // matrix cores / xor-popcount; 64 bits ht = 24: 2.9 / 4.6 ms, 26: 4.5 / 6.5, 28: 8.2 / 10.1, 29:
+    // 10.7 / 12.7; 128 bits ht = 40: 3.0 / 5.4, 48: 3.2 / 5.5, 56: 8.3 / 10.1, 60: 20.7 / 21.0).
     // psc_set_filter_route overrides the rule (for measurements).
-    bool mfma = !dense && m == 8 && nq >= kMfmaMinQueries && random_code_survival(8 * m, ht) < 0.10;
+    bool mfma = !dense && nq >= kMfmaMinQueries;
     const int forced = g_filter_route.load(std::memory_order_relaxed);
     if (forced == PSC_ROUTE_POPCOUNT) mfma = false;
-    if (forced == PSC_ROUTE_MFMA) mfma = !dense && m == 8 && nq >= kMfmaMinQueries;
+    if (forced == PSC_ROUTE_MFMA) mfma = !dense && nq >= kMfmaMinQueries;
     if (mfma) {
         rc = plan_scan(m, nq, n, k, kScanFusedMfma, &p);
         mfma = rc == PSC_OK;  // (k too large for the shape: the popcount kernel's shapes take over)
@@ -2466,8 +2528,10 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
         rc = p.nslice >= 4 ? dispatch_adc<true, true>(m, p.tq, p.nwaves, a, p.ntiles, p.lds_bytes, s)
                            : dispatch_adc<false, true>(m, p.tq, p.nwaves, a, p.ntiles, p.lds_bytes, s);
     else if (mfma)
-        rc = p.nslice >= 4 ? run_scan_mfma<16, true>(a, p.ntiles, p.lds_bytes, s)
-                           : run_scan_mfma<16, false>(a, p.ntiles, p.lds_bytes, s);
+        rc = m == 8 ? (p.nslice >= 4 ? run_scan_mfma<8, 16, true>(a, p.ntiles, p.lds_bytes, s)
+                                     : run_scan_mfma<8, 16, false>(a, p.ntiles, p.lds_bytes, s))
+                    : (p.nslice >= 4 ? run_scan_mfma<16, 16, true>(a, p.ntiles, p.lds_bytes, s)
+                                     : run_scan_mfma<16, 16, false>(a, p.ntiles, p.lds_bytes, s));
     else
         rc = p.nslice >= 4 ? dispatch_scan<false, true>(m, p.tq, p.nwaves, a, p.ntiles, p.lds_bytes, s)
                            : dispatch_scan<false, false>(m, p.tq, p.nwaves, a, p.ntiles, p.lds_bytes, s);
@@ -2563,7 +2627,7 @@ int launch_ivf_scan(int m, int tq, int nwaves, int kpad, size_t lds_bytes, const
         int rc;
         if (on_matrix_cores) {
             PSC_REQUIRE(m == 8 && tq == 16 && nwaves == 16, "the matrix-core scan has one tile shape");
-            rc = run_scan_mfma<16, true, true>(a, max_tiles, lds_bytes, s);
+            rc = run_scan_mfma<8, 16, true, true>(a, max_tiles, lds_bytes, s);
         } else {
             rc = dispatch_scan<true, true>(m, tq, nwaves, a, max_tiles, lds_bytes, s);
         }

@@ -111,6 +111,28 @@ def test_survivor_set_on_the_matrix_cores(psc, force_route):
                 assert sorted(got_ids[q][got_ids[q] >= 0].tolist()) == np.flatnonzero(ref["bitmap"][q]).tolist()
 
 
+@pytest.mark.parametrize("m,nq", [(8, 9), (8, 16), (8, 33), (16, 9), (16, 16), (16, 17)])
+def test_matrix_core_filter_at_block_edges(psc, force_route, m, nq):
+    """Database sizes around the matrix-core kernel's blocks (128 codes at 64 bits, 256 at 128), its 64-code
+    loads and the stride of its 16 waves; extreme codes (all zeros, all ones, a query's own code and
+    its complement) among the random ones; thresholds up to the last before the dense route.  Integer
+    tables: sums are exact in float32, so ids and distances equal the oracle's."""
+    force_route("mfma")
+    stride = 16 * (128 if m == 8 else 256)
+    for n in (1, 15, 16, 17, 63, 65, 127, 128, 129, 255, 256, 257, stride - 1, stride + 1, 2 * stride + 130, 5 * stride - 3):
+        codes, qcodes, lut = _rand_problem(m, n, nq, seed=7 * n + nq, lut_kind="int")
+        for i, c in enumerate((np.zeros(m, np.uint8), np.full(m, 255, np.uint8), qcodes[0], ~qcodes[nq - 1])):
+            codes[(n - 1 - 5 * i) % n] = c
+        qcodes[1], qcodes[2] = 0, 255
+        for ht in (0, 1, 3 * m, 29 if m == 8 else 60):
+            print(f"case m={m} nq={nq} n={n} ht={ht}", flush=True)
+            got_ids, got_d = _run(psc, lut, qcodes, codes, ht, 50)
+            assert psc.last_scan_route().startswith("scan_mfma_kernel ")
+            ref = O.scan(lut.astype(np.float64), qcodes, codes, ht, 50)
+            nd = assert_topk_matches(got_ids, got_d, ref, lut.astype(np.float64), qcodes, codes, ht, what=f"n={n} ht={ht}")
+            assert nd == 0 and np.array_equal(got_d[ref["ids"] >= 0], ref["dists"][ref["ids"] >= 0])
+
+
 @pytest.mark.parametrize("route", ["mfma", "popcount"])
 def test_nested_prefix_patterns_at_every_threshold(psc, force_route, route):
     """Database row r = the first r bits set (r = 0..64, repeated to fill several blocks), query q =
