@@ -202,7 +202,8 @@ int psc_threshold_for_rate(const int64_t *hist_host, int nbits, double max_keep_
  * units, or (9 queries or more) a dot product of the bits as 4-bit floating point on the matrix
  * cores, whose exact result holds the same verdict in one of its bits.
  * psc_set_filter_route forces one of the two where both apply (process-wide; a measurement aid,
- * results do not depend on it); psc_last_scan_route names the kernel, tile shape, database
+ * results do not depend on it; automatic routing also knows scan_pool_kernel, for small scans, and
+ * takes it only when neither is forced); psc_last_scan_route names the kernel, tile shape, database
  * slices and workgroup count the calling thread's last scan launched, e.g.
  * "scan_mfma_kernel m=8 tq=16 waves=16 slices=2 tiles=738" ("" before the first scan). */
 #define PSC_ROUTE_AUTO 0

@@ -25,6 +25,7 @@
 //
 // Ordering everywhere: (distance, id) ascending, lower id first on equal distance.
 #include <atomic>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <type_traits>
@@ -1688,6 +1689,310 @@ adc_kernel(ScanArgs a)
     if (ft.whole && a.nslice > 1) pad_unused_slices(a, q0, nvq, tid, NW * 64);
 }
 
+// ---------------------------------------------------------------------------------------------
+// Small scans: one workgroup of 16 waves per (query, database slice).  What such a scan waits for in
+// the tiled kernels above is not the filter but the lists: with every threshold still at infinity
+// each survivor is an insertion under a lock, one after the other (100 queries x 100k codes, k = 10:
+// 74 us in scan_mfma_kernel for 6 us of filtering), besides 8 to 16 tables to stage per workgroup.
+// Here the survivors' (distance, id) keys are appended to a pool in LDS as they come; only when it
+// is full, and once at the end, are the k smallest selected, by a radix search over the bits in
+// which the keys differ (keys are distinct, ids being so).  One slice per query needs no merge; no
+// launch has to set anything up before it.
+// A wave whose keys find no place waits in `meet`; every wave comes there sooner or later, full
+// pool or no codes left, and the selection makes room and lowers the bound.
+// DENSE: every code is scored and the Hamming test is taken on those below the bound (pure ADC and
+// permissive thresholds), instead of queueing the codes that pass the test.
+// ---------------------------------------------------------------------------------------------
+constexpr int kSmallPool = 4096;   // keys
+constexpr int kSmallCodes = 8;     // codes per lane and turn
+constexpr int kSmallQueue = 128;   // (mask, position) entries per wave: fewer than 64 wait, 64 come at a time
+
+template <int M>
+struct SmallLds {
+    float lut[M * 256];
+    uint64_t pool[kSmallPool];
+    uint64_t queue[16][kSmallQueue];
+    uint64_t lo[16], hi[16];
+    uint32_t hist[256];
+    uint32_t count, stuck, kept, bin, below;
+    float bound;
+};
+
+template <int M, bool DENSE>
+__global__ void __launch_bounds__(1024)
+scan_pool_kernel(ScanArgs a, int *status, int64_t *__restrict__ ids, float *__restrict__ dists)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    PSC_LDS SmallLds<M> &s = *(PSC_LDS SmallLds<M> *)smem;
+    constexpr int WPC = M / 4;
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t words __attribute__((ext_vector_type(WPC)));
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t q = blockIdx.x / a.nslice;
+    const int slice = (int)(blockIdx.x % a.nslice);
+    const int64_t begin = (int64_t)slice * a.slice_len;
+    const int64_t end = begin + a.slice_len < a.n ? begin + a.slice_len : a.n;
+    const int len = (int)(end - begin);
+    const uint8_t *codes = a.codes + begin * M;
+    const int k = a.k;
+    if (blockIdx.x == 0 && tid == 0 && status) *status = 0;
+
+    // codes of the wave's turn `blk`: code blk + 64 l + lane in c[l]; past the end the range check
+    // answers zero
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)codes, 0, len * M, 0x00020000);
+    constexpr int kStride = 16 * 64 * kSmallCodes;
+    auto load = [&](int blk, words (&c)[kSmallCodes]) {
+        const uint32_t at = (uint32_t)(blk + lane) * (uint32_t)M;  // (below 2^31: the planner's slices hold at most 2^24 codes)
+#pragma unroll
+        for (int l = 0; l < kSmallCodes; ++l) {
+            if constexpr (M == 8) c[l] = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)(at + 64u * M * l), 0, 0);
+            else c[l] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(at + 64u * M * l), 0, 0);
+        }
+    };
+    words cur[kSmallCodes];
+    int blk = wave * 64 * kSmallCodes;
+    load(blk, cur);
+    for (int e = tid; e < M * 64; e += 1024) ((PSC_LDS f32x4 *)s.lut)[e] = ((const f32x4 *)(a.lut + q * (M * 256)))[e];
+    uint32_t qw[WPC];
+#pragma unroll
+    for (int w = 0; w < WPC; ++w) qw[w] = __builtin_amdgcn_readfirstlane(((const uint32_t *)a.qcodes)[q * WPC + w]);
+    if (tid == 0) {
+        s.count = 0u;
+        s.stuck = 0u;
+    }
+    __syncthreads();
+    float bound = __builtin_inff();  // (the same in every lane of the workgroup)
+
+    // The k smallest of the pool's n keys to its front, in any order; n > k.  By the whole workgroup.
+    auto select = [&](int n) {
+        uint64_t e[kSmallPool / 1024], lo = ~0ull, hi = 0ull;
+#pragma unroll
+        for (int i = 0; i < kSmallPool / 1024; ++i) {
+            const int p = tid + 1024 * i;
+            e[i] = p < n ? s.pool[p] : ~0ull;
+            if (p < n) {
+                lo = e[i] < lo ? e[i] : lo;
+                hi = e[i] > hi ? e[i] : hi;
+            }
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            const uint64_t l2 = __shfl_xor(lo, off, 64), h2 = __shfl_xor(hi, off, 64);
+            lo = l2 < lo ? l2 : lo;
+            hi = h2 > hi ? h2 : hi;
+        }
+        if (lane == 0) {
+            s.lo[wave] = lo;
+            s.hi[wave] = hi;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            lo = s.lo[w] < lo ? s.lo[w] : lo;
+            hi = s.hi[w] > hi ? s.hi[w] : hi;
+        }
+        // (n > k >= 1 distinct keys: lo != hi) the bits from `shift` on are searched next, those from
+        // shift + width on are `prefix`
+        const int top = 64 - __builtin_clzll(lo ^ hi);
+        int width = top < 8 ? top : 8, shift = top - width;
+        uint64_t prefix = top == 64 ? 0ull : lo >> top;
+        uint32_t need = (uint32_t)k;
+        uint64_t last;
+        while (true) {
+            if (tid < 256) s.hist[tid] = 0u;
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < kSmallPool / 1024; ++i) {
+                const uint64_t d = e[i] >> shift;
+                const bool in = tid + 1024 * i < n && (shift + width == 64 ? 0ull : d >> width) == prefix;
+                if (in) __hip_atomic_fetch_add(&s.hist[(uint32_t)d & ((1u << width) - 1u)], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            __syncthreads();
+            if (wave == 0) {
+                uint32_t h[4], sum = 0u;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    h[i] = s.hist[4 * lane + i];
+                    sum += h[i];
+                }
+                uint32_t incl = sum;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const uint32_t o = __shfl_up(incl, off, 64);
+                    if (lane >= off) incl += o;
+                }
+                uint32_t cum = incl - sum;
+                if (cum < need && incl >= need) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if (cum < need && cum + h[i] >= need) {
+                            s.bin = 4u * lane + i;
+                            s.below = cum;
+                        }
+                        cum += h[i];
+                    }
+                }
+            }
+            __syncthreads();
+            const uint32_t bin = s.bin, inside = s.hist[bin];
+            need -= s.below;
+            prefix = (prefix << width) | bin;
+            if (inside == need || shift == 0) {
+                last = ((prefix + 1) << shift) - 1;  // (prefix + 1 wraps to 0 only with every bit set: last = ~0)
+                break;
+            }
+            width = shift < 8 ? shift : 8;
+            shift -= width;
+            __syncthreads();  // (the histogram is read)
+        }
+        if (tid == 0) s.kept = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kSmallPool / 1024; ++i) {
+            const bool keep = tid + 1024 * i < n && e[i] <= last;
+            const uint64_t m = ballot64(keep);
+            uint32_t base = 0u;
+            if (lane == 0 && m) base = __hip_atomic_fetch_add(&s.kept, (uint32_t)__builtin_popcountll(m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+            if (keep) s.pool[base + prefix_count(m)] = e[i];
+        }
+        // the k-th best distance: (the largest key kept has the bits of `last` above the ones not searched)
+        uint64_t mx = 0ull;
+#pragma unroll
+        for (int i = 0; i < kSmallPool / 1024; ++i)
+            if (tid + 1024 * i < n && e[i] <= last) mx = e[i] > mx ? e[i] : mx;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            const uint64_t o = __shfl_xor(mx, off, 64);
+            mx = o > mx ? o : mx;
+        }
+        if (lane == 0) s.hi[wave] = mx;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < 16; ++w) mx = s.hi[w] > mx ? s.hi[w] : mx;
+        bound = entry_dist(mx);
+    };
+    // Where waves wait for one another: with keys that found no place (stuck) or without codes left.
+    // True when no wave is stuck (then all are done); otherwise there is room again.
+    auto meet = [&](bool stuck) {
+        if (stuck && lane == 0) __hip_atomic_fetch_add(&s.stuck, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __syncthreads();
+        const bool done = s.stuck == 0u;
+        if (!done) {
+            select(kSmallPool);  // (a wave is stuck: the pool is full; k <= 1024 < kSmallPool)
+            if (tid == 0) {
+                s.count = (uint32_t)k;
+                s.stuck = 0u;
+            }
+            __syncthreads();
+        }
+        return done;
+    };
+    // Append the lanes' keys that are still below the bound.
+    auto append = [&](bool pass, float d, uint32_t pos) {
+        const uint64_t key = pack_entry(d, pos);
+        while (true) {
+            pass = pass & (d <= bound);
+            const uint64_t m = ballot64(pass);
+            if (m == 0) return;
+            const int n = __builtin_popcountll(m);
+            uint32_t base = 0u;
+            if (lane == 0) base = __hip_atomic_fetch_add(&s.count, (uint32_t)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+            const uint32_t at = base + (uint32_t)prefix_count(m);
+            if (pass && at < (uint32_t)kSmallPool) {
+                s.pool[at] = key;
+                pass = false;
+            }
+            if (base + (uint32_t)n <= (uint32_t)kSmallPool) return;
+            meet(true);
+        }
+    };
+    auto score = [&](const words &c) {
+        float d = s.lut[c[0] & 0xffu];
+#pragma unroll
+        for (int j = 1; j < M; ++j) d += s.lut[j * 256 + ((c[j >> 2] >> (8 * (j & 3))) & 0xffu)];
+        return d;
+    };
+
+    PSC_LDS uint64_t *queue = s.queue[wave];
+    int fill = 0;
+    auto score_queued = [&](int n) {  // the newest n entries, one survivor of each; what is left of them goes back
+        __builtin_amdgcn_wave_barrier();
+        fill -= n;
+        const uint64_t e = lane < n ? queue[fill + lane] : 0ull;
+        __builtin_amdgcn_wave_barrier();
+        uint32_t sv = (uint32_t)e;
+        const uint32_t pos = lane < n ? (uint32_t)(e >> 32) + 64u * (uint32_t)__builtin_ctz(sv | 0x80000000u) : 0u;
+        const words c = *(const words *)(codes + (uint64_t)pos * M);
+        sv &= sv - 1u;
+        const uint64_t m = ballot64(sv != 0u);
+        if (sv != 0u) queue[fill + prefix_count(m)] = (e >> 32 << 32) | sv;
+        fill += __builtin_popcountll(m);
+        append(lane < n, score(c), pos);
+    };
+    while (blk < len) {
+        words c[kSmallCodes];
+#pragma unroll
+        for (int l = 0; l < kSmallCodes; ++l) c[l] = cur[l];
+        load(blk + kStride, cur);
+        if constexpr (DENSE) {
+#pragma unroll
+            for (int l = 0; l < kSmallCodes; ++l) {
+                const int pos = blk + 64 * l + lane;
+                const float d = score(c[l]);
+                bool pass = (pos < len) & (d <= bound);
+                if (ballot64(pass)) {
+                    uint32_t h = a.bias;
+#pragma unroll
+                    for (int w = 0; w < WPC; ++w) h += (uint32_t)__popc(c[l][w] ^ qw[w]);
+                    append(pass & ((int32_t)h >= 0), d, (uint32_t)pos);
+                }
+            }
+        } else {
+            uint32_t sv = 0u;
+#pragma unroll
+            for (int l = 0; l < kSmallCodes; ++l) {
+                uint32_t h = a.bias;
+#pragma unroll
+                for (int w = 0; w < WPC; ++w) h += (uint32_t)__popc(c[l][w] ^ qw[w]);
+                sv |= ((int32_t)h >= 0 && blk + 64 * l + lane < len) ? 1u << l : 0u;
+            }
+            const uint64_t m = ballot64(sv != 0u);
+            if (sv != 0u) queue[fill + prefix_count(m)] = ((uint64_t)(uint32_t)(blk + lane) << 32) | sv;
+            fill += __builtin_popcountll(m);
+            while (fill >= 64) score_queued(64);
+        }
+        blk += kStride;
+    }
+    if constexpr (!DENSE) {
+        while (fill > 0) score_queued(fill < 64 ? fill : 64);
+    }
+    while (!meet(false)) {}
+    int n = (int)s.count;
+    if (n > k) {
+        __syncthreads();
+        select(n);
+        n = k;
+    }
+    __syncthreads();
+    // every key to its rank among the n <= k <= 1024 kept
+    const int64_t o = (a.nslice == 1 ? q : q * a.nslice + slice) * k;
+    float *od = a.nslice == 1 ? dists : a.part_d;
+    int64_t *oi = a.nslice == 1 ? ids : a.part_i;
+    if (tid < n) {
+        const uint64_t key = s.pool[tid];
+        int rank = 0;
+        for (int j = 0; j < n; ++j) rank += s.pool[j] < key ? 1 : 0;
+        od[o + rank] = entry_dist(key);
+        oi[o + rank] = begin + (int64_t)entry_id(key);
+    } else if (tid < k) {
+        od[o + tid] = __builtin_inff();
+        oi[o + tid] = (int64_t)-1;
+    }
+}
+
 // Merge the nslice sorted partial lists of each query into the final k (one wave per query).
 // Lane l owns lists l, l + 64, ...: it keeps the head of each in registers together with the
 // entry after it, so that a step of the merge (pick the smallest head of the wave, advance that
@@ -2176,6 +2481,21 @@ int run_adc(const ScanArgs &a, int64_t ntiles, size_t lds, hipStream_t s)
     return PSC_OK;
 }
 
+template <int M, bool DENSE>
+int run_scan_pool(const ScanArgs &a, int *status, int64_t *ids, float *dists, hipStream_t s)
+{
+    static std::atomic<bool> configured{false};
+    if (!configured.load(std::memory_order_acquire)) {
+        PSC_HIP_TRY(hipFuncSetAttribute((const void *)scan_pool_kernel<M, DENSE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)sizeof(SmallLds<M>)));
+        configured.store(true, std::memory_order_release);
+    }
+    hipLaunchKernelGGL((scan_pool_kernel<M, DENSE>), dim3((unsigned)(a.nq * a.nslice)), dim3(1024), sizeof(SmallLds<M>), s, a,
+                       status, ids, dists);
+    PSC_HIP_TRY(hipGetLastError());
+    return PSC_OK;
+}
+
 template <bool SHARE, bool FILTER>
 int dispatch_adc(int m, int tq, int nwaves, const ScanArgs &a, int64_t ntiles, size_t lds, hipStream_t s)
 {
@@ -2430,6 +2750,50 @@ static void set_exchange(ScanArgs &a, int slots, int k)
     }
 }
 
+// Whether a flat scan takes scan_pool_kernel, and in how many slices per query (0: it does not): two
+// estimates in microseconds, fitted to measurements over 50k .. 10M codes x 1 .. 10k queries.
+//  * pool: 256 workgroups run at a time; one takes 10 us besides its codes (0.13 us per 1000; scoring
+//    them all 0.37 at 64 bits, 0.72 at 128), all together no more than memory gives (every query
+//    reads the codes for itself); a merge 10 us and its lists' entries.
+//  * tiled: the pairs at the kernels' rates, plus about k (1 + ln(survivors / k)) insertions per list,
+//    one after the other, 0.7 us each, for every round of workgroups.
+// E.g. (pool / tiled, whole call with 25 us of launches): 100 queries x 100k, k = 10 31 / 86 us, 300k,
+// k = 100 60 / 181, 1000 x 100k, k = 100 128 / 564, 10 x 1M pure ADC, k = 100 65 / 257, 1 x 10M 49 / 150;
+// 100 x 1M, k = 10 93 / 84, 4000 x 100k, k = 10 421 / 130.
+static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool dense, const ScanPlan &p, size_t ws_bytes)
+{
+    // (a workgroup per query: past 4096 queries the tiles are ahead; past the caches every query reads
+    //  memory for itself: 50M codes of 64 bits, 1 query 138 / 179 us, 2 queries 205 / 181, 400M 786 / 644)
+    const double bytes = (double)n * m;
+    if (nq > 4096 || bytes > (nq == 1 ? 400e6 : 128e6)) return 0;
+    const double kilo = dense ? (m == 8 ? 0.37 : 0.72) : 0.13;
+    const double memory = (double)nq * bytes / (bytes < 128e6 ? 1e7 : 5.8e6);
+    double best = 1e300;
+    int slices = 0;
+    for (int64_t sN = 1; sN <= 256 && (sN == 1 || (sN * nq <= 256 && sN * 8192 <= n)); sN *= 2) {
+        if ((n + sN - 1) / sN > (1 << 24)) continue;
+        const double rounds = (double)((nq * sN + 255) / 256);
+        const double t = std::max(rounds * (10.0 + 1e-3 * kilo * (double)n / (double)sN), memory) +
+                         (sN > 1 ? 10.0 + 1e-3 * (double)(sN * k) : 0.0);
+        if (t < best) {
+            best = t;
+            slices = (int)sN;
+        }
+    }
+    if (slices == 0) return 0;
+    const double keep = ht >= 8 * m ? 1.0 : std::min(1.0, random_code_survival(8 * m, ht) + 0.01);
+    const double whole = p.tiles_one > 0 ? (double)n : (double)p.slice_len;
+    const double insertions = k * (1.0 + std::log(std::max(1.0, keep * whole / k)));
+    const double rounds = std::max(1.0, (double)p.ntiles / (256.0 * p.wgs_per_cu));
+    const double pairs = (double)((nq + p.tq - 1) / p.tq * p.tq) * (double)n;
+    const double rate = dense ? (m == 8 ? 1.45e6 : 0.75e6) : (m == 8 ? 5e6 : 3.5e6);
+    const double tiled = 6.0 + std::max(pairs / rate, bytes / 5.8e6) + 0.7 * rounds * insertions +
+                         (p.nslice > 1 ? 1e-3 * (double)(p.nslice * k) : 0.0);
+    if (best > 0.9 * tiled) return 0;
+    const size_t need = 256 + ((size_t)nq * slices * k * sizeof(float) + 255) / 256 * 256 + (size_t)nq * slices * k * sizeof(int64_t);
+    return need <= ws_bytes ? slices : 0;
+}
+
 int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t nq,
                 const uint8_t *codes_dev, int64_t n, int ht, int k, int64_t skip_first,
                 bool clear_status, int64_t *ids_dev, float *dists_dev, void *ws, size_t ws_bytes,
@@ -2502,6 +2866,21 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
     // the k-th best: pub_kth words x pub_r entries >= k, with pub_kth about 0.4 of the words (the
     // value then sits near the (1.3 k)-th best of everything scanned so far)
     set_exchange(a, p.pub_slots, k);
+    const int pool_slices = forced == PSC_ROUTE_AUTO && skip_first < 0 ? pool_scan_slices(m, nq, n, k, ht, dense, p, ws_bytes) : 0;
+    if (pool_slices > 0) {
+        a.nslice = pool_slices;
+        a.slice_len = ((n + pool_slices - 1) / pool_slices + 63) / 64 * 64;
+        a.nslice = (int)((n + a.slice_len - 1) / a.slice_len);  // (no empty slice)
+        a.part_d = (float *)((char *)ws + 256);
+        a.part_i = (int64_t *)((char *)a.part_d + ((size_t)nq * a.nslice * k * sizeof(float) + 255) / 256 * 256);
+        int *status = clear_status ? a.status : nullptr;
+        if (m == 8) rc = dense ? run_scan_pool<8, true>(a, status, ids_dev, dists_dev, s) : run_scan_pool<8, false>(a, status, ids_dev, dists_dev, s);
+        else rc = dense ? run_scan_pool<16, true>(a, status, ids_dev, dists_dev, s) : run_scan_pool<16, false>(a, status, ids_dev, dists_dev, s);
+        if (rc != PSC_OK) return rc;
+        note_route(dense ? "scan_pool_kernel+all" : "scan_pool_kernel", m, 1, 16, a.nslice, nq * a.nslice);
+        if (a.nslice == 1) return PSC_OK;
+        return launch_merge(a.part_d, a.part_i, nq, a.nslice, k, a.status, ids_dev, dists_dev, s);
+    }
     const int64_t nwords = nq * p.pub_slots;
     hipLaunchKernelGGL(init_scan_kernel, dim3((unsigned)((nwords + 255) / 256)), dim3(256), 0, s, a.gthr, nwords,
                        clear_status ? a.status : (int *)nullptr);

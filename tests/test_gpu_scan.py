@@ -133,6 +133,27 @@ def test_matrix_core_filter_at_block_edges(psc, force_route, m, nq):
             assert nd == 0 and np.array_equal(got_d[ref["ids"] >= 0], ref["dists"][ref["ids"] >= 0])
 
 
+@pytest.mark.parametrize("m,n,nq,k,lut_kind", [
+    (8, 63, 3, 100, "int"), (8, 513, 2, 100, "int"),          # fewer codes than a wave's turn, one more
+    (8, 8_191, 5, 100, "int"), (16, 8_193, 5, 100, "int"),    # around the workgroup's turn of 8192 codes
+    (8, 100_003, 1, 100, "int"), (16, 40_001, 7, 100, "float"),  # several slices per query, merged
+    (8, 50_000, 150, 64, "int"), (16, 50_001, 150, 200, "int"),  # one slice; many exact ties
+    (8, 60_000, 4, 1024, "float"), (16, 60_000, 130, 1024, "int"),  # the largest k
+])
+def test_pool_scan(psc, m, n, nq, k, lut_kind):
+    """Small scans: survivors' keys pooled and selected.  Thresholds on both sides of the dense route (where
+    every code enters a pool of 4096 until the first selection), exact ties and the ends of the sizes."""
+    codes, qcodes, lut = _rand_problem(m, n, nq, seed=31 * m + n, lut_kind=lut_kind)
+    for ht in (0, 3 * m, 29 if m == 8 else 60, 4 * m, 8 * m):
+        print(f"case m={m} n={n} nq={nq} k={k} ht={ht}", flush=True)
+        got_ids, got_d = _run(psc, lut, qcodes, codes, ht, k)
+        assert psc.last_scan_route().startswith("scan_pool_kernel"), psc.last_scan_route()
+        ref = O.scan(lut.astype(np.float64), qcodes, codes, ht, k)
+        nd = assert_topk_matches(got_ids, got_d, ref, lut.astype(np.float64), qcodes, codes, ht, what=f"n={n} ht={ht}")
+        if lut_kind == "int":
+            assert nd == 0 and np.array_equal(got_d[ref["ids"] >= 0], ref["dists"][ref["ids"] >= 0])
+
+
 @pytest.mark.parametrize("route", ["mfma", "popcount"])
 def test_nested_prefix_patterns_at_every_threshold(psc, force_route, route):
     """Database row r = the first r bits set (r = 0..64, repeated to fill several blocks), query q =
