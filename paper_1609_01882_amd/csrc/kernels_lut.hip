@@ -73,18 +73,15 @@ lut_kernel(const float *__restrict__ cb, int dim, int m, const float *__restrict
     }
 }
 
-// One thread = one row and one sub-quantizer; the sub-codebook sits in LDS and is read by all
-// lanes at the same address (broadcast), the row's sub-vector sits in registers.
+// One thread = one row and one sub-quantizer; the sub-codebook, at the same address in every lane,
+// comes through the scalar cache, the row's sub-vector sits in registers.
 template <int DSUB>
 __global__ void __launch_bounds__(256)
 encode_kernel(const float *__restrict__ cb, int dim, int m, const float *__restrict__ x,
               int64_t nrows, RowMap map, uint8_t *__restrict__ codes)
 {
-    __shared__ float cen[kCentroids * DSUB];
     const int j = blockIdx.y;
-    for (int e = threadIdx.x; e < kCentroids * DSUB; e += 256)
-        cen[e] = cb[(int64_t)j * kCentroids * DSUB + e];
-    __syncthreads();
+    const float *__restrict__ cen = cb + (int64_t)j * kCentroids * DSUB;
     const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (r >= nrows) return;
     float v[DSUB];

@@ -15,10 +15,11 @@ namespace psc {
 namespace {
 
 // ---------------------------------------------------------------------------------------------
-// Product quantizer: grid (row blocks, m).  A workgroup keeps sub-codebook j and a private copy of
-// its cells' sums (float32: a workgroup adds a few members per cell) and counts in LDS, walks its
-// share of the rows (one row per thread and turn), and adds its sums to the global ones (double)
-// at the end.  Per row it also stores the cell and the distance, for the refill of empty cells.
+// Product quantizer: grid (row blocks, m).  A workgroup keeps a private copy of its cells' sums
+// (float32: a workgroup adds a few members per cell) and counts in LDS, walks its share of the rows
+// (one row per thread and turn), and adds its sums to the global ones (double) at the end.  The
+// centroids, the same for every lane, come through the scalar cache: read from LDS, four 16-byte
+// reads per 32 vector instructions, they took as long as the arithmetic did.  Per row it also stores the cell and the distance, for the refill of empty cells.
 // ---------------------------------------------------------------------------------------------
 template <int DSUB>
 __global__ void __launch_bounds__(256)
@@ -27,14 +28,12 @@ pq_lloyd_step_kernel(const float *__restrict__ cb, int dim, int m, const float *
                      uint32_t *__restrict__ gcount, double *__restrict__ gobj)
 {
     extern __shared__ float smem[];
-    float *cen = smem;                                     // [256][DSUB]
-    float *sum = smem + kCentroids * DSUB;                 // [256][DSUB]
-    uint32_t *cnt = (uint32_t *)(smem + 2 * kCentroids * DSUB);  // [256]
+    constexpr int LD = DSUB + 1;  // pitch of a cell's sums: a coordinate's additions hit all banks, not a few
+    float *sum = smem;                                    // [256][LD]
+    uint32_t *cnt = (uint32_t *)(smem + kCentroids * LD);  // [256]
     const int j = blockIdx.y, tid = threadIdx.x;
-    for (int e = tid; e < kCentroids * DSUB; e += 256) {
-        cen[e] = cb[(int64_t)j * kCentroids * DSUB + e];
-        sum[e] = 0.f;
-    }
+    const float *__restrict__ cen = cb + (int64_t)j * kCentroids * DSUB;  // (the same address in every lane)
+    for (int e = tid; e < kCentroids * LD; e += 256) sum[e] = 0.f;
     cnt[tid] = 0u;
     __syncthreads();
     double obj = 0.0;
@@ -61,12 +60,13 @@ pq_lloyd_step_kernel(const float *__restrict__ cb, int dim, int m, const float *
         dmin[r * m + j] = best;
         obj += (double)best;
 #pragma unroll
-        for (int t = 0; t < DSUB; ++t) unsafeAtomicAdd(&sum[bi * DSUB + t], v[t]);
+        for (int t = 0; t < DSUB; ++t) unsafeAtomicAdd(&sum[bi * LD + t], v[t]);
         atomicAdd(&cnt[bi], 1u);
     }
     __syncthreads();
     for (int e = tid; e < kCentroids * DSUB; e += 256)
-        if (cnt[e / DSUB] != 0u) unsafeAtomicAdd(&gsum[(int64_t)j * kCentroids * DSUB + e], (double)sum[e]);
+        if (cnt[e / DSUB] != 0u)
+            unsafeAtomicAdd(&gsum[(int64_t)j * kCentroids * DSUB + e], (double)sum[e / DSUB * LD + e % DSUB]);
     if (cnt[tid] != 0u) atomicAdd(&gcount[j * kCentroids + tid], cnt[tid]);
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) obj += __shfl_xor(obj, off, 64);
@@ -214,12 +214,13 @@ template <int DSUB>
 int run_pq_step(const float *cb, int dim, int m, const float *x, int64_t n, uint8_t *cell, float *dmin,
                 double *gsum, uint32_t *gcount, double *gobj, hipStream_t s)
 {
-    const size_t lds = (size_t)(2 * kCentroids * DSUB + kCentroids) * sizeof(float);
+    const size_t lds = (size_t)(kCentroids * (DSUB + 1) + kCentroids) * sizeof(float);
     if (lds > 48 * 1024)
         PSC_HIP_TRY(hipFuncSetAttribute((const void *)pq_lloyd_step_kernel<DSUB>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    const int64_t want = (n + 255) / 256, cap = 2048 / m;
-    dim3 grid((unsigned)(want < cap ? want : cap), (unsigned)m);
+    // at most 2048 workgroups (8 to a compute unit), all with the same number of turns
+    const int64_t want = (n + 255) / 256, cap = 2048 / m, turns = (want + cap - 1) / cap;
+    dim3 grid((unsigned)((want + turns - 1) / turns), (unsigned)m);
     hipLaunchKernelGGL((pq_lloyd_step_kernel<DSUB>), grid, dim3(256), lds, s, cb, dim, m, x, n, cell, dmin, gsum,
                        gcount, gobj);
     PSC_HIP_TRY(hipGetLastError());
