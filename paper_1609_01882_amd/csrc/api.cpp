@@ -508,8 +508,28 @@ static int sync_coarse_to_device(const psc_index *idx)
         PSC_HIP_TRY(hipFree(idx->coarse_dev));
         idx->coarse_dev = nullptr;
     }
-    PSC_HIP_TRY(hipMalloc((void **)&idx->coarse_dev, bytes));
+    const size_t split_bytes = centroid_split_bytes(idx->nlist, idx->dim);
+    const size_t split_at = (img.size() + 63) / 64 * 64;
+    PSC_HIP_TRY(hipMalloc((void **)&idx->coarse_dev, split_at * sizeof(float) + split_bytes));
     PSC_HIP_TRY(hipMemcpy(idx->coarse_dev, img.data(), bytes, hipMemcpyHostToDevice));
+    idx->coarse_split = 0;
+    if (split_bytes != 0) {
+        float cmax2 = 0.f;
+        for (size_t l = 0; l < nl; ++l) {
+            float c2 = 0.f;
+            for (size_t t = 0; t < dim; ++t) {
+                const float v = img[l * dim + t] - img[nl * dim + t];
+                c2 += v * v;
+            }
+            cmax2 = c2 > cmax2 || c2 != c2 ? c2 : cmax2;
+        }
+        idx->coarse_cmax2 = cmax2 * 1.0001f;
+        int rc = launch_split_centroids(idx->coarse_dev, idx->coarse_dev + nl * dim, idx->nlist, idx->dim,
+                                        idx->coarse_dev + split_at, nullptr);
+        if (rc != PSC_OK) return rc;
+        PSC_HIP_TRY(hipStreamSynchronize(nullptr));
+        idx->coarse_split = split_at;
+    }
     idx->coarse_current = true;
     return PSC_OK;
 }
@@ -902,8 +922,13 @@ int psc_ivf_assign_encode(const psc_index *idx, const float *x_dev, int64_t n, i
     PSC_REQUIRE(n >= 0, "negative n");
     if (n == 0) return PSC_OK;
     PSC_REQUIRE(x_dev && list_no_dev, "null pointer");
-    rc = launch_nearest_centroid(x_dev, n, idx->dim, idx->coarse_dev, idx->nlist,
-                                 idx->coarse_dev + (size_t)idx->nlist * idx->dim, list_no_dev, (hipStream_t)stream);
+    const float *mean = idx->coarse_dev + (size_t)idx->nlist * idx->dim;
+    if (idx->coarse_split != 0)
+        rc = launch_nearest_centroid_split(x_dev, n, idx->dim, idx->coarse_dev, idx->nlist, mean,
+                                           idx->coarse_dev + idx->coarse_split, idx->coarse_cmax2, list_no_dev,
+                                           (hipStream_t)stream);
+    else
+        rc = launch_nearest_centroid(x_dev, n, idx->dim, idx->coarse_dev, idx->nlist, mean, list_no_dev, (hipStream_t)stream);
     if (rc != PSC_OK || !rescodes_dev) return rc;
     rc = need_codebook(idx);
     if (rc != PSC_OK) return rc;

@@ -504,6 +504,223 @@ nearest_centroid_mfma_kernel(const float *__restrict__ x, int64_t n, const float
 }
 
 // ---------------------------------------------------------------------------------------------
+// Nearest centroid with the search on bfloat16 products and the decision in float32.  The float32
+// products above run at 1/16 of the rate of bfloat16 ones.  Every coordinate is split in two
+// bfloat16 parts (x' = x - mu = xh + xl + rest, |rest| <= 2^-18 |x'|), and of
+//     v(c) = || c' ||^2 - 2 x'.c'
+// the three larger products xh ch + xh cl + xl ch are taken (v_mfma_f32_32x32x16_bf16, float32 sums),
+// the factor -2 sitting in x and the norm coming in as three more coordinates.  The result is off by
+//     at most E = (2^-14 + 2^-(22 - b)) (|| x' ||^2 + max || c' ||^2)
+// (3 * 2^-18 a product from what the split leaves out, a rounding per addition, and the b low bits
+// of the mantissa that carry the tile number), so the nearest centroid is among those within 2 E of
+// the smallest v.  Mostly that is one; otherwise (a few per cent of the rows on the SIFT-like
+// vectors) the distances of those centroids are taken by direct differences in float32 and the
+// smallest wins, lower number on ties.  A lane keeps the two smallest v of its columns: if a lane's
+// second is within 2 E too (or v is not a number) the row is compared with every centroid.
+//
+// The centroids' parts are laid out once per quantizer in operand order (split_centroids_kernel):
+// per tile of 32 centroids DIM / 16 pairs of 1 KB operands (high, low) and one with the norms.
+// One workgroup = 4 waves x 32 rows; the rows' parts sit in registers, tiles go through LDS, two in
+// turn.  Bound by the matrix cores: 3 DIM / 16 + 1 products of 32 cycles per 32 x 32 outputs against 48
+// vector instructions (tile number into the mantissa, minimum, median).  1M x 4096 at 128 dimensions:
+// 11.0 -> 3.1 ms (adding vectors to lists, residual codes included, 12.0 -> 4.6).
+// ---------------------------------------------------------------------------------------------
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ float part_of(float v, float &rest)
+{
+    const __bf16 h = (__bf16)v;  // nearest even
+    rest = v - (float)h;         // (exact)
+    return (float)h;
+}
+
+__global__ void __launch_bounds__(64)
+split_centroids_kernel(const float *__restrict__ cent, const float *__restrict__ mu, int nlist, int dim,
+                       bf16x8 *__restrict__ image)
+{
+    const int tile = blockIdx.x, lane = threadIdx.x, half = lane >> 5, c = tile * 32 + (lane & 31);
+    const int steps = dim / 16;
+    bf16x8 *out = image + (int64_t)tile * (2 * steps + 1) * 64;
+    double norm = 0.0;
+    for (int t = 0; t < steps; ++t) {
+        bf16x8 h, l;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int d = 16 * t + 8 * half + i;
+            const float v = c < nlist ? cent[(int64_t)c * dim + d] - mu[d] : 0.f;
+            float r1, r2;
+            h[i] = (__bf16)part_of(v, r1);
+            l[i] = (__bf16)part_of(r1, r2);
+            norm += (double)v * (double)v;
+        }
+        out[(2 * t) * 64 + lane] = h;
+        out[(2 * t + 1) * 64 + lane] = l;
+    }
+    norm += __shfl_xor(norm, 32, 64);
+    bf16x8 n;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) n[i] = (__bf16)0.f;
+    if (half == 0) {  // (places past the last centroid: farther than anything finite)
+        float v = c < nlist ? (float)norm : 3.3e38f;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            float rest;
+            n[i] = (__bf16)part_of(v, rest);
+            v = c < nlist ? rest : 0.f;
+        }
+    }
+    out[(2 * steps) * 64 + lane] = n;
+}
+
+constexpr int kSplitWaves = 4;
+template <int DIM>
+__global__ void __launch_bounds__(kSplitWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+nearest_centroid_split_kernel(const float *__restrict__ x, int64_t n, const float *__restrict__ cent,
+                              const float *__restrict__ mu, const bf16x8 *__restrict__ image, float cmax2, int nlist,
+                              int tile_bits, int32_t *__restrict__ assign)
+{
+    constexpr int KS = DIM / 16;
+    constexpr int kThreads = kSplitWaves * 64;
+    constexpr int kOps = (2 * KS + 1) * 64;  // 16-byte entries of a tile
+    __shared__ __align__(16) u32x4 tile[2][kOps];
+    __shared__ float xnorm[kSplitWaves][32];
+    const int tid = (int)threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, col = lane & 31;
+    const int64_t r0 = (int64_t)blockIdx.x * (32 * kSplitWaves) + wave * 32;
+
+    bf16x8 xh[KS], xl[KS], one;
+    {
+        const int64_t r = r0 + col;
+        const float *xr = x + (r < n ? r : n - 1) * DIM + 8 * half;
+        float norm = 0.f;
+#pragma unroll
+        for (int t = 0; t < KS; ++t) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float v = xr[16 * t + i] - mu[16 * t + 8 * half + i];
+                float r1, r2;
+                norm = fmaf(v, v, norm);
+                xh[t][i] = (__bf16)part_of(-2.f * v, r1);
+                xl[t][i] = (__bf16)part_of(r1, r2);
+            }
+        }
+        norm += __shfl_xor(norm, 32, 64);
+        if (half == 0) xnorm[wave][col] = norm;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) one[i] = (__bf16)(half == 0 && i < 3 ? 1.f : 0.f);
+    }
+    float best[16], next[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) best[v] = next[v] = __builtin_inff();
+    const int ntiles = (nlist + 31) / 32;
+    constexpr int kPer = 2 * KS * 64 / kThreads;  // whole turns of the workgroup, and one of wave 0 for the norms
+    static_assert(kPer * kThreads == 2 * KS * 64, "operands of a tile");
+    u32x4 hold[kPer], hold_norm = {0u, 0u, 0u, 0u};
+    auto fetch = [&](int t) {
+        const u32x4 *src = (const u32x4 *)image + (int64_t)t * kOps;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) hold[i] = src[i * kThreads + tid];
+        if (tid < 64) hold_norm = src[kPer * kThreads + tid];
+    };
+    auto put = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) tile[buf][i * kThreads + tid] = hold[i];
+        if (tid < 64) tile[buf][kPer * kThreads + tid] = hold_norm;
+    };
+    fetch(0);
+    put(0);
+    __syncthreads();
+    uint32_t keep = ~((1u << tile_bits) - 1u);
+    float low = -__builtin_inff();
+    asm("" : "+v"(keep), "+v"(low));
+    for (int t = 0; t < ntiles; ++t) {
+        const bool more = t + 1 < ntiles;
+        fetch(more ? t + 1 : t);
+        const bf16x8 *b = (const bf16x8 *)tile[t & 1];
+        f32x16 acc;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+        bf16x8 op[2 * KS + 1];  // all operands asked for before the first product
+#pragma unroll
+        for (int s = 0; s < 2 * KS + 1; ++s) op[s] = b[(s == 0 ? 2 * KS : s - 1) * 64 + lane];
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(one, op[0], acc, 0, 0, 0);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const bf16x8 ch = op[1 + 2 * s], cl = op[2 + 2 * s];
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[s], ch, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl[s], ch, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[s], cl, acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const float d = __uint_as_float((__float_as_uint(acc[v]) & keep) | (uint32_t)t);
+            next[v] = __builtin_amdgcn_fmed3f(d, best[v], next[v]);
+            best[v] = __builtin_amdgcn_fmed3f(d, best[v], low);  // (the smaller of the two)
+        }
+        put((t + 1) & 1);  // (after the last tile: a copy nobody reads)
+        __syncthreads();
+    }
+    // every row: register v of half h is row 8 (v / 4) + 4 h + v % 4
+    const float unit = 6.103515625e-5f + __uint_as_float((uint32_t)(127 - 22 + tile_bits) << 23);
+    for (int v = 0; v < 16; ++v) {
+        float bv = best[0], nv = next[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) {
+            bv = v == i ? best[i] : bv;
+            nv = v == i ? next[i] : nv;
+        }
+        float least = bv;
+#pragma unroll
+        for (int off = 16; off >= 1; off >>= 1) least = fminf(least, __shfl_xor(least, off, 64));
+        const int row = 8 * (v / 4) + 4 * half + v % 4;
+        const float reach = least + 2.f * unit * (xnorm[wave][row] + cmax2);
+        const uint64_t near2 = __ballot(bv <= reach), deep2 = __ballot(nv <= reach);
+        const int mine = (int)(__float_as_uint(bv) & ~keep) * 32 + col;
+#pragma unroll 1
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t near = (uint32_t)(near2 >> (32 * h)), deep = (uint32_t)(deep2 >> (32 * h));
+            const int64_t r = r0 + 8 * (v / 4) + 4 * h + v % 4;
+            if (r >= n) continue;
+            int winner = 0;
+            if (deep == 0u && __builtin_popcount(near) == 1) {
+                winner = __shfl(mine, 32 * h + __builtin_ctz(near), 64);
+            } else if (deep == 0u && near != 0u) {
+                // each candidate by the whole wave: coordinates lane, lane + 64, ...
+                float bd = __builtin_inff();
+                for (uint32_t left = near; left != 0u; left &= left - 1u) {
+                    const int c = __shfl(mine, 32 * h + __builtin_ctz(left), 64);
+                    float d = 0.f;
+                    for (int e = lane; e < DIM; e += 64) {
+                        const float df = x[r * DIM + e] - cent[(int64_t)c * DIM + e];
+                        d = fmaf(df, df, d);
+                    }
+#pragma unroll
+                    for (int off = 32; off >= 1; off >>= 1) d += __shfl_xor(d, off, 64);
+                    if (d < bd || (d == bd && c < winner)) {
+                        bd = d;
+                        winner = c;
+                    }
+                }
+            } else {
+                uint64_t key = ~0ull;
+                for (int c = lane; c < nlist; c += 64) {
+                    float d = 0.f;
+                    for (int e = 0; e < DIM; ++e) {
+                        const float df = x[r * DIM + e] - cent[(int64_t)c * DIM + e];
+                        d = fmaf(df, df, d);
+                    }
+                    const uint64_t kc = order_key(d, (uint32_t)c);
+                    if (d < __builtin_inff() && kc < key) key = kc;  // (a distance that is not finite wins nothing)
+                }
+                key = wave_min_u64(key);
+                winner = key == ~0ull ? 0 : (int)(uint32_t)key;
+            }
+            if (lane == 0) assign[r] = winner;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
 // Job bookkeeping.  Jobs in query-major order are cut into blocks of kJobBlockQ queries; a
 // stable counting sort by list number (block histograms -> column prefix -> in-order scatter)
 // gives every list its jobs in ascending query order, reproducibly.
@@ -801,6 +1018,46 @@ static int run_nearest_centroid_mfma(const float *x_dev, int64_t n, const float 
 {
     hipLaunchKernelGGL((nearest_centroid_mfma_kernel<DIM, false>), dim3((unsigned)((n + 127) / 128)), dim3(256), 0, s,
                        x_dev, n, cent_dev, mu_dev, nlist, assign_dev, (float *)nullptr);
+    PSC_HIP_TRY(hipGetLastError());
+    return PSC_OK;
+}
+
+size_t centroid_split_bytes(int nlist, int dim)
+{
+    if (dim != 32 && dim != 64 && dim != 96 && dim != 128) return 0;
+    return (size_t)((nlist + 31) / 32) * (size_t)(2 * (dim / 16) + 1) * 64 * 16;
+}
+
+int launch_split_centroids(const float *cent_dev, const float *mu_dev, int nlist, int dim, void *image_dev, hipStream_t s)
+{
+    hipLaunchKernelGGL(split_centroids_kernel, dim3((unsigned)((nlist + 31) / 32)), dim3(64), 0, s, cent_dev, mu_dev, nlist, dim,
+                       (bf16x8 *)image_dev);
+    PSC_HIP_TRY(hipGetLastError());
+    return PSC_OK;
+}
+
+int launch_nearest_centroid_split(const float *x_dev, int64_t n, int dim, const float *cent_dev, int nlist,
+                                  const float *mu_dev, const void *image_dev, float cmax2, int32_t *assign_dev, hipStream_t s)
+{
+    int rc = check_dim(dim, nlist);
+    if (rc != PSC_OK) return rc;
+    if (n == 0) return PSC_OK;
+    constexpr int kRowsPer = 32 * kSplitWaves;
+    PSC_REQUIRE((n + kRowsPer - 1) / kRowsPer <= 0x7fffffffLL, "too many rows");
+    int bits = 0;  // of a tile's number
+    while ((1 << bits) < (nlist + 31) / 32) ++bits;
+    const dim3 grid((unsigned)((n + kRowsPer - 1) / kRowsPer)), block(kSplitWaves * 64);
+#define CALL(D)                                                                                                      \
+    hipLaunchKernelGGL((nearest_centroid_split_kernel<D>), grid, block, 0, s, x_dev, n, cent_dev, mu_dev,            \
+                       (const bf16x8 *)image_dev, cmax2, nlist, bits, assign_dev)
+    switch (dim) {
+    case 32: CALL(32); break;
+    case 64: CALL(64); break;
+    case 96: CALL(96); break;
+    case 128: CALL(128); break;
+    default: set_error("no split assignment for dimension %d", dim); return PSC_EINVAL;
+    }
+#undef CALL
     PSC_HIP_TRY(hipGetLastError());
     return PSC_OK;
 }

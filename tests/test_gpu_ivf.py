@@ -92,6 +92,38 @@ def test_nearest_centroid_assignment(dim, nlist, n):
         assert got[0] == 0
 
 
+@pytest.mark.parametrize("dim,nlist,n,scale", [(32, 33, 257, 1.0), (64, 31, 128, 1e-3), (96, 1025, 700, 1.0),
+                                               (128, 16384, 300, 1e4), (128, 32, 1, 1.0)])
+def test_assignment_decides_close_calls_in_float32(dim, nlist, n, scale):
+    """Rows halfway between two centroids but for 1e-4 of their distance, centroids repeated 32 places apart
+    (the same lane of the kernel) and next to each other, a row that is not finite: the search on
+    bfloat16 parts cannot tell these apart, its float32 comparison must.  Differences of direct float32
+    sums of `dim` terms: 1e-5 of the distance covers them; an exact tie goes to the lower number."""
+    import paper_1609_01882_amd as psc
+    rng = np.random.default_rng(dim * nlist)
+    cent = (rng.random((nlist, dim)) * 100).astype(np.float32)
+    for k in range(0, nlist - 33, 40):
+        cent[k + 32] = cent[k]
+        cent[k + 1] = cent[k]
+    a, b = rng.integers(0, nlist, size=n), rng.integers(0, nlist, size=n)
+    t = np.where(rng.random(n) < 0.5, 0.4999, 0.5001)[:, None]
+    x = (cent[a] * (1 - t) + cent[b] * t).astype(np.float32)
+    x, cent = (x * np.float32(scale)).astype(np.float32), (cent * np.float32(scale)).astype(np.float32)
+    idx = psc.Index(dim, 8)
+    idx.ivf_set_coarse(cent)
+    if n > 2:
+        x[n // 2, 0] = np.inf
+    got = idx.ivf_assign_encode(_dev(x), want_codes=False)[0].cpu().numpy()
+    assert got.min() >= 0 and got.max() < nlist
+    rows = np.isfinite(x).all(axis=1)
+    c64 = cent.astype(np.float64)
+    for i in np.flatnonzero(rows):
+        d = ((x[i].astype(np.float64) - c64) ** 2).sum(axis=1)
+        assert d[got[i]] <= d.min() * (1 + 1e-5) + 1e-30, (i, got[i], int(d.argmin()))
+        same = np.flatnonzero((cent == cent[got[i]]).all(axis=1))
+        assert got[i] == same.min(), (i, got[i], same)
+
+
 @pytest.fixture(scope="module")
 def ivf_many_lists():
     import paper_1609_01882_amd as psc
