@@ -731,9 +731,7 @@ __device__ __forceinline__ void score_survivors(const Lds<M, TQ> &s, const ScanA
         while (true) {
             const uint64_t m = ballot64(sv != 0u);
             if (m == 0) return;
-            int at = fill + prefix_count(m);
-            asm("" : "+v"(at));
-            bits[sv != 0u ? at : 2 * CAP] = ((uint32_t)__builtin_ctz(sv | 0x80000000u) << 27) | rel0;
+            if (sv != 0u) bits[fill + prefix_count(m)] = ((uint32_t)__builtin_ctz(sv) << 27) | rel0;
             sv &= sv - 1u;
             fill += __builtin_popcountll(m);
             if (fill < 64) continue;
@@ -745,13 +743,10 @@ __device__ __forceinline__ void score_survivors(const Lds<M, TQ> &s, const ScanA
             score_batch<M, TQ, IVF, SHARE>(s, a, batch, slice_begin, self0, ask);
         }
     } else {
-        // (lanes without a bit write to the place behind the queue instead of being masked off)
         uint64_t m = ballot64(sv != 0u);
         int total = fill + __builtin_popcountll(m);
         uint32_t at = (uint32_t)(fill + prefix_count(m));
-        asm("" : "+v"(at));  // (a select, not a branch around two instructions)
-        at = sv != 0u ? at : (uint32_t)CAP;
-        queue[at < (uint32_t)CAP ? at : (uint32_t)CAP] = ((uint64_t)rel0 << 32) | sv;
+        if (sv != 0u) queue[at < (uint32_t)CAP ? at : (uint32_t)CAP] = ((uint64_t)rel0 << 32) | sv;  // (CAP: nobody's place)
         fill = total;
         if (total < 64) return;
         uint32_t rest = 0u;  // the block's masks the queue had no place for
@@ -769,9 +764,7 @@ __device__ __forceinline__ void score_survivors(const Lds<M, TQ> &s, const ScanA
             take_batch<M, TQ, MFMA_BITS>(batch, 64, (uint32_t)__builtin_ctz(sv), (uint32_t)(e >> 32), slice_codes);
             sv &= sv - 1u;
             m = ballot64(sv != 0u);
-            at = (uint32_t)(fill + prefix_count(m));
-            asm("" : "+v"(at));
-            queue[sv != 0u ? at : (uint32_t)CAP] = (e >> 32 << 32) | sv;
+            if (sv != 0u) queue[fill + prefix_count(m)] = (e >> 32 << 32) | sv;
             fill += __builtin_popcountll(m);
             if (__builtin_expect(total > CAP, 0)) {
                 m = ballot64(rest != 0u);
