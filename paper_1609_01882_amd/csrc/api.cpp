@@ -514,16 +514,6 @@ static int sync_coarse_to_device(const psc_index *idx)
     PSC_HIP_TRY(hipMemcpy(idx->coarse_dev, img.data(), bytes, hipMemcpyHostToDevice));
     idx->coarse_split = 0;
     if (split_bytes != 0) {
-        float cmax2 = 0.f;
-        for (size_t l = 0; l < nl; ++l) {
-            float c2 = 0.f;
-            for (size_t t = 0; t < dim; ++t) {
-                const float v = img[l * dim + t] - img[nl * dim + t];
-                c2 += v * v;
-            }
-            cmax2 = c2 > cmax2 || c2 != c2 ? c2 : cmax2;
-        }
-        idx->coarse_cmax2 = cmax2 * 1.0001f;
         int rc = launch_split_centroids(idx->coarse_dev, idx->coarse_dev + nl * dim, idx->nlist, idx->dim,
                                         idx->coarse_dev + split_at, nullptr);
         if (rc != PSC_OK) return rc;
@@ -710,6 +700,17 @@ int psc_ivf_get_coarse(const psc_index *idx, float *centroids_host)
     return PSC_OK;
 }
 
+// The assignment step of the coarse quantizer's trainings, by the kernel that adds vectors to lists.
+// cent [nlist + 1][dim], the mean last; split: scratch of centroid_split_bytes.
+static int assign_to_centroids(const float *x_dev, int64_t n, int dim, const float *cent, int nlist, char *split,
+                               int32_t *assign, hipStream_t s)
+{
+    const float *mean = cent + (size_t)nlist * dim;
+    if (centroid_split_bytes(nlist, dim) == 0) return launch_nearest_centroid(x_dev, n, dim, cent, nlist, mean, assign, s);
+    PSC_TRY(launch_split_centroids(cent, mean, nlist, dim, split, s));
+    return launch_nearest_centroid_split(x_dev, n, dim, cent, nlist, mean, split, assign, s);
+}
+
 // k-means of the coarse quantizer: assignment on the device (the nearest-centroid kernel),
 // centroid update on the host in double precision.
 int psc_ivf_train_coarse(psc_index *idx, const float *x_host, int64_t n, int nlist, int iters, uint64_t seed)
@@ -739,6 +740,8 @@ int psc_ivf_train_coarse(psc_index *idx, const float *x_host, int64_t n, int nli
     PSC_TRY(scratch.get(&x_dev, (size_t)n * dim));
     PSC_TRY(scratch.get(&c_dev, (size_t)(nlist + 1) * dim));  // + the mean centroid
     PSC_TRY(scratch.get(&a_dev, (size_t)n));
+    char *split = nullptr;
+    PSC_TRY(scratch.get(&split, centroid_split_bytes(nlist, dim)));
     PSC_HIP_TRY(hipMemcpy(x_dev, x_host, (size_t)n * dim * sizeof(float), hipMemcpyHostToDevice));
     for (int it = 0; it < iters; ++it) {
         PSC_HIP_TRY(hipMemcpy(c_dev, cent.data(), cent.size() * sizeof(float), hipMemcpyHostToDevice));
@@ -750,7 +753,7 @@ int psc_ivf_train_coarse(psc_index *idx, const float *x_host, int64_t n, int nli
             for (int t = 0; t < dim; ++t) mean[(size_t)t] = (float)(acc[(size_t)t] / nlist);
             PSC_HIP_TRY(hipMemcpy(c_dev + (size_t)nlist * dim, mean.data(), (size_t)dim * sizeof(float), hipMemcpyHostToDevice));
         }
-        PSC_TRY(launch_nearest_centroid(x_dev, n, dim, c_dev, nlist, c_dev + (size_t)nlist * dim, a_dev, nullptr));
+        PSC_TRY(assign_to_centroids(x_dev, n, dim, c_dev, nlist, split, a_dev, nullptr));
         PSC_HIP_TRY(hipMemcpy(assign.data(), a_dev, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost));
         std::fill(sum.begin(), sum.end(), 0.0);
         std::fill(count.begin(), count.end(), (int64_t)0);
@@ -874,6 +877,8 @@ int psc_ivf_train_coarse_device(psc_index *idx, const float *x_dev, int64_t n, i
     int64_t *rows = nullptr;
     PSC_TRY(scratch.get(&cent, (size_t)(nlist + 1) * dim));  // + the mean centroid
     PSC_TRY(scratch.get(&assign, (size_t)n));
+    char *split = nullptr;
+    PSC_TRY(scratch.get(&split, centroid_split_bytes(nlist, dim)));
     PSC_TRY(scratch.get(&sum, (size_t)nlist * dim));
     PSC_TRY(scratch.get(&count, (size_t)nlist));
     PSC_TRY(scratch.get(&key, 1));
@@ -894,7 +899,7 @@ int psc_ivf_train_coarse_device(psc_index *idx, const float *x_dev, int64_t n, i
     PSC_TRY(launch_gather_rows(x_dev, dim, rows, nlist, cent, s));
     for (int it = 0; it < iters; ++it) {
         PSC_TRY(launch_mean_centroid(cent, nlist, dim, s));
-        PSC_TRY(launch_nearest_centroid(x_dev, n, dim, cent, nlist, cent + (size_t)nlist * dim, assign, s));
+        PSC_TRY(assign_to_centroids(x_dev, n, dim, cent, nlist, split, assign, s));
         PSC_TRY(launch_coarse_accumulate(x_dev, n, dim, assign, nlist, sum, count, s));
         PSC_HIP_TRY(hipMemcpyAsync(hcount.data(), count, (size_t)nlist * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
         PSC_HIP_TRY(hipStreamSynchronize(s));
@@ -925,7 +930,7 @@ int psc_ivf_assign_encode(const psc_index *idx, const float *x_dev, int64_t n, i
     const float *mean = idx->coarse_dev + (size_t)idx->nlist * idx->dim;
     if (idx->coarse_split != 0)
         rc = launch_nearest_centroid_split(x_dev, n, idx->dim, idx->coarse_dev, idx->nlist, mean,
-                                           idx->coarse_dev + idx->coarse_split, idx->coarse_cmax2, list_no_dev,
+                                           idx->coarse_dev + idx->coarse_split, list_no_dev,
                                            (hipStream_t)stream);
     else
         rc = launch_nearest_centroid(x_dev, n, idx->dim, idx->coarse_dev, idx->nlist, mean, list_no_dev, (hipStream_t)stream);

@@ -152,11 +152,10 @@ int launch_nearest_centroid(const float *x_dev, int64_t n, int dim, const float 
                             const float *mu_dev, int32_t *assign_dev, hipStream_t s);
 // The same with the search on bfloat16 parts of the centroids laid out beforehand (dimensions 32, 64, 96,
 // 128): bytes of the layout (0: no such kernel for the dimension), the layout, the assignment.
-// cmax2: the largest squared distance of a centroid from mu, rounded up.
 size_t centroid_split_bytes(int nlist, int dim);
 int launch_split_centroids(const float *cent_dev, const float *mu_dev, int nlist, int dim, void *image_dev, hipStream_t s);
 int launch_nearest_centroid_split(const float *x_dev, int64_t n, int dim, const float *cent_dev, int nlist,
-                                  const float *mu_dev, const void *image_dev, float cmax2, int32_t *assign_dev, hipStream_t s);
+                                  const float *mu_dev, const void *image_dev, int32_t *assign_dev, hipStream_t s);
 struct IvfJobBuffers {
     int32_t *hist;       // [nblk][2 nlist]
     int32_t *list_begin; // [2 nlist + 1] first sorted job of each sort key (see launch_build_jobs)
@@ -257,7 +256,6 @@ struct psc_index {
     std::vector<float> coarse_host;  // [nlist][dim]
     mutable float *coarse_dev = nullptr;  // [nlist][dim], their mean [dim], then (from coarse_split on) launch_split_centroids' layout
     mutable size_t coarse_split = 0;      // floats before the layout; 0: none for this dimension
-    mutable float coarse_cmax2 = 0.f;
     mutable bool coarse_current = false;
     // the lists' share of the residual tables [nlist][m][256] (launch_list_tables); follows the
     // codebook and the coarse centroids

@@ -195,10 +195,10 @@ select_probes_wave_kernel(const float *__restrict__ dist, int64_t n, int nlist, 
 
 // The same selection by a whole workgroup of 16 waves per row, for a handful of rows (a single
 // query is the case that matters): thread t holds lists t, t + 1024, ...  The nprobe-th smallest
-// (distance, list) pair is found bit by bit as above -- first over the 32 bits of the distance
-// key, then, only if several lists share that distance, over the 14 bits of the list number --
-// with one workgroup-wide count per bit (per-wave sums through LDS, two buffers in turn so that
-// one barrier per bit is enough).  The pairs up to it are exactly the nprobe lists; each goes to
+// (distance, list) pair is found by a radix search over the bits of the distance key and, only if
+// several lists share that distance, bit by bit over the 14 bits of the list number, with one
+// workgroup-wide count per bit (per-wave sums through LDS, two buffers in turn so that one barrier
+// per bit is enough).  Bound by its chain of barriers: 34 of them counting bit by bit, 9 to 15 now.  The pairs up to it are exactly the nprobe lists; each goes to
 // its rank.
 template <int KPL>
 __global__ void __launch_bounds__(1024)
@@ -208,6 +208,7 @@ select_probes_block_kernel(const float *__restrict__ dist, int nlist, int nprobe
     __shared__ uint32_t part[2][16];
     __shared__ uint64_t sel[1024];
     __shared__ uint32_t nsel;
+    __shared__ uint32_t hist[256], found[3];
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t r = blockIdx.x;
     if (settled && settled[r] >= 0) return;  // (the whole workgroup: one row)
@@ -233,11 +234,86 @@ select_probes_block_kernel(const float *__restrict__ dist, int nlist, int nprobe
         turn ^= 1;
         return total;
     };
-    uint32_t pivot = 0;
-    for (int b = 31; b >= 0; --b) {
-        const uint32_t mid = pivot | (1u << b);
-        if (count([&](int i) { return dk[i] < mid; }) < (uint32_t)nprobe) pivot = mid;
+    // The pivot: a key with nprobe keys at or below it, of which those at the nprobe-th smallest distance
+    // are the largest.  The bits in which the keys differ are searched eight at a time, by a histogram of
+    // the keys that share the bits found so far; a search ends as soon as a whole bin is taken.
+    uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+    for (int i = 0; i < KPL; ++i) {
+        if (i * 1024 + tid >= nlist) continue;
+        lo = min(lo, dk[i]);
+        hi = max(hi, dk[i]);
     }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, off, 64));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, off, 64));
+    }
+    if (lane == 0) {
+        part[0][wave] = lo;
+        part[1][wave] = hi;
+    }
+    if (tid < 256) hist[tid] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        lo = min(lo, part[0][w]);
+        hi = max(hi, part[1][w]);
+    }
+    uint32_t pivot = lo;  // (all keys equal)
+    if (lo != hi) {
+        const int top = 32 - __builtin_clz(lo ^ hi);
+        int width = top < 8 ? top : 8, shift = top - width;
+        uint32_t prefix = top == 32 ? 0u : lo >> top, need = (uint32_t)nprobe;
+        while (true) {
+#pragma unroll
+            for (int i = 0; i < KPL; ++i) {
+                const uint32_t d = dk[i] >> shift;
+                if (i * 1024 + tid < nlist && (shift + width == 32 ? 0u : d >> width) == prefix)
+                    atomicAdd(&hist[d & ((1u << width) - 1u)], 1u);
+            }
+            __syncthreads();
+            if (wave == 0) {
+                uint32_t h[4], sum = 0u;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    h[i] = hist[4 * lane + i];
+                    sum += h[i];
+                }
+                uint32_t incl = sum;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const uint32_t o = (uint32_t)__shfl_up((int)incl, off, 64);
+                    if (lane >= off) incl += o;
+                }
+                uint32_t cum = incl - sum;
+                if (cum < need && incl >= need) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if (cum < need && cum + h[i] >= need) {
+                            found[0] = 4u * lane + i;
+                            found[1] = cum;
+                            found[2] = h[i];
+                        }
+                        cum += h[i];
+                    }
+                }
+            }
+            __syncthreads();
+            const uint32_t inside = found[2];
+            need -= found[1];
+            prefix = (prefix << width) | found[0];
+            if (inside == need || shift == 0) {
+                pivot = min(((prefix + 1u) << shift) - 1u, 0xfffffffeu);  // (below the places past the last list)
+                break;
+            }
+            width = shift < 8 ? shift : 8;
+            shift -= width;
+            if (tid < 256) hist[tid] = 0u;
+            __syncthreads();
+        }
+    }
+    __syncthreads();  // (`part` and `found` are read)
     // lists at the pivot distance: all of them belong unless they are too many; then the
     // lowest-numbered ones do, up to list number `last`
     const uint32_t below = count([&](int i) { return dk[i] < pivot; });
@@ -537,7 +613,7 @@ __device__ __forceinline__ float part_of(float v, float &rest)
 
 __global__ void __launch_bounds__(64)
 split_centroids_kernel(const float *__restrict__ cent, const float *__restrict__ mu, int nlist, int dim,
-                       bf16x8 *__restrict__ image)
+                       bf16x8 *__restrict__ image, uint32_t *__restrict__ cmax2)
 {
     const int tile = blockIdx.x, lane = threadIdx.x, half = lane >> 5, c = tile * 32 + (lane & 31);
     const int steps = dim / 16;
@@ -558,6 +634,9 @@ split_centroids_kernel(const float *__restrict__ cent, const float *__restrict__
         out[(2 * t + 1) * 64 + lane] = l;
     }
     norm += __shfl_xor(norm, 32, 64);
+    // (bits of floats that are not negative are ordered as the floats are; one that is not a number
+    //  stays on top and sends every row to the comparison with all centroids)
+    if (half == 0 && c < nlist) atomicMax(cmax2, __float_as_uint((float)norm * 1.0001f));
     bf16x8 n;
 #pragma unroll
     for (int i = 0; i < 8; ++i) n[i] = (__bf16)0.f;
@@ -577,7 +656,7 @@ constexpr int kSplitWaves = 4;
 template <int DIM>
 __global__ void __launch_bounds__(kSplitWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 nearest_centroid_split_kernel(const float *__restrict__ x, int64_t n, const float *__restrict__ cent,
-                              const float *__restrict__ mu, const bf16x8 *__restrict__ image, float cmax2, int nlist,
+                              const float *__restrict__ mu, const bf16x8 *__restrict__ image, const float *__restrict__ cmax2_dev, int nlist,
                               int tile_bits, int32_t *__restrict__ assign)
 {
     constexpr int KS = DIM / 16;
@@ -661,6 +740,7 @@ nearest_centroid_split_kernel(const float *__restrict__ x, int64_t n, const floa
         __syncthreads();
     }
     // every row: register v of half h is row 8 (v / 4) + 4 h + v % 4
+    const float cmax2 = *cmax2_dev;
     const float unit = 6.103515625e-5f + __uint_as_float((uint32_t)(127 - 22 + tile_bits) << 23);
     for (int v = 0; v < 16; ++v) {
         float bv = best[0], nv = next[0];
@@ -1022,28 +1102,33 @@ static int run_nearest_centroid_mfma(const float *x_dev, int64_t n, const float 
     return PSC_OK;
 }
 
+static size_t split_operand_bytes(int nlist, int dim) { return (size_t)((nlist + 31) / 32) * (size_t)(2 * (dim / 16) + 1) * 64 * 16; }
+
 size_t centroid_split_bytes(int nlist, int dim)
 {
     if (dim != 32 && dim != 64 && dim != 96 && dim != 128) return 0;
-    return (size_t)((nlist + 31) / 32) * (size_t)(2 * (dim / 16) + 1) * 64 * 16;
+    return split_operand_bytes(nlist, dim) + 64;  // (then the largest norm)
 }
 
 int launch_split_centroids(const float *cent_dev, const float *mu_dev, int nlist, int dim, void *image_dev, hipStream_t s)
 {
+    uint32_t *cmax2 = (uint32_t *)((char *)image_dev + split_operand_bytes(nlist, dim));
+    hipLaunchKernelGGL(zero_i32_kernel, dim3(1), dim3(64), 0, s, (int32_t *)cmax2, (int64_t)1);
     hipLaunchKernelGGL(split_centroids_kernel, dim3((unsigned)((nlist + 31) / 32)), dim3(64), 0, s, cent_dev, mu_dev, nlist, dim,
-                       (bf16x8 *)image_dev);
+                       (bf16x8 *)image_dev, cmax2);
     PSC_HIP_TRY(hipGetLastError());
     return PSC_OK;
 }
 
 int launch_nearest_centroid_split(const float *x_dev, int64_t n, int dim, const float *cent_dev, int nlist,
-                                  const float *mu_dev, const void *image_dev, float cmax2, int32_t *assign_dev, hipStream_t s)
+                                  const float *mu_dev, const void *image_dev, int32_t *assign_dev, hipStream_t s)
 {
     int rc = check_dim(dim, nlist);
     if (rc != PSC_OK) return rc;
     if (n == 0) return PSC_OK;
     constexpr int kRowsPer = 32 * kSplitWaves;
     PSC_REQUIRE((n + kRowsPer - 1) / kRowsPer <= 0x7fffffffLL, "too many rows");
+    const float *cmax2 = (const float *)((const char *)image_dev + split_operand_bytes(nlist, dim));
     int bits = 0;  // of a tile's number
     while ((1 << bits) < (nlist + 31) / 32) ++bits;
     const dim3 grid((unsigned)((n + kRowsPer - 1) / kRowsPer)), block(kSplitWaves * 64);
