@@ -25,6 +25,7 @@
 //
 // Ordering everywhere: (distance, id) ascending, lower id first on equal distance.
 #include <atomic>
+#include <cfloat>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -630,6 +631,10 @@ __device__ __forceinline__ void take_batch(Batch<M> &p, const int n, const uint3
     }
 }
 
+// Sub-quantizers summed before a survivor may be rejected.
+template <int M>
+constexpr int kEarly = (M * 3) / 8;
+
 // Score a batch and feed the survivors that beat the current threshold to the lists.  `self0 + q` =
 // the position query slot q must not return (graph mode; a value no position can take otherwise).
 template <int M, int TQ, bool IVF, bool SHARE>
@@ -666,7 +671,7 @@ __device__ __forceinline__ void score_batch(const Lds<M, TQ> &s, const ScanArgs 
             // rejects nearly every survivor, and the other gathers are issued only if some lane
             // of the wave still needs them.  The additions keep their order (j ascending), so a
             // distance that is finished is the same float32 as without the shortcut.
-            constexpr int M0 = (M * 3) / 8;
+            constexpr int M0 = kEarly<M>;
             float tv[M];
 #pragma unroll
             for (int j = M0 - 1; j >= 0; --j) {
@@ -1695,6 +1700,7 @@ adc_kernel(ScanArgs a)
 // pool or no codes left, and the selection makes room and lowers the bound.
 // DENSE: every code is scored and the Hamming test is taken on those below the bound (pure ADC and
 // permissive thresholds), instead of queueing the codes that pass the test.
+// `open`: the largest distance that is listed while there are fewer than k.
 // ---------------------------------------------------------------------------------------------
 constexpr int kSmallPool = 4096;   // keys
 constexpr int kSmallCodes = 8;     // codes per lane and turn
@@ -1713,7 +1719,7 @@ struct SmallLds {
 
 template <int M, bool DENSE>
 __global__ void __launch_bounds__(1024)
-scan_pool_kernel(ScanArgs a, int *status, int64_t *__restrict__ ids, float *__restrict__ dists)
+scan_pool_kernel(ScanArgs a, float open, int *status, int64_t *__restrict__ ids, float *__restrict__ dists)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     PSC_LDS SmallLds<M> &s = *(PSC_LDS SmallLds<M> *)smem;
@@ -1755,7 +1761,7 @@ scan_pool_kernel(ScanArgs a, int *status, int64_t *__restrict__ ids, float *__re
         s.stuck = 0u;
     }
     __syncthreads();
-    float bound = __builtin_inff();  // (the same in every lane of the workgroup)
+    float bound = open;  // (the same in every lane of the workgroup)
 
     // The k smallest of the pool's n keys to its front, in any order; n > k.  By the whole workgroup.
     auto select = [&](int n) {
@@ -1902,11 +1908,17 @@ scan_pool_kernel(ScanArgs a, int *status, int64_t *__restrict__ ids, float *__re
             meet(true);
         }
     };
+    // (a sum that is not a number after kEarly sub-quantizers: at infinity in the fused form, as
+    //  score_batch has it; one that comes to be so later, and any in the dense form, passes nowhere)
     auto score = [&](const words &c) {
         float d = s.lut[c[0] & 0xffu];
+        bool number = true;
 #pragma unroll
-        for (int j = 1; j < M; ++j) d += s.lut[j * 256 + ((c[j >> 2] >> (8 * (j & 3))) & 0xffu)];
-        return d;
+        for (int j = 1; j < M; ++j) {
+            d += s.lut[j * 256 + ((c[j >> 2] >> (8 * (j & 3))) & 0xffu)];
+            if (j == kEarly<M> - 1) number = d == d;
+        }
+        return DENSE || number ? d : __builtin_inff();
     };
 
     PSC_LDS uint64_t *queue = s.queue[wave];
@@ -2107,7 +2119,7 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
 template <int KPL>
 __global__ void __launch_bounds__(1024)
 merge_select_kernel(const float *__restrict__ part_d, const int64_t *__restrict__ part_i, int nslice, int k,
-                    const int *__restrict__ status, int64_t *__restrict__ ids, float *__restrict__ dists)
+                    bool infinite, const int *__restrict__ status, int64_t *__restrict__ ids, float *__restrict__ dists)
 {
     __shared__ uint32_t part[2][16];
     __shared__ __align__(16) uint32_t selk[1024];
@@ -2138,9 +2150,9 @@ merge_select_kernel(const float *__restrict__ part_d, const int64_t *__restrict_
     const int64_t *pi = part_i + q * total;
     const bool poisoned = *status != 0;
     constexpr uint32_t kNone = 0xffffffffu;  // padding and places past the end; real keys stay below
-    // (Places a list does not fill hold distance +infinity, which no scored code has: the distances
-    //  alone tell them apart, so all loads of a thread are independent of one another and in flight
-    //  together -- one trip to memory instead of one per entry.)
+    // (Places a list does not fill hold distance +infinity, which no scored code has unless `infinite`:
+    //  the distances alone tell them apart, so all loads of a thread are independent of one another and
+    //  in flight together -- one trip to memory instead of one per entry.)
     uint32_t dk[KPL];
     {
         float dv[KPL];
@@ -2152,7 +2164,8 @@ merge_select_kernel(const float *__restrict__ part_d, const int64_t *__restrict_
 #pragma unroll
         for (int i = 0; i < KPL; ++i) {
             const int e = i * 1024 + tid;
-            dk[i] = (e < total && dv[i] != __builtin_inff()) ? min(dist_key(dv[i]), kNone - 1u) : kNone;
+            const bool real = e < total && (dv[i] != __builtin_inff() || (infinite && pi[e] >= 0));
+            dk[i] = real ? min(dist_key(dv[i]), kNone - 1u) : kNone;
         }
     }
     if (tid == 0) nsel = 0u;
@@ -2298,18 +2311,26 @@ merge_select_kernel(const float *__restrict__ part_d, const int64_t *__restrict_
     }
 }
 
+bool merge_selects(int64_t nq, int nlists, int k)
+{
+    return (nq <= kMergeSelectQueries || (nq <= kMergeSelectManyQueries && nlists >= 32)) &&
+           (int64_t)nlists * k <= kMergeSelectEntries && k >= kMergeSelectMinK && k <= 1024;
+}
+
 // One wave per query; the lists are spread over the lanes, OWN to a lane.
-int launch_merge(const float *part_d, const int64_t *part_i, int64_t nq, int nlists, int k, const int *status,
-                 int64_t *ids, float *dists, hipStream_t s)
+// infinite: codes at distance +infinity are listed by the selecting merge too (the other always does).
+int launch_merge(const float *part_d, const int64_t *part_i, int64_t nq, int nlists, int k, bool infinite,
+                 const int *status, int64_t *ids, float *dists, hipStream_t s)
 {
     PSC_REQUIRE(nlists >= 1 && nlists <= 1024, "between 1 and 1024 partial lists per query, got %d", nlists);
     const dim3 grid((unsigned)nq), block(64);
-    if ((nq <= kMergeSelectQueries || (nq <= kMergeSelectManyQueries && nlists >= 32)) &&
-        (int64_t)nlists * k <= kMergeSelectEntries && k >= kMergeSelectMinK && k <= 1024) {
+    if (merge_selects(nq, nlists, k)) {
         if ((int64_t)nlists * k <= 8 * 1024)
-            hipLaunchKernelGGL(merge_select_kernel<8>, grid, dim3(1024), 0, s, part_d, part_i, nlists, k, status, ids, dists);
+            hipLaunchKernelGGL(merge_select_kernel<8>, grid, dim3(1024), 0, s, part_d, part_i, nlists, k, infinite, status,
+                               ids, dists);
         else
-            hipLaunchKernelGGL(merge_select_kernel<32>, grid, dim3(1024), 0, s, part_d, part_i, nlists, k, status, ids, dists);
+            hipLaunchKernelGGL(merge_select_kernel<32>, grid, dim3(1024), 0, s, part_d, part_i, nlists, k, infinite, status,
+                               ids, dists);
         PSC_HIP_TRY(hipGetLastError());
         return PSC_OK;
     }
@@ -2475,7 +2496,7 @@ int run_adc(const ScanArgs &a, int64_t ntiles, size_t lds, hipStream_t s)
 }
 
 template <int M, bool DENSE>
-int run_scan_pool(const ScanArgs &a, int *status, int64_t *ids, float *dists, hipStream_t s)
+int run_scan_pool(const ScanArgs &a, float open, int *status, int64_t *ids, float *dists, hipStream_t s)
 {
     static std::atomic<bool> configured{false};
     if (!configured.load(std::memory_order_acquire)) {
@@ -2484,7 +2505,7 @@ int run_scan_pool(const ScanArgs &a, int *status, int64_t *ids, float *dists, hi
         configured.store(true, std::memory_order_release);
     }
     hipLaunchKernelGGL((scan_pool_kernel<M, DENSE>), dim3((unsigned)(a.nq * a.nslice)), dim3(1024), sizeof(SmallLds<M>), s, a,
-                       status, ids, dists);
+                       open, status, ids, dists);
     PSC_HIP_TRY(hipGetLastError());
     return PSC_OK;
 }
@@ -2709,7 +2730,7 @@ int plan_scan(int m, int64_t nq, int64_t n, int k, int kind, ScanPlan *plan)
 int merge_partial_lists(const float *part_d, const int64_t *part_i, int64_t nq, int nlists, int k, const int *status,
                         int64_t *ids, float *dists, hipStream_t s)
 {
-    return launch_merge(part_d, part_i, nq, nlists, k, status, ids, dists, s);
+    return launch_merge(part_d, part_i, nq, nlists, k, false, status, ids, dists, s);
 }
 
 int shared_threshold_words(int64_t lists_per_query)
@@ -2867,12 +2888,19 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
         a.part_d = (float *)((char *)ws + 256);
         a.part_i = (int64_t *)((char *)a.part_d + ((size_t)nq * a.nslice * k * sizeof(float) + 255) / 256 * 256);
         int *status = clear_status ? a.status : nullptr;
-        if (m == 8) rc = dense ? run_scan_pool<8, true>(a, status, ids_dev, dists_dev, s) : run_scan_pool<8, false>(a, status, ids_dev, dists_dev, s);
-        else rc = dense ? run_scan_pool<16, true>(a, status, ids_dev, dists_dev, s) : run_scan_pool<16, false>(a, status, ids_dev, dists_dev, s);
+        // (codes at distance +infinity are listed where the merge of the tiled kernels' lists would list them)
+        const bool infinite = !merge_selects(nq, p.nslice, k);
+        const float open = infinite ? HUGE_VALF : FLT_MAX;
+        if (m == 8)
+            rc = dense ? run_scan_pool<8, true>(a, open, status, ids_dev, dists_dev, s)
+                       : run_scan_pool<8, false>(a, open, status, ids_dev, dists_dev, s);
+        else
+            rc = dense ? run_scan_pool<16, true>(a, open, status, ids_dev, dists_dev, s)
+                       : run_scan_pool<16, false>(a, open, status, ids_dev, dists_dev, s);
         if (rc != PSC_OK) return rc;
         note_route(dense ? "scan_pool_kernel+all" : "scan_pool_kernel", m, 1, 16, a.nslice, nq * a.nslice);
         if (a.nslice == 1) return PSC_OK;
-        return launch_merge(a.part_d, a.part_i, nq, a.nslice, k, a.status, ids_dev, dists_dev, s);
+        return launch_merge(a.part_d, a.part_i, nq, a.nslice, k, infinite, a.status, ids_dev, dists_dev, s);
     }
     const int64_t nwords = nq * p.pub_slots;
     hipLaunchKernelGGL(init_scan_kernel, dim3((unsigned)((nwords + 255) / 256)), dim3(256), 0, s, a.gthr, nwords,
@@ -2910,7 +2938,7 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
     if (rc != PSC_OK) return rc;
     note_route(ht >= nbits ? "adc_kernel" : dense ? "adc_kernel+filter" : mfma ? "scan_mfma_kernel" : "scan_kernel",
                m, p.tq, p.nwaves, p.nslice, p.ntiles);
-    return launch_merge(a.part_d, a.part_i, nq, p.nslice, k, a.status, ids_dev, dists_dev, s);
+    return launch_merge(a.part_d, a.part_i, nq, p.nslice, k, false, a.status, ids_dev, dists_dev, s);
 }
 
 // Which filter the grouped inverted-file scan takes.  The matrix-core kernel needs 64-bit codes,
@@ -3008,7 +3036,7 @@ int launch_ivf_scan(int m, int tq, int nwaves, int kpad, size_t lds_bytes, const
     note_route(on_matrix_cores ? (list_tab_dev ? "scan_mfma_kernel+lists" : "scan_mfma_kernel+lists+direct-tables")
                                : (list_tab_dev ? "scan_kernel+lists" : "scan_kernel+lists+direct-tables"),
                m, tq, nwaves, 1, max_tiles);
-    return launch_merge(part_d, part_i, nq, nprobe, k, status, ids_dev, dists_dev, s);
+    return launch_merge(part_d, part_i, nq, nprobe, k, false, status, ids_dev, dists_dev, s);
 }
 
 int launch_hamming_filter(int m, const uint8_t *qcodes_dev, int64_t nq, const uint8_t *codes_dev,

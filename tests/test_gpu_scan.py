@@ -154,6 +154,46 @@ def test_pool_scan(psc, m, n, nq, k, lut_kind):
             assert nd == 0 and np.array_equal(got_d[ref["ids"] >= 0], ref["dists"][ref["ids"] >= 0])
 
 
+@pytest.mark.parametrize("m,n,nq,k", [(8, 20_000, 12, 40), (8, 100_003, 40, 300), (16, 20_000, 12, 300),
+                                      (16, 40_001, 1, 1024), (8, 40_001, 2, 50), (8, 1_200_000, 2, 600)])
+def test_small_scans_answer_tables_that_are_not_finite_as_the_tiled_kernels_do(psc, force_route, m, n, nq, k):
+    """Table entries that are not numbers (of a query that is not) or infinite: the fused tiled kernels put a
+    survivor at distance +inf where the sum over the first 3 m / 8 sub-quantizers is not a number and leave
+    it out where only a later entry makes it so; codes at +inf come after all others in order of their ids,
+    except that the merge for a handful of queries and 64 results or more leaves them out.  Small scans, pooled
+    in one slice or several, answer the same."""
+    codes, qcodes, lut = _rand_problem(m, n, nq, seed=5 * m + nq, lut_kind="int")
+    early = 3 * m // 8
+    lut[0, early - 1, ::2] = np.nan       # some codes, in an early sub-quantizer
+    lut[0, early - 1, 1::4] = np.inf      # not finite, but a number
+    if nq > 1:
+        lut[1] = np.nan                   # a query that is no vector
+    if nq > 2:
+        lut[2, m - 1, ::3] = np.nan       # a late sub-quantizer
+        lut[3, 0, :] = np.inf
+    for ht in (3 * m, 3 * m + 2, 4 * m, 8 * m):
+        print(f"case m={m} n={n} nq={nq} k={k} ht={ht}", flush=True)
+        got_ids, got_d = _run(psc, lut, qcodes, codes, ht, k)
+        assert psc.last_scan_route().startswith("scan_pool_kernel"), psc.last_scan_route()
+        for route in ("popcount", "mfma") if nq >= 9 else ("popcount",):
+            force_route(route)
+            want_ids, want_d = _run(psc, lut, qcodes, codes, ht, k)
+            force_route("auto")
+            assert np.array_equal(got_ids, want_ids) and np.array_equal(got_d, want_d), (m, ht, route)
+        if k >= 64 or ht >= 4 * m:
+            continue
+        near = O.hamming_matrix(qcodes, codes) <= ht  # by the rule as stated
+        for q in range(nq):
+            rows = np.flatnonzero(near[q])
+            entry = np.stack([lut[q, j, codes[rows, j]] for j in range(m)], 1).astype(np.float64)
+            d = entry.sum(1)
+            d[np.isnan(entry[:, :early].sum(1))] = np.inf
+            rows, d = rows[~np.isnan(d)], d[~np.isnan(d)]
+            order = np.lexsort((rows, d))[:k]
+            assert np.array_equal(got_ids[q][: len(order)], rows[order]) and np.all(got_ids[q][len(order):] == -1), (q, ht)
+            assert np.array_equal(got_d[q][: len(order)], d[order].astype(np.float32))
+
+
 @pytest.mark.parametrize("route", ["mfma", "popcount"])
 def test_nested_prefix_patterns_at_every_threshold(psc, force_route, route):
     """Database row r = the first r bits set (r = 0..64, repeated to fill several blocks), query q =
