@@ -457,11 +457,12 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // tiles into groups of kDistTilesPerGroup so that a small batch of rows still fills the chip.
 constexpr int kDistTilesPerGroup = 8;
 
-template <int DIM, bool DIST>
-__global__ void __launch_bounds__(256)
-nearest_centroid_mfma_kernel(const float *__restrict__ x, int64_t n, const float *__restrict__ cent,
-                             const float *__restrict__ mu, int nlist, int32_t *__restrict__ assign,
-                             float *__restrict__ dist)
+// One turn of a workgroup: the 128 rows row_at(0), row_at(1), ... (n or more: no such row).
+template <int DIM, bool DIST, typename RowAt>
+__device__ __forceinline__ void
+nearest_centroid_turn(const float *__restrict__ x, int64_t n, const float *__restrict__ cent,
+                      const float *__restrict__ mu, int nlist, const RowAt &row_at, int32_t *__restrict__ assign,
+                      float *__restrict__ dist)
 {
     static_assert(DIM % 8 == 0 && DIM <= 128, "rows are held in registers");
     constexpr int KS = DIM / 2;
@@ -472,11 +473,10 @@ nearest_centroid_mfma_kernel(const float *__restrict__ x, int64_t n, const float
     const int tid = (int)threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int half = lane >> 5, col = lane & 31;
-    const int64_t r0 = (int64_t)blockIdx.x * 128 + wave * 32;
 
     float a[KS];
     {
-        const int64_t r = r0 + col;
+        const int64_t r = row_at(wave * 32 + col);
         const float *xr = x + (r < n ? r : n - 1) * DIM;
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) a[kk] = xr[2 * kk + half] - mu[2 * kk + half];
@@ -548,9 +548,10 @@ nearest_centroid_mfma_kernel(const float *__restrict__ x, int64_t n, const float
             const float d = fmaf(-2.0f, acc[v], cn);  // (+inf for the padding of the last tile)
             if constexpr (DIST) {
                 const int i = 8 * (v / 4) + 4 * half + v % 4;
-                if (r0 + i < n && ci < nlist) {
+                const int64_t r = row_at(wave * 32 + i);
+                if (r < n && ci < nlist) {
                     const float full = d + xnorm[wave][i];
-                    dist[(r0 + i) * nlist + ci] = full > 0.f ? full : 0.f;
+                    dist[r * nlist + ci] = full > 0.f ? full : 0.f;
                 }
             } else if (d < bestv[v]) {
                 bestv[v] = d;
@@ -574,9 +575,44 @@ nearest_centroid_mfma_kernel(const float *__restrict__ x, int64_t n, const float
                 bi = oi;
             }
         }
-        const int64_t r = r0 + 8 * (v / 4) + 4 * half + v % 4;
+        const int64_t r = row_at(wave * 32 + 8 * (v / 4) + 4 * half + v % 4);
         if (col == 0 && r < n) assign[r] = bi;
     }
+}
+
+template <int DIM, bool DIST>
+__global__ void __launch_bounds__(256)
+nearest_centroid_mfma_kernel(const float *__restrict__ x, int64_t n, const float *__restrict__ cent,
+                             const float *__restrict__ mu, int nlist, int32_t *__restrict__ assign,
+                             float *__restrict__ dist)
+{
+    const int64_t r0 = (int64_t)blockIdx.x * 128;
+    nearest_centroid_turn<DIM, DIST>(x, n, cent, mu, nlist, [&](int i) { return r0 + i; }, assign, dist);
+}
+
+// The same for the rows that hold kUndecided in `assign` only: a workgroup gathers those of its `chunk`
+// rows (at most kMarkedChunk) and takes them 128 at a time.  Without any it is a read of `assign`.
+constexpr int32_t kUndecided = -1;
+constexpr int kMarkedChunk = 4096;
+
+template <int DIM>
+__global__ void __launch_bounds__(256)
+nearest_centroid_marked_kernel(const float *__restrict__ x, int64_t n, const float *__restrict__ cent,
+                               const float *__restrict__ mu, int nlist, int chunk, int32_t *__restrict__ assign)
+{
+    __shared__ uint16_t marked[kMarkedChunk];
+    __shared__ int nmarked;
+    const int64_t first = (int64_t)blockIdx.x * chunk;
+    if (threadIdx.x == 0) nmarked = 0;
+    __syncthreads();
+    for (int e = (int)threadIdx.x; e < chunk && first + e < n; e += 256)
+        if (assign[first + e] == kUndecided) marked[atomicAdd(&nmarked, 1)] = (uint16_t)e;
+    __syncthreads();
+    const int count = nmarked;
+    for (int turn = 0; turn < count; turn += 128)
+        nearest_centroid_turn<DIM, false>(x, n, cent, mu, nlist,
+                                          [&](int i) { return turn + i < count ? first + marked[turn + i] : n; },
+                                          assign, (float *)nullptr);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -586,20 +622,33 @@ nearest_centroid_mfma_kernel(const float *__restrict__ x, int64_t n, const float
 //     v(c) = || c' ||^2 - 2 x'.c'
 // the three larger products xh ch + xh cl + xl ch are taken (v_mfma_f32_32x32x16_bf16, float32 sums),
 // the factor -2 sitting in x and the norm coming in as three more coordinates.  The result is off by
-//     at most E = (2^-14 + 2^-(22 - b)) (|| x' ||^2 + max || c' ||^2)
-// (3 * 2^-18 a product from what the split leaves out, a rounding per addition, and the b low bits
-// of the mantissa that carry the tile number), so the nearest centroid is among those within 2 E of
-// the smallest v.  Mostly that is one; otherwise (a few per cent of the rows on the SIFT-like
-// vectors) the distances of those centroids are taken by direct differences in float32 and the
-// smallest wins, lower number on ties.  A lane keeps the two smallest v of its columns: if a lane's
-// second is within 2 E too (or v is not a number) the row is compared with every centroid.
+// at most u (|| x' ||^2 + || c' ||^2), u = 2^-14 + 2^-(22 - b) (3 * 2^-18 a product from what the split
+// leaves out, a rounding per addition, and the b low bits of the mantissa that carry the tile number).
+// With c1 the centroid of the smallest value and d1 its distance, || x' ||^2 + v(c1) gives
+// d1^2 <= (1 + 3 u) (|| x' ||^2 + v(c1) + 3 u || x' ||^2); the nearest centroid is no farther, so it and c1 are
+// no longer than || x' || + d1, and the nearest one's value is within
+//     2 u (|| x' ||^2 + min(max || c' ||^2, (|| x' || + d1)^2))
+// of the smallest (the bound by the row keeps one long centroid from widening it for all: 1M x 4096 with
+// one centroid 30 times as far from the mean as the others took as long as without it).  Mostly one
+// centroid is; otherwise the distances of those that are (the close calls) are taken by direct
+// differences in float32 and the smallest wins, lower number on ties.
+//
+// A lane keeps the two smallest v of its columns.  If a lane's second is a close call too, all
+// centroids of that lane are compared; if that happens in more than a few lanes, or too many lanes have a
+// close call, the tiles are gone through again and every value within reach is listed.  That is the
+// dearer the more there are: a workgroup whose rows have more than kManyNear lanes each with a close call
+// after an eighth of the tiles gives up, and so does a row with kMostLanes at the end or with lengths
+// that squares or sums in float32 do not hold; nearest_centroid_marked_kernel takes those.
+// 1M x 4096 at 128 dimensions (10.6 ms by the float32 products alone): 3.1 ms for the mixture of the
+// workloads, 2.9 with one of the centroids 30 times as far out, 3.0 with squared lengths log-normal, 5.5
+// with every centroid twice; clusters of spread 4 / 2 / 1 / 0.3 around 100 centres in 0 .. 100 (2, 7, 26
+// and 41 close calls a row) 3.3 / 5.8 / 10.5 / 10.0.
 //
 // The centroids' parts are laid out once per quantizer in operand order (split_centroids_kernel):
 // per tile of 32 centroids DIM / 16 pairs of 1 KB operands (high, low) and one with the norms.
 // One workgroup = 4 waves x 32 rows; the rows' parts sit in registers, tiles go through LDS, two in
 // turn.  Bound by the matrix cores: 3 DIM / 16 + 1 products of 32 cycles per 32 x 32 outputs against 48
-// vector instructions (tile number into the mantissa, minimum, median).  1M x 4096 at 128 dimensions:
-// 11.0 -> 3.1 ms (adding vectors to lists, residual codes included, 12.0 -> 4.6).
+// vector instructions (tile number into the mantissa, minimum, median).
 // ---------------------------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -653,19 +702,34 @@ split_centroids_kernel(const float *__restrict__ cent, const float *__restrict__
 }
 
 constexpr int kSplitWaves = 4;
+constexpr int kPairList = 512;    // pairs a wave lists before it takes their distances
+constexpr int kManyNear = 3;      // (some 25 close calls a row in all: listing them takes as long as the float32
+                                  //  products, 8.7 / 10.0 ms for 1M x 4096, 1.35 / 1.24 for 100k)
+constexpr int kMostLanes = 28;    // of 32
+constexpr int kDeepLanes = 16;    // of a workgroup's rows: comparing all centroids of so many lanes takes as long
+                                  // as going through the tiles again
+// (Three waves per SIMD hide the ends of the workgroups' turns: two take 3.15 ms for the mixture, 0.43 instead
+//  of 0.33 with 256 centroids.)
 template <int DIM>
-__global__ void __launch_bounds__(kSplitWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ void __launch_bounds__(kSplitWaves * 64) __attribute__((amdgpu_waves_per_eu(3)))
 nearest_centroid_split_kernel(const float *__restrict__ x, int64_t n, const float *__restrict__ cent,
-                              const float *__restrict__ mu, const bf16x8 *__restrict__ image, const float *__restrict__ cmax2_dev, int nlist,
-                              int tile_bits, int32_t *__restrict__ assign)
+                              const float *__restrict__ mu, const bf16x8 *__restrict__ image,
+                              const float *__restrict__ cmax2_dev, int nlist, int tile_bits,
+                              int32_t *__restrict__ assign)
 {
     constexpr int KS = DIM / 16;
     constexpr int kThreads = kSplitWaves * 64;
     constexpr int kOps = (2 * KS + 1) * 64;  // 16-byte entries of a tile
     __shared__ __align__(16) u32x4 tile[2][kOps];
     __shared__ float xnorm[kSplitWaves][32];
+    __shared__ float limit[kSplitWaves][32];        // rows gone through again: what counts as a close call
+    __shared__ unsigned long long nearest[kSplitWaves][32];  // (distance, number) of the best listed pair
+    __shared__ uint32_t pairs[kSplitWaves][kPairList];  // row << 16 | centroid
+    __shared__ int tally[2];
     const int tid = (int)threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, col = lane & 31;
     const int64_t r0 = (int64_t)blockIdx.x * (32 * kSplitWaves) + wave * 32;
+    const float cmax2 = *cmax2_dev;
+    const float unit = 6.103515625e-5f + __uint_as_float((uint32_t)(127 - 22 + tile_bits) << 23);
 
     bf16x8 xh[KS], xl[KS], one;
     {
@@ -684,13 +748,15 @@ nearest_centroid_split_kernel(const float *__restrict__ x, int64_t n, const floa
             }
         }
         norm += __shfl_xor(norm, 32, 64);
-        if (half == 0) xnorm[wave][col] = norm;
+        if (half == 0) {
+            xnorm[wave][col] = norm;
+            nearest[wave][col] = ~0ull;
+            limit[wave][col] = __builtin_nanf("");  // (no value is within it)
+        }
+        if (tid < 2) tally[tid] = 0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) one[i] = (__bf16)(half == 0 && i < 3 ? 1.f : 0.f);
     }
-    float best[16], next[16];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) best[v] = next[v] = __builtin_inff();
     const int ntiles = (nlist + 31) / 32;
     constexpr int kPer = 2 * KS * 64 / kThreads;  // whole turns of the workgroup, and one of wave 0 for the norms
     static_assert(kPer * kThreads == 2 * KS * 64, "operands of a tile");
@@ -706,98 +772,188 @@ nearest_centroid_split_kernel(const float *__restrict__ x, int64_t n, const floa
         for (int i = 0; i < kPer; ++i) tile[buf][i * kThreads + tid] = hold[i];
         if (tid < 64) tile[buf][kPer * kThreads + tid] = hold_norm;
     };
-    fetch(0);
-    put(0);
-    __syncthreads();
+    // Tiles [from, to), the first of which waits in LDS, as does tile `to` afterwards: see(t, values).
+    auto sweep = [&](int from, int to, auto &&see) {
+        for (int t = from; t < to; ++t) {
+            fetch(t + 1 < ntiles ? t + 1 : t);
+            const bf16x8 *b = (const bf16x8 *)tile[t & 1];
+            f32x16 acc;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+            bf16x8 op[2 * KS + 1];  // all operands asked for before the first product
+#pragma unroll
+            for (int s = 0; s < 2 * KS + 1; ++s) op[s] = b[(s == 0 ? 2 * KS : s - 1) * 64 + lane];
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(one, op[0], acc, 0, 0, 0);
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const bf16x8 ch = op[1 + 2 * s], cl = op[2 + 2 * s];
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[s], ch, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl[s], ch, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[s], cl, acc, 0, 0, 0);
+            }
+            see(t, acc);
+            put((t + 1) & 1);  // (after the last tile: a copy nobody reads)
+            __syncthreads();
+        }
+    };
     uint32_t keep = ~((1u << tile_bits) - 1u);
     float low = -__builtin_inff();
     asm("" : "+v"(keep), "+v"(low));
-    for (int t = 0; t < ntiles; ++t) {
-        const bool more = t + 1 < ntiles;
-        fetch(more ? t + 1 : t);
-        const bf16x8 *b = (const bf16x8 *)tile[t & 1];
-        f32x16 acc;
+    float best[16], next[16];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-        bf16x8 op[2 * KS + 1];  // all operands asked for before the first product
-#pragma unroll
-        for (int s = 0; s < 2 * KS + 1; ++s) op[s] = b[(s == 0 ? 2 * KS : s - 1) * 64 + lane];
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(one, op[0], acc, 0, 0, 0);
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            const bf16x8 ch = op[1 + 2 * s], cl = op[2 + 2 * s];
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[s], ch, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl[s], ch, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[s], cl, acc, 0, 0, 0);
-        }
+    for (int v = 0; v < 16; ++v) best[v] = next[v] = __builtin_inff();
+    auto two_smallest = [&](int t, const f32x16 &acc) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const float d = __uint_as_float((__float_as_uint(acc[v]) & keep) | (uint32_t)t);
             next[v] = __builtin_amdgcn_fmed3f(d, best[v], next[v]);
             best[v] = __builtin_amdgcn_fmed3f(d, best[v], low);  // (the smaller of the two)
         }
-        put((t + 1) & 1);  // (after the last tile: a copy nobody reads)
-        __syncthreads();
-    }
-    // every row: register v of half h is row 8 (v / 4) + 4 h + v % 4
-    const float cmax2 = *cmax2_dev;
-    const float unit = 6.103515625e-5f + __uint_as_float((uint32_t)(127 - 22 + tile_bits) << 23);
-    for (int v = 0; v < 16; ++v) {
-        float bv = best[0], nv = next[0];
-#pragma unroll
-        for (int i = 1; i < 16; ++i) {
-            bv = v == i ? best[i] : bv;
-            nv = v == i ? next[i] : nv;
-        }
+    };
+    // the largest value of a close call for the row of register v, by the smallest value of its 32 lanes
+    auto reach_of = [&](int v, float bv) {
         float least = bv;
 #pragma unroll
         for (int off = 16; off >= 1; off >>= 1) least = fminf(least, __shfl_xor(least, off, 64));
-        const int row = 8 * (v / 4) + 4 * half + v % 4;
-        const float reach = least + 2.f * unit * (xnorm[wave][row] + cmax2);
+        const float x2 = xnorm[wave][8 * (v / 4) + 4 * half + v % 4];
+        const float d2 = (fmaxf(least + x2, 0.f) + 3.f * unit * x2) * (1.f + 3.f * unit);
+        const float len = __builtin_amdgcn_sqrtf(x2) + __builtin_amdgcn_sqrtf(d2);
+        const float reach = least + 2.f * unit * (x2 + fminf(cmax2, 1.001f * len * len));
+        // (below that all values and the places past the last centroid are finite; no number if the row is none)
+        return x2 + cmax2 < 1e37f ? reach : __builtin_nanf("");
+    };
+
+    fetch(0);
+    put(0);
+    __syncthreads();
+    const int early = ntiles >= 16 ? ntiles / 8 : 0;
+    sweep(0, early, two_smallest);
+    if (early > 0) {
+        int lanes = 0;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) lanes += __builtin_popcountll(__ballot(best[v] <= reach_of(v, best[v])));
+        if (lane == 0) atomicAdd(&tally[0], lanes);
+        __syncthreads();
+        if (tally[0] > kManyNear * 32 * kSplitWaves) {
+            if (lane < 32 && r0 + lane < n) assign[r0 + lane] = kUndecided;
+            return;
+        }
+    }
+    sweep(early, ntiles, two_smallest);
+
+    // The distances of the listed pairs, four at a time, 16 lanes to a pair.
+    int npairs = 0;
+    auto settle = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int l16 = lane & 15;
+#pragma unroll 4
+        for (int i = lane >> 4; i - (lane >> 4) < npairs; i += 4) {
+            const uint32_t e = pairs[wave][i < npairs ? i : npairs - 1];  // (the last one again: the same key)
+            const int row = (int)(e >> 16), c = (int)(e & 0xffffu);
+            const float4 *xr = (const float4 *)(x + (r0 + row) * DIM), *cr = (const float4 *)(cent + (int64_t)c * DIM);
+            float d = 0.f;
+#pragma unroll
+            for (int p = 0; p < (DIM / 4 + 15) / 16; ++p) {
+                if (16 * p + l16 >= DIM / 4) continue;
+                const float4 xv = xr[16 * p + l16], cv = cr[16 * p + l16];
+                const float dx = xv.x - cv.x, dy = xv.y - cv.y, dz = xv.z - cv.z, dw = xv.w - cv.w;
+                d = fmaf(dx, dx, d);
+                d = fmaf(dy, dy, d);
+                d = fmaf(dz, dz, d);
+                d = fmaf(dw, dw, d);
+            }
+#pragma unroll
+            for (int off = 8; off >= 1; off >>= 1) d += __shfl_xor(d, off, 64);
+            if (l16 == 0) atomicMin(&nearest[wave][row], (unsigned long long)order_key(d, (uint32_t)c));
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        npairs = 0;
+    };
+    auto list_pairs = [&](bool take, int row, int c) {
+        take = take && c < nlist;  // (the places past the last centroid are no centroids)
+        const uint64_t m = __ballot(take);
+        if (npairs + __builtin_popcountll(m) > kPairList) settle();
+        const int at = npairs + __builtin_popcountll(m & ((1ull << lane) - 1ull));
+        if (take) pairs[wave][at] = (uint32_t)row << 16 | (uint32_t)c;
+        npairs += __builtin_popcountll(m);
+    };
+
+    // every row: register v of half h is row 8 (v / 4) + 4 h + v % 4
+    float reaches[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) reaches[v] = reach_of(v, best[v]);
+    auto each_register = [&](auto &&f) {
+#pragma unroll 1
+        for (int v = 0; v < 16; ++v) {
+            float bv = best[0], nv = next[0], reach = reaches[0];
+#pragma unroll
+            for (int i = 1; i < 16; ++i) {
+                bv = v == i ? best[i] : bv;
+                nv = v == i ? next[i] : nv;
+                reach = v == i ? reaches[i] : reach;
+            }
+            f(v, bv, nv, reach);
+        }
+    };
+    int decided = kUndecided;  // lane l < 32: what is known of row l
+    int deep_lanes = 0;
+    each_register([&](int v, float bv, float nv, float reach) {
         const uint64_t near2 = __ballot(bv <= reach), deep2 = __ballot(nv <= reach);
         const int mine = (int)(__float_as_uint(bv) & ~keep) * 32 + col;
 #pragma unroll 1
         for (int h = 0; h < 2; ++h) {
             const uint32_t near = (uint32_t)(near2 >> (32 * h)), deep = (uint32_t)(deep2 >> (32 * h));
-            const int64_t r = r0 + 8 * (v / 4) + 4 * h + v % 4;
-            if (r >= n) continue;
-            int winner = 0;
-            if (deep == 0u && __builtin_popcount(near) == 1) {
-                winner = __shfl(mine, 32 * h + __builtin_ctz(near), 64);
-            } else if (deep == 0u && near != 0u) {
-                // each candidate by the whole wave: coordinates lane, lane + 64, ...
-                float bd = __builtin_inff();
-                for (uint32_t left = near; left != 0u; left &= left - 1u) {
-                    const int c = __shfl(mine, 32 * h + __builtin_ctz(left), 64);
-                    float d = 0.f;
-                    for (int e = lane; e < DIM; e += 64) {
-                        const float df = x[r * DIM + e] - cent[(int64_t)c * DIM + e];
-                        d = fmaf(df, df, d);
-                    }
-#pragma unroll
-                    for (int off = 32; off >= 1; off >>= 1) d += __shfl_xor(d, off, 64);
-                    if (d < bd || (d == bd && c < winner)) {
-                        bd = d;
-                        winner = c;
-                    }
-                }
-            } else {
-                uint64_t key = ~0ull;
-                for (int c = lane; c < nlist; c += 64) {
-                    float d = 0.f;
-                    for (int e = 0; e < DIM; ++e) {
-                        const float df = x[r * DIM + e] - cent[(int64_t)c * DIM + e];
-                        d = fmaf(df, df, d);
-                    }
-                    const uint64_t kc = order_key(d, (uint32_t)c);
-                    if (d < __builtin_inff() && kc < key) key = kc;  // (a distance that is not finite wins nothing)
-                }
-                key = wave_min_u64(key);
-                winner = key == ~0ull ? 0 : (int)(uint32_t)key;
+            const int row = 8 * (v / 4) + 4 * h + v % 4;
+            if (r0 + row >= n) continue;
+            if (deep != 0u) {
+                if (__builtin_popcount(near) >= kMostLanes) continue;  // (undecided)
+                deep_lanes += __builtin_popcount(deep);
+                if (half == h && col == 0) limit[wave][row] = reach;
+            } else if ((near & (near - 1u)) != 0u) {
+                list_pairs(half == h && (near >> col & 1u) != 0u, row, mine);
+            } else if (near != 0u) {
+                const int winner = __builtin_amdgcn_readlane(mine, 32 * h + __builtin_ctz(near));
+                if (lane == row && winner < nlist) decided = winner;
             }
-            if (lane == 0) assign[r] = winner;
         }
+    });
+    if (deep_lanes != 0 && lane == 0) atomicAdd(&tally[1], deep_lanes);
+    __syncthreads();
+    const int deep_all = tally[1];
+    if (deep_all > kDeepLanes) {
+        asm("" : "+s"(image));  // (addresses kept from above would go to scratch memory)
+        float lim[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) lim[v] = limit[wave][8 * (v / 4) + 4 * half + v % 4];
+        fetch(0);
+        put(0);
+        __syncthreads();
+        sweep(0, ntiles, [&](int t, const f32x16 &acc) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const bool close = __uint_as_float((__float_as_uint(acc[v]) & keep) | (uint32_t)t) <= lim[v];
+                if (__ballot(close) != 0) list_pairs(close, 8 * (v / 4) + 4 * half + v % 4, t * 32 + col);
+            }
+        });
+    } else if (deep_lanes != 0) {
+        each_register([&](int v, float bv, float nv, float) {
+            const int own = 8 * (v / 4) + 4 * half + v % 4;
+            const bool near = bv <= limit[wave][own];
+            uint64_t deep = __ballot(nv <= limit[wave][own]);
+            if (__ballot(near) == 0) return;
+            list_pairs(near && (deep >> lane & 1u) == 0, own, (int)(__float_as_uint(bv) & ~keep) * 32 + col);
+            for (; deep != 0; deep &= deep - 1u) {
+                const int l = __builtin_ctzll(deep);
+                for (int t = 0; t < ntiles; t += 64)
+                    list_pairs(t + lane < ntiles, 8 * (v / 4) + 4 * (l >> 5) + v % 4, (t + lane) * 32 + (l & 31));
+            }
+        });
     }
+    settle();
+    if (lane < 32 && r0 + lane < n)
+        assign[r0 + lane] = nearest[wave][lane] != ~0ull ? (int32_t)(uint32_t)nearest[wave][lane] : decided;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1132,9 +1288,17 @@ int launch_nearest_centroid_split(const float *x_dev, int64_t n, int dim, const 
     int bits = 0;  // of a tile's number
     while ((1 << bits) < (nlist + 31) / 32) ++bits;
     const dim3 grid((unsigned)((n + kRowsPer - 1) / kRowsPer)), block(kSplitWaves * 64);
+    // (512 workgroups of whole turns for the rows left over, once there are as many)
+    const int64_t share = (n / 512 + kRowsPer - 1) / kRowsPer * kRowsPer;
+    const int chunk = (int)(share < kRowsPer ? kRowsPer : share < kMarkedChunk ? share : kMarkedChunk);
+    const dim3 mgrid((unsigned)((n + chunk - 1) / chunk));
 #define CALL(D)                                                                                                      \
-    hipLaunchKernelGGL((nearest_centroid_split_kernel<D>), grid, block, 0, s, x_dev, n, cent_dev, mu_dev,            \
-                       (const bf16x8 *)image_dev, cmax2, nlist, bits, assign_dev)
+    do {                                                                                                             \
+        hipLaunchKernelGGL((nearest_centroid_split_kernel<D>), grid, block, 0, s, x_dev, n, cent_dev, mu_dev,        \
+                           (const bf16x8 *)image_dev, cmax2, nlist, bits, assign_dev);                               \
+        hipLaunchKernelGGL((nearest_centroid_marked_kernel<D>), mgrid, dim3(256), 0, s, x_dev, n, cent_dev, mu_dev,  \
+                           nlist, chunk, assign_dev);                                                                \
+    } while (0)
     switch (dim) {
     case 32: CALL(32); break;
     case 64: CALL(64); break;
