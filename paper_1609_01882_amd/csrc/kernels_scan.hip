@@ -39,10 +39,12 @@ namespace {
 constexpr int kQueueCap = 95;         // queue entries per wave (8 bytes each, and one to spare; see score_survivors)
 constexpr int kMfmaQueueCap = 111;    // the same for the matrix-core filter, whose blocks bring more of them
 constexpr int64_t kMaxSliceLen = (int64_t)1 << 27;
-constexpr int kMfmaRelBits = 25;      // bits of a queue entry of the matrix-core filter that hold the position inside
-                                      // the slice (two more name the lane's row group)
-constexpr uint32_t kMfmaRelMask = (1u << kMfmaRelBits) - 1;
-constexpr int64_t kMfmaMaxSliceLen = (int64_t)1 << kMfmaRelBits;
+// Queue entries of the matrix-core filter: a lane's first code is at most the block's position (a multiple of
+// 128, of 256 at 128 bits) + 15 (31), so the bits above hold the lane's group of query slots.
+template <int M>
+constexpr uint32_t kGroupShift = M == 8 ? 4u : 5u;
+template <int M>
+constexpr uint32_t kGroupMask = M == 8 ? 3u : 1u;
 // Fewer queries than this take the narrower xor/popcount tiles (those scans are bound by memory; 128
 // bits, 50M codes, 5 and 8 queries, k = 100: 0.18 to 0.24 ms at ht = 0 .. 48 with either filter).
 constexpr int64_t kMfmaMinQueries = 9;
@@ -609,9 +611,9 @@ __device__ __forceinline__ void take_batch(Batch<M> &p, const int n, const uint3
                                            const uint8_t *slice_codes)
 {
     p.n = n;
-    if constexpr (MFMA_BITS) {  // b = 4 * (16-code group; 128 bits: 32) + row; rel0 = position | row group << kMfmaRelBits
-        p.q = (int)(4u * ((rel0 >> kMfmaRelBits) & 3u) + (b & 3u));
-        p.rel = (rel0 & kMfmaRelMask) + (M == 8 ? 16u : 32u) * (b >> 2);
+    if constexpr (MFMA_BITS) {  // b = 4 * (16-code group; 128 bits: 32) + row; rel0 = position | row group << kGroupShift
+        p.q = (int)(4u * ((rel0 >> kGroupShift<M>) & kGroupMask<M>) + (b & 3u));
+        p.rel = (rel0 & ~(kGroupMask<M> << kGroupShift<M>)) + (M == 8 ? 16u : 32u) * (b >> 2);
     } else {  // b = c * TQ + (TQ - 1 - q); rel0 = position of the lane's first code
         p.q = (int)((TQ - 1) - (b & (TQ - 1)));
         p.rel = rel0 + b / TQ;
@@ -1262,7 +1264,7 @@ scan_kernel(ScanArgs a)
 //
 // Survivor masks: bit 4 * t + r of a lane's mask <=> (code 16 * t + col of the 128-code block,
 // query slot 4 * grp + r), t = 0..7.  Queue entries carry the mask, grp and the position of the
-// block's code `col` (kMfmaRelBits bits).
+// block's code `col`.
 //
 // 128 bits: one product takes words 0 and 2 of its two codes (lanes read 8 bytes: row 0 of lanes the
 // first half of a code, row 1 the second, rows 2 and 3 those of the code 64 on), the next, into the
@@ -1320,9 +1322,8 @@ scan_mfma_kernel(ScanArgs a)
         slice_begin = ft.slice_begin;
         slice_end = ft.slice_end;
     }
-    // the queue entries take a position in kMfmaRelBits bits: flag the run instead of returning
-    // something wrong
-    if (slice_end - slice_begin > kMfmaMaxSliceLen) {
+    // the queue entries take a position in 27 bits: flag the run instead of returning something wrong
+    if (slice_end - slice_begin > kMaxSliceLen) {
         if (tid == 0) atomicExch(a.status, 1);
         return;
     }
@@ -1409,18 +1410,18 @@ scan_mfma_kernel(ScanArgs a)
     uint32_t self0 = 0x80000000u;
     if (!IVF && a.skip_first >= 0) {
         const int64_t at = a.skip_first + q0 - slice_begin;
-        if (at > -64 && at < kMfmaMaxSliceLen) self0 = (uint32_t)at;
+        if (at > -64 && at < kMaxSliceLen) self0 = (uint32_t)at;
     }
     // what a queue entry adds to the block's position: the place of the mask's first code in the block
-    // and, above kMfmaRelBits, the lane's group of query slots
+    // and, in the bits that both leave free, the lane's group of query slots
     const uint32_t lane_code = (uint32_t)(M == 8 ? col : col + 16 * (grp >> 1));
-    const uint32_t lane_bits = lane_code | ((uint32_t)(M == 8 ? grp : grp & 1) << kMfmaRelBits);
+    const uint32_t lane_bits = lane_code | (((uint32_t)grp & kGroupMask<M>) << kGroupShift<M>);
     constexpr int kStep = M == 8 ? 16 : 32;  // codes from one group of four mask bits to the next
     uint32_t m1 = 0x11111111u, m2 = 0x22222222u, m4 = 0x44444444u, m8 = 0x88888888u, ones = 0x22222222u;
     asm("" : "+s"(m1), "+s"(m2), "+s"(m4), "+s"(m8), "+v"(ones));  // (in registers: half the code size of literals)
 
     // The wave's blocks: wave, wave + NW, ... of the slice's 128-code blocks, positions counted from
-    // the slice's start (at most 2^25).  Two register sets in turn: a block's next-but-one is asked
+    // the slice's start (at most 2^27).  Two register sets in turn: a block's next-but-one is asked
     // for as soon as its codes have become operands.  Past the slice's end the buffer's range check
     // answers zero (and the bits are masked below).
     const int len = (int)(slice_end - slice_begin);
@@ -1428,9 +1429,9 @@ scan_mfma_kernel(ScanArgs a)
     // (128 bits: rows 0, 1 of lanes read the halves of 16 codes, rows 2, 3 those of the 16 codes 64 on)
     const uint32_t lane_off = M == 8 ? (uint32_t)lane * 8u : (uint32_t)(64 * (grp >> 1) + col) * 16u + 8u * (grp & 1);
     const __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc((void *)slice_codes, 0, len * M, 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc((void *)slice_codes, 0, (int)((uint32_t)len * (uint32_t)M), 0x00020000);
     auto load_block = [&](int blk, u32x2 (&c)[NLD]) {
-        const uint32_t at = (uint32_t)blk * (uint32_t)M + lane_off;  // (below 2^31: blk < len + 3 * stride)
+        const uint32_t at = (uint32_t)blk * (uint32_t)M + lane_off;  // (below 2^31 + 2^18: blk < len + 3 * stride)
 #pragma unroll
         for (int l = 0; l < NLD; ++l) {
             // 64 bits: 64 codes in a row; 128 bits: two runs of 16, l = 4 p + 2 t + h as used below
@@ -2662,7 +2663,6 @@ int plan_scan(int m, int64_t nq, int64_t n, int k, int kind, ScanPlan *plan)
     const int64_t block = 512;  // codes per wave and step, at most (64 lanes x 8 codes)
     const int64_t min_slice = p.nwaves * block;  // at least one block per wave
     const int64_t max_by_size = std::max<int64_t>(1, n / min_slice);
-    const int64_t max_slice = kind == kScanFusedMfma ? kMfmaMaxSliceLen : kMaxSliceLen;
     const int64_t wg_limit = std::max<int64_t>(8 * round, nqt);
     int64_t want = 1, tiles_one = 0;
     if (nqt > 0 && nq <= 16) {
@@ -2684,7 +2684,7 @@ int plan_scan(int m, int64_t nq, int64_t n, int k, int kind, ScanPlan *plan)
         // every extra list of a query is charged 4% (measured: two lists instead of one for all
         // queries cost about 8% at the headline size).
         double best_cost = 1e300;
-        const int64_t whole_rounds_tiles = n <= max_slice ? (nqt / round) * round : 0;
+        const int64_t whole_rounds_tiles = n <= kMaxSliceLen ? (nqt / round) * round : 0;
         for (int64_t t1 : {whole_rounds_tiles, (int64_t)0}) {
             const int64_t rest = nqt - t1;
             for (int64_t sN = 1; sN <= std::min<int64_t>(max_by_size, 1024) && rest * sN <= wg_limit; ++sN) {
@@ -2703,8 +2703,8 @@ int plan_scan(int m, int64_t nq, int64_t n, int k, int kind, ScanPlan *plan)
     }
     int64_t nslice = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, max_by_size), 1024));
     int64_t slice_len = (((n + nslice - 1) / nslice) + block - 1) / block * block;
-    if (slice_len > max_slice) {
-        slice_len = max_slice;
+    if (slice_len > kMaxSliceLen) {
+        slice_len = kMaxSliceLen;
         nslice = (n + slice_len - 1) / slice_len;
         if (nslice > 1024) {
             set_error("database too large for one scan call");
@@ -2833,7 +2833,8 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
     if (forced == PSC_ROUTE_MFMA) mfma = !dense && nq >= kMfmaMinQueries;
     if (mfma) {
         rc = plan_scan(m, nq, n, k, kScanFusedMfma, &p);
-        mfma = rc == PSC_OK;  // (k too large for the shape: the popcount kernel's shapes take over)
+        // (k too large for the shape, or a workspace that holds only the popcount kernel's plan: that one takes over)
+        mfma = rc == PSC_OK && ws_bytes >= p.total_bytes;
     }
     if (!mfma)
         rc = plan_scan(m, nq, n, k, !dense ? kScanFused : (ht >= 8 * m ? kScanDense : kScanDenseFiltered), &p);
@@ -2942,7 +2943,7 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
 }
 
 // Which filter the grouped inverted-file scan takes.  The matrix-core kernel needs 64-bit codes,
-// k small enough for its 16-job tile, lists within its position field and enough jobs per list
+// k small enough for its 16-job tile and enough jobs per list
 // to fill its tiles (a tile costs the same filter work whether 16 or 4 of its slots are taken).
 // It pays only while next to nothing survives the test: its one 16-wave workgroup per compute
 // unit cannot overlap one tile's set-up and list work with another tile's filtering as three
@@ -2953,7 +2954,7 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
 // psc_set_filter_route overrides the rule where the kernel can run at all.
 bool ivf_scan_on_matrix_cores(int m, int ht, int k, int64_t njobs, int nlist, int64_t max_list_len, ScanPlan *plan)
 {
-    if (m != 8 || ht >= 64 || max_list_len > kMfmaMaxSliceLen || njobs < kMfmaMinQueries) return false;
+    if (m != 8 || ht >= 64 || njobs < kMfmaMinQueries) return false;
     bool take = njobs >= 12 * (int64_t)nlist && random_code_survival(64, ht) < 1e-4;
     const int forced = g_filter_route.load(std::memory_order_relaxed);
     if (forced == PSC_ROUTE_POPCOUNT) take = false;

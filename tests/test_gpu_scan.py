@@ -253,6 +253,57 @@ def test_whole_and_sliced_query_tiles_in_one_launch(psc, force_route, route):
         assert np.array_equal((got_ids >= 0).sum(axis=1), np.minimum(ns.cpu().numpy(), k))
 
 
+@pytest.mark.parametrize("m,nq", [(16, 2051), (8, 4099)])
+def test_whole_tiles_over_more_than_2_to_the_25_codes(psc, force_route, m, nq):
+    """Enough query tiles to scan 34M codes in one piece: positions past 2^25 come through the matrix-core
+    filter's queue entries whole.  Rows near both ends and past 2^25 repeat query codes (distance 0); the rest
+    against the popcount kernel's answer."""
+    n, k, ht = (1 << 25) + 70_003, 5, 8 * m // 4
+    g = torch.Generator(device="cuda")
+    g.manual_seed(17 + m)
+    codes = torch.randint(0, 256, (n, m), generator=g, device="cuda", dtype=torch.uint8)
+    qcodes = torch.randint(0, 256, (nq, m), generator=g, device="cuda", dtype=torch.uint8)
+    rows = torch.tensor([3, (1 << 25) - 1, 1 << 25, (1 << 25) + 16, (1 << 25) + 65_537, n - 1], device="cuda")
+    owner = torch.tensor([0, 15, 16, 1000, 2047, nq - 1], device="cuda")
+    codes[rows] = qcodes[owner]
+    lut = torch.empty((nq, m, 256), device="cuda").uniform_(1.0, 1000.0, generator=g)
+    lut.scatter_(2, qcodes.long()[:, :, None], 0.0)  # the query's own code: distance 0
+    out = {}
+    for route in ("mfma", "popcount"):
+        force_route(route)
+        out[route] = psc.scan(lut, qcodes, codes, ht, k)
+        torch.cuda.synchronize()
+        assert psc.last_scan_route().startswith("scan_mfma_kernel " if route == "mfma" else "scan_kernel ")
+    assert torch.equal(out["mfma"][0][owner, 0], rows) and torch.all(out["mfma"][1][owner, 0] == 0)
+    assert torch.equal(out["mfma"][0], out["popcount"][0]) and torch.equal(out["mfma"][1], out["popcount"][1])
+
+
+@pytest.mark.parametrize("m,nq,ht,fewer", [(8, 2721, 28, True), (16, 1000, 56, False)])
+def test_a_workspace_for_the_popcount_plan_is_enough(psc, force_route, m, nq, ht, fewer):
+    """A caller's fixed workspace that holds the xor/popcount kernel's partial lists but not the matrix-core
+    kernel's is taken, by the former (128-bit codes: the two plans are the same); one byte less is refused."""
+    n, k = 1_000_001, 100
+    codes, qcodes, lut = (_dev(a) for a in _rand_problem(m, n, nq, seed=3, lut_kind="float"))
+    slices = {}
+    for route in ("popcount", "mfma"):
+        force_route(route)
+        want = psc.scan(lut, qcodes, codes, ht, k)
+        slices[route] = int(psc.last_scan_route().split("slices=")[1].split()[0])
+    force_route("auto")
+    words = lambda s: min(s, 64) if s >= 4 else 1
+    r = lambda b: -(-b // 256) * 256
+    need = 256 + r(4 * nq * words(slices["popcount"])) + r(4 * nq * k * slices["popcount"]) + 8 * nq * k * slices["popcount"]
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    got = psc.scan(lut, qcodes, codes, ht, k, workspace=ws)
+    torch.cuda.synchronize()
+    print(f"m={m}: slices {slices}, {psc.last_scan_route()}", flush=True)
+    assert (slices["mfma"] > slices["popcount"]) == fewer
+    assert psc.last_scan_route().startswith("scan_kernel " if fewer else "scan_mfma_kernel ")
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    with pytest.raises(psc.PscError, match="workspace too small"):
+        psc.scan(lut, qcodes, codes, ht, k, workspace=ws[:-1])
+
+
 def test_many_slices_for_few_queries(psc):
     """Two queries over 3M codes: 256 database slices, whose partial lists the merge takes four to a lane."""
     codes, qcodes, lut = _rand_problem(8, 3_000_001, 2, seed=321, lut_kind="float")

@@ -224,3 +224,14 @@ def test_workspace_sizes_over_a_grid(psc):
     assert 0 < small < big
     # more probes than lists: clipped to the number of lists
     assert idx.ivf_search_workspace_bytes(10, 2000, 10) == idx.ivf_search_workspace_bytes(10, 50, 10)
+
+
+def test_scan_workspace_of_large_databases(psc):
+    """Batches that fill the chip scan a database in one piece up to 2^27 codes, whatever the filter: one
+    partial list per query, so that the sizes below fit the static scratch array."""
+    for m, n, nq, k in ((16, 100_000_000, 10_000, 100), (16, 134_000_000, 16_384, 100), (8, 100_000_000, 8192, 100),
+                        (16, 200_000_000, 10_000, 100)):
+        slices = -(-n // (1 << 27))
+        b = psc.scan_workspace_bytes(m, nq, n, k)
+        assert b <= 256 + 4 * nq * slices + 12 * nq * k * slices + 1024, (m, n, b)
+        assert b <= psc.PSC_STATIC_SCRATCH_BYTES
