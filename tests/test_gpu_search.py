@@ -73,6 +73,33 @@ def test_encode(setup, m):
     s["codes"] = codes
 
 
+@pytest.mark.parametrize("m,dsub", [(16, 1), (8, 6), (8, 8), (8, 12), (8, 16), (16, 24), (8, 32), (16, 48), (8, 64)])
+def test_encode_of_many_rows_equals_encode_of_few(m, dsub):
+    """The encoder has two forms, by the number of codes (the last a few rows past the largest of the limits):
+    same sums, so the codes are those of the same rows 1000 at a time, which are the oracle's."""
+    import paper_1609_01882_amd as psc
+    dim, n = m * dsub, 3_200_000 // m + 259
+    rng = np.random.default_rng(dim)
+    cb = rng.normal(size=(m, 256, dsub)).astype(np.float32)
+    idx = psc.Index(dim, m)
+    idx.set_codebook(cb)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(dim)
+    x = torch.randn((n, dim), generator=g, device="cuda")
+    few = torch.cat([idx.encode(x[s:s + 1000]) for s in range(0, 20_000, 1000)] + [idx.encode(x[-1000:])])
+    for count in (799_999 // m, 800_000 // m, 1_600_000 // m, n):
+        many = idx.encode(x[:count])
+        assert torch.equal(many[:20_000], few[:20_000]), count
+    assert torch.equal(many[-1000:], few[-1000:])
+    ref = O.encode(x[:2000].cpu().numpy(), cb)
+    bad = np.argwhere(few[:2000].cpu().numpy() != ref)
+    assert len(bad) <= 4
+    for i, j in bad:  # only near-ties
+        v = x[i, j * dsub:(j + 1) * dsub].cpu().numpy().astype(np.float64)
+        da, db = ((v - cb[j, int(few[i, j])]) ** 2).sum(), ((v - cb[j, ref[i, j]]) ** 2).sum()
+        assert abs(da - db) <= RTOL * db
+
+
 @pytest.mark.parametrize("m", [8, 16])
 def test_whole_search_matches_oracle(setup, m):
     s = setup[m]
