@@ -17,11 +17,14 @@ namespace {
 // ---------------------------------------------------------------------------------------------
 // Product quantizer: grid (row blocks, m).  A workgroup keeps a private copy of its cells' sums
 // (float32: a workgroup adds a few members per cell) and counts in LDS, walks its share of the rows
-// (one row per thread and turn), and adds its sums to the global ones (double) at the end.  The
-// centroids, the same for every lane, come through the scalar cache: read from LDS, four 16-byte
-// reads per 32 vector instructions, they took as long as the arithmetic did.  Per row it also stores the cell and the distance, for the refill of empty cells.
+// (one row per thread and turn), and adds its sums to the global ones (double) at the end.  Per row
+// it also stores the cell and the distance, for the refill of empty cells.  The centroids, the same
+// for every lane, come through the scalar cache (SCALAR): read from LDS, four 16-byte reads per 32
+// vector instructions, they take as long as the arithmetic.  With few rows there are not the waves to
+// hide the scalar cache's trips, and they are read from LDS.  An iteration with LDS / scalar cache, us:
+// sub-vectors of 16, 8 sub-quantizers, 1k rows 97 / 117, 100k 356 / 281; of 32 121 / 177 and 685 / 530.
 // ---------------------------------------------------------------------------------------------
-template <int DSUB>
+template <int DSUB, bool SCALAR>
 __global__ void __launch_bounds__(256)
 pq_lloyd_step_kernel(const float *__restrict__ cb, int dim, int m, const float *__restrict__ x, int64_t n,
                      uint8_t *__restrict__ cell, float *__restrict__ dmin, double *__restrict__ gsum,
@@ -31,8 +34,12 @@ pq_lloyd_step_kernel(const float *__restrict__ cb, int dim, int m, const float *
     constexpr int LD = DSUB + 1;  // pitch of a cell's sums: a coordinate's additions hit all banks, not a few
     float *sum = smem;                                    // [256][LD]
     uint32_t *cnt = (uint32_t *)(smem + kCentroids * LD);  // [256]
+    float *staged = smem + kCentroids * (LD + 1);          // [256][DSUB], not with SCALAR
     const int j = blockIdx.y, tid = threadIdx.x;
-    const float *__restrict__ cen = cb + (int64_t)j * kCentroids * DSUB;  // (the same address in every lane)
+    const float *__restrict__ from = cb + (int64_t)j * kCentroids * DSUB;
+    if constexpr (!SCALAR)
+        for (int e = tid; e < kCentroids * DSUB; e += 256) staged[e] = from[e];
+    const float *cen = SCALAR ? from : staged;  // (the same address in every lane)
     for (int e = tid; e < kCentroids * LD; e += 256) sum[e] = 0.f;
     cnt[tid] = 0u;
     __syncthreads();
@@ -210,21 +217,33 @@ mean_centroid_kernel(float *__restrict__ cent, int ncent, int dim)
     if (threadIdx.x == 0) cent[(int64_t)ncent * dim + t] = (float)((part[0] + part[1] + part[2] + part[3]) / ncent);
 }
 
-template <int DSUB>
-int run_pq_step(const float *cb, int dim, int m, const float *x, int64_t n, uint8_t *cell, float *dmin,
+template <int DSUB, bool SCALAR>
+int run_pq_step_form(const float *cb, int dim, int m, const float *x, int64_t n, uint8_t *cell, float *dmin,
                 double *gsum, uint32_t *gcount, double *gobj, hipStream_t s)
 {
-    const size_t lds = (size_t)(kCentroids * (DSUB + 1) + kCentroids) * sizeof(float);
+    const size_t lds = (size_t)(kCentroids * (DSUB + 2) + (SCALAR ? 0 : kCentroids * DSUB)) * sizeof(float);
     if (lds > 48 * 1024)
-        PSC_HIP_TRY(hipFuncSetAttribute((const void *)pq_lloyd_step_kernel<DSUB>,
+        PSC_HIP_TRY(hipFuncSetAttribute((const void *)pq_lloyd_step_kernel<DSUB, SCALAR>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     // at most 2048 workgroups (8 to a compute unit), all with the same number of turns
     const int64_t want = (n + 255) / 256, cap = 2048 / m, turns = (want + cap - 1) / cap;
     dim3 grid((unsigned)((want + turns - 1) / turns), (unsigned)m);
-    hipLaunchKernelGGL((pq_lloyd_step_kernel<DSUB>), grid, dim3(256), lds, s, cb, dim, m, x, n, cell, dmin, gsum,
-                       gcount, gobj);
+    hipLaunchKernelGGL((pq_lloyd_step_kernel<DSUB, SCALAR>), grid, dim3(256), lds, s, cb, dim, m, x, n, cell, dmin,
+                       gsum, gcount, gobj);
     PSC_HIP_TRY(hipGetLastError());
     return PSC_OK;
+}
+
+template <int DSUB>
+int run_pq_step(const float *cb, int dim, int m, const float *x, int64_t n, uint8_t *cell, float *dmin,
+                double *gsum, uint32_t *gcount, double *gobj, hipStream_t s)
+{
+    // the number of sub-vectors from which the scalar cache is ahead (measured at 300 .. 100k rows, 8 and 16
+    // sub-quantizers; long ones: at any number)
+    constexpr int64_t from = DSUB <= 16 ? 600'000 : DSUB <= 32 ? 160'000 : 0;
+    if constexpr (from != 0)
+        if (n * m < from) return run_pq_step_form<DSUB, false>(cb, dim, m, x, n, cell, dmin, gsum, gcount, gobj, s);
+    return run_pq_step_form<DSUB, true>(cb, dim, m, x, n, cell, dmin, gsum, gcount, gobj, s);
 }
 
 }  // namespace

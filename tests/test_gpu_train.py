@@ -93,6 +93,26 @@ def test_pq_lloyd_iterations_from_a_common_start(psc, dim, m):
         cb = nxt  # both sides go on from the oracle's centroids
 
 
+@pytest.mark.parametrize("dim,m,n", [(128, 8, 75_101), (64, 16, 37_400), (256, 8, 20_003), (256, 8, 19_999)])
+def test_pq_lloyd_iteration_of_many_rows(psc, dim, m, n):
+    """The step kernel has two forms, by the number of sub-vectors: sizes around the limits."""
+    dsub = dim // m
+    x = (W.sift_like(n, seed=33, stream=1) if dim <= 128 else W.relu_like(n, seed=33, stream=1))[:, :dim].copy()
+    xd = _dev(x)
+    idx = psc.Index(dim, m)
+    rng = np.random.default_rng(5)
+    cb = np.stack([x[rng.choice(n, 256, replace=False), j * dsub:(j + 1) * dsub] for j in range(m)]).astype(np.float32)
+    idx.set_codebook(cb)
+    cells = idx.encode(xd).cpu().numpy()
+    obj = idx.train_pq_device(xd, iters=1, from_current=True)
+    got = idx.get_codebook()
+    for j in range(0, m, 3):
+        sub = x[:, j * dsub:(j + 1) * dsub]
+        ref, robj = O.kmeans(sub, 256, 1, seed=0, start=cb[j])
+        assert np.isclose(obj[0, j], robj[0], rtol=1e-6), (j, obj[0, j], robj[0])
+        check_update(sub, cb[j], cells[:, j].astype(np.int64), got[j], ref, GAP_PQ, f"sub-quantizer {j}")
+
+
 def test_pq_seeded_start_and_the_host_training(psc):
     """Seeded start: iteration 1 equals the oracle's from the documented starting rows; over
     several iterations the objective never rises and the result quantizes as well as the host
