@@ -660,45 +660,64 @@ __device__ __forceinline__ float part_of(float v, float &rest)
     return (float)h;
 }
 
+// tile_max2: per tile the largest squared length of its centroids (rounded up; one that is not a number stays
+// on top and leaves every row undecided).
+template <int DIM>
 __global__ void __launch_bounds__(64)
-split_centroids_kernel(const float *__restrict__ cent, const float *__restrict__ mu, int nlist, int dim,
-                       bf16x8 *__restrict__ image, uint32_t *__restrict__ cmax2)
+split_centroids_kernel(const float *__restrict__ cent, const float *__restrict__ mu, int nlist,
+                       bf16x8 *__restrict__ image, float *__restrict__ tile_max2)
 {
+    constexpr int KS = DIM / 16;
     const int tile = blockIdx.x, lane = threadIdx.x, half = lane >> 5, c = tile * 32 + (lane & 31);
-    const int steps = dim / 16;
-    bf16x8 *out = image + (int64_t)tile * (2 * steps + 1) * 64;
+    bf16x8 *out = image + (int64_t)tile * (2 * KS + 1) * 64;
+    float4 v[2 * KS], m[2 * KS];
+#pragma unroll
+    for (int i = 0; i < 2 * KS; ++i) {
+        const int d = 16 * (i >> 1) + 8 * half + 4 * (i & 1);
+        v[i] = c < nlist ? *(const float4 *)(cent + (int64_t)c * DIM + d) : make_float4(0.f, 0.f, 0.f, 0.f);
+        m[i] = c < nlist ? *(const float4 *)(mu + d) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
     double norm = 0.0;
-    for (int t = 0; t < steps; ++t) {
+#pragma unroll
+    for (int t = 0; t < KS; ++t) {
         bf16x8 h, l;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int d = 16 * t + 8 * half + i;
-            const float v = c < nlist ? cent[(int64_t)c * dim + d] - mu[d] : 0.f;
-            float r1, r2;
-            h[i] = (__bf16)part_of(v, r1);
-            l[i] = (__bf16)part_of(r1, r2);
-            norm += (double)v * (double)v;
+        for (int i = 0; i < 2; ++i) {
+            const float4 a = v[2 * t + i], b = m[2 * t + i];
+            const float e[4] = {a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w};
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                float r1, r2;
+                h[4 * i + p] = (__bf16)part_of(e[p], r1);
+                l[4 * i + p] = (__bf16)part_of(r1, r2);
+                norm += (double)e[p] * (double)e[p];
+            }
         }
         out[(2 * t) * 64 + lane] = h;
         out[(2 * t + 1) * 64 + lane] = l;
     }
     norm += __shfl_xor(norm, 32, 64);
-    // (bits of floats that are not negative are ordered as the floats are; one that is not a number
-    //  stays on top and sends every row to the comparison with all centroids)
-    if (half == 0 && c < nlist) atomicMax(cmax2, __float_as_uint((float)norm * 1.0001f));
     bf16x8 n;
 #pragma unroll
     for (int i = 0; i < 8; ++i) n[i] = (__bf16)0.f;
     if (half == 0) {  // (places past the last centroid: farther than anything finite)
-        float v = c < nlist ? (float)norm : 3.3e38f;
+        float r = c < nlist ? (float)norm : 3.3e38f;
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             float rest;
-            n[i] = (__bf16)part_of(v, rest);
-            v = c < nlist ? rest : 0.f;
+            n[i] = (__bf16)part_of(r, rest);
+            r = c < nlist ? rest : 0.f;
         }
     }
-    out[(2 * steps) * 64 + lane] = n;
+    out[(2 * KS) * 64 + lane] = n;
+    // (bits of floats that are not negative are ordered as the floats are)
+    uint32_t top = c < nlist ? __float_as_uint((float)norm * 1.0001f) : 0u;
+#pragma unroll
+    for (int off = 16; off >= 1; off >>= 1) {
+        const uint32_t o = (uint32_t)__shfl_xor((int)top, off, 64);
+        top = o > top ? o : top;
+    }
+    if (lane == 0) tile_max2[tile] = __uint_as_float(top);
 }
 
 constexpr int kSplitWaves = 4;
@@ -714,7 +733,7 @@ template <int DIM>
 __global__ void __launch_bounds__(kSplitWaves * 64) __attribute__((amdgpu_waves_per_eu(3)))
 nearest_centroid_split_kernel(const float *__restrict__ x, int64_t n, const float *__restrict__ cent,
                               const float *__restrict__ mu, const bf16x8 *__restrict__ image,
-                              const float *__restrict__ cmax2_dev, int nlist, int tile_bits,
+                              const float *__restrict__ tile_max2, int nlist, int tile_bits,
                               int32_t *__restrict__ assign)
 {
     constexpr int KS = DIM / 16;
@@ -728,7 +747,12 @@ nearest_centroid_split_kernel(const float *__restrict__ x, int64_t n, const floa
     __shared__ int tally[2];
     const int tid = (int)threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, col = lane & 31;
     const int64_t r0 = (int64_t)blockIdx.x * (32 * kSplitWaves) + wave * 32;
-    const float cmax2 = *cmax2_dev;
+    const int ntiles = (nlist + 31) / 32;
+    uint32_t top = 0u;  // (as in split_centroids_kernel)
+    for (int i = lane; i < ntiles; i += 64) top = max(top, __float_as_uint(tile_max2[i]));
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) top = max(top, (uint32_t)__shfl_xor((int)top, off, 64));
+    const float cmax2 = __uint_as_float(__builtin_amdgcn_readfirstlane((int)top));
     const float unit = 6.103515625e-5f + __uint_as_float((uint32_t)(127 - 22 + tile_bits) << 23);
 
     bf16x8 xh[KS], xl[KS], one;
@@ -757,7 +781,6 @@ nearest_centroid_split_kernel(const float *__restrict__ x, int64_t n, const floa
 #pragma unroll
         for (int i = 0; i < 8; ++i) one[i] = (__bf16)(half == 0 && i < 3 ? 1.f : 0.f);
     }
-    const int ntiles = (nlist + 31) / 32;
     constexpr int kPer = 2 * KS * 64 / kThreads;  // whole turns of the workgroup, and one of wave 0 for the norms
     static_assert(kPer * kThreads == 2 * KS * 64, "operands of a tile");
     u32x4 hold[kPer], hold_norm = {0u, 0u, 0u, 0u};
@@ -851,12 +874,15 @@ nearest_centroid_split_kernel(const float *__restrict__ x, int64_t n, const floa
         for (int i = lane >> 4; i - (lane >> 4) < npairs; i += 4) {
             const uint32_t e = pairs[wave][i < npairs ? i : npairs - 1];  // (the last one again: the same key)
             const int row = (int)(e >> 16), c = (int)(e & 0xffffu);
-            const float4 *xr = (const float4 *)(x + (r0 + row) * DIM), *cr = (const float4 *)(cent + (int64_t)c * DIM);
+            typedef float row4 __attribute__((ext_vector_type(4), aligned(4)));  // (rows of the caller's start anywhere)
+            const row4 *xr = (const row4 *)(x + (r0 + row) * DIM);
+            const float4 *cr = (const float4 *)(cent + (int64_t)c * DIM);
             float d = 0.f;
 #pragma unroll
             for (int p = 0; p < (DIM / 4 + 15) / 16; ++p) {
                 if (16 * p + l16 >= DIM / 4) continue;
-                const float4 xv = xr[16 * p + l16], cv = cr[16 * p + l16];
+                const row4 xv = xr[16 * p + l16];
+                const float4 cv = cr[16 * p + l16];
                 const float dx = xv.x - cv.x, dy = xv.y - cv.y, dz = xv.z - cv.z, dw = xv.w - cv.w;
                 d = fmaf(dx, dx, d);
                 d = fmaf(dy, dy, d);
@@ -1263,17 +1289,35 @@ static size_t split_operand_bytes(int nlist, int dim) { return (size_t)((nlist +
 size_t centroid_split_bytes(int nlist, int dim)
 {
     if (dim != 32 && dim != 64 && dim != 96 && dim != 128) return 0;
-    return split_operand_bytes(nlist, dim) + 64;  // (then the largest norm)
+    return split_operand_bytes(nlist, dim) + (size_t)((nlist + 31) / 32) * sizeof(float);  // (tile_max2)
 }
 
 int launch_split_centroids(const float *cent_dev, const float *mu_dev, int nlist, int dim, void *image_dev, hipStream_t s)
 {
-    uint32_t *cmax2 = (uint32_t *)((char *)image_dev + split_operand_bytes(nlist, dim));
-    hipLaunchKernelGGL(zero_i32_kernel, dim3(1), dim3(64), 0, s, (int32_t *)cmax2, (int64_t)1);
-    hipLaunchKernelGGL(split_centroids_kernel, dim3((unsigned)((nlist + 31) / 32)), dim3(64), 0, s, cent_dev, mu_dev, nlist, dim,
-                       (bf16x8 *)image_dev, cmax2);
+    float *tile_max2 = (float *)((char *)image_dev + split_operand_bytes(nlist, dim));
+    const dim3 grid((unsigned)((nlist + 31) / 32)), block(64);
+#define CALL(D)                                                                                                  \
+    hipLaunchKernelGGL((split_centroids_kernel<D>), grid, block, 0, s, cent_dev, mu_dev, nlist, (bf16x8 *)image_dev, \
+                       tile_max2)
+    switch (dim) {
+    case 32: CALL(32); break;
+    case 64: CALL(64); break;
+    case 96: CALL(96); break;
+    case 128: CALL(128); break;
+    default: set_error("no split assignment for dimension %d", dim); return PSC_EINVAL;
+    }
+#undef CALL
     PSC_HIP_TRY(hipGetLastError());
     return PSC_OK;
+}
+
+// The float32 products are done sooner where there is little for either to do (float32 / split, us: 32 lists of
+// 32 dimensions, 1k rows 13 / 18, 1M 112 / 161; 128 of 64, 20k rows 21 / 23, 1M 294 / 218; 256 of 64, 26 / 26
+// and 424 / 250); rows of 96 dimensions and more pass through the split search faster in any case (32
+// lists of 128 dimensions, 20k rows 21 / 21, 1M 421 / 221).
+bool split_assignment_pays(int64_t n, int dim, int nlist)
+{
+    return (int64_t)nlist * dim >= 16384 || (dim >= 96 && n >= 50'000);
 }
 
 int launch_nearest_centroid_split(const float *x_dev, int64_t n, int dim, const float *cent_dev, int nlist,
@@ -1284,7 +1328,7 @@ int launch_nearest_centroid_split(const float *x_dev, int64_t n, int dim, const 
     if (n == 0) return PSC_OK;
     constexpr int kRowsPer = 32 * kSplitWaves;
     PSC_REQUIRE((n + kRowsPer - 1) / kRowsPer <= 0x7fffffffLL, "too many rows");
-    const float *cmax2 = (const float *)((const char *)image_dev + split_operand_bytes(nlist, dim));
+    const float *tile_max2 = (const float *)((const char *)image_dev + split_operand_bytes(nlist, dim));
     int bits = 0;  // of a tile's number
     while ((1 << bits) < (nlist + 31) / 32) ++bits;
     const dim3 grid((unsigned)((n + kRowsPer - 1) / kRowsPer)), block(kSplitWaves * 64);
@@ -1295,7 +1339,7 @@ int launch_nearest_centroid_split(const float *x_dev, int64_t n, int dim, const 
 #define CALL(D)                                                                                                      \
     do {                                                                                                             \
         hipLaunchKernelGGL((nearest_centroid_split_kernel<D>), grid, block, 0, s, x_dev, n, cent_dev, mu_dev,        \
-                           (const bf16x8 *)image_dev, cmax2, nlist, bits, assign_dev);                               \
+                           (const bf16x8 *)image_dev, tile_max2, nlist, bits, assign_dev);                           \
         hipLaunchKernelGGL((nearest_centroid_marked_kernel<D>), mgrid, dim3(256), 0, s, x_dev, n, cent_dev, mu_dev,  \
                            nlist, chunk, assign_dev);                                                                \
     } while (0)

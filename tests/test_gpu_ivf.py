@@ -181,7 +181,8 @@ def test_assignment_with_many_close_calls(kind, dim, nlist, n):
     x, cent = _close_calls(kind, dim, nlist, n, seed=dim + nlist)
     idx = psc.Index(dim, 8)
     idx.ivf_set_coarse(cent)
-    got = idx.ivf_assign_encode(_dev(x), want_codes=False)[0].cpu().numpy()
+    x_dev = torch.empty(n * dim + 1, device="cuda")[1:].view(n, dim).copy_(_dev(x))  # (rows that start at any float)
+    got = idx.ivf_assign_encode(x_dev, want_codes=False)[0].cpu().numpy()
     assert got.min() >= 0 and got.max() < nlist
     c64, x64 = cent.astype(np.float64), x.astype(np.float64)
     mu = c64.mean(axis=0)
