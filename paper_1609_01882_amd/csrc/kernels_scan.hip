@@ -2765,47 +2765,68 @@ static void set_exchange(ScanArgs &a, int slots, int k)
 }
 
 // Whether a flat scan takes scan_pool_kernel, and in how many slices per query (0: it does not): two
-// estimates in microseconds, fitted to measurements over 50k .. 10M codes x 1 .. 10k queries.
-//  * pool: 256 workgroups run at a time; one takes 10 us besides its codes (0.13 us per 1000; scoring
-//    them all 0.37 at 64 bits, 0.72 at 128), all together no more than memory gives (every query
-//    reads the codes for itself); a merge 10 us and its lists' entries.
-//  * tiled: the pairs at the kernels' rates, plus about k (1 + ln(survivors / k)) insertions per list,
-//    one after the other, 0.7 us each, for every round of workgroups.
-// E.g. (pool / tiled, whole call with 25 us of launches): 100 queries x 100k, k = 10 31 / 86 us, 300k,
-// k = 100 60 / 181, 1000 x 100k, k = 100 128 / 564, 10 x 1M pure ADC, k = 100 65 / 257, 1 x 10M 49 / 150;
-// 100 x 1M, k = 10 93 / 84, 4000 x 100k, k = 10 421 / 130.
-static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool dense, const ScanPlan &p, size_t ws_bytes)
+// estimates in microseconds, from what each kernel does.
+//  * pool: 256 workgroups run at a time; each takes its start, its selections, its codes and its survivors,
+//    all together no less than memory gives (every query reads the codes for itself); several slices a merge.
+//  * tiled: a round of workgroups takes a tile's set-up, its pairs and surviving pairs, and about k (1 +
+//    ln(survivors / k)) insertions into each list, one after the other; then the merge.
+// The survivors are those of random codes and a share for one's own cluster (1 % of all codes at ht =
+// 3 m, falling with the threshold).  Coefficients fitted to, and the rule checked on, 5634 random calls (3k ..
+// 10M codes, random and clustered, x 1 .. 4000 queries, k = 1 .. 1000, thresholds 0 .. 8 m): the time is
+// 0.350 of the tiled kernels' in geometric mean (0.345 if the faster were always taken); the pool is taken
+// and more than 5 % slower in 48 calls, not taken and more than 5 % faster in 266.  E.g. (pool / tiled, us):
+// 100 queries x 100k, k = 10 31 / 86; 1000 x 100k, k = 100 128 / 564; 63 x 1.2M, ht = 0, k = 1000 233 / 48.
+struct ScanCosts {
+    // pool: a workgroup, a selection, 100 keys kept, 1000 codes, 1000 survivors
+    double group, select, kept, code, survivor;
+    // tiled: the launches, a tile, 1000 pairs by either filter and 1000 surviving pairs (to 16 waves), an insertion,
+    // the merge per result
+    double launch, tile, pair, pair_mfma, surviving_pair, insertion, merge_k;
+};
+static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool dense, bool mfma, const ScanPlan &p,
+                            size_t ws_bytes)
 {
     // (a workgroup per query: past 4096 queries the tiles are ahead; past the caches every query reads
     //  memory for itself: 50M codes of 64 bits, 1 query 138 / 179 us, 2 queries 205 / 181, 400M 786 / 644)
     const double bytes = (double)n * m;
     if (nq > 4096 || bytes > (nq == 1 ? 400e6 : 128e6)) return 0;
-    const double kilo = dense ? (m == 8 ? 0.37 : 0.72) : 0.13;
+    static constexpr ScanCosts kCosts[2][2] = {
+        {{1.4, 6.7, 2.3, 0.11, 0.58, 0.0, 24.0, 0.059, 0.0149, 0.45, 0.68, 0.25},
+         {2.0, 8.0, 2.2, 0.126, 0.92, 9.0, 11.0, 0.19, 0.035, 0.76, 0.61, 0.25}},
+        {{11.7, 0.0, 2.8, 0.385, 0.0, 0.0, 44.0, 0.213, 0.213, 0.0, 0.68, 1.7},
+         {12.2, 0.0, 2.7, 0.742, 0.0, 0.0, 28.0, 0.346, 0.346, 0.0, 0.5, 1.4}}};
+    const ScanCosts &c = kCosts[dense ? 1 : 0][m == 8 ? 0 : 1];
+    const double in_cluster = 0.01 * std::pow((double)ht / (3 * m), 6);
+    const double keep = ht >= 8 * m ? 1.0 : std::min(1.0, random_code_survival(8 * m, ht) + in_cluster);
     const double memory = (double)nq * bytes / (bytes < 128e6 ? 1e7 : 5.8e6);
+    // the slices: a merge against the codes of a workgroup (the plain estimate the fit's slices were chosen by)
+    const double kilo = dense ? (m == 8 ? 0.37 : 0.72) : 0.13;
     double best = 1e300;
-    int slices = 0;
+    int64_t slices = 0;
     for (int64_t sN = 1; sN <= 256 && (sN == 1 || (sN * nq <= 256 && sN * 8192 <= n)); sN *= 2) {
         if ((n + sN - 1) / sN > (1 << 24)) continue;
-        const double rounds = (double)((nq * sN + 255) / 256);
-        const double t = std::max(rounds * (10.0 + 1e-3 * kilo * (double)n / (double)sN), memory) +
+        const double t = std::max((double)((nq * sN + 255) / 256) * (10.0 + 1e-3 * kilo * (double)n / (double)sN), memory) +
                          (sN > 1 ? 10.0 + 1e-3 * (double)(sN * k) : 0.0);
         if (t < best) {
             best = t;
-            slices = (int)sN;
+            slices = sN;
         }
     }
     if (slices == 0) return 0;
-    const double keep = ht >= 8 * m ? 1.0 : std::min(1.0, random_code_survival(8 * m, ht) + 0.01);
-    const double whole = p.tiles_one > 0 ? (double)n : (double)p.slice_len;
-    const double insertions = k * (1.0 + std::log(std::max(1.0, keep * whole / k)));
+    const double codes = (double)n / (double)slices;
+    const double group = c.group + c.select * std::min(1.0, keep * codes / k) + 0.01 * c.kept * std::min(keep * codes, (double)k) +
+                         1e-3 * codes * (c.code + c.survivor * keep);
+    const double pool_merge = merge_selects(nq, (int)slices, k) ? 17.0 + 2.1e-3 * (double)(slices * k) : 10.0 + 0.31 * k;
+    const double pool = 10.5 + std::max((double)((nq * slices + 255) / 256) * group, memory) + (slices > 1 ? pool_merge : 0.0);
+    const double len = p.tiles_one > 0 ? (double)n : (double)p.slice_len, survivors = keep * len;
+    const double insertions = std::min(survivors, k * (1.0 + std::log(std::max(1.0, survivors / k))));
     const double rounds = std::max(1.0, (double)p.ntiles / (256.0 * p.wgs_per_cu));
-    const double pairs = (double)((nq + p.tq - 1) / p.tq * p.tq) * (double)n;
-    const double rate = dense ? (m == 8 ? 1.45e6 : 0.75e6) : (m == 8 ? 5e6 : 3.5e6);
-    const double tiled = 6.0 + std::max(pairs / rate, bytes / 5.8e6) + 0.7 * rounds * insertions +
-                         (p.nslice > 1 ? 1e-3 * (double)(p.nslice * k) : 0.0);
-    if (best > 0.9 * tiled) return 0;
+    const double tile = c.tile + c.insertion * insertions + 1e-3 * len * p.tq * 16.0 / p.nwaves *
+                                                                ((mfma ? c.pair_mfma : c.pair) + c.surviving_pair * keep);
+    const double merge = merge_selects(nq, p.nslice, k) ? 13.0 + 5e-4 * (double)p.nslice * k : c.merge_k * k;
+    if (pool > 0.95 * (c.launch + std::max(rounds * tile, bytes / 5.8e6) + merge)) return 0;
     const size_t need = 256 + ((size_t)nq * slices * k * sizeof(float) + 255) / 256 * 256 + (size_t)nq * slices * k * sizeof(int64_t);
-    return need <= ws_bytes ? slices : 0;
+    return need <= ws_bytes ? (int)slices : 0;
 }
 
 int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t nq,
@@ -2816,21 +2837,24 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
     PSC_REQUIRE(ht >= 0, "ht must be >= 0, got %d", ht);
     // survivor share from which scoring every pair is the faster route: the dense kernel takes the
     // same time whatever the threshold (it tests only the pairs that beat the k-th best), the fused
-    // one grows with the survivors (measured at 10M x 10k random codes, fused / dense: 64-bit codes
-    // ht = 29: 67.8 / 68.5 ms, ht = 30: 83.1 / 68.6; 128-bit codes ht = 60: 112 / 135, ht = 62: 152 / 135)
+    // one grows with the survivors (10M x 10k random codes, k = 100, fused / dense: 64-bit codes ht = 29:
+    // 52.1 / 68.8 ms, 30: 67.2 / 69.0, 31: 83.7 / 69.0; 128-bit codes ht = 61: 124 / 136, 62: 148 / 136)
     const double dense_from = 0.34;
     const bool dense = ht >= 8 * m || random_code_survival(8 * m, ht) >= dense_from;
     ScanPlan p;
     int rc = PSC_EINVAL;
-    // Matrix-core filter: 9 queries or more and k small enough for its tile of 16 (128 bits: 8).  Ahead
-    // at every threshold that is not the dense route's (10M random codes, 2000 queries, k = 100,
-    // matrix cores / xor-popcount; 64 bits ht = 24: 2.9 / 4.6 ms, 26: 4.5 / 6.5, 28: 8.2 / 10.1, 29:
-    // 10.7 / 12.7; 128 bits ht = 40: 3.0 / 5.4, 48: 3.2 / 5.5, 56: 8.3 / 10.1, 60: 20.7 / 21.0).
+    // Matrix-core filter: 9 queries or more and k small enough for its tile of 16 (128 bits: 8).  128 bits: ahead
+    // at every threshold that is not the dense route's (10M random codes, 2000 queries, k = 100, matrix cores
+    // / xor-popcount; ht = 40: 3.0 / 5.4 ms, 48: 3.2 / 5.5, 56: 8.3 / 10.1, 60: 20.7 / 21.0).  64 bits: so
+    // too while few pairs survive (ht = 24: 2.9 / 4.6); with a tenth or more of them surviving the lists
+    // decide, and the smaller tiles of the other keep more of them moving until there are some 5e8 pairs (2000
+    // x 10M ht = 26: 4.5 / 6.5 ms, 28: 8.2 / 10.1, 29: 10.7 / 12.7; 93 x 55k, k = 1, ht = 28: 67 / 41 us).
     // psc_set_filter_route overrides the rule (for measurements).
-    bool mfma = !dense && nq >= kMfmaMinQueries;
+    const bool enough = nq >= kMfmaMinQueries;
+    bool mfma = !dense && enough && (m == 16 || random_code_survival(64, ht) < 0.10 || (double)nq * (double)n >= 5e8);
     const int forced = g_filter_route.load(std::memory_order_relaxed);
     if (forced == PSC_ROUTE_POPCOUNT) mfma = false;
-    if (forced == PSC_ROUTE_MFMA) mfma = !dense && nq >= kMfmaMinQueries;
+    if (forced == PSC_ROUTE_MFMA) mfma = !dense && enough;
     if (mfma) {
         rc = plan_scan(m, nq, n, k, kScanFusedMfma, &p);
         // (k too large for the shape, or a workspace that holds only the popcount kernel's plan: that one takes over)
@@ -2881,7 +2905,9 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
     // the k-th best: pub_kth words x pub_r entries >= k, with pub_kth about 0.4 of the words (the
     // value then sits near the (1.3 k)-th best of everything scanned so far)
     set_exchange(a, p.pub_slots, k);
-    const int pool_slices = forced == PSC_ROUTE_AUTO && skip_first < 0 ? pool_scan_slices(m, nq, n, k, ht, dense, p, ws_bytes) : 0;
+    const int pool_slices = forced == PSC_ROUTE_AUTO && skip_first < 0
+                                ? pool_scan_slices(m, nq, n, k, ht, dense, mfma, p, ws_bytes)
+                                : 0;
     if (pool_slices > 0) {
         a.nslice = pool_slices;
         a.slice_len = ((n + pool_slices - 1) / pool_slices + 63) / 64 * 64;

@@ -154,6 +154,21 @@ def test_pool_scan(psc, m, n, nq, k, lut_kind):
             assert nd == 0 and np.array_equal(got_d[ref["ids"] >= 0], ref["dists"][ref["ids"] >= 0])
 
 
+@pytest.mark.parametrize("m,n,nq,k,ht,kernel", [
+    (8, 650_403, 273, 100, 0, "scan_mfma_kernel"), (16, 3_942_775, 22, 100, 32, "scan_mfma_kernel"),
+    (8, 160_602, 2384, 100, 0, "scan_mfma_kernel"), (8, 54_554, 4300, 1, 28, "scan_kernel"), (8, 12_123, 4200, 10, 29, "scan_kernel")])
+def test_few_survivors_and_small_lists_take_the_tiled_kernels(psc, force_route, m, n, nq, k, ht, kernel):
+    """Sizes at which the pool (hardly anything survives: the lists cost nothing) or the matrix-core filter (many
+    survive few pairs) takes 1.5 to 3 times as long as the kernel named; the answer is that of the others."""
+    codes, qcodes, lut = (_dev(a) for a in _rand_problem(m, n, nq, seed=n % 1000, lut_kind="float"))
+    got = psc.scan(lut, qcodes, codes, ht, k)
+    assert psc.last_scan_route().split()[0] == kernel, psc.last_scan_route()
+    force_route("popcount" if kernel == "scan_mfma_kernel" else "mfma")
+    want = psc.scan(lut, qcodes, codes, ht, k)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
 @pytest.mark.parametrize("m,n,nq,k", [(8, 20_000, 12, 40), (8, 100_003, 40, 300), (16, 20_000, 12, 300),
                                       (16, 40_001, 1, 1024), (8, 40_001, 2, 50), (8, 1_200_000, 2, 600)])
 def test_small_scans_answer_tables_that_are_not_finite_as_the_tiled_kernels_do(psc, force_route, m, n, nq, k):
