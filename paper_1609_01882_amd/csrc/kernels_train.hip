@@ -238,9 +238,9 @@ template <int DSUB>
 int run_pq_step(const float *cb, int dim, int m, const float *x, int64_t n, uint8_t *cell, float *dmin,
                 double *gsum, uint32_t *gcount, double *gobj, hipStream_t s)
 {
-    // the number of sub-vectors from which the scalar cache is ahead (measured at 300 .. 100k rows, 8 and 16
-    // sub-quantizers; long ones: at any number)
-    constexpr int64_t from = DSUB <= 16 ? 600'000 : DSUB <= 32 ? 160'000 : 0;
+    // the number of sub-vectors from which the scalar cache is ahead (measured at 300 .. 130k rows, 8 and 16
+    // sub-quantizers; sub-vectors of up to 4: even; long ones: at any number)
+    constexpr int64_t from = DSUB <= 8 ? 700'000 : DSUB <= 24 ? 220'000 : DSUB <= 32 ? 130'000 : 0;
     if constexpr (from != 0)
         if (n * m < from) return run_pq_step_form<DSUB, false>(cb, dim, m, x, n, cell, dmin, gsum, gcount, gobj, s);
     return run_pq_step_form<DSUB, true>(cb, dim, m, x, n, cell, dmin, gsum, gcount, gobj, s);

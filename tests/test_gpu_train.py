@@ -93,7 +93,7 @@ def test_pq_lloyd_iterations_from_a_common_start(psc, dim, m):
         cb = nxt  # both sides go on from the oracle's centroids
 
 
-@pytest.mark.parametrize("dim,m,n", [(128, 8, 75_101), (64, 16, 37_400), (256, 8, 20_003), (256, 8, 19_999)])
+@pytest.mark.parametrize("dim,m,n", [(128, 8, 27_501), (64, 16, 43_751), (256, 8, 16_251), (256, 8, 16_249)])
 def test_pq_lloyd_iteration_of_many_rows(psc, dim, m, n):
     """The step kernel has two forms, by the number of sub-vectors: sizes around the limits."""
     dsub = dim // m
