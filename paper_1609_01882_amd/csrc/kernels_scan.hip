@@ -2818,13 +2818,16 @@ static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool de
                          1e-3 * codes * (c.code + c.survivor * keep);
     const double pool_merge = merge_selects(nq, (int)slices, k) ? 17.0 + 2.1e-3 * (double)(slices * k) : 10.0 + 0.31 * k;
     const double pool = 10.5 + std::max((double)((nq * slices + 255) / 256) * group, memory) + (slices > 1 ? pool_merge : 0.0);
-    const double len = p.tiles_one > 0 ? (double)n : (double)p.slice_len, survivors = keep * len;
-    const double insertions = std::min(survivors, k * (1.0 + std::log(std::max(1.0, survivors / k))));
-    const double rounds = std::max(1.0, (double)p.ntiles / (256.0 * p.wgs_per_cu));
-    const double tile = c.tile + c.insertion * insertions + 1e-3 * len * p.tq * 16.0 / p.nwaves *
-                                                                ((mfma ? c.pair_mfma : c.pair) + c.surviving_pair * keep);
+    auto tile_time = [&](double len) {
+        const double survivors = keep * len, insertions = std::min(survivors, k * (1.0 + std::log(std::max(1.0, survivors / k))));
+        return c.tile + c.insertion * insertions +
+               1e-3 * len * p.tq * 16.0 / p.nwaves * ((mfma ? c.pair_mfma : c.pair) + c.surviving_pair * keep);
+    };
+    const double at_a_time = 256.0 * p.wgs_per_cu, sliced = (double)(p.ntiles - p.tiles_one) / at_a_time;
+    const double scan = (double)p.tiles_one / at_a_time * tile_time((double)n) +
+                        (p.tiles_one > 0 ? sliced : std::max(1.0, sliced)) * tile_time((double)p.slice_len);
     const double merge = merge_selects(nq, p.nslice, k) ? 13.0 + 5e-4 * (double)p.nslice * k : c.merge_k * k;
-    if (pool > 0.95 * (c.launch + std::max(rounds * tile, bytes / 5.8e6) + merge)) return 0;
+    if (pool > 0.95 * (c.launch + std::max(scan, bytes / 5.8e6) + merge)) return 0;
     const size_t need = 256 + ((size_t)nq * slices * k * sizeof(float) + 255) / 256 * 256 + (size_t)nq * slices * k * sizeof(int64_t);
     return need <= ws_bytes ? (int)slices : 0;
 }
