@@ -24,9 +24,33 @@ def graph_setup():
     return psc, idx
 
 
+@pytest.fixture(scope="module")
+def graph_setup_128bit():
+    import paper_1609_01882_amd as psc
+    xt = W.relu_like(3000, seed=95, stream=1)
+    idx = psc.Index(256, 16)
+    idx.train_pq(xt, iters=4, seed=1)
+    idx.optimize_index_assignment(n_iter=20_000, seed=2)
+    return psc, idx
+
+
+@pytest.mark.parametrize("route", ["auto", "popcount"])
+@pytest.mark.parametrize("n,ht,k", [(6001, 40, 10), (40_000, 44, 10), (3000, 61, 100)])
+def test_graph_of_128_bit_codes_matches_oracle(graph_setup_128bit, force_route, route, n, ht, k):
+    """Tiles of 8 queries whose own rows are skipped, by either filter."""
+    psc, idx = graph_setup_128bit
+    force_route(route)
+    _check_graph(psc, idx, n, ht, k)
+    assert psc.last_scan_route().startswith("scan_mfma_kernel " if route == "auto" else "scan_kernel ")
+
+
 @pytest.mark.parametrize("n,ht,k", [(6001, 20, 10), (6001, 64, 10), (40_000, 22, 10), (3000, 26, 100)])
 def test_graph_matches_oracle(graph_setup, n, ht, k):
     psc, idx = graph_setup
+    _check_graph(psc, idx, n, ht, k)
+
+
+def _check_graph(psc, idx, n, ht, k):
     x = W.relu_like(n, seed=91, stream=2)
     x_dev = _dev(x)
     codes = idx.encode(x_dev)

@@ -13,9 +13,11 @@ from gpu_util import assert_topk_matches
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("route", ["auto", "popcount", "mfma"])
 @pytest.mark.parametrize("n,nq,ht,k", [(300_001, 12, 24, 100), (1_200_003, 1, 22, 10)])
-def test_replays_of_a_recorded_scan_equal_eager_calls(n, nq, ht, k):
+def test_replays_of_a_recorded_scan_equal_eager_calls(force_route, route, n, nq, ht, k):
     import paper_1609_01882_amd as psc
+    force_route(route)  # (forced: the tiled kernels, without the pool)
     m = 8
     rng = np.random.default_rng(31 + nq)
     codes = W.random_codes(n, m, seed=61)

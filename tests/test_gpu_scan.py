@@ -41,6 +41,20 @@ def _run(psc, lut, qcodes, codes, ht, k):
     return ids.cpu().numpy(), d.cpu().numpy()
 
 
+def _took(psc, route, m, nq, ht, k=1):
+    """The kernel a forced route launches (None: automatic, which also knows the pool)."""
+    took = psc.last_scan_route().split()[0]
+    dense_from = 30 if m == 8 else 62
+    if ht >= 8 * m:
+        want = "adc_kernel"
+    elif ht >= dense_from:
+        want = "adc_kernel+filter"
+    else:  # (k past the largest that fits its tile of 16 queries, 8 at 128 bits: the narrower tiles of the other)
+        want = "scan_mfma_kernel" if route == "mfma" and nq >= 9 and k <= (136 if m == 8 else 272) else "scan_kernel"
+    assert route == "auto" or took == want, (route, took, want)
+
+
+@pytest.mark.parametrize("route", ["auto", "mfma", "popcount"])
 @pytest.mark.parametrize("m,n,nq,k,lut_kind", [
     (8, 100_003, 37, 10, "float"),      # ragged tail (odd n), ragged query tile
     (8, 100_003, 37, 100, "int"),       # exact ties: ids must match exactly
@@ -55,12 +69,14 @@ def _run(psc, lut, qcodes, codes, ht, k):
     (16, 33_001, 2, 100, "int"),
     (16, 40_001, 7, 10, "float"),
 ])
-def test_scan_random_codes(psc, m, n, nq, k, lut_kind):
+def test_scan_random_codes(psc, force_route, route, m, n, nq, k, lut_kind):
+    force_route(route)
     codes, qcodes, lut = _rand_problem(m, n, nq, seed=100 + m + k, lut_kind=lut_kind)
     nb = 8 * m
     for ht in sorted({0, nb // 4, nb * 3 // 8, nb // 2 - 4, nb // 2, nb, nb + 50}):
         print(f"case m={m} n={n} nq={nq} k={k} lut={lut_kind} ht={ht}", flush=True)
         got_ids, got_d = _run(psc, lut, qcodes, codes, ht, k)
+        _took(psc, route, m, nq, ht, k)
         ref = O.scan(lut.astype(np.float64), qcodes, codes, ht, k)
         nd = assert_topk_matches(got_ids, got_d, ref, lut.astype(np.float64), qcodes, codes, min(ht, nb),
                                  what=f"m={m} ht={ht} k={k}")
@@ -69,28 +85,32 @@ def test_scan_random_codes(psc, m, n, nq, k, lut_kind):
 
 
 @pytest.mark.parametrize("route", ["mfma", "popcount"])
-@pytest.mark.parametrize("n,nq,k,lut_kind", [
-    (100_003, 37, 10, "float"),     # ragged last block (n % 128 = 35), ragged query tile (37 = 2 * 16 + 5)
-    (100_003, 37, 100, "int"),      # exact ties: ids must match exactly
-    (65_536 + 127, 160, 136, "int"),  # the largest k of the 16-query tile
-    (9_000, 17, 5, "float"),        # barely more than one tile of queries, one slice
-    (300_001, 9, 10, "int"),        # the fewest queries the matrix-core route takes: many slices
-    (50_000, 16, 100, "float"),     # exactly one full tile
-    (1_000_001, 48, 20, "float"),   # several slices per query tile
+@pytest.mark.parametrize("m,n,nq,k,lut_kind", [
+    (8, 100_003, 37, 10, "float"),     # ragged last block (n % 128 = 35), ragged query tile (37 = 2 * 16 + 5)
+    (8, 100_003, 37, 100, "int"),      # exact ties: ids must match exactly
+    (8, 65_536 + 127, 160, 136, "int"),  # the largest k of the 16-query tile
+    (8, 9_000, 17, 5, "float"),        # barely more than one tile of queries, one slice
+    (8, 300_001, 9, 10, "int"),        # the fewest queries the matrix-core route takes: many slices
+    (8, 50_000, 16, 100, "float"),     # exactly one full tile
+    (8, 1_000_001, 48, 20, "float"),   # several slices per query tile
+    (16, 100_003, 37, 10, "float"),    # 128 bits: blocks of 256 codes, tiles of 8 queries (37 = 4 * 8 + 5)
+    (16, 100_003, 37, 100, "int"),
+    (16, 65_536 + 255, 80, 272, "int"),  # the largest k of the 8-query tile
+    (16, 300_001, 9, 10, "int"),
+    (16, 500_001, 48, 20, "float"),
 ])
-def test_both_filter_routes(psc, force_route, route, n, nq, k, lut_kind):
+def test_both_filter_routes(psc, force_route, route, m, n, nq, k, lut_kind):
     """The Hamming test runs either as xor/popcount or on the matrix cores; the library picks by
-    shape and threshold.  Here each route is forced in turn (psc_set_filter_route) on 64-bit codes
-    with 9 queries or more and must give the oracle's result at every threshold, including
+    shape and threshold.  Here each route is forced in turn (psc_set_filter_route) on batches
+    of 9 queries or more and must give the oracle's result at every threshold, including
     those the rule would hand to the other route."""
     force_route(route)
-    codes, qcodes, lut = _rand_problem(8, n, nq, seed=900 + k, lut_kind=lut_kind)
-    for ht in (0, 9, 16, 22, 24, 27, 29, 30, 33):
-        print(f"case route={route} n={n} nq={nq} k={k} ht={ht}", flush=True)
+    codes, qcodes, lut = _rand_problem(m, n, nq, seed=900 + k, lut_kind=lut_kind)
+    for ht in (0, 9, 16, 22, 24, 27, 29, 30, 33) if m == 8 else (0, 20, 40, 48, 54, 59, 61, 62, 66):
+        print(f"case route={route} m={m} n={n} nq={nq} k={k} ht={ht}", flush=True)
         got_ids, got_d = _run(psc, lut, qcodes, codes, ht, k)
         # the library says which kernel it launched: the forced filter below the dense route's thresholds
-        took = psc.last_scan_route().split()[0]
-        assert took == ("adc_kernel+filter" if ht >= 30 else "scan_mfma_kernel" if route == "mfma" else "scan_kernel"), took
+        _took(psc, route, m, nq, ht, k)
         ref = O.scan(lut.astype(np.float64), qcodes, codes, ht, k)
         nd = assert_topk_matches(got_ids, got_d, ref, lut.astype(np.float64), qcodes, codes, ht,
                                  what=f"route={route} ht={ht} k={k}")
@@ -98,17 +118,44 @@ def test_both_filter_routes(psc, force_route, route, n, nq, k, lut_kind):
             assert nd == 0 and np.array_equal(got_d[ref["ids"] >= 0], ref["dists"][ref["ids"] >= 0])
 
 
-def test_survivor_set_on_the_matrix_cores(psc, force_route):
-    """k above the number of survivors: the matrix-core route lists exactly the survivor set, for
-    thresholds on both sides of every bit count the +-1 dot product can take near them."""
+@pytest.mark.parametrize("m,hts", [(8, (17, 18, 19, 20)), (16, (39, 41, 43, 44))])
+def test_survivor_set_on_the_matrix_cores(psc, force_route, m, hts):
+    """k above the number of survivors: the matrix-core route lists exactly the survivor set."""
     force_route("mfma")
-    codes, qcodes, lut = _rand_problem(8, 40_000, 33, seed=77, lut_kind="float")
-    for ht in (17, 18, 19, 20):
-        ref = O.scan(lut.astype(np.float64), qcodes, codes, ht, 136, want_bitmap=True)
-        got_ids, _ = _run(psc, lut, qcodes, codes, ht, 136)
+    k = 136
+    codes, qcodes, lut = _rand_problem(m, 40_000, 33, seed=77, lut_kind="float")
+    for ht in hts:
+        ref = O.scan(lut.astype(np.float64), qcodes, codes, ht, k, want_bitmap=True)
+        got_ids, _ = _run(psc, lut, qcodes, codes, ht, k)
+        _took(psc, "mfma", m, 33, ht, k)
+        assert (ref["nsurv"] <= k).any()
         for q in range(33):
-            if ref["nsurv"][q] <= 136:
+            if ref["nsurv"][q] <= k:
                 assert sorted(got_ids[q][got_ids[q] >= 0].tolist()) == np.flatnonzero(ref["bitmap"][q]).tolist()
+
+
+@pytest.mark.parametrize("m", [8, 16])
+def test_pairs_at_the_threshold(psc, force_route, m):
+    """Codes at distance ht and ht + 1 of a query, the differing bits drawn anywhere, at every threshold of the
+    matrix-core filter: the fields of its results hold ht + 8 m - distance in 7 (8) bits, whose
+    verdict changes between these two.  Every query slot, place in a block and result register has some."""
+    force_route("mfma")
+    nq, per, k = 24, 96, 100
+    rng = np.random.default_rng(m)
+    for ht in range(0, 30 if m == 8 else 62):
+        qcodes = W.random_codes(nq, m, seed=ht)
+        owner = rng.permutation(np.repeat(np.arange(nq), per))
+        bits = np.unpackbits(qcodes[owner], axis=1)
+        far = rng.integers(0, 2, size=len(owner))
+        order = rng.random(bits.shape).argsort(axis=1)
+        bits ^= (order < (ht + far)[:, None]).astype(np.uint8)
+        codes = np.packbits(bits, axis=1)
+        lut = rng.integers(0, 4, size=(nq, m, 256)).astype(np.float32)
+        got_ids, got_d = _run(psc, lut, qcodes, codes, ht, k)
+        _took(psc, "mfma", m, nq, ht, k)
+        ref = O.scan(lut.astype(np.float64), qcodes, codes, ht, k)
+        assert np.array_equal(got_ids, ref["ids"]), (m, ht)
+        assert np.array_equal(got_d[ref["ids"] >= 0], ref["dists"][ref["ids"] >= 0])
 
 
 @pytest.mark.parametrize("m,nq", [(8, 9), (8, 16), (8, 33), (16, 9), (16, 16), (16, 17)])
@@ -209,15 +256,16 @@ def test_small_scans_answer_tables_that_are_not_finite_as_the_tiled_kernels_do(p
             assert np.array_equal(got_d[q][: len(order)], d[order].astype(np.float32))
 
 
+@pytest.mark.parametrize("m", [8, 16])
 @pytest.mark.parametrize("route", ["mfma", "popcount"])
-def test_nested_prefix_patterns_at_every_threshold(psc, force_route, route):
-    """Database row r = the first r bits set (r = 0..64, repeated to fill several blocks), query q =
-    the first 3q bits set: their Hamming distance is |r - 3q| exactly, so the survivor set at every
-    threshold is known in closed form.  Both filters at every threshold they serve, and the dense
-    route, which tests only the pairs that beat the k-th best, at the thresholds above (30 and
+def test_nested_prefix_patterns_at_every_threshold(psc, force_route, route, m):
+    """Database row r = the first r bits set (r = 0..8m, repeated to fill several blocks), query q =
+    the first 3q (128 bits: 6q) bits set: their Hamming distance is |r - 3q| exactly, so the survivor set
+    at every threshold is known in closed form.  Both filters at every threshold they serve, and the dense
+    route, which tests only the pairs that beat the k-th best, at the thresholds above (30, 62 and
     more); the table makes the distance itself the score."""
     force_route(route)
-    m, reps, nq = 8, 7, 20
+    reps, nq = 7, 20
     def prefix(r):
         c = np.zeros(m, np.uint8)
         full, rem = divmod(r, 8)
@@ -225,9 +273,9 @@ def test_nested_prefix_patterns_at_every_threshold(psc, force_route, route):
         if rem:
             c[full] = (1 << rem) - 1
         return c
-    rows = np.array([r for _ in range(reps) for r in range(65)])
+    rows = np.array([r for _ in range(reps) for r in range(8 * m + 1)])
     codes = np.stack([prefix(r) for r in rows])
-    qbits = np.array([3 * q for q in range(nq)])
+    qbits = np.array([3 * m // 8 * q for q in range(nq)])
     qc = np.stack([prefix(b) for b in qbits])
     lut = np.zeros((nq, m, 256), np.float32)
     pc = np.array([bin(v).count("1") for v in range(256)], np.float32)
@@ -235,8 +283,9 @@ def test_nested_prefix_patterns_at_every_threshold(psc, force_route, route):
         for j in range(m):
             lut[q, j] = pc[np.arange(256) ^ int(qc[q, j])]
     k = 136
-    for ht in range(0, 36):
+    for ht in range(0, 36 if m == 8 else 67):
         ids, d = _run(psc, lut, qc, codes, ht, k)
+        _took(psc, route, m, nq, ht, k)
         for q in range(nq):
             want = np.flatnonzero(np.abs(rows - qbits[q]) <= ht)
             got = ids[q][ids[q] >= 0]
@@ -247,17 +296,22 @@ def test_nested_prefix_patterns_at_every_threshold(psc, force_route, route):
             assert np.array_equal(d[q][: len(got)], np.abs(rows[got] - qbits[q]).astype(np.float32)), (route, ht, q)
 
 
+@pytest.mark.parametrize("m,nq,hts", [(8, 4100 + 13, (14, 22)), (16, 2048 + 13, (30, 44))])
 @pytest.mark.parametrize("route", ["mfma", "popcount"])
-def test_whole_and_sliced_query_tiles_in_one_launch(psc, force_route, route):
+def test_whole_and_sliced_query_tiles_in_one_launch(psc, force_route, route, m, nq, hts):
     """More query tiles than workgroups run at a time: the tiles of the whole rounds scan the
     database in one piece, those of the last partial round in slices.  Queries from both regions
     (and the last, ragged tile) against the oracle."""
     force_route(route)
-    n, nq, k = 150_011, 4100 + 13, 20
-    codes, qcodes, lut = _rand_problem(8, n, nq, seed=4242, lut_kind="float")
-    sel = np.array([0, 1, 15, 16, 2047, 4079, 4080, 4095, 4096, 4097, 4111, 4112])
-    for ht in (14, 22):
+    n, k = 150_011, 20
+    codes, qcodes, lut = _rand_problem(m, n, nq, seed=4242, lut_kind="float")
+    sel = np.array([0, 1, 7, 8, 15, 16, nq // 2, nq - 34, nq - 33, nq - 18, nq - 17, nq - 16, nq - 13, nq - 6, nq - 5, nq - 2, nq - 1])
+    for ht in hts:
         got_ids, got_d = _run(psc, lut, qcodes, codes, ht, k)
+        _took(psc, route, m, nq, ht, k)
+        took = dict(f.split("=") for f in psc.last_scan_route().split()[1:])
+        whole = int(took["tiles"]) < -(-nq // int(took["tq"])) * int(took["slices"])
+        assert whole, psc.last_scan_route()  # (some tiles in one piece, others in slices)
         ref = O.scan(lut[sel].astype(np.float64), qcodes[sel], codes, ht, k)
         assert_topk_matches(got_ids[sel], got_d[sel], ref, lut[sel].astype(np.float64), qcodes[sel], codes, ht,
                             what=f"two regions route={route} ht={ht}")
@@ -319,24 +373,31 @@ def test_a_workspace_for_the_popcount_plan_is_enough(psc, force_route, m, nq, ht
         psc.scan(lut, qcodes, codes, ht, k, workspace=ws[:-1])
 
 
-def test_many_slices_for_few_queries(psc):
-    """Two queries over 3M codes: 256 database slices, whose partial lists the merge takes four to a lane."""
+@pytest.mark.parametrize("route", ["auto", "popcount"])
+def test_many_slices_for_few_queries(psc, force_route, route):
+    """Two queries over 3M codes: 256 database slices, whose partial lists the merge takes four to a lane (without
+    the pool, which a forced route excludes)."""
+    force_route(route)
     codes, qcodes, lut = _rand_problem(8, 3_000_001, 2, seed=321, lut_kind="float")
     for ht, k in ((22, 10), (64, 3)):
         got_ids, got_d = _run(psc, lut, qcodes, codes, ht, k)
+        _took(psc, route, 8, 2, ht, k)
+        assert route == "auto" or int(psc.last_scan_route().split("slices=")[1].split()[0]) > 128
         ref = O.scan(lut.astype(np.float64), qcodes, codes, ht, k)
         assert_topk_matches(got_ids, got_d, ref, lut.astype(np.float64), qcodes, codes, ht, what=f"many slices ht={ht}")
 
 
 @pytest.mark.parametrize("case", ["all tied", "best in one slice", "wide range"])
-@pytest.mark.parametrize("nq,k", [(1, 100), (3, 7), (12, 1), (5, 640)])
-def test_what_the_slices_tell_each_other_costs_no_result(psc, case, nq, k):
+@pytest.mark.parametrize("route", ["auto", "popcount"])
+@pytest.mark.parametrize("nq,k,m", [(1, 100, 8), (3, 7, 8), (12, 1, 8), (5, 640, 8), (3, 100, 16)])
+def test_what_the_slices_tell_each_other_costs_no_result(psc, force_route, route, case, nq, k, m):
     """Queries cut into many slices prune with a bound taken from the other slices' lists (the
     r-th best of each, and the value enough of them have reached).  Where that bound equals the
     k-th distance (everything tied), where one slice holds the whole answer, and where distances
     span sixty binary orders of magnitude (the bound is rounded up in the float's bits), the result
     is still the oracle's."""
-    n, m = 1_200_007, 8
+    force_route(route)
+    n = 1_200_007
     rng = np.random.default_rng(900 + k)
     codes, qcodes, lut = _rand_problem(m, n, nq, seed=901 + k, lut_kind="int")
     if case == "all tied":
@@ -349,8 +410,10 @@ def test_what_the_slices_tell_each_other_costs_no_result(psc, case, nq, k):
         lut[:, 0, 16:] = 50.0
     else:
         lut = np.exp2(rng.uniform(-30.0, 30.0, size=(nq, m, 256))).astype(np.float32)
-    for ht in (26, 64):
+    for ht in (26, 64) if m == 8 else (56, 128):
         got_ids, got_d = _run(psc, lut, qcodes, codes, ht, k)
+        _took(psc, route, m, nq, ht, k)
+        assert route == "auto" or int(psc.last_scan_route().split("slices=")[1].split()[0]) >= 64
         ref = O.scan(lut.astype(np.float64), qcodes, codes, ht, k)
         nd = assert_topk_matches(got_ids, got_d, ref, lut.astype(np.float64), qcodes, codes, ht,
                                  what=f"{case} nq={nq} k={k} ht={ht}")
@@ -358,34 +421,40 @@ def test_what_the_slices_tell_each_other_costs_no_result(psc, case, nq, k):
             assert nd == 0
 
 
+@pytest.mark.parametrize("route", ["auto", "popcount"])
 @pytest.mark.parametrize("nq,n,k,lut_kind", [(1, 3_000_001, 100, "int"), (3, 1_000_003, 64, "int"),
                                              (8, 400_009, 128, "float"), (2, 70_001, 1024, "int"),
                                              (1, 300, 500, "int")])
-def test_selecting_merge_for_a_handful_of_queries(psc, nq, n, k, lut_kind):
+def test_selecting_merge_for_a_handful_of_queries(psc, force_route, route, nq, n, k, lut_kind):
     """A handful of queries (up to 32, or 512 with many lists each) and k >= 64: the partial lists of the slices are merged by a workgroup that
     selects the k smallest (distance, id) pairs.  Integer tables put hundreds of entries at the
     k-th distance, so the last place is decided by the id; short databases leave padding."""
+    force_route(route)
     codes, qcodes, lut = _rand_problem(8, n, nq, seed=77 + k, lut_kind=lut_kind)
     for ht in (24, 64):
         got_ids, got_d = _run(psc, lut, qcodes, codes, ht, k)
+        _took(psc, route, 8, nq, ht, k)
         ref = O.scan(lut.astype(np.float64), qcodes, codes, ht, k)
         nd = assert_topk_matches(got_ids, got_d, ref, lut.astype(np.float64), qcodes, codes, ht, what=f"nq={nq} k={k} ht={ht}")
         if lut_kind == "int":
             assert nd == 0  # exact sums: ties must resolve exactly as in the oracle
 
 
+@pytest.mark.parametrize("route", ["auto", "popcount"])
 @pytest.mark.parametrize("m,n,k,lut_kind", [(8, 2_000_003, 100, "int"), (8, 2_000_003, 130, "int"), (8, 900, 100, "float"),
                                             (8, 5_000_001, 1, "float"), (16, 700_001, 100, "int"), (8, 300_001, 64, "int"),
                                             (16, 200_003, 200, "float")])
-def test_a_single_query_spreads_its_candidates_over_four_lists(psc, m, n, k, lut_kind):
+def test_a_single_query_spreads_its_candidates_over_four_lists(psc, force_route, route, m, n, k, lut_kind):
     """One query: the three empty slots of the tile hold copies of its tables, every wave feeds the
     list of slot wave % 4 and the four lists are merged when the slice ends (one slice for small
     databases, 256 for large ones).  Exact ties (small-integer tables) must come out in id order."""
+    force_route(route)
     codes, qcodes, lut = _rand_problem(m, n, 1, seed=400 + k, lut_kind=lut_kind)
     nb = 8 * m
     for ht in (nb // 4, nb * 3 // 8, nb // 2 - 3):
         print(f"single query m={m} n={n} k={k} ht={ht}", flush=True)
         got_ids, got_d = _run(psc, lut, qcodes, codes, ht, k)
+        _took(psc, route, m, 1, ht, k)
         ref = O.scan(lut.astype(np.float64), qcodes, codes, ht, k)
         nd = assert_topk_matches(got_ids, got_d, ref, lut.astype(np.float64), qcodes, codes, ht, what=f"single m={m} ht={ht}")
         if lut_kind == "int":
@@ -405,9 +474,11 @@ def test_hamming_filter_is_bit_exact(psc, m):
         assert np.array_equal(ns.cpu().numpy(), ref["nsurv"])
 
 
+@pytest.mark.parametrize("route", ["auto", "mfma", "popcount"])
 @pytest.mark.parametrize("m", [8, 16])
-def test_survivor_set_through_the_fused_scan(psc, m):
+def test_survivor_set_through_the_fused_scan(psc, force_route, route, m):
     """With k above the number of survivors the result lists exactly the survivor set."""
+    force_route(route)
     codes, qcodes, lut = _rand_problem(m, 60_000, 11, seed=50 + m, lut_kind="float")
     ht = 2 * m + 2
     ref = O.scan(lut.astype(np.float64), qcodes, codes, ht, 1024, want_bitmap=True)

@@ -100,8 +100,10 @@ def test_encode_of_many_rows_equals_encode_of_few(m, dsub):
         assert abs(da - db) <= RTOL * db
 
 
+@pytest.mark.parametrize("route", ["auto", "popcount", "mfma"])
 @pytest.mark.parametrize("m", [8, 16])
-def test_whole_search_matches_oracle(setup, m):
+def test_whole_search_matches_oracle(setup, force_route, route, m):
+    force_route(route)
     s = setup[m]
     idx = s["idx"]
     if "codes" not in s:

@@ -22,8 +22,10 @@ def _problem(n, nq, seed):
     return codes, qcodes, lut
 
 
-def test_static_scratch_scan_equals_workspace_scan():
+@pytest.mark.parametrize("route", ["auto", "popcount", "mfma"])
+def test_static_scratch_scan_equals_workspace_scan(force_route, route):
     import paper_1609_01882_amd as psc
+    force_route(route)  # (forced: the tiled kernels, without the pool)
     cases = [(300_001, 41, 24, 100, 5), (70_003, 9, 22, 10, 6), (2_000_001, 3, 26, 7, 7), (5_000, 1, 64, 20, 8)]
     # the first call on a device looks the array up, at which point the HIP runtime places it in
     # device memory (once per process); from then on the device's free memory must not move
