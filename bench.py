@@ -31,7 +31,7 @@ if ROOT not in sys.path:
 PEAK_INT_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 # LDS: 128 bytes per clock and compute unit.  The ADC of a survivor gathers m 4-byte table entries.
 PEAK_LDS_TBPS = 256 * 128 * 2.4e9 / 1e12
-PEAK_MFMA_INT8_TOPS = 5000.0
+PEAK_MFMA_FP4_TOPS = 10000.0
 # Algorithmic integer work per (query, code) pair: per 32-bit word one xor and one
 # popcount-accumulate, plus one compare against the threshold.
 OPS_PER_PAIR = {8: 5, 16: 9}
@@ -39,11 +39,12 @@ OPS_PER_PAIR = {8: 5, 16: 9}
 # Bytes per launch of the dominant kernel between L2 and the memory fabric, measured with
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (two runs, each scaled by what the same counter reads for
 # a 1 GiB copy: x2.0 and x1.0), keyed by what the library says it launched (kernel, tile shape,
-# slices, workgroups): a change of kernel or shape makes the figure null instead of stale.
-# Sources: profiles/scan_mfma_kernel_flat64_ht24.md, profiles/scan_kernel_flat64_ht24.md.
+# slices, workgroups): a change of shape makes the figure null instead of stale; a kernel that moves
+# its data differently in the same shape has to be measured again.
+# Source: profiles/scan_mfma_kernel_flat64_ht24.md.
 MEASURED_TRAFFIC_BYTES = {
-    ("flat64", 24, "scan_mfma_kernel m=8 tq=16 waves=16 slices=2 tiles=738"): 1.9387e10,
-    ("flat64", 24, "scan_kernel m=8 tq=8 waves=8 slices=2 tiles=1476"): 9.7082e10,
+    ("flat64", 24, "scan_mfma_kernel m=8 tq=16 waves=16 slices=2 tiles=738"): 2.6293e10,
+    ("flat64", 24, "scan_kernel m=8 tq=8 waves=8 slices=2 tiles=1476"): 9.6131e10,
 }
 
 
@@ -58,8 +59,8 @@ def alu_roofline(m, pairs, kernel_ms, route, traffic=None, note=None):
          "unit": "TOP/s (int32 lane-ops)", "frac": achieved / PEAK_INT_TOPS, "ops_per_pair": OPS_PER_PAIR[m],
          "kernel_ms": kernel_ms, "traffic": traffic}
     if route.startswith("scan_mfma_kernel"):
-        # the same pairs as int8 matrix-core work: 2 x 64 multiply-adds per 64-bit pair
-        r["mfma_int8_frac"] = 128.0 * pairs / (kernel_ms * 1e-3) / 1e12 / PEAK_MFMA_INT8_TOPS
+        # the same pairs as matrix-core work on 4-bit floats: 8 m multiply-adds per pair
+        r["mfma_fp4_frac"] = 16.0 * m * pairs / (kernel_ms * 1e-3) / 1e12 / PEAK_MFMA_FP4_TOPS
     if note:
         r["note"] = note
     return r
@@ -622,7 +623,7 @@ def main():
                     help="queries of the headline workload the oracle re-does (the other workloads take a fraction)")
     ap.add_argument("--filter-route", choices=["auto", "popcount", "mfma"], default="auto",
                     help="which Hamming filter the fused scan uses: the library's own choice (matrix cores "
-                         "below about 10%% survivors), or one of the two forced (psc_set_filter_route)")
+                         "for batches), or one of the two forced (psc_set_filter_route)")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run one 1 GiB device-to-device copy (known traffic, for scaling the "
                          "FETCH_SIZE / WRITE_SIZE counters of a rocprofv3 --pmc run)")
@@ -673,7 +674,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": ("i8 MFMA Hamming test" if on_mfma else "u32 xor/popcount Hamming test") + " + f32 ADC",
+        "dtype": ("fp4 MFMA Hamming test (exact)" if on_mfma else "u32 xor/popcount Hamming test") + " + f32 ADC",
         "data": "synthetic",
         "config": {"workload": head["workload"], "n_db": head["n_db"], "n_query": head["n_query"],
                    "code_bits": head["code_bits"], "ht": head["ht"], "k": head["k"]},
@@ -682,8 +683,8 @@ def main():
         "survivor_rate": head["survivor_rate"],
         # `achieved` counts the algorithmic work of the filter (5 integer operations per 64-bit pair)
         # against the vector-ALU peak, whichever unit executes it (`kernel` is what the library says it
-        # launched).  With the test on the matrix cores the same pairs are also 128 int8 operations
-        # each against the 5 POP/s MFMA peak (`mfma_int8_frac`), and `other_filter_route` holds the
+        # launched).  With the test on the matrix cores the same pairs are also 128 operations on 4-bit
+        # floats each against the 10 PFLOP/s MFMA peak (`mfma_fp4_frac`), and `other_filter_route` holds the
         # same launch with the xor/popcount kernel forced: that one executes the 5 operations per
         # pair on the vector ALUs, so its `frac` is the share of the integer popcount peak proper.
         "roofline": head["roofline"],

@@ -373,8 +373,8 @@ int psc_scan_static(int m, const float *lut_dev, const uint8_t *qcodes_dev, int6
     void *ws = nullptr;
     int rc = static_scratch(&ws);
     if (rc != PSC_OK) return rc;
-    // (launch_scan clears the status word and the shared thresholds with a small kernel, and the
-    //  scan kernels write every partial list they later merge: nothing of the previous call is read)
+    // (launch_scan has the status word cleared, and the shared thresholds where the kernel taken has any, and
+    //  the scan kernels write every partial list they later merge: nothing of the previous call is read)
     return launch_scan(m, lut_dev, qcodes_dev, nq, codes_dev, n, ht, k, -1, true, ids_dev, dists_dev, ws,
                        (size_t)PSC_STATIC_SCRATCH_BYTES, (hipStream_t)stream);
 }

@@ -198,8 +198,8 @@ select_probes_wave_kernel(const float *__restrict__ dist, int64_t n, int nlist, 
 // (distance, list) pair is found by a radix search over the bits of the distance key and, only if
 // several lists share that distance, bit by bit over the 14 bits of the list number, with one
 // workgroup-wide count per bit (per-wave sums through LDS, two buffers in turn so that one barrier
-// per bit is enough).  Bound by its chain of barriers: 34 of them counting bit by bit, 9 to 15 now.  The pairs up to it are exactly the nprobe lists; each goes to
-// its rank.
+// per bit is enough).  Bound by its chain of barriers: 34 of them counting bit by bit, 9 to 15 now.  The
+// pairs up to it are exactly the nprobe lists; each goes to its rank.
 template <int KPL>
 __global__ void __launch_bounds__(1024)
 select_probes_block_kernel(const float *__restrict__ dist, int nlist, int nprobe, const int32_t *__restrict__ settled,
@@ -436,8 +436,9 @@ nearest_centroid_kernel(const float *__restrict__ x, int64_t n, int dim, const f
 }
 
 // ---------------------------------------------------------------------------------------------
-// Nearest centroid on the matrix cores (the assignment step of Section 4.3's index, and of the
-// coarse k-means): arg-min over c of || x - c ||^2 = arg-min of || c' ||^2 - 2 x'.c' with
+// Nearest centroid on the matrix cores in float32 (the multi-index's halves, and of the assignment
+// step of Section 4.3's index and the coarse k-means what the search on bfloat16 parts below does not
+// take or leaves undecided): arg-min over c of || x - c ||^2 = arg-min of || c' ||^2 - 2 x'.c' with
 // x' = x - mu, c' = c - mu (mu: any common reference point, here the mean centroid; centring keeps
 // the terms small and with them the rounding error of the expansion, about 1e-7 of the distance).
 // The cross term is a dense [rows x DIM] . [DIM x nlist] contraction in full float32

@@ -721,8 +721,9 @@ __device__ __forceinline__ void score_batch(const Lds<M, TQ> &s, const ScanArgs 
 // every lane takes one, scores its lowest bit and what is left of the masks is appended again.  Per
 // block that is one append whatever the number of bits, where queueing bit by bit takes a turn of
 // about 16 instructions per bit of the fullest lane (4 turns at 1 bit per lane).  What the queue
-// cannot take of a block's masks waits in its lanes.  1M x 1M at ht = 20 106.3 -> 95.1 ms, 10M x 10k at ht = 24 24.6 -> 20.6 (batches scored when
-// the next one is taken instead of waiting for their codes: 23.0 -> 20.6 of that).
+// cannot take of a block's masks waits in its lanes.  1M x 1M at ht = 20 106.3 -> 95.1 ms, 10M x 10k at ht
+// = 24 24.6 -> 20.6 (batches scored when the next one is taken instead of waiting for their codes: 23.0 ->
+// 20.6 of that).
 //
 // Inverted lists queue bits: a wave sees a block or two of a list, so nearly everything it queues is
 // left over when its list ends (10k x 64 probes of 10M vectors 4.46 -> 4.64 ms with masks whose bits
@@ -1235,9 +1236,10 @@ scan_kernel(ScanArgs a)
 }
 
 // ---------------------------------------------------------------------------------------------
-// The fused scan with the Hamming test of Section 3.3 ("dual" in Section 4.2) on the matrix cores (tiles of 16 queries
-// at 64 bits, of 8 at 128; the description is for 64 bits up to the last paragraph).  With the code's bits c_i in {0, 1}, the query's bits turned
-// into s_i = +1 (bit 0) or -1 (bit 1) and p the number of ones of the query,
+// The fused scan with the Hamming test of Section 3.3 ("dual" in Section 4.2) on the matrix cores (tiles
+// of 16 queries at 64 bits, of 8 at 128; the description is for 64 bits up to the last paragraph).  With
+// the code's bits c_i in {0, 1}, the query's bits turned into s_i = +1 (bit 0) or -1 (bit 1) and p the
+// number of ones of the query,
 //     distance = p + sum_i s_i c_i,   so   f = (ht + 64 - p) - sum_i s_i c_i = ht + 64 - distance
 // lies in 0 .. 127 (ht <= 63) and its bit 6 says "within ht": a contraction whose small-integer
 // operands 4-bit floating point (E2M1) holds exactly, v_mfma_scale_f32_16x16x128_f8f6f4.
@@ -1271,20 +1273,25 @@ scan_kernel(ScanArgs a)
 // same result, words 1 and 3; no word changes lanes.  8 queries fill half of the rows, so two such
 // pairs serve one result, the first with the queries in rows 0 .. 7 (the others zero), the second,
 // with the next 16 codes, in rows 8 .. 15.  The fields are ht + 128 - distance, 8 bits, their bit 7 at
-// 7 + s and 15 + s.  Bit 4 * t + r of a mask is code 32 * t + 16 * (grp / 2) + col of a 256-code
-// block and query slot 4 * (grp % 2) + r.
+// 7 + s and 15 + s.  Their lowest bit is the accumulator's (2^23's) last one at s = 0, so the +-0.5 of
+// the nibbles' top bits have to be added up before they meet it: a word has eight of them, whose sum is
+// whole, and the hardware adds a block's products first (tested at every threshold, on pairs at the
+// threshold and one beyond; 64 bits leave a bit to spare and do not depend on it).  Bit 4 * t + r of a
+// mask is code 32 * t + 16 * (grp / 2) + col of a 256-code block and query slot 4 * (grp % 2) + r.
 //
-// What bounds it: vector instruction issue, about 45 per 2048 pairs for the test (22 to make
-// operands, the rest to collect verdicts) beside 4 products of 16 cycles.  Against bytes of +-1 from
-// a table in LDS and one int8 product per 16 codes (16 look-ups, 80 vector instructions), 1M x 1M
-// at ht = 20: 134.8 -> 106.3 ms; 10M x 10k at ht = 24, k = 100: 28.2 -> 24.6 ms on one box.
+// What bounds it: vector instruction issue (10M x 10k, 64 bits, ht = 24: 73 % of the slots, matrix cores 10
+// %, LDS 38 %), about 45 per 2048 pairs for the test (22 to make operands, the rest to collect verdicts)
+// beside 4 products of 16 cycles; at 128 bits what crosses the fabric (162 GB in 25.9 ms; vector issue 50
+// %, matrix cores 22 %).  Bytes of +-1 from a table in LDS and one int8 product per 16 codes (16
+// look-ups, 80 vector instructions) took 134.8 ms for 1M x 1M at ht = 20 where this takes 80.3, queues
+// that hold survivors bit by bit 106.3; 10M x 10k at ht = 24, k = 100 13.9 ms with the workload's data.
 // ---------------------------------------------------------------------------------------------
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float mfma_f32x4 __attribute__((ext_vector_type(4)));
 
 // (One 16-wave workgroup per compute unit = 4 waves per SIMD: telling the compiler so lets it
-//  spend registers on keeping the eight products of a block in flight together.)
+//  spend registers on keeping the products of a block in flight together.)
 // IVF: tiles are (inverted list, up to 16 of its jobs), as in scan_kernel.
 template <int M, int NW, bool SHARE, bool IVF = false>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
@@ -2779,8 +2786,8 @@ static void set_exchange(ScanArgs &a, int slots, int k)
 struct ScanCosts {
     // pool: a workgroup, a selection, 100 keys kept, 1000 codes, 1000 survivors
     double group, select, kept, code, survivor;
-    // tiled: the launches, a tile, 1000 pairs by either filter and 1000 surviving pairs (to 16 waves), an insertion,
-    // the merge per result
+    // tiled: the launches, a tile, 1000 pairs by either filter and 1000 surviving pairs (to 16 waves), an
+    // insertion, the merge per result
     double launch, tile, pair, pair_mfma, surviving_pair, insertion, merge_k;
 };
 static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool dense, bool mfma, const ScanPlan &p,
@@ -2860,7 +2867,8 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
     if (forced == PSC_ROUTE_MFMA) mfma = !dense && enough;
     if (mfma) {
         rc = plan_scan(m, nq, n, k, kScanFusedMfma, &p);
-        // (k too large for the shape, or a workspace that holds only the popcount kernel's plan: that one takes over)
+        // (k too large for the shape, or a workspace that holds only the popcount kernel's plan: that one
+        // takes over)
         mfma = rc == PSC_OK && ws_bytes >= p.total_bytes;
     }
     if (!mfma)
