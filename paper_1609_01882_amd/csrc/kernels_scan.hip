@@ -196,6 +196,7 @@ __device__ __forceinline__ float key_dist(uint32_t key)
     return __uint_as_float(key ^ ((key >> 31) ? 0x80000000u : 0xffffffffu));
 }
 constexpr uint32_t kKeyInf = 0xff800000u;  // dist_key(+infinity)
+constexpr uint64_t kNoEntry = ~0ull;       // above every entry
 __device__ __forceinline__ uint64_t pack_entry(float d, uint32_t id)
 {
     return ((uint64_t)dist_key(d) << 32) | id;
@@ -335,6 +336,18 @@ __device__ __forceinline__ uint64_t lane_value_u64(uint64_t v, int l)
 {
     return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l) << 32) |
            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+}
+// Whether a candidate comes before the k-th entry of slot q's list.  A place past the list's end holds
+// kNoEntry, entries only ever get smaller, and a 64-bit LDS access is one access: whatever is read is a bound.
+// The thresholds are distances alone and let every candidate through that ties with the k-th entry, though
+// it loses by its id nearly always (ids rise during a scan); clustered vectors share codes by the thousand, and
+// each such tie took the list's lock to be turned away.  Asked only when a batch has a candidate at all.
+// 10M x 10k at ht = 24, k = 100 24.6 -> 14.0 ms (of seeds with many codes at the k-th distance), 1M x 777 pure
+// ADC 829 -> 744 us, 1M x 1M graph at ht = 20 80.4 -> 77.4 ms.  Inverted lists do without: 4.43 / 4.48 ms.
+template <int M, int TQ>
+__device__ __forceinline__ bool before_kth(const Lds<M, TQ> &s, const ScanArgs &a, int q, float d, uint32_t id)
+{
+    return pack_entry(d, id) < s.top[q * a.kpad + a.k - 1];
 }
 // Lower a threshold in LDS, no answer awaited.
 __device__ __forceinline__ void lower_threshold(lds_vf32 *p, float v)
@@ -704,6 +717,12 @@ __device__ __forceinline__ void score_batch(const Lds<M, TQ> &s, const ScanArgs 
     }
     uint64_t pm = ballot64(pass);
     ask.wanted = pm != 0;
+    if constexpr (!IVF) {
+        if (pm) {
+            pass = pass && before_kth(s, a, q, d, key);
+            pm = ballot64(pass);
+        }
+    }
     while (pm) {
         const int leader = __builtin_ctzll(pm);
         const int qcur = __builtin_amdgcn_readlane(q, leader);
@@ -983,6 +1002,7 @@ scan_kernel(ScanArgs a)
         }
         s.thr[tid] = t0;
         s.lock[tid] = 0;
+        s.top[tid * a.kpad + a.k - 1] = kNoEntry;
         s.gidx[tid] = gi;
         s.pslot[tid] = (IVF ? (gi >= 0 ? a.job_slot[q0 + job] : 0) : slice) % a.pub_slots;
     }
@@ -1344,6 +1364,7 @@ scan_mfma_kernel(ScanArgs a)
         }
         s.thr[tid] = t0;
         s.lock[tid] = 0;
+        s.top[tid * a.kpad + a.k - 1] = kNoEntry;
         s.gidx[tid] = gi;
         s.pslot[tid] = (IVF ? (gi >= 0 ? a.job_slot[q0 + tid] : 0) : slice) % a.pub_slots;
     }
@@ -1593,6 +1614,7 @@ adc_kernel(ScanArgs a)
             }
             s.thr[tid] = t0;
             s.lock[tid] = 0;
+            s.top[tid * a.kpad + a.k - 1] = kNoEntry;
             s.gidx[tid] = tid < nvq ? (int)(q0 + tid) : -1;
             s.pslot[tid] = slice % a.pub_slots;
         }
@@ -1672,6 +1694,7 @@ adc_kernel(ScanArgs a)
                             for (int ww = 0; ww < WPC; ++ww) acc += (uint32_t)__popc(w[c * WPC + ww] ^ qw[q][ww]);
                             pass[i] = pass[i] && (int32_t)acc >= 0;
                         }
+                        pass[i] = pass[i] && before_kth(s, a, g * 4 + i, d[i], rel);
                         const uint64_t mine = ballot64(pass[i]);
                         if (mine) {
                             ask.wanted = true;

@@ -551,3 +551,24 @@ def test_hamming_histogram_is_bit_exact(psc, m):
     assert psc.threshold_for_rate(got, 0.05) == O.threshold_for_rate(want, 0.05)
     empty = psc.hamming_histogram(_dev(qcodes), torch.empty((0, m), dtype=torch.uint8, device="cuda"))
     assert int(empty.sum()) == 0
+
+
+@pytest.mark.parametrize("route", ["auto", "mfma", "popcount"])
+@pytest.mark.parametrize("m,n,nq,k", [
+    (8, 60_001, 37, 1), (8, 60_001, 37, 64), (8, 60_001, 20, 100), (8, 60_001, 9, 129), (8, 60_001, 1, 100),
+    (8, 40_003, 3, 300), (16, 40_003, 19, 100), (16, 40_003, 2, 65), (16, 40_003, 9, 272),
+])
+def test_thousands_of_codes_at_the_kth_distance(psc, force_route, route, m, n, nq, k):
+    """Six distinct codes share every database: each list fills with copies of a few of them, everything
+    else at the k-th distance ties and is told apart by its id alone.  Whole-number tables: ids are exact."""
+    force_route(route)
+    rng = np.random.default_rng(77 + k)
+    few = W.random_codes(6, m, seed=5)
+    codes = np.ascontiguousarray(few[rng.integers(0, 6, size=n)])
+    qcodes = np.ascontiguousarray(few[rng.integers(0, 6, size=nq)])
+    lut = rng.integers(0, 50, size=(nq, m, 256)).astype(np.float32)
+    for ht in (0, 7 * m // 2, 8 * m):
+        got_ids, got_d = _run(psc, lut, qcodes, codes, ht, k)
+        _took(psc, route, m, nq, ht, k)
+        ref = O.scan(lut.astype(np.float64), qcodes, codes, ht, k)
+        assert np.array_equal(got_ids, ref["ids"]) and np.array_equal(got_d, ref["dists"]), (m, n, nq, k, ht)
