@@ -7,6 +7,7 @@
 #include <limits>
 #include <numeric>
 #include <thread>
+#include <unordered_map>
 
 #include "common.h"
 
@@ -50,12 +51,18 @@ void parallel_rows(int64_t n, F &&body)
 // draw c of the counter-based generator picks the c-th row).
 void kmeans_start_rows(int64_t n, int ncent, uint64_t seed, int64_t *rows)
 {
-    std::vector<int64_t> perm((size_t)n);
-    std::iota(perm.begin(), perm.end(), (int64_t)0);
+    // the first ncent steps of a shuffle of 0 .. n-1: only the places those touched are held (all n of them, for
+    // each of 8 sub-quantizers, took 0.6 of the 5.4 ms of a training on 100k vectors)
+    std::unordered_map<int64_t, int64_t> moved;
+    moved.reserve((size_t)ncent * 2);
+    auto at = [&](int64_t place) {
+        const auto it = moved.find(place);
+        return it == moved.end() ? place : it->second;
+    };
     for (int c = 0; c < ncent; ++c) {
-        int64_t r = c + (int64_t)(counter_draw(seed, (uint64_t)c) % (uint64_t)(n - c));
-        std::swap(perm[(size_t)c], perm[(size_t)r]);
-        rows[c] = perm[(size_t)c];
+        const int64_t r = c + (int64_t)(counter_draw(seed, (uint64_t)c) % (uint64_t)(n - c));
+        rows[c] = at(r);
+        moved[r] = at(c);  // (place c is not looked at again)
     }
 }
 

@@ -2696,10 +2696,13 @@ int plan_scan(int m, int64_t nq, int64_t n, int k, int kind, ScanPlan *plan)
     const int64_t wg_limit = std::max<int64_t>(8 * round, nqt);
     int64_t want = 1, tiles_one = 0;
     if (nqt > 0 && nq <= 16) {
-        // a handful of queries: score = share of the rounds' places that are used, less 1% per round
+        // a handful of queries: score = share of the rounds' places that are used, less 1% per round.  Of
+        // the slices that take the same number of rounds the most score best, so one candidate per round
+        // is looked at (all 2048 slices, four plans to a call, took 45 of 1 query x 100k codes' 65 us)
         double best_score = -1.0;
-        for (int64_t sN = 1; sN * nqt <= wg_limit; ++sN) {
-            const int64_t wg = nqt * sN, rounds = (wg + round - 1) / round;
+        for (int64_t rounds = 1; rounds * round <= wg_limit; ++rounds) {
+            const int64_t sN = rounds * round / nqt, wg = nqt * sN;
+            if (sN < 1 || wg <= (rounds - 1) * round) continue;
             const double score = (double)wg / (double)(rounds * round) - 0.01 * (double)rounds;
             if (score > best_score + 1e-9) {
                 best_score = score;
