@@ -815,7 +815,15 @@ int psc_train_pq_device(psc_index *idx, const float *x_dev, int64_t n, int iters
     PSC_TRY(scratch.get(&cb, ncell * dsub));
     PSC_TRY(scratch.get(&sum, ncell * dsub));
     PSC_TRY(scratch.get(&count, ncell));
-    PSC_TRY(scratch.get(&obj, (size_t)m));
+    const int parts = pq_lloyd_parts(dim, m, n);
+    double *part_sum = nullptr, *part_obj = nullptr;
+    uint32_t *part_count = nullptr;
+    int *stop = nullptr;
+    PSC_TRY(scratch.get(&obj, (size_t)m * (parts > 0 ? iters : 1)));
+    PSC_TRY(scratch.get(&part_sum, ncell * dsub * parts));
+    PSC_TRY(scratch.get(&part_count, ncell * parts));
+    PSC_TRY(scratch.get(&part_obj, (size_t)m * parts));
+    PSC_TRY(scratch.get(&stop, 1));
     PSC_TRY(scratch.get(&cell, (size_t)n * m));
     PSC_TRY(scratch.get(&dmin, (size_t)n * m));
     PSC_TRY(scratch.get(&key, 1));
@@ -836,19 +844,13 @@ int psc_train_pq_device(psc_index *idx, const float *x_dev, int64_t n, int iters
         set_error("out of host memory");
         return PSC_ENOMEM;
     }
-    for (int it = 0; it < iters; ++it) {
-        PSC_TRY(launch_pq_lloyd_step(cb, dim, m, x_dev, n, cell, dmin, sum, count, obj, s));
-        PSC_HIP_TRY(hipMemcpyAsync(hcount.data(), count, ncell * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-        if (objective_out_host)
-            PSC_HIP_TRY(hipMemcpyAsync(objective_out_host + (size_t)it * m, obj, (size_t)m * sizeof(double),
-                                       hipMemcpyDeviceToHost, s));
-        PSC_HIP_TRY(hipStreamSynchronize(s));
+    // Cells without members (hcount: the counts of the iteration): each takes the member of the (currently) most
+    // populated cell that lies farthest from that cell's centroid; the donor's own mean is left as computed.
+    auto refill = [&]() {
         for (int j = 0; j < m; ++j) {
             uint32_t *cj = &hcount[(size_t)j * kCentroids];
             for (int c = 0; c < kCentroids; ++c) {
                 if (cj[c] != 0u) continue;
-                // empty cell: it takes the member of the (currently) most populated cell that lies
-                // farthest from that cell's centroid; the donor's own mean is left as computed
                 const int big = (int)(std::max_element(cj, cj + kCentroids) - cj);
                 if (cj[big] == 0u) continue;
                 PSC_TRY(launch_pq_refill(x_dev, n, dim, m, j, big, c, cell, dmin, sum, count, key, s));
@@ -856,6 +858,43 @@ int psc_train_pq_device(psc_index *idx, const float *x_dev, int64_t n, int iters
                 cj[c] = 1u;
             }
         }
+        return (int)PSC_OK;
+    };
+    if (parts > 0) {
+        const PqLloydArgs args{cb, dim, m, x_dev, n, cell, dmin, sum, count, obj, parts, part_sum, part_count, part_obj, stop};
+        // All iterations are enqueued at once; one that leaves a cell empty stops those behind it.  Data that
+        // does so is taken in shorter runs.
+        int ahead = iters;
+        for (int it = 0; it < iters;) {
+            PSC_HIP_TRY(hipMemsetAsync(stop, 0, sizeof(int), s));
+            const int until = std::min(iters, it + ahead);
+            for (int i = it; i < until; ++i) PSC_TRY(launch_pq_lloyd(args, i, s));
+            int stopped = 0;
+            PSC_HIP_TRY(hipMemcpyAsync(&stopped, stop, sizeof(int), hipMemcpyDeviceToHost, s));
+            PSC_HIP_TRY(hipStreamSynchronize(s));
+            if (stopped == 0) {
+                it = until;
+                ahead *= 2;
+                continue;
+            }
+            PSC_HIP_TRY(hipMemcpyAsync(hcount.data(), count, ncell * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+            PSC_HIP_TRY(hipStreamSynchronize(s));
+            PSC_TRY(refill());
+            PSC_TRY(launch_centroid_update(sum, count, (int64_t)ncell, dsub, cb, s));
+            it = stopped;
+            ahead = 1;
+        }
+        if (objective_out_host)
+            PSC_HIP_TRY(hipMemcpyAsync(objective_out_host, obj, (size_t)iters * m * sizeof(double), hipMemcpyDeviceToHost, s));
+    }
+    for (int it = 0; parts == 0 && it < iters; ++it) {
+        PSC_TRY(launch_pq_lloyd_step(cb, dim, m, x_dev, n, cell, dmin, sum, count, obj, s));
+        PSC_HIP_TRY(hipMemcpyAsync(hcount.data(), count, ncell * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+        if (objective_out_host)
+            PSC_HIP_TRY(hipMemcpyAsync(objective_out_host + (size_t)it * m, obj, (size_t)m * sizeof(double),
+                                       hipMemcpyDeviceToHost, s));
+        PSC_HIP_TRY(hipStreamSynchronize(s));
+        PSC_TRY(refill());
         PSC_TRY(launch_centroid_update(sum, count, (int64_t)ncell, dsub, cb, s));
     }
     PSC_HIP_TRY(hipMemcpyAsync(idx->cb_host.data(), cb, ncell * dsub * sizeof(float), hipMemcpyDeviceToHost, s));

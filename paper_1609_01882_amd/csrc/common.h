@@ -213,6 +213,28 @@ int launch_imi_scan(int m, const float *lut_dev, const float *tab1_dev, const fl
 // (sum [m][256][dsub], double) and their number; per sub-quantizer the sum of the distances.
 int launch_pq_lloyd_step(const float *cb_dev, int dim, int m, const float *x_dev, int64_t n, uint8_t *cell_dev,
                          float *dmin_dev, double *sum_dev, uint32_t *count_dev, double *obj_dev, hipStream_t s);
+// The same step for sub-vectors of 2 to 32 with the search on the matrix cores, and the update of the centroids
+// (cells without members keep theirs and set stop = iteration + 1, after which launches do nothing until it is
+// cleared).  `parts` workgroups per sub-quantizer (pq_lloyd_parts; 0: not for this length) leave their sums in
+// part_sum [m][parts][256][dsub], part_count [m][parts][256], part_obj [m][parts]; obj [iterations][m].
+struct PqLloydArgs {
+    float *cb;
+    int dim, m;
+    const float *x;
+    int64_t n;
+    uint8_t *cell;
+    float *dmin;
+    double *sum;
+    uint32_t *count;
+    double *obj;
+    int parts;
+    double *part_sum;
+    uint32_t *part_count;
+    double *part_obj;
+    int *stop;
+};
+int pq_lloyd_parts(int dim, int m, int64_t n);
+int launch_pq_lloyd(const PqLloydArgs &a, int iteration, hipStream_t s);
 // Starting centroids: sub-vector j of row rows[j][c] for every (j, c).
 int launch_pq_gather_start(const float *x_dev, int dim, int m, const int64_t *rows_dev, float *cb_dev, hipStream_t s);
 // The farthest member of cell `big` of sub-quantizer j becomes the only member of the empty cell c

@@ -9,7 +9,10 @@
 //
 // v_r is row r of the input, optionally re-indexed and with a coarse centroid subtracted
 // (residual tables / residual codes of the inverted-file variant, Section 4.3).
+#include <algorithm>
+
 #include "common.h"
+#include "pq_nearest.h"
 
 namespace psc {
 namespace {
@@ -22,6 +25,19 @@ __device__ __forceinline__ float sub_term(const RowMap &map, int64_t r, int dim,
         return col < half ? map.sub[(int64_t)a * half + col] : map.sub_b[(int64_t)b * half + col - half];
     }
     return map.sub ? map.sub[(int64_t)(map.sub_idx ? map.sub_idx[r] : 0) * dim + col] : 0.0f;
+}
+
+// The same for the sub-vector from coordinate col on (it lies within one half: there is an even number of
+// sub-quantizers), where something is subtracted at all: asked for coordinate by coordinate, every load waits
+// behind the branches of the one before.
+__device__ __forceinline__ const float *sub_vector(const RowMap &map, int64_t r, int dim, int col)
+{
+    const int at = map.sub_idx ? map.sub_idx[r] : 0;
+    if (map.k2 > 0) {
+        const int half = dim / 2, a = at / map.k2, b = at - a * map.k2;
+        return col < half ? map.sub + (int64_t)a * half + col : map.sub_b + (int64_t)b * half + col - half;
+    }
+    return map.sub + (int64_t)at * dim + col;
 }
 
 // One workgroup = one sub-quantizer j and ROWS consecutive rows; thread c owns centroid c,
@@ -76,9 +92,9 @@ lut_kernel(const float *__restrict__ cb, int dim, int m, const float *__restrict
 // One thread = one row and one sub-quantizer; the row's sub-vector sits in registers, the sub-codebook, at
 // the same address in every lane, in LDS or (SCALAR) comes through the scalar cache.  Bound by its
 // arithmetic, two instructions per coordinate; LDS adds a read per four of them, the scalar cache trips that
-// only many waves hide and, past 48 KB of sub-codebook, misses.  LDS / scalar cache, us: sub-vectors of 16, 8
-// sub-quantizers, 20k rows 53 / 58, 1M rows 1308 / 1172; of 32 116 / 105 and 2970 / 2282; of 6 25 / 33 and
-// 581 / 561; of 64 211 / 232, 200k rows 1343 / 1914, 1M 6437 / 6418.
+// only many waves hide and, past 48 KB of sub-codebook, misses.  For sub-vectors of 1, 2, 48 and 64 (between them
+// encode_mfma_kernel).  LDS / scalar cache, us, 8 sub-quantizers: of 64, 20k rows 211 / 232, 200k 1343 / 1914, 1M
+// 6437 / 6418.
 template <int DSUB, bool SCALAR>
 __global__ void __launch_bounds__(256)
 encode_kernel(const float *__restrict__ cb, int dim, int m, const float *__restrict__ x,
@@ -115,6 +131,45 @@ encode_kernel(const float *__restrict__ cb, int dim, int m, const float *__restr
         }
     }
     codes[r * m + j] = (uint8_t)bi;
+}
+
+// The encoder for sub-vectors of 4 to 32, the search on the matrix cores (pq_nearest.h; the same codes): 8 waves to a
+// workgroup, 32 rows a turn, one sub-quantizer (neighbouring workgroups go to different XCDs: with 8
+// sub-quantizers an XCD's L2 holds one).  Bound by vector issue (2.5 instructions per centroid and row).  Plain
+// form / this, us: 8 sub-vectors of 16, 500 rows 29 / 15, 16k 38 / 23, 1M 1190 / 409; of 32 69 / 25, 107 / 32, 2316 /
+// 653; of 8 22 / 11, 25 / 16, 693 / 307; 16 of 4 18 / 10, 24 / 16, 897 / 495.  Left to the plain form: sub-vectors of
+// 2 (even), 1 (1M rows 497 / 1380) and 48 and 64 (registers).
+template <int DSUB>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PqNearest<DSUB>::kWavesPerEu)))
+encode_mfma_kernel(const float *__restrict__ cb, int dim, int m, const float *__restrict__ x, int64_t nrows,
+                   RowMap map, uint8_t *__restrict__ codes)
+{
+    typedef PqNearest<DSUB> Nearest;
+    extern __shared__ __align__(16) unsigned char smem[];
+    typename Nearest::Shared &s = *(typename Nearest::Shared *)smem;
+    const int j = (int)(blockIdx.x % (unsigned)m), nb = (int)(gridDim.x / (unsigned)m);
+    const int lane = (int)(threadIdx.x & 63), wave = (int)(threadIdx.x >> 6);
+    const float *cbj = cb + (int64_t)j * kCentroids * DSUB;
+    Nearest::prepare(s, cbj);
+    const int64_t step = (int64_t)nb * (8 * 32);
+    bool plain = false;  // (wave-uniform) a row to each lane: two turns' rows at once
+    for (int64_t r0 = ((int64_t)(blockIdx.x / (unsigned)m) * 8 + wave) * 32; r0 < nrows;) {
+        const int64_t own = r0 + (lane & 31) + (plain && lane >= 32 ? step : 0);
+        const bool live = own < nrows && (plain || lane < 32);
+        const int64_t r = own < nrows ? own : nrows - 1;
+        const int64_t src = map.row_idx ? (int64_t)map.row_idx[r] : r;
+        float v[DSUB];
+#pragma unroll
+        for (int t = 0; t < DSUB; ++t) v[t] = x[src * dim + j * DSUB + t];
+        if (map.sub != nullptr) {
+            const float *sub = sub_vector(map, r, dim, j * DSUB);
+#pragma unroll
+            for (int t = 0; t < DSUB; ++t) v[t] -= sub[t];
+        }
+        r0 += plain ? 2 * step : step;
+        const int c = plain ? Nearest::all_distances(cbj, v) : Nearest::search(s, cbj, v, plain);
+        if (live) codes[r * m + j] = (uint8_t)c;
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -264,21 +319,29 @@ template <int DSUB>
 int run_encode(const float *cb, int dim, int m, const float *x, int64_t nrows, const RowMap &map,
                uint8_t *codes, hipStream_t s)
 {
-    // the number of codes from which the scalar cache is ahead (measured at 1k .. 1M rows, 8 and 16
-    // sub-quantizers; at its edge the two are within 3 %)
-    constexpr int64_t kNever = INT64_MAX;
-    constexpr int64_t from = DSUB == 32 ? 0 : DSUB >= 12 && DSUB <= 24 ? 800'000 : DSUB == 48 ? 1'600'000
-                             : DSUB == 8 ? 3'200'000 : kNever;
-    dim3 grid((unsigned)((nrows + 255) / 256), (unsigned)m);
-    if constexpr (from != kNever) {
-        if (nrows * m >= from) {
-            hipLaunchKernelGGL((encode_kernel<DSUB, true>), grid, dim3(256), 0, s, cb, dim, m, x, nrows, map, codes);
-            PSC_HIP_TRY(hipGetLastError());
-            return PSC_OK;
+    if constexpr (DSUB >= 4 && DSUB <= 32) {
+        const size_t lds = sizeof(typename PqNearest<DSUB>::Shared);
+        if (lds > 48 * 1024)
+            PSC_HIP_TRY(hipFuncSetAttribute((const void *)encode_mfma_kernel<DSUB>,
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        // at most the workgroups that run together (by their registers), all with the same number of turns
+        const int64_t fit = DSUB <= 16 ? 2 : 1;
+        const int64_t want = (nrows + 255) / 256, cap = std::max<int64_t>(1, 256 * fit / m), turns = (want + cap - 1) / cap;
+        hipLaunchKernelGGL((encode_mfma_kernel<DSUB>), dim3((unsigned)((want + turns - 1) / turns * m)), dim3(512), lds, s,
+                           cb, dim, m, x, nrows, map, codes);
+    } else {
+        // the number of codes from which the scalar cache is ahead (measured at 1k .. 1M rows)
+        constexpr int64_t kNever = INT64_MAX, from = DSUB == 48 ? 1'600'000 : kNever;
+        dim3 grid((unsigned)((nrows + 255) / 256), (unsigned)m);
+        if constexpr (from != kNever) {
+            if (nrows * m >= from) {
+                hipLaunchKernelGGL((encode_kernel<DSUB, true>), grid, dim3(256), 0, s, cb, dim, m, x, nrows, map, codes);
+                PSC_HIP_TRY(hipGetLastError());
+                return PSC_OK;
+            }
         }
-    }
-    if constexpr (from != 0)
         hipLaunchKernelGGL((encode_kernel<DSUB, false>), grid, dim3(256), 0, s, cb, dim, m, x, nrows, map, codes);
+    }
     PSC_HIP_TRY(hipGetLastError());
     return PSC_OK;
 }

@@ -8,7 +8,10 @@
 // bit for bit.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "common.h"
+#include "pq_nearest.h"
 
 namespace psc {
 
@@ -19,12 +22,12 @@ namespace {
 // (float32: a workgroup adds a few members per cell) and counts in LDS, walks its share of the rows
 // (one row per thread and turn), and adds its sums to the global ones (double) at the end.  Per row
 // it also stores the cell and the distance, for the refill of empty cells.  The centroids, the same
-// for every lane, come through the scalar cache (SCALAR): read from LDS, four 16-byte reads per 32
-// vector instructions, they take as long as the arithmetic.  With few rows there are not the waves to
-// hide the scalar cache's trips, and they are read from LDS.  An iteration with LDS / scalar cache, us:
-// sub-vectors of 16, 8 sub-quantizers, 1k rows 97 / 117, 100k 356 / 281; of 32 121 / 177 and 685 / 530.
+// for every lane, come through the scalar cache: read from LDS, four 16-byte reads per 32 vector
+// instructions, they take as long as the arithmetic.  For sub-vectors of 48 and 64, whose operands and sums do not
+// fit LDS, and of 1, where nearly every row is a close call (1M rows, 16 sub-quantizers 677 / 1600 us an
+// iteration); the others take pq_lloyd_mfma_kernel.
 // ---------------------------------------------------------------------------------------------
-template <int DSUB, bool SCALAR>
+template <int DSUB>
 __global__ void __launch_bounds__(256)
 pq_lloyd_step_kernel(const float *__restrict__ cb, int dim, int m, const float *__restrict__ x, int64_t n,
                      uint8_t *__restrict__ cell, float *__restrict__ dmin, double *__restrict__ gsum,
@@ -34,12 +37,8 @@ pq_lloyd_step_kernel(const float *__restrict__ cb, int dim, int m, const float *
     constexpr int LD = DSUB + 1;  // pitch of a cell's sums: a coordinate's additions hit all banks, not a few
     float *sum = smem;                                    // [256][LD]
     uint32_t *cnt = (uint32_t *)(smem + kCentroids * LD);  // [256]
-    float *staged = smem + kCentroids * (LD + 1);          // [256][DSUB], not with SCALAR
     const int j = blockIdx.y, tid = threadIdx.x;
-    const float *__restrict__ from = cb + (int64_t)j * kCentroids * DSUB;
-    if constexpr (!SCALAR)
-        for (int e = tid; e < kCentroids * DSUB; e += 256) staged[e] = from[e];
-    const float *cen = SCALAR ? from : staged;  // (the same address in every lane)
+    const float *__restrict__ cen = cb + (int64_t)j * kCentroids * DSUB;  // (the same address in every lane)
     for (int e = tid; e < kCentroids * LD; e += 256) sum[e] = 0.f;
     cnt[tid] = 0u;
     __syncthreads();
@@ -78,6 +77,120 @@ pq_lloyd_step_kernel(const float *__restrict__ cb, int dim, int m, const float *
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) obj += __shfl_xor(obj, off, 64);
     if ((tid & 63) == 0) unsafeAtomicAdd(&gobj[j], obj);
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same step with the search on the matrix cores (pq_nearest.h), for sub-vectors whose operands and sums fit
+// LDS together.  Workgroup b of sub-quantizer j (block b * m + j) walks every nb-th 32 x waves rows, adds its rows
+// to sums in LDS (double precision) and writes them, its counts and its share of the objective to part b
+// of the scratch arrays; pq_lloyd_update_kernel adds the parts up in a fixed order.  No launch clears anything and
+// nothing but LDS is added to atomically: 196 workgroups a sub-quantizer adding 4096 doubles each to the
+// same addresses took most of what the search left.
+// `stop`: set by the update when a cell came out empty (iteration + 1): everything after it leaves at once, and
+// the host refills the cells and goes on from there.
+// Bound by vector issue (2.5 instructions per centroid and row), then by its start and end.  An iteration, before /
+// after, us: 8 sub-vectors of 16, 300 rows 81 / 21, 100k 254 / 74, 1M 1508 / 447; of 32 114 / 33, 506 / 111,
+// 3546 / 747; 16 of 4, 100k 196 / 77; 8 of 2, 1M 442 / 255.
+// ---------------------------------------------------------------------------------------------
+template <int DSUB>
+struct LloydLds {
+    static constexpr int LD = DSUB + 1;  // pitch of a cell's sums: a coordinate's additions hit all banks, not a few
+    typename PqNearest<DSUB>::Shared nearest;
+    double sum[kCentroids * LD];
+    uint32_t cnt[kCentroids];
+    double obj;
+};
+constexpr int kLloydThreads = 512;
+
+template <int DSUB>
+__global__ void __launch_bounds__(kLloydThreads) __attribute__((amdgpu_waves_per_eu(PqNearest<DSUB>::kWavesPerEu)))
+pq_lloyd_mfma_kernel(const float *__restrict__ cb, int dim, int m, const float *__restrict__ x, int64_t n,
+                     uint8_t *__restrict__ cell, float *__restrict__ dmin, double *__restrict__ part_sum,
+                     uint32_t *__restrict__ part_count, double *__restrict__ part_obj, const int *__restrict__ stop)
+{
+    if (*stop != 0) return;
+    typedef PqNearest<DSUB> Nearest;
+    constexpr int kThreads = kLloydThreads, kWaves = kThreads / 64, LD = LloydLds<DSUB>::LD;
+    extern __shared__ __align__(16) unsigned char lloyd_smem[];
+    LloydLds<DSUB> &s = *(LloydLds<DSUB> *)lloyd_smem;
+    const int j = (int)(blockIdx.x % (unsigned)m), b = (int)(blockIdx.x / (unsigned)m), nb = (int)(gridDim.x / (unsigned)m);
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
+    const float *cbj = cb + (int64_t)j * kCentroids * DSUB;
+    for (int e = tid; e < kCentroids * LD; e += kThreads) s.sum[e] = 0.0;
+    if (tid < kCentroids) s.cnt[tid] = 0u;
+    if (tid == 0) s.obj = 0.0;
+    Nearest::prepare(s.nearest, cbj);
+    double obj = 0.0;
+    const int64_t step = (int64_t)nb * (kWaves * 32);
+    bool plain = false;  // (wave-uniform) a row to each lane: two turns' rows at once
+    for (int64_t r0 = ((int64_t)b * kWaves + wave) * 32; r0 < n;) {
+        const int64_t own = r0 + (lane & 31) + (plain && half ? step : 0);
+        const bool live = own < n;
+        const int64_t r = live ? own : n - 1;
+        float v[DSUB];
+#pragma unroll
+        for (int t = 0; t < DSUB; ++t) v[t] = x[r * dim + j * DSUB + t];
+        r0 += plain ? 2 * step : step;
+        const bool alone = plain;
+        const int c = plain ? Nearest::all_distances(cbj, v) : Nearest::search(s.nearest, cbj, v, plain);
+        const float d = Nearest::distance(v, cbj + c * DSUB);
+        if (!live) continue;
+        if (half == 0 || alone) {
+            cell[r * m + j] = (uint8_t)c;
+            dmin[r * m + j] = d;
+            obj += (double)d;
+            atomicAdd(&s.cnt[c], 1u);
+        }
+        double *to = s.sum + c * LD;
+        if (alone) {
+#pragma unroll
+            for (int t = 0; t < DSUB; ++t) unsafeAtomicAdd(to + t, (double)v[t]);
+        } else {  // a coordinate each from the row's two lanes
+#pragma unroll
+            for (int t = 0; t < DSUB; t += 2) unsafeAtomicAdd(to + t + half, (double)(half ? v[t + 1] : v[t]));
+        }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) obj += __shfl_xor(obj, off, 64);
+    if (lane == 0) unsafeAtomicAdd(&s.obj, obj);
+    __syncthreads();
+    double *out = part_sum + ((int64_t)j * nb + b) * (kCentroids * DSUB);
+    for (int e = tid; e < kCentroids * DSUB; e += kThreads) out[e] = s.sum[e / DSUB * LD + e % DSUB];
+    if (tid < kCentroids) part_count[((int64_t)j * nb + b) * kCentroids + tid] = s.cnt[tid];
+    if (tid == 0) part_obj[j * nb + b] = s.obj;
+}
+
+// Sums, counts and objective of the step's parts; the new centroid of every cell that has members.
+// One thread per coordinate of a cell, 256 to a workgroup (a workgroup sees one sub-quantizer).
+__global__ void __launch_bounds__(256)
+pq_lloyd_update_kernel(const double *__restrict__ part_sum, const uint32_t *__restrict__ part_count,
+                       const double *__restrict__ part_obj, int nb, int dsub, int iteration, double *__restrict__ gsum,
+                       uint32_t *__restrict__ gcount, double *__restrict__ gobj, float *__restrict__ cb, int *__restrict__ stop)
+{
+    const int seen = *(volatile int *)stop;
+    if (seen != 0 && seen != iteration + 1) return;
+    const int j = (int)blockIdx.y, per = kCentroids * dsub, e = (int)blockIdx.x * 256 + (int)threadIdx.x;
+    const int c = e / dsub;
+    const double *sums = part_sum + (int64_t)j * nb * per + e;
+    const uint32_t *counts = part_count + (int64_t)j * nb * kCentroids + c;
+    double sum = 0.0;
+    uint32_t cnt = 0u;
+#pragma unroll 8
+    for (int b = 0; b < nb; ++b) {
+        sum += sums[(int64_t)b * per];
+        cnt += counts[b * kCentroids];
+    }
+    gsum[(int64_t)j * per + e] = sum;
+    if (cnt != 0u) cb[(int64_t)j * per + e] = (float)(sum / (double)cnt);
+    if (e % dsub == 0) {
+        gcount[j * kCentroids + c] = cnt;
+        if (cnt == 0u) *stop = iteration + 1;
+    }
+    if (e == 0) {
+        double obj = 0.0;
+        for (int b = 0; b < nb; ++b) obj += part_obj[j * nb + b];
+        gobj[j] = obj;
+    }
 }
 
 // The 256 starting centroids of every sub-quantizer: sub-vector j of row rows[j][c].
@@ -217,33 +330,21 @@ mean_centroid_kernel(float *__restrict__ cent, int ncent, int dim)
     if (threadIdx.x == 0) cent[(int64_t)ncent * dim + t] = (float)((part[0] + part[1] + part[2] + part[3]) / ncent);
 }
 
-template <int DSUB, bool SCALAR>
-int run_pq_step_form(const float *cb, int dim, int m, const float *x, int64_t n, uint8_t *cell, float *dmin,
-                double *gsum, uint32_t *gcount, double *gobj, hipStream_t s)
-{
-    const size_t lds = (size_t)(kCentroids * (DSUB + 2) + (SCALAR ? 0 : kCentroids * DSUB)) * sizeof(float);
-    if (lds > 48 * 1024)
-        PSC_HIP_TRY(hipFuncSetAttribute((const void *)pq_lloyd_step_kernel<DSUB, SCALAR>,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    // at most 2048 workgroups (8 to a compute unit), all with the same number of turns
-    const int64_t want = (n + 255) / 256, cap = 2048 / m, turns = (want + cap - 1) / cap;
-    dim3 grid((unsigned)((want + turns - 1) / turns), (unsigned)m);
-    hipLaunchKernelGGL((pq_lloyd_step_kernel<DSUB, SCALAR>), grid, dim3(256), lds, s, cb, dim, m, x, n, cell, dmin,
-                       gsum, gcount, gobj);
-    PSC_HIP_TRY(hipGetLastError());
-    return PSC_OK;
-}
-
 template <int DSUB>
 int run_pq_step(const float *cb, int dim, int m, const float *x, int64_t n, uint8_t *cell, float *dmin,
                 double *gsum, uint32_t *gcount, double *gobj, hipStream_t s)
 {
-    // the number of sub-vectors from which the scalar cache is ahead (measured at 300 .. 130k rows, 8 and 16
-    // sub-quantizers; sub-vectors of up to 4: even; long ones: at any number)
-    constexpr int64_t from = DSUB <= 8 ? 700'000 : DSUB <= 24 ? 220'000 : DSUB <= 32 ? 130'000 : 0;
-    if constexpr (from != 0)
-        if (n * m < from) return run_pq_step_form<DSUB, false>(cb, dim, m, x, n, cell, dmin, gsum, gcount, gobj, s);
-    return run_pq_step_form<DSUB, true>(cb, dim, m, x, n, cell, dmin, gsum, gcount, gobj, s);
+    const size_t lds = (size_t)(kCentroids * (DSUB + 2)) * sizeof(float);
+    if (lds > 48 * 1024)
+        PSC_HIP_TRY(hipFuncSetAttribute((const void *)pq_lloyd_step_kernel<DSUB>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    // at most 2048 workgroups (8 to a compute unit), all with the same number of turns
+    const int64_t want = (n + 255) / 256, cap = 2048 / m, turns = (want + cap - 1) / cap;
+    dim3 grid((unsigned)((want + turns - 1) / turns), (unsigned)m);
+    hipLaunchKernelGGL((pq_lloyd_step_kernel<DSUB>), grid, dim3(256), lds, s, cb, dim, m, x, n, cell, dmin,
+                       gsum, gcount, gobj);
+    PSC_HIP_TRY(hipGetLastError());
+    return PSC_OK;
 }
 
 }  // namespace
@@ -258,14 +359,6 @@ int launch_pq_lloyd_step(const float *cb_dev, int dim, int m, const float *x_dev
 #define CALL(DS) run_pq_step<DS>(cb_dev, dim, m, x_dev, n, cell_dev, dmin_dev, sum_dev, count_dev, obj_dev, s)
     switch (dim / m) {
     case 1: return CALL(1);
-    case 2: return CALL(2);
-    case 4: return CALL(4);
-    case 6: return CALL(6);
-    case 8: return CALL(8);
-    case 12: return CALL(12);
-    case 16: return CALL(16);
-    case 24: return CALL(24);
-    case 32: return CALL(32);
     case 48: return CALL(48);
     case 64: return CALL(64);
     default:
@@ -273,6 +366,46 @@ int launch_pq_lloyd_step(const float *cb_dev, int dim, int m, const float *x_dev
         return PSC_EINVAL;
     }
 #undef CALL
+}
+
+template <int DSUB>
+static int run_pq_lloyd(const PqLloydArgs &a, int iteration, hipStream_t s)
+{
+    const size_t lds = sizeof(LloydLds<DSUB>);
+    PSC_HIP_TRY(hipFuncSetAttribute((const void *)pq_lloyd_mfma_kernel<DSUB>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)lds));
+    hipLaunchKernelGGL((pq_lloyd_mfma_kernel<DSUB>), dim3((unsigned)(a.parts * a.m)), dim3(kLloydThreads), lds, s, a.cb,
+                       a.dim, a.m, a.x, a.n, a.cell, a.dmin, a.part_sum, a.part_count, a.part_obj, a.stop);
+    PSC_HIP_TRY(hipGetLastError());
+    hipLaunchKernelGGL(pq_lloyd_update_kernel, dim3((unsigned)DSUB, (unsigned)a.m), dim3(256), 0, s, a.part_sum, a.part_count,
+                       a.part_obj, a.parts, DSUB, iteration, a.sum, a.count, a.obj + (int64_t)iteration * a.m, a.cb, a.stop);
+    PSC_HIP_TRY(hipGetLastError());
+    return PSC_OK;
+}
+
+int pq_lloyd_parts(int dim, int m, int64_t n)
+{
+    const int dsub = dim / m;
+    if (dsub < 2 || dsub > 32) return 0;
+    // as many workgroups as run together (two to a compute unit up to sub-vectors of 16), at least a turn each
+    const int rows = 32 * kLloydThreads / 64;
+    const int64_t want = (n + rows - 1) / rows, cap = std::max(1, (dsub <= 16 ? 512 : 256) / m), turns = (want + cap - 1) / cap;
+    return (int)((want + turns - 1) / turns);
+}
+
+int launch_pq_lloyd(const PqLloydArgs &a, int iteration, hipStream_t s)
+{
+    switch (a.dim / a.m) {
+    case 2: return run_pq_lloyd<2>(a, iteration, s);
+    case 4: return run_pq_lloyd<4>(a, iteration, s);
+    case 6: return run_pq_lloyd<6>(a, iteration, s);
+    case 8: return run_pq_lloyd<8>(a, iteration, s);
+    case 12: return run_pq_lloyd<12>(a, iteration, s);
+    case 16: return run_pq_lloyd<16>(a, iteration, s);
+    case 24: return run_pq_lloyd<24>(a, iteration, s);
+    case 32: return run_pq_lloyd<32>(a, iteration, s);
+    default: set_error("no matrix-core step for sub-vectors of %d", a.dim / a.m); return PSC_EINVAL;
+    }
 }
 
 int launch_pq_gather_start(const float *x_dev, int dim, int m, const int64_t *rows_dev, float *cb_dev, hipStream_t s)

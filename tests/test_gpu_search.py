@@ -100,6 +100,63 @@ def test_encode_of_many_rows_equals_encode_of_few(m, dsub):
         assert abs(da - db) <= RTOL * db
 
 
+@pytest.mark.parametrize("data", ["twins", "one", "far", "tiny", "huge", "wide", "grid"])
+@pytest.mark.parametrize("m,dsub", [(16, 1), (8, 2), (16, 4), (8, 6), (16, 8), (8, 12), (8, 16), (16, 24), (8, 32)])
+def test_encode_where_centroids_are_close(m, dsub, data):
+    """The search runs on bfloat16 parts, close calls are decided by the float32 distances: the codes are the
+    first arg-min of those where nearly every row is a close call (every centroid twice, all centroids one, points
+    of a grid halfway between centroids), where one centroid is far out, at the ends of float32's range and
+    with infinities and NaNs among the rows; from one row to several turns of every workgroup."""
+    import paper_1609_01882_amd as psc
+    dim, n = m * dsub, 40_000 // m + 8_193
+    rng = np.random.default_rng(dim + len(data))
+    cb = rng.normal(size=(m, 256, dsub)).astype(np.float32)
+    x = rng.normal(size=(n, dim)).astype(np.float32)
+    if data == "twins":
+        cb[:, 128:] = cb[:, 127::-1]
+    elif data == "one":
+        cb[:] = cb[:, :1]
+    elif data == "far":
+        cb[:, 77] *= 1000.0
+    elif data == "tiny":
+        cb, x = cb * np.float32(1e-21), x * np.float32(1e-21)
+    elif data == "huge":
+        cb, x = cb * np.float32(3e18), x * np.float32(3e18)
+    elif data == "wide":
+        x[::3] *= np.float32(1e15)
+        x[1::97, 0] = np.inf
+        x[2::89, dim - 1] = np.nan
+        x[5::83] = 0.0
+    else:
+        cb, x = np.round(cb * 2), np.round(x * 4) / 2
+    idx = psc.Index(dim, m)
+    idx.set_codebook(np.ascontiguousarray(cb))
+    xd = torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    # differences and multiply-adds in ascending order as the encoder states them: a float64 product and sum of
+    # float32 values, rounded once to float32, is the fused multiply-add (but for double roundings: near-ties of
+    # the last bit, of which a code may be either)
+    want = np.zeros((n, m), np.uint8)
+    tied = np.zeros((n, m), bool)
+    with np.errstate(all="ignore"):
+        for j in range(m):
+            v = xd[:, j * dsub:(j + 1) * dsub]
+            c = torch.from_numpy(np.ascontiguousarray(cb[j])).cuda()
+            acc = torch.zeros((n, 256), dtype=torch.float32, device="cuda")
+            for t in range(dsub):
+                df = (v[:, t:t + 1] - c[None, :, t]).double()
+                acc = (df * df + acc.double()).float()
+            acc = torch.where(torch.isnan(acc), torch.inf, acc)
+            least = acc.min(1, keepdim=True).values
+            want[:, j] = (acc == least).int().argmax(1).cpu().numpy()
+            got = idx.encode(xd)[:, j:j + 1].long()
+            tied[:, j] = (acc.gather(1, got) <= least * (1 + 2e-7))[:, 0].cpu().numpy()
+    got = idx.encode(xd).cpu().numpy()
+    differs = got != want
+    assert np.all(tied[differs]) and differs.sum() <= 1e-4 * differs.size, (int(differs.sum()), int((~tied & differs).sum()))
+    for count in (1, 31, 33, 257, n - 1):
+        assert np.array_equal(idx.encode(xd[:count].contiguous()).cpu().numpy(), got[:count]), count
+
+
 @pytest.mark.parametrize("route", ["auto", "popcount", "mfma"])
 @pytest.mark.parametrize("m", [8, 16])
 def test_whole_search_matches_oracle(setup, force_route, route, m):
