@@ -41,23 +41,22 @@ __device__ __forceinline__ float fkey_value(uint32_t k)
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
-// Smallest value of v over the wave, in every lane: four row-local steps on the data-parallel
+// The smallest number of v over the wave, the same in every lane: four row-local steps on the data-parallel
 // path, then the four row results through scalar registers.
-__device__ __forceinline__ uint32_t wave_min_key(uint32_t v)
+__device__ __forceinline__ float wave_min_f32(float v)
 {
-    auto step = [](uint32_t x, uint32_t y) { return y < x ? y : x; };
-    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0xB1, 0xf, 0xf, false));   // lane ^ 1
-    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x4E, 0xf, 0xf, false));   // lane ^ 2
-    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x141, 0xf, 0xf, false));  // mirror in 8
-    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x140, 0xf, 0xf, false));  // mirror in 16
-    const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)v, 0);
-    const uint32_t r1 = (uint32_t)__builtin_amdgcn_readlane((int)v, 16);
-    const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)v, 32);
-    const uint32_t r3 = (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
-    return step(step(r0, r1), step(r2, r3));
+    v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(0x7f800000, __float_as_int(v), 0xB1, 0xf, 0xf, false)));
+    v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(0x7f800000, __float_as_int(v), 0x4E, 0xf, 0xf, false)));
+    v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(0x7f800000, __float_as_int(v), 0x141, 0xf, 0xf, false)));
+    v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(0x7f800000, __float_as_int(v), 0x140, 0xf, 0xf, false)));
+    const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
+    const float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
+    const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
+    const float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
+    return fminf(fminf(r0, r1), fminf(r2, r3));
 }
 
-// Sum of v over the wave, the same in every lane (the same steps as wave_min_key).
+// Sum of v over the wave, the same in every lane (the same steps).
 __device__ __forceinline__ float wave_sum_f32(float v)
 {
     v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, false));   // lane ^ 1
@@ -197,6 +196,8 @@ imi_cells_kernel(const int32_t *__restrict__ sel1, const float *__restrict__ dis
     for (int t = tid; t < lmax; t += 256) cells[q * lmax + t] = t < ntake ? (int32_t)(uint32_t)keys[t] : -1;
 }
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 struct ImiScanArgs {
     const float *lut;        // [nq][M][256] the queries' share ||c||^2 - 2 (q-o).c (unused when direct)
     const float *tab1;       // [k1][M/2][256] 2 (c1[a]-o1)_j . c
@@ -214,24 +215,28 @@ struct ImiScanArgs {
     float *dists;            // [nq][k]
     int64_t *part_i;         // [nq][split][k]     (split > 1: one list per workgroup, merged afterwards)
     float *part_d;           // [nq][split][k]
-    int dim, k2, lmax, ht, k, cap, direct;
+    int dim, k2, lmax, ht, k, cap;
     int split;               // workgroups per query: workgroup s of a query takes its cells s, s + split, ...
 };
 
-// Dynamic LDS: [M][256] query share, [M][256] cell table, dim floats (residual; dim is even), cap keys.
+// Dynamic LDS: [M][256] cell table, dim floats (residual; dim is even), cap keys.
 //
 // A cell is short work behind several trips to memory (its bounds, its two half-centroids, its
 // two half tables, its codes), so the trips are taken off the path of the cell they belong to: the
 // bounds of the workgroup's next kWindow cells are staged in LDS at once, and while one cell is
 // worked on every thread already holds, in registers, what it will need of the next one (its
 // element of the residual, its entry of each table row, its code of the first step).
-template <int M>
+// Bound by instructions.  A lane builds four entries in a row of each of its wave's table rows: the query's share
+// stays in its registers, everything else is one 16-byte access, the row's minimum is one of numbers with the
+// place found by comparison, and a cell's codes are counted in 32 bits from a scalar base.  10k queries x 16
+// cells of 10M vectors, the whole call 1012 -> 874 us (with the query's share in LDS, single entries 64 apart,
+// (key, place) minima and 64-bit positions before).
+template <int M, bool DIRECT>
 __global__ void __launch_bounds__(256)
 imi_scan_kernel(ImiScanArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    float *tq = (float *)smem;
-    float *cellt = tq + M * 256;
+    float *cellt = (float *)smem;
     float *res = cellt + M * 256;
     unsigned long long *pool = (unsigned long long *)(res + a.dim);
     constexpr int kWindow = 32;
@@ -247,9 +252,12 @@ imi_scan_kernel(ImiScanArgs a)
     constexpr int WPC = M / 4;
     constexpr int RPW = M / 4;  // table rows per wave: wave w builds rows w * RPW .. and finds their minima alone
 
-    if (!a.direct)
-        for (int e = tid; e < M * 64; e += 256)
-            ((float4 *)tq)[e] = ((const float4 *)(a.lut + q * (M * 256)))[e];
+    // the query's share of the tables: a lane's four entries of each row its wave builds, the same for every cell
+    f32x4 tq[RPW];
+#pragma unroll
+    for (int r = 0; r < RPW; ++r)
+        tq[r] = DIRECT ? f32x4{0.f, 0.f, 0.f, 0.f}
+                         : ((const f32x4 *)(a.lut + q * (M * 256) + (wave * RPW + r) * 256))[lane];
     for (int e = tid; e < a.cap; e += 256) pool[e] = ~0ull;
     if (tid == 0) {
         count_s = 0;
@@ -262,38 +270,43 @@ imi_scan_kernel(ImiScanArgs a)
     // what a thread holds of a cell before the cell's turn
     struct Inputs {
         float g;            // its element of the cell centroid (tid < dim)
-        float th[M];        // its entries of the half tables' rows (not direct): rows of its wave, four each
+        f32x4 th[RPW];      // its entries of the half tables' rows (not direct): rows of its wave, four each
         uint32_t cw[WPC];   // its code of the cell's first 256
         int32_t id;         // and that code's id
     };
+    // (a cell's place is the same in every lane and its codes are counted in 32 bits: ids are)
+    auto uniform64 = [](long long v) {
+        return (long long)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)((uint64_t)v >> 32)) << 32) |
+                           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v));
+    };
+    auto load_code = [&](long long first, int i, uint32_t (&w)[WPC], int32_t &id) {
+        const uint32_t *src = (const uint32_t *)(a.codes + first * M) + (uint32_t)i * WPC;
+#pragma unroll
+        for (int ww = 0; ww < WPC; ++ww) w[ww] = src[ww];
+        id = (a.ext_ids + first)[(uint32_t)i];
+    };
     auto fetch = [&](int w, Inputs &in) {  // w: place in the window
-        const int cell = win_cell[w];
+        const int cell = __builtin_amdgcn_readfirstlane(win_cell[w]);
         in.g = 0.f;
 #pragma unroll
-        for (int jj = 0; jj < M; ++jj) in.th[jj] = 0.f;
+        for (int r = 0; r < RPW; ++r) in.th[r] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ww = 0; ww < WPC; ++ww) in.cw[ww] = 0u;
         in.id = 0;
         if (cell < 0) return;
         const int ca = cell / a.k2, cb_ = cell - ca * a.k2;
         if (tid < a.dim) in.g = tid < half ? a.c1[(int64_t)ca * half + tid] : a.c2[(int64_t)cb_ * half + tid - half];
-        if (!a.direct) {
+        if constexpr (!DIRECT) {
 #pragma unroll
             for (int r = 0; r < RPW; ++r) {
                 const int jj = wave * RPW + r;  // (a wave's rows lie in one half: RPW divides M / 2)
                 const float *row = jj < M / 2 ? a.tab1 + ((int64_t)ca * (M / 2) + jj) * 256
                                               : a.tab2 + ((int64_t)cb_ * (M / 2) + jj - M / 2) * 256;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) in.th[r * 4 + c] = row[c * 64 + lane];
+                in.th[r] = ((const f32x4 *)row)[lane];
             }
         }
-        const long long i = win_begin[w] + tid;
-        if (i < win_end[w]) {
-            const uint32_t *src = (const uint32_t *)(a.codes + i * M);
-#pragma unroll
-            for (int ww = 0; ww < WPC; ++ww) in.cw[ww] = src[ww];
-            in.id = a.ext_ids[i];
-        }
+        const long long first = uniform64(win_begin[w]);
+        if (tid < (int)(uniform64(win_end[w]) - first)) load_code(first, tid, in.cw, in.id);
     };
 
     for (int base = 0; base < mine; base += kWindow) {
@@ -316,9 +329,10 @@ imi_scan_kernel(ImiScanArgs a)
         fetch(0, cur);
         for (int w = 0; w < nwin; ++w) {
             const int p = sub + (base + w) * a.split;  // the cell's place in the query's order
-            const long long begin = win_begin[w], end = win_end[w];
+            const long long begin = uniform64(win_begin[w]);
+            const int len = (int)(uniform64(win_end[w]) - begin);
             if (w + 1 < nwin) fetch(w + 1, nxt);
-            if (!(begin == end && !a.qcodes_out)) {  // (uniform over the workgroup)
+            if (!(len == 0 && !a.qcodes_out)) {  // (uniform over the workgroup)
                 // ---- residual to the cell centroid (one element per thread, held since the cell before;
                 //      vectors of more than 256 dimensions take theirs from memory here)
                 if (a.dim <= 256) {
@@ -340,32 +354,30 @@ imi_scan_kernel(ImiScanArgs a)
                     float part = 0.f;
                     for (int t = lane; t < dsub; t += 64) part = fmaf(res[jj * dsub + t], res[jj * dsub + t], part);
                     const float sq = wave_sum_f32(part);
-                    uint32_t best = 0xffffffffu;
-                    int besti = 0;
+                    f32x4 v;  // entries 4 * lane ..
+                    if constexpr (DIRECT) {
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const int e = c * 64 + lane;
-                        float v;
-                        if (a.direct) {
-                            const float *cr = a.cb + ((int64_t)jj * 256 + e) * dsub;
-                            v = 0.f;
+                        for (int c = 0; c < 4; ++c) {
+                            const float *cr = a.cb + ((int64_t)jj * 256 + 4 * lane + c) * dsub;
+                            float acc = 0.f;
                             for (int t = 0; t < dsub; ++t) {
                                 const float df = res[jj * dsub + t] - cr[t];
-                                v = fmaf(df, df, v);
+                                acc = fmaf(df, df, acc);
                             }
-                        } else {
-                            v = (tq[jj * 256 + e] + cur.th[r * 4 + c]) + sq;
+                            v[c] = acc;
                         }
-                        cellt[jj * 256 + e] = v;
-                        const uint32_t key = fkey(v);
-                        if (key < best) {  // (ascending e: the lowest index stays on ties)
-                            best = key;
-                            besti = e;
-                        }
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) v[c] = (tq[r][c] + cur.th[r][c]) + sq;
                     }
-                    // the smallest key of the wave, then the lowest index among the lanes that hold it
-                    const uint32_t wmin = wave_min_key(best);
-                    const uint32_t imin = wave_min_key(best == wmin ? (uint32_t)besti : 0xffffffffu);
+                    ((f32x4 *)(cellt + jj * 256))[lane] = v;
+                    // the row's minimum, then its lowest place: the first lane that holds it, the first of its four
+                    // (not among numbers: whatever place 0 of the search gives)
+                    const float least = wave_min_f32(fminf(fminf(v[0], v[1]), fminf(v[2], v[3])));
+                    const int in4 = v[0] == least ? 0 : v[1] == least ? 1 : v[2] == least ? 2 : 3;
+                    const uint64_t holds = __ballot(v[0] == least || v[1] == least || v[2] == least || v[3] == least);
+                    const int first = holds != 0 ? __builtin_ctzll(holds) : 0;
+                    const int imin = 4 * first + __builtin_amdgcn_readlane(in4, first);
                     if (lane == 0) ((volatile uint8_t *)qcw)[jj] = (uint8_t)imin;
                 }
                 __syncthreads();
@@ -379,19 +391,14 @@ imi_scan_kernel(ImiScanArgs a)
 #pragma unroll
                 for (int ww = 0; ww < WPC; ++ww) cw[ww] = cur.cw[ww];
                 int32_t id = cur.id;  // (asked for with the code: a survivor's id is not one more trip to memory)
-                for (long long i0 = begin; i0 < end; i0 += 256) {
-                    const long long i = i0 + tid;
+                for (int i0 = 0; i0 < len; i0 += 256) {
+                    const int i = i0 + tid;
                     uint32_t nw[WPC];
                     int32_t nid = 0;
 #pragma unroll
                     for (int ww = 0; ww < WPC; ++ww) nw[ww] = 0u;
-                    if (i + 256 < end) {
-                        const uint32_t *src = (const uint32_t *)(a.codes + (i + 256) * M);
-#pragma unroll
-                        for (int ww = 0; ww < WPC; ++ww) nw[ww] = src[ww];
-                        nid = a.ext_ids[i + 256];
-                    }
-                    if (i < end) {
+                    if (i < len - 256) load_code(begin, i + 256, nw, nid);
+                    if (i < len) {
                         int h = 0;
 #pragma unroll
                         for (int ww = 0; ww < WPC; ++ww) h += __builtin_popcount(cw[ww] ^ qw[ww]);
@@ -535,20 +542,13 @@ int launch_imi_scan(int m, const float *lut_dev, const float *tab1_dev, const fl
     int cap = 512;  // room for the best k plus one step of 256 survivors
     while (cap < k + 256) cap <<= 1;
     a.cap = cap;
-    a.direct = direct ? 1 : 0;
-    const size_t lds = (size_t)2 * m * 256 * 4 + (size_t)dim * 4 + (size_t)cap * 8;  // (dim = 2 * m * ..: a multiple of 8 bytes)
-    PSC_REQUIRE(lds <= 96 * 1024, "dimension and k too large for the multi-index scan");
-    if (m == 8) {
-        hipLaunchKernelGGL(imi_scan_kernel<8>, dim3((unsigned)(nq * split)), dim3(256), lds, s, a);
-    } else {
-        static bool configured = false;
-        if (!configured) {
-            PSC_HIP_TRY(hipFuncSetAttribute((const void *)imi_scan_kernel<16>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                            96 * 1024));
-            configured = true;
-        }
-        hipLaunchKernelGGL(imi_scan_kernel<16>, dim3((unsigned)(nq * split)), dim3(256), lds, s, a);
-    }
+    const size_t lds = (size_t)m * 256 * 4 + (size_t)dim * 4 + (size_t)cap * 8;  // (dim = 2 * m * ..: a multiple of 8 bytes)
+    PSC_REQUIRE(lds <= 48 * 1024, "dimension and k too large for the multi-index scan");  // (at most 40 KB: dim up to 2048, k up to 1024)
+    const dim3 grid((unsigned)(nq * split));
+    if (m == 8 && !direct) hipLaunchKernelGGL((imi_scan_kernel<8, false>), grid, dim3(256), lds, s, a);
+    else if (m == 8) hipLaunchKernelGGL((imi_scan_kernel<8, true>), grid, dim3(256), lds, s, a);
+    else if (!direct) hipLaunchKernelGGL((imi_scan_kernel<16, false>), grid, dim3(256), lds, s, a);
+    else hipLaunchKernelGGL((imi_scan_kernel<16, true>), grid, dim3(256), lds, s, a);
     PSC_HIP_TRY(hipGetLastError());
     char text[96];
     snprintf(text, sizeof text, "imi_scan_kernel%s m=%d cells<=%d pool=%d queries=%lld x%d", direct ? "+direct-tables" : "", m,
