@@ -258,8 +258,9 @@ int psc_encode(const psc_index *idx, const float *x_dev, int64_t n, uint8_t *cod
     return launch_encode(idx->cb_dev, idx->dim, idx->m, x_dev, n, RowMap{}, codes_dev, (hipStream_t)stream);
 }
 
-int psc_build_lut(const psc_index *idx, const float *q_dev, int64_t nq, float *lut_dev,
-                  uint8_t *qcodes_dev, psc_stream stream)
+// preset_dev / npreset: words to set on the way (launch_lut_mfma); *preset: whether that was done.
+static int build_lut(const psc_index *idx, const float *q_dev, int64_t nq, float *lut_dev, uint8_t *qcodes_dev,
+                     uint32_t *preset_dev, int npreset, bool *preset, hipStream_t s)
 {
     int rc = need_codebook(idx);
     if (rc != PSC_OK) return rc;
@@ -269,14 +270,20 @@ int psc_build_lut(const psc_index *idx, const float *q_dev, int64_t nq, float *l
     if (idx->dsub % 2 == 0) {
         // the dense contraction of the path: matrix cores
         const size_t n = idx->cb_host.size();
-        rc = launch_lut_mfma(idx->cb_dev, idx->cb_dev + n, idx->cb_dev + 2 * n, idx->dim, idx->m, q_dev, nq, lut_dev,
-                             (hipStream_t)stream);
-    } else {
-        rc = launch_lut(idx->cb_dev, idx->dim, idx->m, q_dev, nq, RowMap{}, false, lut_dev, (hipStream_t)stream);
+        *preset = npreset > 0;
+        return launch_lut_mfma(idx->cb_dev, idx->cb_dev + n, idx->cb_dev + 2 * n, idx->dim, idx->m, q_dev, nq, lut_dev,
+                               qcodes_dev, preset_dev, npreset, s);
     }
-    if (rc != PSC_OK) return rc;
-    if (qcodes_dev) rc = launch_row_argmin(lut_dev, nq * idx->m, qcodes_dev, (hipStream_t)stream);
+    rc = launch_lut(idx->cb_dev, idx->dim, idx->m, q_dev, nq, RowMap{}, false, lut_dev, s);
+    if (rc == PSC_OK && qcodes_dev) rc = launch_row_argmin(lut_dev, nq * idx->m, qcodes_dev, s);
     return rc;
+}
+
+int psc_build_lut(const psc_index *idx, const float *q_dev, int64_t nq, float *lut_dev,
+                  uint8_t *qcodes_dev, psc_stream stream)
+{
+    bool preset = false;
+    return build_lut(idx, q_dev, nq, lut_dev, qcodes_dev, nullptr, 0, &preset, (hipStream_t)stream);
 }
 
 int psc_hamming_histogram(int m, const uint8_t *qcodes_dev, int64_t nq, const uint8_t *codes_dev,
@@ -323,7 +330,7 @@ int psc_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t nq,
              const uint8_t *codes_dev, int64_t n, int ht, int k, int64_t *ids_dev,
              float *dists_dev, void *workspace_dev, size_t workspace_bytes, psc_stream stream)
 {
-    return launch_scan(m, lut_dev, qcodes_dev, nq, codes_dev, n, ht, k, -1, true, ids_dev, dists_dev,
+    return launch_scan(m, lut_dev, qcodes_dev, nq, codes_dev, n, ht, k, -1, true, false, ids_dev, dists_dev,
                        workspace_dev, workspace_bytes, (hipStream_t)stream);
 }
 
@@ -375,7 +382,7 @@ int psc_scan_static(int m, const float *lut_dev, const uint8_t *qcodes_dev, int6
     if (rc != PSC_OK) return rc;
     // (launch_scan has the status word cleared, and the shared thresholds where the kernel taken has any, and
     //  the scan kernels write every partial list they later merge: nothing of the previous call is read)
-    return launch_scan(m, lut_dev, qcodes_dev, nq, codes_dev, n, ht, k, -1, true, ids_dev, dists_dev, ws,
+    return launch_scan(m, lut_dev, qcodes_dev, nq, codes_dev, n, ht, k, -1, true, false, ids_dev, dists_dev, ws,
                        (size_t)PSC_STATIC_SCRATCH_BYTES, (hipStream_t)stream);
 }
 
@@ -408,9 +415,11 @@ int psc_search(const psc_index *idx, const float *q_dev, int64_t nq, const uint8
     float *lut = (float *)w;
     w += round256((size_t)nq * idx->m * kCentroids * sizeof(float));
     uint8_t *qcodes = (uint8_t *)w;
-    rc = psc_build_lut(idx, q_dev, nq, lut, qcodes, stream);
+    bool preset = false;  // (the scan workspace holds its status word and at least a word per query)
+    rc = build_lut(idx, q_dev, nq, lut, qcodes, (uint32_t *)((char *)workspace_dev + 256),
+                   (int)std::min<int64_t>(nq, kPresetQueries), &preset, (hipStream_t)stream);
     if (rc != PSC_OK) return rc;
-    return launch_scan(idx->m, lut, qcodes, nq, codes_dev, n, ht, k, -1, true, ids_dev, dists_dev,
+    return launch_scan(idx->m, lut, qcodes, nq, codes_dev, n, ht, k, -1, true, preset, ids_dev, dists_dev,
                        workspace_dev, scan_bytes, (hipStream_t)stream);
 }
 
@@ -472,13 +481,13 @@ int psc_knn_graph(const psc_index *idx, const float *x_dev, const uint8_t *codes
         if (idx->dsub % 2 == 0) {
             const size_t nc = idx->cb_host.size();
             rc = launch_lut_mfma(idx->cb_dev, idx->cb_dev + nc, idx->cb_dev + 2 * nc, idx->dim, idx->m,
-                                 x_dev + (size_t)c0 * idx->dim, qc, lut, (hipStream_t)stream);
+                                 x_dev + (size_t)c0 * idx->dim, qc, lut, nullptr, nullptr, 0, (hipStream_t)stream);
         } else {
             rc = launch_lut(idx->cb_dev, idx->dim, idx->m, x_dev + (size_t)c0 * idx->dim, qc, RowMap{}, false, lut,
                             (hipStream_t)stream);
         }
         if (rc != PSC_OK) return rc;
-        rc = launch_scan(idx->m, lut, codes_dev + (size_t)c0 * idx->m, qc, codes_dev, n, ht, k, c0, c0 == 0,
+        rc = launch_scan(idx->m, lut, codes_dev + (size_t)c0 * idx->m, qc, codes_dev, n, ht, k, c0, c0 == 0, false,
                          ids_dev + (size_t)c0 * k, dists_dev + (size_t)c0 * k, scan_ws, scan_ws_bytes,
                          (hipStream_t)stream);
         if (rc != PSC_OK) return rc;

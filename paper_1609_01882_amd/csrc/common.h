@@ -68,9 +68,12 @@ int launch_encode(const float *cb_dev, int dim, int m, const float *x_dev, int64
                   const RowMap &map, uint8_t *codes_dev, hipStream_t s);
 // Tables on the matrix cores from the centred codebook cbc [m][256][dsub] and the per-sub-quantizer
 // mean centroids mu [m][dsub] (entries that cancel badly are redone from the codebook cb by direct
-// differences); and the arg-min of every table row (nrows_total = rows x m).
+// differences), with the arg-min of every row if codes_dev; npreset words at preset_dev are set to kPresetWord
+// (launch_scan's counters).  And the arg-min of tables that launch_lut built (nrows_total = rows x m).
+constexpr uint32_t kPresetWord = 0xff800000u;
 int launch_lut_mfma(const float *cb_dev, const float *cbc_dev, const float *mu_dev, int dim, int m,
-                    const float *x_dev, int64_t nrows, float *lut_dev, hipStream_t s);
+                    const float *x_dev, int64_t nrows, float *lut_dev, uint8_t *codes_dev, uint32_t *preset_dev,
+                    int npreset, hipStream_t s);
 int launch_row_argmin(const float *lut_dev, int64_t nrows_total, uint8_t *codes_dev, hipStream_t s);
 
 // ---- linear transformation in front of the quantizer (kernels_rotate.hip)
@@ -115,9 +118,11 @@ int shared_threshold_words(int64_t lists_per_query);
 size_t flat_scan_workspace_bytes(int m, int64_t nq, int64_t n, int k);
 // skip_first >= 0: query q never returns database row skip_first + q (k-NN-graph mode).
 // clear_status: reset the workspace's status word first (false for follow-up chunks of one call).
+// preset: the first min(nq, kPresetQueries) words after the status word's 256 bytes hold kPresetWord already.
+constexpr int kPresetQueries = 128;
 int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t nq,
                 const uint8_t *codes_dev, int64_t n, int ht, int k, int64_t skip_first,
-                bool clear_status, int64_t *ids_dev, float *dists_dev, void *ws, size_t ws_bytes,
+                bool clear_status, bool preset, int64_t *ids_dev, float *dists_dev, void *ws, size_t ws_bytes,
                 hipStream_t s);
 // lut_dev: tables of the queries minus the mean coarse centroid, [nq][m][256]; list_tab_dev:
 // the lists' share of the residual tables (launch_list_tables); job_qcodes_dev: out, the query

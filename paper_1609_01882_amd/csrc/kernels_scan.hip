@@ -196,6 +196,7 @@ __device__ __forceinline__ float key_dist(uint32_t key)
     return __uint_as_float(key ^ ((key >> 31) ? 0x80000000u : 0xffffffffu));
 }
 constexpr uint32_t kKeyInf = 0xff800000u;  // dist_key(+infinity)
+static_assert(kPresetWord == kKeyInf, "init_scan_kernel presets the words too");
 constexpr uint64_t kNoEntry = ~0ull;       // above every entry
 __device__ __forceinline__ uint64_t pack_entry(float d, uint32_t id)
 {
@@ -341,7 +342,7 @@ __device__ __forceinline__ uint64_t lane_value_u64(uint64_t v, int l)
 // kNoEntry, entries only ever get smaller, and a 64-bit LDS access is one access: whatever is read is a bound.
 // The thresholds are distances alone and let every candidate through that ties with the k-th entry, though
 // it loses by its id nearly always (ids rise during a scan); clustered vectors share codes by the thousand, and
-// each such tie took the list's lock to be turned away.  Asked only when a batch has a candidate at all.
+// each such tie took the list's lock to be turned away.  Asked only when a batch has a tie.
 // 10M x 10k at ht = 24, k = 100 24.6 -> 14.0 ms (of seeds with many codes at the k-th distance), 1M x 777 pure
 // ADC 829 -> 744 us, 1M x 1M graph at ht = 20 80.4 -> 77.4 ms.  Inverted lists do without: 4.43 / 4.48 ms.
 template <int M, int TQ>
@@ -719,8 +720,10 @@ __device__ __forceinline__ void score_batch(const Lds<M, TQ> &s, const ScanArgs 
     ask.wanted = pm != 0;
     if constexpr (!IVF) {
         if (pm) {
-            pass = pass && before_kth(s, a, q, d, key);
-            pm = ballot64(pass);
+            if (ballot64(pass && d == thr)) {
+                pass = pass && before_kth(s, a, q, d, key);
+                pm = ballot64(pass);
+            }
         }
     }
     while (pm) {
@@ -1694,10 +1697,13 @@ adc_kernel(ScanArgs a)
                             for (int ww = 0; ww < WPC; ++ww) acc += (uint32_t)__popc(w[c * WPC + ww] ^ qw[q][ww]);
                             pass[i] = pass[i] && (int32_t)acc >= 0;
                         }
-                        pass[i] = pass[i] && before_kth(s, a, g * 4 + i, d[i], rel);
-                        const uint64_t mine = ballot64(pass[i]);
+                        uint64_t mine = ballot64(pass[i]);
                         if (mine) {
                             ask.wanted = true;
+                            if (ballot64(pass[i] && d[i] == bcast_f(thr_v, g * 4 + i)))
+                                mine = ballot64(pass[i] && before_kth(s, a, g * 4 + i, d[i], rel));
+                        }
+                        if (mine) {
                             insert_candidates<M, TQ, SHARE, SHARE>(s, a, g * 4 + i, mine, d[i], rel);
                         }
                     }
@@ -1725,8 +1731,10 @@ adc_kernel(ScanArgs a)
 // 74 us in scan_mfma_kernel for 6 us of filtering), besides 8 to 16 tables to stage per workgroup.
 // Here the survivors' (distance, id) keys are appended to a pool in LDS as they come; only when it
 // is full, and once at the end, are the k smallest selected, by a radix search over the bits in
-// which the keys differ (keys are distinct, ids being so).  One slice per query needs no merge; no
-// launch has to set anything up before it.
+// which the keys differ (keys are distinct, ids being so).  One slice per query needs no merge and nothing set
+// up; the slices of a query (`arrived`: a word per query, kPresetWord before) are put together by the one of its
+// workgroups that ends last: 1 query x 100k codes 31 -> 27 us, 100 x 100k 49 -> 42 (with the tables' arg-min
+// taken where the tables are built), 64 x 1M, k = 100 109 -> 72, where the merge was a launch of its own.
 // A wave whose keys find no place waits in `meet`; every wave comes there sooner or later, full
 // pool or no codes left, and the selection makes room and lowers the bound.
 // DENSE: every code is scored and the Hamming test is taken on those below the bound (pure ADC and
@@ -1750,7 +1758,8 @@ struct SmallLds {
 
 template <int M, bool DENSE>
 __global__ void __launch_bounds__(1024)
-scan_pool_kernel(ScanArgs a, float open, int *status, int64_t *__restrict__ ids, float *__restrict__ dists)
+scan_pool_kernel(ScanArgs a, float open, int *status, uint32_t *arrived, int64_t *__restrict__ ids,
+                 float *__restrict__ dists)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     PSC_LDS SmallLds<M> &s = *(PSC_LDS SmallLds<M> *)smem;
@@ -2013,16 +2022,59 @@ scan_pool_kernel(ScanArgs a, float open, int *status, int64_t *__restrict__ ids,
         n = k;
     }
     __syncthreads();
+    if (arrived != nullptr) {
+        // several slices, put together by the workgroup of the query that comes last: each leaves its keys where
+        // every XCD sees them, counts itself, and all but the last are done
+        const int total = a.nslice * k;  // (<= kSmallPool, the launcher sees to it)
+        float *pd = a.part_d + q * total;
+        int64_t *pi = a.part_i + q * total;
+        if (tid < k) {
+            const uint64_t key = tid < n ? s.pool[tid] : 0ull;
+            __hip_atomic_store(pd + slice * k + tid, tid < n ? entry_dist(key) : 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(pi + slice * k + tid, tid < n ? begin + (int64_t)entry_id(key) : (int64_t)-1, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        }
+        // (Agent-scope stores write through to where agent-scope loads read, whatever the XCD, so having waited
+        //  for them is all the order there is to keep.  A release fence would write back the whole L2, from
+        //  each of the 16 waves: 100 queries x 100k codes 82 us.)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) {
+            s.stuck = __hip_atomic_fetch_add(arrived + q, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s.count = 0u;
+        }
+        __syncthreads();
+        if (s.stuck != kPresetWord + (uint32_t)a.nslice - 1u) return;
+        asm volatile("" ::: "memory");
+        for (int e0 = 0; e0 < total; e0 += 1024) {
+            const int e = e0 + tid;
+            const int64_t id = e < total ? __hip_atomic_load(pi + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (int64_t)-1;
+            const float d = e < total ? __hip_atomic_load(pd + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
+            const uint64_t m = ballot64(id >= 0);
+            uint32_t base = 0u;
+            if (lane == 0 && m) base = __hip_atomic_fetch_add(&s.count, (uint32_t)__builtin_popcountll(m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+            if (id >= 0) s.pool[base + prefix_count(m)] = pack_entry(d, (uint32_t)id);
+        }
+        __syncthreads();
+        n = (int)s.count;
+        if (n > k) {
+            select(n);
+            n = k;
+        }
+        __syncthreads();
+    }
     // every key to its rank among the n <= k <= 1024 kept
-    const int64_t o = (a.nslice == 1 ? q : q * a.nslice + slice) * k;
-    float *od = a.nslice == 1 ? dists : a.part_d;
-    int64_t *oi = a.nslice == 1 ? ids : a.part_i;
+    const bool final = arrived != nullptr || a.nslice == 1;
+    const int64_t o = (final ? q : q * a.nslice + slice) * k, first = arrived != nullptr ? 0 : begin;
+    float *od = final ? dists : a.part_d;
+    int64_t *oi = final ? ids : a.part_i;
     if (tid < n) {
         const uint64_t key = s.pool[tid];
         int rank = 0;
         for (int j = 0; j < n; ++j) rank += s.pool[j] < key ? 1 : 0;
         od[o + rank] = entry_dist(key);
-        oi[o + rank] = begin + (int64_t)entry_id(key);
+        oi[o + rank] = first + (int64_t)entry_id(key);
     } else if (tid < k) {
         od[o + tid] = __builtin_inff();
         oi[o + tid] = (int64_t)-1;
@@ -2527,7 +2579,7 @@ int run_adc(const ScanArgs &a, int64_t ntiles, size_t lds, hipStream_t s)
 }
 
 template <int M, bool DENSE>
-int run_scan_pool(const ScanArgs &a, float open, int *status, int64_t *ids, float *dists, hipStream_t s)
+int run_scan_pool(const ScanArgs &a, float open, int *status, uint32_t *arrived, int64_t *ids, float *dists, hipStream_t s)
 {
     static std::atomic<bool> configured{false};
     if (!configured.load(std::memory_order_acquire)) {
@@ -2536,7 +2588,7 @@ int run_scan_pool(const ScanArgs &a, float open, int *status, int64_t *ids, floa
         configured.store(true, std::memory_order_release);
     }
     hipLaunchKernelGGL((scan_pool_kernel<M, DENSE>), dim3((unsigned)(a.nq * a.nslice)), dim3(1024), sizeof(SmallLds<M>), s, a,
-                       open, status, ids, dists);
+                       open, status, arrived, ids, dists);
     PSC_HIP_TRY(hipGetLastError());
     return PSC_OK;
 }
@@ -2800,7 +2852,8 @@ static void set_exchange(ScanArgs &a, int slots, int k)
 // Whether a flat scan takes scan_pool_kernel, and in how many slices per query (0: it does not): two
 // estimates in microseconds, from what each kernel does.
 //  * pool: 256 workgroups run at a time; each takes its start, its selections, its codes and its survivors,
-//    all together no less than memory gives (every query reads the codes for itself); several slices a merge.
+//    all together no less than memory gives (every query reads the codes for itself); several slices a merge
+//    (5 us in the query's last workgroup, 10 and more in a launch of its own).
 //  * tiled: a round of workgroups takes a tile's set-up, its pairs and surviving pairs, and about k (1 +
 //    ln(survivors / k)) insertions into each list, one after the other; then the merge.
 // The survivors are those of random codes and a share for one's own cluster (1 % of all codes at ht =
@@ -2816,6 +2869,7 @@ struct ScanCosts {
     // insertion, the merge per result
     double launch, tile, pair, pair_mfma, surviving_pair, insertion, merge_k;
 };
+static bool pool_merges_itself(int64_t slices, int64_t n, int k) { return slices * k <= kSmallPool && n < ((int64_t)1 << 31); }
 static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool dense, bool mfma, const ScanPlan &p,
                             size_t ws_bytes)
 {
@@ -2839,7 +2893,7 @@ static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool de
     for (int64_t sN = 1; sN <= 256 && (sN == 1 || (sN * nq <= 256 && sN * 8192 <= n)); sN *= 2) {
         if ((n + sN - 1) / sN > (1 << 24)) continue;
         const double t = std::max((double)((nq * sN + 255) / 256) * (10.0 + 1e-3 * kilo * (double)n / (double)sN), memory) +
-                         (sN > 1 ? 10.0 + 1e-3 * (double)(sN * k) : 0.0);
+                         (sN > 1 ? (pool_merges_itself(sN, n, k) && nq <= kPresetQueries ? 5.0 : 10.0) + 1e-3 * (double)(sN * k) : 0.0);
         if (t < best) {
             best = t;
             slices = sN;
@@ -2849,7 +2903,7 @@ static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool de
     const double codes = (double)n / (double)slices;
     const double group = c.group + c.select * std::min(1.0, keep * codes / k) + 0.01 * c.kept * std::min(keep * codes, (double)k) +
                          1e-3 * codes * (c.code + c.survivor * keep);
-    const double pool_merge = merge_selects(nq, (int)slices, k) ? 17.0 + 2.1e-3 * (double)(slices * k) : 10.0 + 0.31 * k;
+    const double pool_merge = pool_merges_itself(slices, n, k) && nq <= kPresetQueries ? 5.0 + 1e-3 * (double)(slices * k) : merge_selects(nq, (int)slices, k) ? 17.0 + 2.1e-3 * (double)(slices * k) : 10.0 + 0.31 * k;
     const double pool = 10.5 + std::max((double)((nq * slices + 255) / 256) * group, memory) + (slices > 1 ? pool_merge : 0.0);
     auto tile_time = [&](double len) {
         const double survivors = keep * len, insertions = std::min(survivors, k * (1.0 + std::log(std::max(1.0, survivors / k))));
@@ -2867,7 +2921,7 @@ static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool de
 
 int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t nq,
                 const uint8_t *codes_dev, int64_t n, int ht, int k, int64_t skip_first,
-                bool clear_status, int64_t *ids_dev, float *dists_dev, void *ws, size_t ws_bytes,
+                bool clear_status, bool preset, int64_t *ids_dev, float *dists_dev, void *ws, size_t ws_bytes,
                 hipStream_t s)
 {
     PSC_REQUIRE(ht >= 0, "ht must be >= 0, got %d", ht);
@@ -2949,21 +3003,33 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
         a.nslice = pool_slices;
         a.slice_len = ((n + pool_slices - 1) / pool_slices + 63) / 64 * 64;
         a.nslice = (int)((n + a.slice_len - 1) / a.slice_len);  // (no empty slice)
-        a.part_d = (float *)((char *)ws + 256);
-        a.part_i = (int64_t *)((char *)a.part_d + ((size_t)nq * a.nslice * k * sizeof(float) + 255) / 256 * 256);
+        // the slices' keys are put together by the query's last workgroup where they fit its pool (and the
+        // words it is told by fit the workspace beside them), by a merge launch otherwise
+        const size_t dist_bytes = ((size_t)nq * a.nslice * k * sizeof(float) + 255) / 256 * 256;
+        const size_t key_bytes = dist_bytes + (size_t)nq * a.nslice * k * sizeof(int64_t);
+        const size_t words = ((size_t)nq * sizeof(uint32_t) + 255) / 256 * 256;
+        const bool self_merge = a.nslice > 1 && nq <= kPresetQueries && pool_merges_itself(a.nslice, n, k) &&
+                                256 + words + key_bytes <= ws_bytes;
+        uint32_t *arrived = self_merge ? a.gthr : nullptr;
+        a.part_d = (float *)((char *)ws + 256 + (self_merge ? words : 0));
+        a.part_i = (int64_t *)((char *)a.part_d + dist_bytes);
+        if (self_merge && !preset) {
+            hipLaunchKernelGGL(init_scan_kernel, dim3((unsigned)((nq + 255) / 256)), dim3(256), 0, s, arrived, nq, (int *)nullptr);
+            PSC_HIP_TRY(hipGetLastError());
+        }
         int *status = clear_status ? a.status : nullptr;
         // (codes at distance +infinity are listed where the merge of the tiled kernels' lists would list them)
         const bool infinite = !merge_selects(nq, p.nslice, k);
         const float open = infinite ? HUGE_VALF : FLT_MAX;
         if (m == 8)
-            rc = dense ? run_scan_pool<8, true>(a, open, status, ids_dev, dists_dev, s)
-                       : run_scan_pool<8, false>(a, open, status, ids_dev, dists_dev, s);
+            rc = dense ? run_scan_pool<8, true>(a, open, status, arrived, ids_dev, dists_dev, s)
+                       : run_scan_pool<8, false>(a, open, status, arrived, ids_dev, dists_dev, s);
         else
-            rc = dense ? run_scan_pool<16, true>(a, open, status, ids_dev, dists_dev, s)
-                       : run_scan_pool<16, false>(a, open, status, ids_dev, dists_dev, s);
+            rc = dense ? run_scan_pool<16, true>(a, open, status, arrived, ids_dev, dists_dev, s)
+                       : run_scan_pool<16, false>(a, open, status, arrived, ids_dev, dists_dev, s);
         if (rc != PSC_OK) return rc;
         note_route(dense ? "scan_pool_kernel+all" : "scan_pool_kernel", m, 1, 16, a.nslice, nq * a.nslice);
-        if (a.nslice == 1) return PSC_OK;
+        if (a.nslice == 1 || self_merge) return PSC_OK;
         return launch_merge(a.part_d, a.part_i, nq, a.nslice, k, infinite, a.status, ids_dev, dists_dev, s);
     }
     const int64_t nwords = nq * p.pub_slots;

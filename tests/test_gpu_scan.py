@@ -572,3 +572,18 @@ def test_thousands_of_codes_at_the_kth_distance(psc, force_route, route, m, n, n
         _took(psc, route, m, nq, ht, k)
         ref = O.scan(lut.astype(np.float64), qcodes, codes, ht, k)
         assert np.array_equal(got_ids, ref["ids"]) and np.array_equal(got_d, ref["dists"]), (m, n, nq, k, ht)
+
+
+@pytest.mark.parametrize("nq", [1, 3, 64, 128, 129])
+@pytest.mark.parametrize("m,n,ht", [(8, 200_003, 24), (16, 100_001, 64), (8, 65_536, 64)])
+def test_slices_put_together_by_the_last_workgroup(psc, m, n, nq, ht):
+    """Small scans of a few queries are cut into slices whose keys the query's last workgroup selects from, or a
+    merge launch where they do not fit its pool (8 slices of 513 or more): the same workspace call after call."""
+    codes, qcodes, lut = _rand_problem(m, n, nq, seed=41 + nq, lut_kind="int")
+    ws = torch.full((psc.scan_workspace_bytes(m, nq, n, 1024),), 0xa5, dtype=torch.uint8, device="cuda")
+    args = _dev(lut), _dev(qcodes), _dev(codes)
+    for k in (1, 10, 512, 513, 1024, 10):
+        ids, d = psc.scan(*args, ht, k, workspace=ws)
+        torch.cuda.synchronize()
+        ref = O.scan(lut.astype(np.float64), qcodes, codes, ht, k)
+        assert np.array_equal(ids.cpu().numpy(), ref["ids"]) and np.array_equal(d.cpu().numpy(), ref["dists"]), k
