@@ -344,7 +344,8 @@ __device__ __forceinline__ uint64_t lane_value_u64(uint64_t v, int l)
 // it loses by its id nearly always (ids rise during a scan); clustered vectors share codes by the thousand, and
 // each such tie took the list's lock to be turned away.  Asked only when a batch has a tie.
 // 10M x 10k at ht = 24, k = 100 24.6 -> 14.0 ms (of seeds with many codes at the k-th distance), 1M x 777 pure
-// ADC 829 -> 744 us, 1M x 1M graph at ht = 20 80.4 -> 77.4 ms.  Inverted lists do without: 4.43 / 4.48 ms.
+// ADC 829 -> 744 us, 1M x 1M graph at ht = 20 80.4 -> 77.4 ms.  The fused scans of inverted lists and of 128-bit codes, where
+// few distances tie, do without: 4.43 / 4.48 ms with it, 10M x 10k 25.56 / 25.68.
 template <int M, int TQ>
 __device__ __forceinline__ bool before_kth(const Lds<M, TQ> &s, const ScanArgs &a, int q, float d, uint32_t id)
 {
@@ -718,7 +719,7 @@ __device__ __forceinline__ void score_batch(const Lds<M, TQ> &s, const ScanArgs 
     }
     uint64_t pm = ballot64(pass);
     ask.wanted = pm != 0;
-    if constexpr (!IVF) {
+    if constexpr (!IVF && M == 8) {
         if (pm) {
             if (ballot64(pass && d == thr)) {
                 pass = pass && before_kth(s, a, q, d, key);

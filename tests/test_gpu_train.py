@@ -237,3 +237,23 @@ def test_coarse_refill_and_argument_errors(psc):
         psc.Index(128, 8).train_pq_device(_dev(np.zeros((100, 128), np.float32)), iters=1)  # fewer than 256 rows
     with pytest.raises(psc.PscError):
         psc.Index(128, 8).train_pq_device(_dev(np.zeros((300, 128), np.float32)), iters=1, from_current=True)
+
+
+@pytest.mark.parametrize("dim,m,n,distinct", [(16, 8, 300, 40), (64, 16, 2_001, 200), (96, 8, 5_000, 290), (128, 8, 20_011, 400),
+                                              (256, 8, 3_000, 260), (8, 8, 1_000, 6)])
+def test_pq_iterations_enqueued_together_stop_at_an_empty_cell(psc, dim, m, n, distinct):
+    """Whole numbers, few distinct rows: cells come out empty in some iterations and are refilled.  Six iterations
+    of one call (enqueued together, taken up again after a refill) are six calls of one iteration each."""
+    rng = np.random.default_rng(dim)
+    pts = rng.integers(0, 8, size=(distinct, dim)).astype(np.float32)
+    xd = _dev(pts[rng.integers(0, distinct, size=n)])
+    cb = np.stack([rng.integers(0, 8, size=(256, dim // m)) for _ in range(m)]).astype(np.float32)
+    one, many = psc.Index(dim, m), psc.Index(dim, m)
+    one.set_codebook(cb)
+    many.set_codebook(cb)
+    obj = many.train_pq_device(xd, iters=6, from_current=True)
+    for it in range(6):
+        got = one.train_pq_device(xd, iters=1, from_current=True)
+        assert np.allclose(got[0], obj[it], rtol=1e-6, atol=1e-9), it
+    # (a mean of whole numbers is rounded once; rows at equal distances are told apart by the centroid's number)
+    assert np.array_equal(one.get_codebook(), many.get_codebook())
