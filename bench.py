@@ -335,7 +335,7 @@ def bench_tiny(args):
     res = dict(workload="tiny", n_db=cfg.n_db, n_query=cfg.n_query, code_bits=64, ht=ht, k=k, ms_per_step=wall_ms,
                pairs_per_s=pairs / (wall_ms * 1e-3),
                roofline=alu_roofline(cfg.m, pairs, call_ms, route,
-                                     note="1e7 pairs: the call is four launches of a few microseconds each, "
+                                     note="1e7 pairs: the call is two launches, tables and scan, "
                                           "launch-bound; kernel_ms is the whole psc_search call"))
     if not args.no_cpu:
         import oracle as O
