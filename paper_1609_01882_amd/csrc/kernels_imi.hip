@@ -228,9 +228,9 @@ struct ImiScanArgs {
 // element of the residual, its entry of each table row, its code of the first step).
 // Bound by instructions.  A lane builds four entries in a row of each of its wave's table rows: the query's share
 // stays in its registers, everything else is one 16-byte access, the row's minimum is one of numbers with the
-// place found by comparison, and a cell's codes are counted in 32 bits from a scalar base.  10k queries x 16
-// cells of 10M vectors, the whole call 1012 -> 874 us (with the query's share in LDS, single entries 64 apart,
-// (key, place) minima and 64-bit positions before).
+// place found by comparison, and a cell's codes are read at a scalar place of 64 bits and counted down in 32 (a
+// cell may hold more).  10k queries x 16 cells of 10M vectors, the whole call 1012 -> 877 us (with the query's share
+// in LDS, single entries 64 apart, (key, place) minima and 64-bit positions in every lane before).
 template <int M, bool DIRECT>
 __global__ void __launch_bounds__(256)
 imi_scan_kernel(ImiScanArgs a)
@@ -274,17 +274,20 @@ imi_scan_kernel(ImiScanArgs a)
         uint32_t cw[WPC];   // its code of the cell's first 256
         int32_t id;         // and that code's id
     };
-    // (a cell's place is the same in every lane and its codes are counted in 32 bits: ids are)
+    // (a cell's bounds are the same in every lane)
     auto uniform64 = [](long long v) {
         return (long long)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)((uint64_t)v >> 32)) << 32) |
                            (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v));
     };
-    auto load_code = [&](long long first, int i, uint32_t (&w)[WPC], int32_t &id) {
-        const uint32_t *src = (const uint32_t *)(a.codes + first * M) + (uint32_t)i * WPC;
+    // the thread's of the 256 codes from place `first` on
+    auto load_code = [&](long long first, uint32_t (&w)[WPC], int32_t &id) {
+        const uint32_t *src = (const uint32_t *)(a.codes + first * M) + tid * WPC;
 #pragma unroll
         for (int ww = 0; ww < WPC; ++ww) w[ww] = src[ww];
-        id = (a.ext_ids + first)[(uint32_t)i];
+        id = (a.ext_ids + first)[tid];
     };
+    // codes left of a cell, in 32 bits: 2^30 stands for more
+    auto piece = [](long long left) { return ((uint64_t)left >> 30) != 0 ? 1 << 30 : (int)left; };
     auto fetch = [&](int w, Inputs &in) {  // w: place in the window
         const int cell = __builtin_amdgcn_readfirstlane(win_cell[w]);
         in.g = 0.f;
@@ -306,7 +309,7 @@ imi_scan_kernel(ImiScanArgs a)
             }
         }
         const long long first = uniform64(win_begin[w]);
-        if (tid < (int)(uniform64(win_end[w]) - first)) load_code(first, tid, in.cw, in.id);
+        if (tid < piece(uniform64(win_end[w]) - first)) load_code(first, in.cw, in.id);
     };
 
     for (int base = 0; base < mine; base += kWindow) {
@@ -329,8 +332,8 @@ imi_scan_kernel(ImiScanArgs a)
         fetch(0, cur);
         for (int w = 0; w < nwin; ++w) {
             const int p = sub + (base + w) * a.split;  // the cell's place in the query's order
-            const long long begin = uniform64(win_begin[w]);
-            const int len = (int)(uniform64(win_end[w]) - begin);
+            long long begin = uniform64(win_begin[w]);
+            int len = piece(uniform64(win_end[w]) - begin);
             if (w + 1 < nwin) fetch(w + 1, nxt);
             if (!(len == 0 && !a.qcodes_out)) {  // (uniform over the workgroup)
                 // ---- residual to the cell centroid (one element per thread, held since the cell before;
@@ -391,14 +394,15 @@ imi_scan_kernel(ImiScanArgs a)
 #pragma unroll
                 for (int ww = 0; ww < WPC; ++ww) cw[ww] = cur.cw[ww];
                 int32_t id = cur.id;  // (asked for with the code: a survivor's id is not one more trip to memory)
-                for (int i0 = 0; i0 < len; i0 += 256) {
-                    const int i = i0 + tid;
+                for (; len > 0; len -= 256) {
+                    if (len == 1024) len = piece(uniform64(win_end[w]) - begin);  // (there may be more)
+                    begin += 256;
                     uint32_t nw[WPC];
                     int32_t nid = 0;
 #pragma unroll
                     for (int ww = 0; ww < WPC; ++ww) nw[ww] = 0u;
-                    if (i < len - 256) load_code(begin, i + 256, nw, nid);
-                    if (i < len) {
+                    if (tid < len - 256) load_code(begin, nw, nid);
+                    if (tid < len) {
                         int h = 0;
 #pragma unroll
                         for (int ww = 0; ww < WPC; ++ww) h += __builtin_popcount(cw[ww] ^ qw[ww]);

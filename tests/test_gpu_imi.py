@@ -249,3 +249,36 @@ def test_imi_distances_when_the_half_centroids_lie_far_apart(spread, sigma, dire
         assert (own["cells"] != cells).mean() < 0.02
     # which path ran (the rule's ratio is about 0.03 x spread for sigma = 10, its limit 16)
     assert psc.last_scan_route().split()[0] == ("imi_scan_kernel+direct-tables" if direct else "imi_scan_kernel")
+
+
+@pytest.mark.parametrize("m,n", [(16, (1 << 30) + 777), (8, (1 << 31) + 777)])
+def test_imi_cell_of_a_billion_codes(m, n):
+    """One cell of more than 2^30 codes of four words, or of more than 2^31 codes: places and word offsets go past
+    32 bits.  Every code but a few is the complement of the query's bit string; the few stand on both sides of
+    where a 32-bit offset or length would wrap, and no id but theirs can come back."""
+    import paper_1609_01882_amd as psc
+    dim = 2 * m
+    rng = np.random.default_rng(m)
+    cb = rng.integers(-50, 50, size=(m, 256, 2)).astype(np.float32)
+    cb[:, 1:] += 200.0  # (centroid 0 far from the others: the query below is its own nearest)
+    idx = psc.Index(dim, m)
+    idx.set_codebook(cb)
+    idx.imi_set_coarse(np.zeros((1, dim // 2), np.float32), np.zeros((1, dim // 2), np.float32))
+    places = [5, 300, (1 << 30) - 1, (1 << 30) + 5, (1 << 30) + 700]
+    if n > 1 << 31:
+        places += [(1 << 31) - 1, (1 << 31) + 5, (1 << 31) + 300]
+    places += [n - 1]
+    codes = torch.full((n, m), 0xff, dtype=torch.uint8, device="cuda")
+    ids = torch.zeros(n, dtype=torch.int32, device="cuda")
+    for r, i in enumerate(places):
+        codes[i] = 0
+        codes[i, r % m] = 1 << (r // m)  # (a distance of its own)
+        ids[i] = 1000 + r
+    want = np.array([((cb[:, 0] - cb[np.arange(m), codes[i].cpu().numpy()]) ** 2).sum() for i in places], np.float64)
+    idx.imi_set_lists(torch.tensor([0, n], dtype=torch.int64, device="cuda"), codes, ids)
+    got, d = idx.imi_search(_dev(cb[:, 0].reshape(1, dim)), 1, 0, 1, len(places) + 3)
+    torch.cuda.synchronize()
+    got, d = got.cpu().numpy()[0], d.cpu().numpy()[0]
+    order = np.lexsort((np.arange(len(places)), want))
+    assert got[:len(places)].tolist() == (1000 + order).tolist() and got[len(places):].tolist() == [-1] * 3
+    assert np.allclose(d[:len(places)], want[order], rtol=RTOL)
