@@ -375,12 +375,12 @@ imi_scan_kernel(ImiScanArgs a)
                     }
                     ((f32x4 *)(cellt + jj * 256))[lane] = v;
                     // the row's minimum, then its lowest place: the first lane that holds it, the first of its four
-                    // (not among numbers: whatever place 0 of the search gives)
+                    // (place 0 of a row without a number)
                     const float least = wave_min_f32(fminf(fminf(v[0], v[1]), fminf(v[2], v[3])));
                     const int in4 = v[0] == least ? 0 : v[1] == least ? 1 : v[2] == least ? 2 : 3;
                     const uint64_t holds = __ballot(v[0] == least || v[1] == least || v[2] == least || v[3] == least);
-                    const int first = holds != 0 ? __builtin_ctzll(holds) : 0;
-                    const int imin = 4 * first + __builtin_amdgcn_readlane(in4, first);
+                    const int first = __builtin_ctzll(holds | (1ull << 63));
+                    const int imin = holds != 0 ? 4 * first + __builtin_amdgcn_readlane(in4, first) : 0;
                     if (lane == 0) ((volatile uint8_t *)qcw)[jj] = (uint8_t)imin;
                 }
                 __syncthreads();

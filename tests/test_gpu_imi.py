@@ -282,3 +282,30 @@ def test_imi_cell_of_a_billion_codes(m, n):
     order = np.lexsort((np.arange(len(places)), want))
     assert got[:len(places)].tolist() == (1000 + order).tolist() and got[len(places):].tolist() == [-1] * 3
     assert np.allclose(d[:len(places)], want[order], rtol=RTOL)
+
+
+@pytest.mark.parametrize("m", [8, 16])
+def test_imi_query_that_is_not_a_number(m):
+    """Table rows without a number have place 0 as their minimum, and distances that are not numbers come last, by
+    id: a query with such coordinates is answered by the codes within the threshold, in the order of their ids."""
+    import paper_1609_01882_amd as psc
+    s = build_imi(psc, 5_000, 4, 3, seed=86, m=m)
+    idx, ht, k, dsub = s["idx"], 3 * m, 40, 128 // m
+    xq = W.sift_like(6, seed=86, stream=3)
+    xq[1, 0] = np.nan
+    xq[2, 127] = np.nan
+    xq[3, 3 * dsub:5 * dsub] = np.nan
+    xq[4] = np.nan
+    ids, d, cells, qcodes = idx.imi_search(_dev(xq), 12, 0, ht, k, want_debug=True)
+    torch.cuda.synchronize()
+    ids, d, cells, qcodes = (t.cpu().numpy() for t in (ids, d, cells, qcodes))
+    for q in range(1, 5):
+        rows = np.flatnonzero(np.isnan(xq[q].reshape(m, dsub)).any(axis=1))
+        assert sorted(cells[q].tolist()) == list(range(12)) and np.all(qcodes[q][:, rows] == 0), (q, qcodes[q][:, rows])
+        keep = []
+        for p, c in enumerate(cells[q]):
+            lo, hi = s["offsets"][c], s["offsets"][c + 1]
+            h = np.unpackbits(s["lcodes"][lo:hi] ^ qcodes[q, p], axis=1).sum(axis=1)
+            keep += s["lids"][lo:hi][h <= ht].tolist()
+        keep = sorted(keep)[:k]
+        assert ids[q].tolist() == keep + [-1] * (k - len(keep)) and np.all(np.isnan(d[q, :len(keep)])), q
