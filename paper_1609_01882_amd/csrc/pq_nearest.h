@@ -14,10 +14,14 @@
 // sums stay below twice the sum of the two squared lengths) and 2^-18 for the 4 mantissa bits that carry
 // the place within a tile, all relative to || x' ||^2 + || c' ||^2: below kUnit, with 2^-16 to spare for the
 // rounding of the float32 distances.  By the smallest value v1, the nearest centroid is no longer than
-// || x' || + d1, d1^2 <= (1 + 3 u) (|| x' ||^2 + v1 + 3 u || x' ||^2), so its value lies within
-//     2 u (|| x' ||^2 + min(max || c' ||^2, (|| x' || + d1)^2))
-// of v1.  A row with one centroid there has its answer; with one in each half of its two lanes the two are
-// compared; otherwise (and where squares come near the ends of float32's range) the row's 256 distances are taken,
+// || x' || + d1, d1^2 <= (1 + 3 u) (|| x' ||^2 + v1 + 3 u || x' ||^2) + kLost, so its value lies within
+//     2 u (|| x' ||^2 + min(max || c' ||^2, (|| x' || + d1)^2)) + kLost
+// of v1.  kLost = 2^-116 is what numbers below 2^-126 lose, which no relative bound covers (centroids within 1e-18
+// of mu, another one far out): in a value at most 2^-126 for each of the 3 parts of its norm, 6 DSUB of its products
+// (times the other factor: below 1, or the relative bound is larger by far), 3 DSUB + 3 products, 16 kSteps
+// additions and DSUB terms of || x' ||^2, 438 in all for DSUB = 32, and that twice.
+// A row with one centroid there has its answer; with one in each half of its two lanes the two are compared;
+// otherwise (and where squares come near the end of float32's range) the row's 256 distances are taken,
 // by the whole wave for it, or by every row's own lanes if the wave has many such rows.  A wave that met many
 // takes all distances of its further rows without searching first (`all_distances`, a row to each of its 64
 // lanes), so that no data takes much longer than that does: 400k rows, 8 sub-vectors of 16, against taking all
@@ -39,6 +43,7 @@ struct PqNearest {
     static constexpr int kManyRows = 10;  // rows of a wave from which every row's own lanes take all distances
     static constexpr float kUnit = DSUB <= 32 ? 6.103515625e-5f + 3.814697265625e-6f   // 2^-14 + 2^-18
                                               : 1.220703125e-4f + 3.814697265625e-6f;  // 2^-13 + 2^-18
+    static constexpr float kLost = 0x1p-116f;
     struct Shared {
         pq_bf16x8 image[kTiles * kSteps * 64];  // operands in the order of the products
         float mu[DSUB];
@@ -225,10 +230,10 @@ struct PqNearest {
         const int mine = at * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
         const float least = fminf(best, __shfl_xor(best, 32, 64));
         const float cmax2 = __uint_as_float(s.cmax2);
-        const float d2 = (fmaxf(least + x2, 0.f) + 3.f * kUnit * x2) * (1.f + 3.f * kUnit);
+        const float d2 = (fmaxf(least + x2, 0.f) + 3.f * kUnit * x2) * (1.f + 3.f * kUnit) + kLost;
         const float len = __builtin_amdgcn_sqrtf(x2) + __builtin_amdgcn_sqrtf(d2);
-        const float reach = least + 2.f * kUnit * (x2 + fminf(cmax2, 1.001f * len * len));
-        const bool finite = x2 + cmax2 < 1e37f && cmax2 > 1e-30f;  // (no if either is not a number)
+        const float reach = least + (2.f * kUnit * (x2 + fminf(cmax2, 1.001f * len * len)) + kLost);
+        const bool finite = x2 + cmax2 < 1e37f;  // (no if either is not a number)
         const int near = best <= reach ? 1 : 0, deep = !finite || next <= reach ? 2 : 0;
         const int other = __shfl_xor(near | deep, 32, 64), theirs = __shfl_xor(mine, 32, 64);
         int winner = near ? mine : theirs;

@@ -100,12 +100,13 @@ def test_encode_of_many_rows_equals_encode_of_few(m, dsub):
         assert abs(da - db) <= RTOL * db
 
 
-@pytest.mark.parametrize("data", ["twins", "one", "far", "tiny", "huge", "wide", "grid"])
+@pytest.mark.parametrize("data", ["twins", "one", "far", "tiny", "huge", "wide", "grid", "far and tiny"])
 @pytest.mark.parametrize("m,dsub", [(16, 1), (8, 2), (16, 4), (8, 6), (16, 8), (8, 12), (8, 16), (16, 24), (8, 32)])
 def test_encode_where_centroids_are_close(m, dsub, data):
     """The search runs on bfloat16 parts, close calls are decided by the float32 distances: the codes are the
     first arg-min of those where nearly every row is a close call (every centroid twice, all centroids one, points
-    of a grid halfway between centroids), where one centroid is far out, at the ends of float32's range and
+    of a grid halfway between centroids), where one centroid is far out, at the ends of float32's range (in "far and tiny" with
+    two centroids far out, so that the squared lengths among the others are below what bfloat16 parts can hold) and
     with infinities and NaNs among the rows; from one row to several turns of every workgroup."""
     import paper_1609_01882_amd as psc
     dim, n = m * dsub, 40_000 // m + 8_193
@@ -122,6 +123,11 @@ def test_encode_where_centroids_are_close(m, dsub, data):
         cb, x = cb * np.float32(1e-21), x * np.float32(1e-21)
     elif data == "huge":
         cb, x = cb * np.float32(3e18), x * np.float32(3e18)
+    elif data == "far and tiny":
+        scale = 10.0 ** np.linspace(-22.0, -17.0, m)[:, None, None]
+        cb = (cb * scale).astype(np.float32)
+        cb[:, 0], cb[:, min(255, 256 // dsub)] = 1.0, -1.0  # (one after the other in one sum: the mean stays with the others)
+        x = (x.reshape(n, m, dsub) * scale[:, 0]).astype(np.float32).reshape(n, dim)
     elif data == "wide":
         x[::3] *= np.float32(1e15)
         x[1::97, 0] = np.inf
