@@ -191,6 +191,29 @@ def test_whole_search_matches_oracle(setup, force_route, route, m):
         assert np.allclose(gd[fin], ref2["dists"][same_codes][fin], rtol=RTOL)
 
 
+@pytest.mark.parametrize("m", [8, 16])
+def test_small_searches_on_a_workspace_of_earlier_ones(setup, m):
+    """The words by which a query's slices find out which ends last are set while the tables are built: searches of
+    changing sizes on one workspace, which holds the words, keys and tables of the calls before."""
+    psc, s = setup["psc"], setup[m]
+    idx, codes = s["idx"], W.random_codes(100_001, m, seed=m)
+    q = _dev(W.sift_like(129, seed=60 + m, stream=4))
+    lut, qc = idx.build_lut(q)
+    lut, qc, codes_d = lut.cpu().numpy().astype(np.float64), qc.cpu().numpy(), _dev(codes)
+    calls = ((1, 10), (128, 10), (129, 10), (3, 100), (128, 513), (1, 1024), (100, 10), (128, 1024), (1, 10), (2, 1))
+    need = max(idx.search_workspace_bytes(nq, len(codes), k) for nq, k in calls)
+    ws = torch.full((need,), 0xa5, dtype=torch.uint8, device="cuda")
+    sliced = 0
+    for nq, k in calls:
+        ids, d = idx.search(q[:nq], codes_d, 3 * m, k, workspace=ws)
+        torch.cuda.synchronize()
+        words = psc.last_scan_route().split()
+        sliced += words[0] == "scan_pool_kernel" and words[4] != "slices=1"
+        ref = O.scan(lut[:nq], qc[:nq], codes, 3 * m, k)
+        assert_topk_matches(ids.cpu().numpy(), d.cpu().numpy(), ref, lut[:nq], qc[:nq], codes, 3 * m, what=f"{nq} queries, k={k}")
+    assert sliced >= 5, sliced  # (the others take the tiles or one workgroup per query)
+
+
 def test_tiny_workload_as_configured():
     """The smallest named workload, whole: 10k training vectors, product quantizer with optimised
     index assignment (the paper's annealing constants), 100 000 database vectors, 100 queries,
