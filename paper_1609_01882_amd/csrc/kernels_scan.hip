@@ -1743,6 +1743,7 @@ adc_kernel(ScanArgs a)
 // `open`: the largest distance that is listed while there are fewer than k.
 // ---------------------------------------------------------------------------------------------
 constexpr int kSmallPool = 4096;   // keys
+constexpr int kRankedKeys = 512;   // of that many every key's rank is taken sooner than a search among them ends
 constexpr int kSmallCodes = 8;     // codes per lane and turn
 constexpr int kSmallQueue = 128;   // (mask, position) entries per wave: fewer than 64 wait, 64 come at a time
 
@@ -2061,13 +2062,13 @@ scan_pool_kernel(ScanArgs a, float open, int *status, uint32_t *arrived, int64_t
         }
         __syncthreads();
         n = (int)s.count;
-        if (n > k) {
+        if (n > kRankedKeys && n > k) {  // (otherwise the ranks below decide)
             select(n);
             n = k;
         }
         __syncthreads();
     }
-    // every key to its rank among the n <= k <= 1024 kept
+    // every key to its rank among the n kept (at most 1024: a key per thread)
     const bool final = arrived != nullptr || a.nslice == 1;
     const int64_t o = (final ? q : q * a.nslice + slice) * k, first = arrived != nullptr ? 0 : begin;
     float *od = final ? dists : a.part_d;
@@ -2076,8 +2077,10 @@ scan_pool_kernel(ScanArgs a, float open, int *status, uint32_t *arrived, int64_t
         const uint64_t key = s.pool[tid];
         int rank = 0;
         for (int j = 0; j < n; ++j) rank += s.pool[j] < key ? 1 : 0;
-        od[o + rank] = entry_dist(key);
-        oi[o + rank] = first + (int64_t)entry_id(key);
+        if (rank < k) {
+            od[o + rank] = entry_dist(key);
+            oi[o + rank] = first + (int64_t)entry_id(key);
+        }
     } else if (tid < k) {
         od[o + tid] = __builtin_inff();
         oi[o + tid] = (int64_t)-1;
@@ -2856,15 +2859,16 @@ static void set_exchange(ScanArgs &a, int slots, int k)
 // estimates in microseconds, from what each kernel does.
 //  * pool: 256 workgroups run at a time; each takes its start, its selections, its codes and its survivors,
 //    all together no less than memory gives (every query reads the codes for itself); several slices a merge
-//    (5 us in the query's last workgroup, 10 and more in a launch of its own).
+//    (pool_merge_cost).
 //  * tiled: a round of workgroups takes a tile's set-up, its pairs and surviving pairs, and about k (1 +
 //    ln(survivors / k)) insertions into each list, one after the other; then the merge.
 // The survivors are those of random codes and a share for one's own cluster (1 % of all codes at ht =
-// 3 m, falling with the threshold).  Coefficients fitted to, and the rule checked on, 5634 random calls (3k ..
-// 10M codes, random and clustered, x 1 .. 4000 queries, k = 1 .. 1000, thresholds 0 .. 8 m): the time is
-// 0.350 of the tiled kernels' in geometric mean (0.345 if the faster were always taken); the pool is taken
-// and more than 5 % slower in 48 calls, not taken and more than 5 % faster in 266.  E.g. (pool / tiled, us):
-// 100 queries x 100k, k = 10 31 / 86; 1000 x 100k, k = 100 128 / 564; 63 x 1.2M, ht = 0, k = 1000 233 / 48.
+// 3 m, falling with the threshold).  Coefficients fitted to 5634 random calls (3k .. 10M codes, random and
+// clustered, x 1 .. 4000 queries, k = 1 .. 1000, thresholds 0 .. 8 m) before the last workgroup merged.  The rule as it
+// is, on 3000 other calls (x 1 .. 1000 queries): 0.361 of the tiled kernels' time in geometric mean over 2000 calls of
+// psc_scan, 0.436 over 1000 of psc_search (0.360 and 0.436 if the faster were always taken); the pool is
+// taken and more than 5 % slower in 17 of 2396.  E.g. (pool / tiled, us): 500k x 83 queries, k = 1000 65 / 457; 165k
+// x 97, k = 100 29 / 123; 4M x 75, k = 100 287 / 218.
 struct ScanCosts {
     // pool: a workgroup, a selection, 100 keys kept, 1000 codes, 1000 survivors
     double group, select, kept, code, survivor;
@@ -2872,8 +2876,22 @@ struct ScanCosts {
     // insertion, the merge per result
     double launch, tile, pair, pair_mfma, surviving_pair, insertion, merge_k;
 };
-static bool pool_merges_itself(int64_t slices, int64_t n, int k) { return slices * k <= kSmallPool && n < ((int64_t)1 << 31); }
-static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool dense, bool mfma, const ScanPlan &p,
+// Several slices: whether the query's last workgroup puts them together, and what that takes in microseconds (a merge
+// launch: `launch`).  The last workgroup ranks up to kRankedKeys keys and searches among more; where the tables' kernel
+// has not set its word (preset), a launch that sets it comes first, and with few results out of many keys a merge
+// launch instead is the faster one (4M codes x 4 queries, k = 10, 64 slices 33.1 / 36.8 us; k = 100: 39.7 / 35.0).
+static bool pool_merges_itself(int64_t slices, int64_t n, int k, bool preset)
+{
+    return slices * k <= kSmallPool && n < ((int64_t)1 << 31) && (preset || k > 16 || slices * k <= 256);
+}
+static double pool_merge_cost(int64_t slices, int64_t n, int k, bool preset, double launch)
+{
+    const double keys = (double)(slices * k);
+    if (slices == 1) return 0.0;
+    if (!pool_merges_itself(slices, n, k, preset)) return launch;
+    return (preset ? 3.0 : 5.5) + (keys <= kRankedKeys ? 1.3e-5 * keys * keys : 6.0);
+}
+static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool dense, bool mfma, bool preset, const ScanPlan &p,
                             size_t ws_bytes)
 {
     // (a workgroup per query: past 4096 queries the tiles are ahead; past the caches every query reads
@@ -2896,7 +2914,7 @@ static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool de
     for (int64_t sN = 1; sN <= 256 && (sN == 1 || (sN * nq <= 256 && sN * 8192 <= n)); sN *= 2) {
         if ((n + sN - 1) / sN > (1 << 24)) continue;
         const double t = std::max((double)((nq * sN + 255) / 256) * (10.0 + 1e-3 * kilo * (double)n / (double)sN), memory) +
-                         (sN > 1 ? (pool_merges_itself(sN, n, k) && nq <= kPresetQueries ? 5.0 : 10.0) + 1e-3 * (double)(sN * k) : 0.0);
+                         pool_merge_cost(sN, n, k, preset, 10.0 + 1e-3 * (double)(sN * k));
         if (t < best) {
             best = t;
             slices = sN;
@@ -2906,8 +2924,11 @@ static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool de
     const double codes = (double)n / (double)slices;
     const double group = c.group + c.select * std::min(1.0, keep * codes / k) + 0.01 * c.kept * std::min(keep * codes, (double)k) +
                          1e-3 * codes * (c.code + c.survivor * keep);
-    const double pool_merge = pool_merges_itself(slices, n, k) && nq <= kPresetQueries ? 5.0 + 1e-3 * (double)(slices * k) : merge_selects(nq, (int)slices, k) ? 17.0 + 2.1e-3 * (double)(slices * k) : 10.0 + 0.31 * k;
-    const double pool = 10.5 + std::max((double)((nq * slices + 255) / 256) * group, memory) + (slices > 1 ? pool_merge : 0.0);
+    // (where the queries read more than 1.2 GB in all the estimate is low by about what a merge of their own saves:
+    //  58 queries x 1.5M codes of 128 bits 155 / 125 us in tiles, 44 x 4.4M of 64 bits 168 / 133)
+    const double launch_merge = merge_selects(nq, (int)slices, k) ? 17.0 + 2.1e-3 * (double)(slices * k) : 10.0 + 0.31 * k;
+    const double merged = (double)nq * bytes > 1.2e9 && slices > 1 ? launch_merge : pool_merge_cost(slices, n, k, preset, launch_merge);
+    const double pool = 10.5 + std::max((double)((nq * slices + 255) / 256) * group, memory) + merged;
     auto tile_time = [&](double len) {
         const double survivors = keep * len, insertions = std::min(survivors, k * (1.0 + std::log(std::max(1.0, survivors / k))));
         return c.tile + c.insertion * insertions +
@@ -3000,7 +3021,7 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
     // value then sits near the (1.3 k)-th best of everything scanned so far)
     set_exchange(a, p.pub_slots, k);
     const int pool_slices = forced == PSC_ROUTE_AUTO && skip_first < 0
-                                ? pool_scan_slices(m, nq, n, k, ht, dense, mfma, p, ws_bytes)
+                                ? pool_scan_slices(m, nq, n, k, ht, dense, mfma, preset, p, ws_bytes)
                                 : 0;
     if (pool_slices > 0) {
         a.nslice = pool_slices;
@@ -3011,7 +3032,8 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
         const size_t dist_bytes = ((size_t)nq * a.nslice * k * sizeof(float) + 255) / 256 * 256;
         const size_t key_bytes = dist_bytes + (size_t)nq * a.nslice * k * sizeof(int64_t);
         const size_t words = ((size_t)nq * sizeof(uint32_t) + 255) / 256 * 256;
-        const bool self_merge = a.nslice > 1 && nq <= kPresetQueries && pool_merges_itself(a.nslice, n, k) &&
+        // (several slices: at most 128 queries)
+        const bool self_merge = a.nslice > 1 && pool_merges_itself(a.nslice, n, k, preset) &&
                                 256 + words + key_bytes <= ws_bytes;
         uint32_t *arrived = self_merge ? a.gthr : nullptr;
         a.part_d = (float *)((char *)ws + 256 + (self_merge ? words : 0));

@@ -578,19 +578,22 @@ def test_thousands_of_codes_at_the_kth_distance(psc, force_route, route, m, n, n
 @pytest.mark.parametrize("m,n,ht", [(8, 200_003, 24), (16, 100_001, 64), (8, 65_536, 64)])
 def test_slices_put_together_by_the_last_workgroup(psc, m, n, nq, ht):
     """Small scans of up to 128 queries are cut into slices whose keys the query's last workgroup selects from, or
-    a merge launch where they do not fit its pool (8 slices of 513): the same workspace call after call."""
+    a merge launch where they do not fit its pool (8 slices of 513 or more) or are many for few results: the same
+    workspace call after call."""
     codes, qcodes, lut = _rand_problem(m, n, nq, seed=41 + nq, lut_kind="int")
     ws = torch.full((psc.scan_workspace_bytes(m, nq, n, 1024),), 0xa5, dtype=torch.uint8, device="cuda")
     args = _dev(lut), _dev(qcodes), _dev(codes)
+    fit = []
     for k in (1, 10, 512, 513, 1024, 10):
         ids, d = psc.scan(*args, ht, k, workspace=ws)
         torch.cuda.synchronize()
         if k > 1:  # (for k = 1 some of these sizes take the tiles)
             kernel, slices = _route(psc)
             assert kernel.startswith("scan_pool_kernel") and (slices > 1) == (nq <= 128), (k, kernel, slices)
-            assert (slices * k > 4096) == (m == 16 and nq <= 3 and k == 513), (k, kernel, slices)
+            fit.append(slices * k <= (256 if k <= 16 else 4096))
         ref = O.scan(lut.astype(np.float64), qcodes, codes, ht, k)
         assert np.array_equal(ids.cpu().numpy(), ref["ids"]) and np.array_equal(d.cpu().numpy(), ref["dists"]), k
+    assert sum(fit) >= 3 and all(fit) == (nq > 3), fit
 
 
 def _route(psc):
