@@ -344,8 +344,10 @@ __device__ __forceinline__ uint64_t lane_value_u64(uint64_t v, int l)
 // it loses by its id nearly always (ids rise during a scan); clustered vectors share codes by the thousand, and
 // each such tie took the list's lock to be turned away.  Asked only when a batch has a tie.
 // 10M x 10k at ht = 24, k = 100 24.6 -> 14.0 ms (of seeds with many codes at the k-th distance), 1M x 777 pure
-// ADC 829 -> 744 us, 1M x 1M graph at ht = 20 80.4 -> 77.4 ms.  The fused scans of inverted lists and of 128-bit codes, where
-// few distances tie, do without: 4.43 / 4.48 ms with it, 10M x 10k 25.56 / 25.68.
+// ADC 829 -> 744 us, 1M x 1M graph at ht = 20 80.4 -> 77.4 ms.  128-bit codes, 10M x 2000 at ht = 48: 10k distinct
+// codes 3.33 -> 3.14 ms (by xor and popcount 5.66 -> 5.49), 1M x 2000, k = 10 0.331 -> 0.311; all distinct 3.12 / 3.08.
+// Inverted lists do without: of 1M codes 1000 distinct 1.109 / 1.106 ms with it, of 10M of 128 bits 2.307 / 2.342, all
+// distinct 2.195 / 2.219 (a job's list fills once, and few of its ties come after that).
 template <int M, int TQ>
 __device__ __forceinline__ bool before_kth(const Lds<M, TQ> &s, const ScanArgs &a, int q, float d, uint32_t id)
 {
@@ -719,7 +721,7 @@ __device__ __forceinline__ void score_batch(const Lds<M, TQ> &s, const ScanArgs 
     }
     uint64_t pm = ballot64(pass);
     ask.wanted = pm != 0;
-    if constexpr (!IVF && M == 8) {
+    if constexpr (!IVF) {
         if (pm) {
             if (ballot64(pass && d == thr)) {
                 pass = pass && before_kth(s, a, q, d, key);
