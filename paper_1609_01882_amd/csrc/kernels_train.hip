@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <iterator>
 
 #include "common.h"
 #include "pq_nearest.h"
@@ -387,7 +388,8 @@ static int run_pq_lloyd(const PqLloydArgs &a, int iteration, hipStream_t s)
 int pq_lloyd_parts(int dim, int m, int64_t n)
 {
     const int dsub = dim / m;
-    if (dsub < 2 || dsub > 32) return 0;
+    static constexpr int kLengths[] = {2, 4, 6, 8, 12, 16, 24, 32};  // (launch_pq_lloyd's; the plain step refuses the rest)
+    if (std::find(std::begin(kLengths), std::end(kLengths), dsub) == std::end(kLengths)) return 0;
     // as many workgroups as run together (two to a compute unit up to sub-vectors of 16), at least a turn each
     const int rows = 32 * kLloydThreads / 64;
     const int64_t want = (n + rows - 1) / rows, cap = std::max(1, (dsub <= 16 ? 512 : 256) / m), turns = (want + cap - 1) / cap;

@@ -257,3 +257,12 @@ def test_pq_iterations_enqueued_together_stop_at_an_empty_cell(psc, dim, m, n, d
         assert np.allclose(got[0], obj[it], rtol=1e-6, atol=1e-9), it
     # (a mean of whole numbers is rounded once; rows at equal distances are told apart by the centroid's number)
     assert np.array_equal(one.get_codebook(), many.get_codebook())
+
+
+@pytest.mark.parametrize("dsub", [3, 5, 20, 40, 63])
+def test_lengths_that_no_kernel_has_are_named(psc, dsub):
+    """Sub-vectors of other lengths are refused with the ones there are, by training as by the encoder."""
+    x = torch.zeros((300, 8 * dsub), device="cuda")
+    for call in (lambda i: i.train_pq_device(x, iters=1, seed=0), lambda i: (i.set_codebook(np.zeros((8, 256, dsub), np.float32)), i.encode(x))):
+        with pytest.raises(psc.PscError, match=f"unsupported sub-vector length {dsub} .supported: 1,2,4,6,8,12,16,24,32,48,64"):
+            call(psc.Index(8 * dsub, 8))
