@@ -75,8 +75,8 @@ def test_encode(setup, m):
 
 @pytest.mark.parametrize("m,dsub", [(16, 1), (8, 6), (8, 8), (8, 12), (8, 16), (16, 24), (8, 32), (16, 48), (8, 64)])
 def test_encode_of_many_rows_equals_encode_of_few(m, dsub):
-    """The encoder has two forms, by the number of codes (the last a few rows past the largest of the limits):
-    same sums, so the codes are those of the same rows 1000 at a time, which are the oracle's."""
+    """The encoder's workgroups take several turns, for sub-vectors of 48 it reads the centroids another way from 1.6M
+    codes on: the same sums, so the codes are those of the same rows 1000 at a time, which are the oracle's."""
     import paper_1609_01882_amd as psc
     dim, n = m * dsub, 3_200_000 // m + 259
     rng = np.random.default_rng(dim)
@@ -87,7 +87,7 @@ def test_encode_of_many_rows_equals_encode_of_few(m, dsub):
     g.manual_seed(dim)
     x = torch.randn((n, dim), generator=g, device="cuda")
     few = torch.cat([idx.encode(x[s:s + 1000]) for s in range(0, 20_000, 1000)] + [idx.encode(x[-1000:])])
-    for count in (799_999 // m, 800_000 // m, 1_600_000 // m, n):
+    for count in (799_999 // m, 800_000 // m, 1_600_000 // m - 1, 1_600_000 // m, n):
         many = idx.encode(x[:count])
         assert torch.equal(many[:20_000], few[:20_000]), count
     assert torch.equal(many[-1000:], few[-1000:])
@@ -107,9 +107,11 @@ def test_encode_where_centroids_are_close(m, dsub, data):
     first arg-min of those where nearly every row is a close call (every centroid twice, all centroids one, points
     of a grid halfway between centroids), where one centroid is far out, at the ends of float32's range (in "far and tiny" with
     two centroids far out, so that the squared lengths among the others are below what bfloat16 parts can hold) and
-    with infinities and NaNs among the rows; from one row to several turns of every workgroup."""
+    with infinities and NaNs among the rows; from one row to four turns of a workgroup, of which a
+    wave that met many close calls takes two at once."""
     import paper_1609_01882_amd as psc
-    dim, n = m * dsub, 40_000 // m + 8_193
+    dim, turn = m * dsub, 256 * ((512 if dsub <= 16 else 256) // m)  # (rows that the workgroups take in one turn)
+    n = 3 * turn + 1_077
     rng = np.random.default_rng(dim + len(data))
     cb = rng.normal(size=(m, 256, dsub)).astype(np.float32)
     x = rng.normal(size=(n, dim)).astype(np.float32)
@@ -159,7 +161,7 @@ def test_encode_where_centroids_are_close(m, dsub, data):
     got = idx.encode(xd).cpu().numpy()
     differs = got != want
     assert np.all(tied[differs]) and differs.sum() <= 1e-4 * differs.size, (int(differs.sum()), int((~tied & differs).sum()))
-    for count in (1, 31, 33, 257, n - 1):
+    for count in (1, 31, 33, 257, turn + 40, 2 * turn + 100, n - 1):
         assert np.array_equal(idx.encode(xd[:count].contiguous()).cpu().numpy(), got[:count]), count
 
 

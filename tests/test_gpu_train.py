@@ -93,11 +93,14 @@ def test_pq_lloyd_iterations_from_a_common_start(psc, dim, m):
         cb = nxt  # both sides go on from the oracle's centroids
 
 
-@pytest.mark.parametrize("dim,m,n", [(128, 8, 27_501), (64, 16, 43_751), (256, 8, 16_251), (256, 8, 16_249)])
+@pytest.mark.parametrize("dim,m,n", [
+    (128, 8, 27_501), (64, 16, 43_751), (256, 8, 16_251), (256, 8, 16_249),
+    (128, 8, 16_384), (128, 8, 16_385), (128, 8, 32_769), (256, 8, 8_193), (48, 8, 33_000), (192, 8, 16_500), (384, 8, 5_000)])
 def test_pq_lloyd_iteration_of_many_rows(psc, dim, m, n):
-    """The step kernel has two forms, by the number of sub-vectors: sizes around the limits."""
+    """One, two and more turns of the step's workgroups (256 rows each; 512 / m workgroups run together, 256 / m
+    for sub-vectors of more than 16), every length of sub-vector that the test above does not have."""
     dsub = dim // m
-    x = (W.sift_like(n, seed=33, stream=1) if dim <= 128 else W.relu_like(n, seed=33, stream=1))[:, :dim].copy()
+    x = (W.sift_like(n, seed=33, stream=1) if dim <= 128 else W.relu_like(n, seed=33, stream=1, dim=max(dim, 256)))[:, :dim].copy()
     xd = _dev(x)
     idx = psc.Index(dim, m)
     rng = np.random.default_rng(5)
@@ -266,3 +269,41 @@ def test_lengths_that_no_kernel_has_are_named(psc, dsub):
     for call in (lambda i: i.train_pq_device(x, iters=1, seed=0), lambda i: (i.set_codebook(np.zeros((8, 256, dsub), np.float32)), i.encode(x))):
         with pytest.raises(psc.PscError, match=f"unsupported sub-vector length {dsub} .supported: 1,2,4,6,8,12,16,24,32,48,64"):
             call(psc.Index(8 * dsub, 8))
+
+
+@pytest.mark.parametrize("dim,m,n", [(128, 8, 50_229), (128, 8, 33_000), (16, 8, 49_153), (96, 8, 32_768 + 16_384 + 40), (64, 16, 25_700),
+                                     (256, 8, 25_653), (192, 8, 8_300)])
+def test_pq_lloyd_iteration_where_nearly_every_row_is_close(psc, dim, m, n):
+    """Centroids in pairs 3e-6 apart: too close for the search, not for the float32 distances.  A wave that meets
+    many such rows takes the rows of two turns at once from then on; three and more turns with a ragged end, and ends
+    at which only some of the second turn's rows are left.  Every row counts once: cells as the encoder gives them
+    for a few rows at a time, means, counts and objective of those members in float64."""
+    dsub = dim // m
+    rng = np.random.default_rng(n)
+    cb = rng.normal(size=(m, 256, dsub)).astype(np.float32)
+    cb[:, 128:] = cb[:, :128] + (3e-6 * np.sqrt(2.0) * rng.normal(size=(m, 128, dsub))).astype(np.float32)
+    x = rng.normal(size=(n, dim)).astype(np.float32)
+    xd = _dev(x)
+    idx = psc.Index(dim, m)
+    idx.set_codebook(cb)
+    cells = torch.cat([idx.encode(xd[r:r + 2000]) for r in range(0, n, 2000)])  # (one turn: no rows taken in twos)
+    assert torch.equal(idx.encode(xd), cells)
+    cells = cells.cpu().numpy().astype(np.int64)
+    obj = idx.train_pq_device(xd, iters=1, from_current=True)
+    got = idx.get_codebook()
+    close = 0
+    for j in range(m):
+        sub, start = x[:, j * dsub:(j + 1) * dsub].astype(np.float64), cb[j].astype(np.float64)
+        _, dmin = O.nearest(sub, start)
+        d = ((sub - start[cells[:, j]]) ** 2).sum(axis=1)
+        assert np.all(d <= dmin * (1 + GAP_PQ) + 1e-9)
+        assert np.isclose(obj[0, j], d.sum(), rtol=1e-6)
+        count = np.bincount(cells[:, j], minlength=256)
+        want = np.zeros((256, dsub))
+        np.add.at(want, cells[:, j], sub)
+        full = count > 0  # (a cell without members takes another's)
+        assert full.sum() > 200
+        err = np.abs(got[j][full] - want[full] / count[full, None]).max()
+        assert err <= CENT_RTOL * np.abs(want[full] / count[full, None]).max(), (j, err)
+        close += int(((cells[:, j] >= 128) & full[cells[:, j] - 128]).sum())
+    assert close > 0.3 * n * m  # (nearly half the rows lie nearer to the later one of a pair)
