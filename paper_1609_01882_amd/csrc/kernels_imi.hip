@@ -103,6 +103,34 @@ __device__ __forceinline__ void bitonic_sort(unsigned long long *keys, int n)
     __syncthreads();
 }
 
+// The place of the smallest of a row's 256 entries in the order of their keys, lowest on ties: for rows that hold
+// something that is not a number, whose places in that order depend on their signs.
+__device__ __forceinline__ int row_min_place_by_keys(const float *row)
+{
+    const int lane = (int)(threadIdx.x & 63);
+    uint32_t best = 0xffffffffu;
+    int place = 0;
+    __builtin_amdgcn_wave_barrier();  // (the wave wrote the row; LDS keeps a wave's accesses in order)
+#pragma unroll 1
+    for (int c = lane; c < 256; c += 64) {
+        const uint32_t key = fkey(row[c]);
+        if (key < best) {
+            best = key;
+            place = c;
+        }
+    }
+#pragma unroll 1
+    for (int off = 32; off >= 1; off >>= 1) {
+        const uint32_t o = (uint32_t)__shfl_xor((int)best, off, 64);
+        const int op = __shfl_xor(place, off, 64);
+        if (o < best || (o == best && op < place)) {
+            best = o;
+            place = op;
+        }
+    }
+    return __builtin_amdgcn_readfirstlane(place);
+}
+
 __global__ void split_halves_kernel(const float *__restrict__ x, int64_t n, int dim, float *__restrict__ h1,
                                     float *__restrict__ h2)
 {
@@ -375,12 +403,16 @@ imi_scan_kernel(ImiScanArgs a)
                     }
                     ((f32x4 *)(cellt + jj * 256))[lane] = v;
                     // the row's minimum, then its lowest place: the first lane that holds it, the first of its four
-                    // (place 0 of a row without a number)
-                    const float least = wave_min_f32(fminf(fminf(v[0], v[1]), fminf(v[2], v[3])));
+                    const float four = __builtin_elementwise_minimum(
+                        __builtin_elementwise_minimum(__builtin_elementwise_minimum(v[0], v[1]), v[2]), v[3]);
+                    const float least = wave_min_f32(four);
                     const int in4 = v[0] == least ? 0 : v[1] == least ? 1 : v[2] == least ? 2 : 3;
                     const uint64_t holds = __ballot(v[0] == least || v[1] == least || v[2] == least || v[3] == least);
                     const int first = __builtin_ctzll(holds | (1ull << 63));
-                    const int imin = holds != 0 ? 4 * first + __builtin_amdgcn_readlane(in4, first) : 0;
+                    int imin = 4 * first + __builtin_amdgcn_readlane(in4, first);
+                    // (an entry that is not a number makes its lane's minimum none: the query is none, or squares or
+                    //  the codebook are past float32's range)
+                    if (__builtin_expect(__ballot(__builtin_isnan(four)) != 0, 0)) imin = row_min_place_by_keys(cellt + jj * 256);
                     if (lane == 0) ((volatile uint8_t *)qcw)[jj] = (uint8_t)imin;
                 }
                 __syncthreads();

@@ -287,7 +287,9 @@ def test_imi_cell_of_a_billion_codes(m, n):
 @pytest.mark.parametrize("m", [8, 16])
 def test_imi_query_that_is_not_a_number(m):
     """Table rows without a number have place 0 as their minimum, and distances that are not numbers come last, by
-    id: a query with such coordinates is answered by the codes within the threshold, in the order of their ids."""
+    id: a query with such coordinates is answered by the codes within the threshold, in the order of their ids.
+    An infinite coordinate makes a row's entries infinity for one sign of the centroids' and infinity less infinity
+    for the other: the minimum is taken in the order of the keys, where that one's sign counts."""
     import paper_1609_01882_amd as psc
     s = build_imi(psc, 5_000, 4, 3, seed=86, m=m)
     idx, ht, k, dsub = s["idx"], 3 * m, 40, 128 // m
@@ -296,6 +298,7 @@ def test_imi_query_that_is_not_a_number(m):
     xq[2, 127] = np.nan
     xq[3, 3 * dsub:5 * dsub] = np.nan
     xq[4] = np.nan
+    xq[5, 2], xq[5, 126] = np.inf, -np.inf
     ids, d, cells, qcodes = idx.imi_search(_dev(xq), 12, 0, ht, k, want_debug=True)
     torch.cuda.synchronize()
     ids, d, cells, qcodes = (t.cpu().numpy() for t in (ids, d, cells, qcodes))
@@ -309,3 +312,8 @@ def test_imi_query_that_is_not_a_number(m):
             keep += s["lids"][lo:hi][h <= ht].tolist()
         keep = sorted(keep)[:k]
         assert ids[q].tolist() == keep + [-1] * (k - len(keep)) and np.all(np.isnan(d[q, :len(keep)])), q
+    inf = torch.full((1,), np.inf, device="cuda")
+    first = bool(np.signbit((inf - inf).cpu().numpy())[0])  # (not a number, with a sign: below every number)
+    for t, sign in ((2, 1.0), (126, -1.0)):
+        along = s["cb"][t // dsub][:, t % dsub] * sign > 0  # (2 q.c = infinity)
+        assert along.any() and not along.all() and np.all(qcodes[5][:, t // dsub] == np.flatnonzero(along == first)[0])
