@@ -7,7 +7,6 @@
 #include <limits>
 #include <numeric>
 #include <thread>
-#include <unordered_map>
 
 #include "common.h"
 
@@ -51,18 +50,29 @@ void parallel_rows(int64_t n, F &&body)
 // draw c of the counter-based generator picks the c-th row).
 void kmeans_start_rows(int64_t n, int ncent, uint64_t seed, int64_t *rows)
 {
-    // the first ncent steps of a shuffle of 0 .. n-1: only the places those touched are held (all n of them, for
-    // each of 8 sub-quantizers, took 0.6 of the 5.4 ms of a training on 100k vectors)
-    std::unordered_map<int64_t, int64_t> moved;
-    moved.reserve((size_t)ncent * 2);
-    auto at = [&](int64_t place) {
-        const auto it = moved.find(place);
-        return it == moved.end() ? place : it->second;
+    // The first ncent steps of a shuffle of 0 .. n-1: only the places those touched are held, in an open hash
+    // table a quarter full at most.  8 sub-quantizers, us: all places n = 300 11, 3000 27, 100k 675; a
+    // std::unordered_map 100, 150, 155; this 22 at each.
+    int bits = 4;
+    while ((1 << bits) < 4 * ncent) ++bits;
+    struct Moved {
+        int64_t place, row;
+    };
+    std::vector<Moved> moved((size_t)1 << bits, Moved{-1, 0});
+    auto slot = [&](int64_t place) -> Moved & {  // the place's, or the free one where it would be
+        size_t at = (size_t)(((uint64_t)place * 0x9e3779b97f4a7c15ull) >> (64 - bits));
+        while (moved[at].place >= 0 && moved[at].place != place) at = (at + 1) & (moved.size() - 1);
+        return moved[at];
+    };
+    auto row_at = [&](int64_t place) {
+        const Moved &m = slot(place);
+        return m.place >= 0 ? m.row : place;
     };
     for (int c = 0; c < ncent; ++c) {
         const int64_t r = c + (int64_t)(counter_draw(seed, (uint64_t)c) % (uint64_t)(n - c));
-        rows[c] = at(r);
-        moved[r] = at(c);  // (place c is not looked at again)
+        const int64_t from = row_at(c);
+        rows[c] = row_at(r);
+        slot(r) = Moved{r, from};  // (place c is not looked at again)
     }
 }
 
