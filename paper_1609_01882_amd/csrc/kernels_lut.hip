@@ -178,10 +178,11 @@ encode_mfma_kernel(const float *__restrict__ cb, int dim, int m, const float *__
 // where mu_j is the mean centroid of sub-quantizer j (distances do not change under a common
 // shift; centring keeps the three terms small, which keeps the cancellation error small).
 // One workgroup = 32 rows x the 256 centroids of one sub-quantizer; each of its 4 waves owns two
-// 32 x 32 output tiles and runs DSUB/2 v_mfma_f32_32x32x2f32 steps per tile.  The tables leave through LDS, whole
-// rows of 1 KB to a store, and a row's smallest entry, the query's code, is found on the way (before: stored by
-// lane, read again by a launch of its own; 10k queries 58 -> 43 us, 100 15 -> 12, 32768 of sub-vectors of 8,
-// 16 sub-quantizers, 281 -> 188).
+// 32 x 32 output tiles and runs DSUB/2 v_mfma_f32_32x32x2f32 steps per tile.  With codes the tables leave
+// through LDS, whole rows of 1 KB to a store, and a row's smallest entry, the query's code, is found on the way
+// (before: stored by lane, read again by a launch of its own; 10k queries 58 -> 43 us, 100 15 -> 12, 32768 of
+// sub-vectors of 8, 16 sub-quantizers, 281 -> 188).  Without codes they are stored by lane: through LDS 8000 rows, 16
+// sub-vectors of 4, take 40.7 us and not 32.3, 30k 132.9 / 120.8, of 16 198.2 / 197.9 (fewer workgroups fit).
 //
 // v_mfma_f32_32x32x2f32 operand layout (wave64, lane l): A[i][k] with i = l % 32, k = l / 32;
 // B[k][j] with k = l / 32, j = l % 32; D[i][j] in 16 registers, register v holding row
@@ -214,7 +215,7 @@ __device__ __forceinline__ int row_argmin(const row4 v)
 // others keep a relative error of a few float32 roundings x 16 (about 3e-6 at worst).
 constexpr float kRefineBelow = 1.0f / 16.0f;
 
-template <int DSUB>
+template <int DSUB, bool CODES>
 __global__ void __launch_bounds__(256)
 lut_mfma_kernel(const float *__restrict__ cb, const float *__restrict__ cbc /* centred codebook */,
                 const float *__restrict__ mu, int dim, int m, const float *__restrict__ x, int64_t nrows,
@@ -224,7 +225,7 @@ lut_mfma_kernel(const float *__restrict__ cb, const float *__restrict__ cbc /* c
     constexpr int KS = DSUB / 2;
     constexpr int LD = kCentroids + 4;  // pitch of a row: the two rows a store writes lie in different banks
     __shared__ float qn_s[4][32];
-    __shared__ __align__(16) float rows[32 * LD];
+    __shared__ __align__(16) float rows[CODES ? 32 * LD : 4];
     if (blockIdx.x == 0 && blockIdx.y == 0)
         for (int e = (int)threadIdx.x; e < npreset; e += 256) preset[e] = kPresetWord;
     const int j = blockIdx.y;
@@ -288,19 +289,23 @@ lut_mfma_kernel(const float *__restrict__ cb, const float *__restrict__ cbc /* c
                     }
                     d = e;
                 }
-                rows[i * LD + c0 + col] = d > 0.f ? d : 0.f;
+                d = d > 0.f ? d : 0.f;
+                if constexpr (CODES)
+                    rows[i * LD + c0 + col] = d;
+                else
+                    lut[(r * m + j) * kCentroids + c0 + col] = d;
             }
         }
     }
-    __syncthreads();
-    // whole rows to memory, a wave each, with the place of the row's smallest entry
+    if constexpr (CODES) {
+        __syncthreads();
+        // whole rows to memory, a wave each, with the place of the row's smallest entry
 #pragma unroll 2
-    for (int i = wave; i < 32 && r0 + i < nrows; i += 4) {
-        typedef float row4_any __attribute__((ext_vector_type(4), aligned(4)));
-        const row4 v = *(const row4 *)(rows + i * LD + 4 * lane);
-        const int64_t row = (r0 + i) * m + j;
-        *(row4_any *)(lut + row * kCentroids + 4 * lane) = v;
-        if (codes != nullptr) {
+        for (int i = wave; i < 32 && r0 + i < nrows; i += 4) {
+            typedef float row4_any __attribute__((ext_vector_type(4), aligned(4)));
+            const row4 v = *(const row4 *)(rows + i * LD + 4 * lane);
+            const int64_t row = (r0 + i) * m + j;
+            *(row4_any *)(lut + row * kCentroids + 4 * lane) = v;
             const int c = row_argmin(v);
             if (lane == 0) codes[row] = (uint8_t)c;
         }
@@ -338,8 +343,12 @@ int run_lut_mfma(const float *cb, const float *cbc, const float *mu, int dim, in
                  float *lut, uint8_t *codes, uint32_t *preset, int npreset, hipStream_t s)
 {
     dim3 grid((unsigned)((nrows + 31) / 32), (unsigned)m);
-    hipLaunchKernelGGL((lut_mfma_kernel<DSUB>), grid, dim3(256), 0, s, cb, cbc, mu, dim, m, x, nrows, lut, codes, preset,
-                       npreset);
+    if (codes != nullptr)
+        hipLaunchKernelGGL((lut_mfma_kernel<DSUB, true>), grid, dim3(256), 0, s, cb, cbc, mu, dim, m, x, nrows, lut, codes,
+                           preset, npreset);
+    else
+        hipLaunchKernelGGL((lut_mfma_kernel<DSUB, false>), grid, dim3(256), 0, s, cb, cbc, mu, dim, m, x, nrows, lut, codes,
+                           preset, npreset);
     PSC_HIP_TRY(hipGetLastError());
     return PSC_OK;
 }

@@ -56,6 +56,21 @@ def test_tables_and_query_codes(setup, m):
     assert (qc == O.query_codes(ref)).mean() > 0.999
 
 
+@pytest.mark.parametrize("m,dsub", [(16, 2), (8, 4), (16, 6), (8, 8), (8, 12), (16, 16), (8, 24), (8, 32), (8, 48), (8, 64)])
+def test_tables_without_codes_are_the_same_tables(m, dsub):
+    """The table kernel stores the entries by lane where no codes are asked for and whole rows where they are."""
+    import paper_1609_01882_amd as psc
+    rng = np.random.default_rng(dsub)
+    idx = psc.Index(m * dsub, m)
+    idx.set_codebook(rng.normal(size=(m, 256, dsub)).astype(np.float32))
+    q = _dev(rng.normal(size=(131, m * dsub)).astype(np.float32))
+    for nq in (1, 31, 32, 33, 131):
+        lut, codes = idx.build_lut(q[:nq].contiguous())
+        alone, none = idx.build_lut(q[:nq].contiguous(), want_codes=False)
+        assert none is None and torch.equal(lut, alone)
+        assert torch.equal(codes.long(), lut.argmin(dim=2))
+
+
 @pytest.mark.parametrize("m", [8, 16])
 def test_encode(setup, m):
     s = setup[m]
