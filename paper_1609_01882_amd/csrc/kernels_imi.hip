@@ -579,7 +579,7 @@ int launch_imi_scan(int m, const float *lut_dev, const float *tab1_dev, const fl
     while (cap < k + 256) cap <<= 1;
     a.cap = cap;
     const size_t lds = (size_t)m * 256 * 4 + (size_t)dim * 4 + (size_t)cap * 8;  // (dim = 2 * m * ..: a multiple of 8 bytes)
-    PSC_REQUIRE(lds <= 48 * 1024, "dimension and k too large for the multi-index scan");  // (at most 40 KB: dim up to 2048, k up to 1024)
+    PSC_REQUIRE(lds <= 48 * 1024, "dimension and k too large for the multi-index scan");  // (at most 36 KB: dim and k up to 1024)
     const dim3 grid((unsigned)(nq * split));
     if (m == 8 && !direct) hipLaunchKernelGGL((imi_scan_kernel<8, false>), grid, dim3(256), lds, s, a);
     else if (m == 8) hipLaunchKernelGGL((imi_scan_kernel<8, true>), grid, dim3(256), lds, s, a);

@@ -41,8 +41,8 @@ struct PqNearest {
     static constexpr int kTiles = kCentroids / 32;
     static constexpr int kWavesPerEu = DSUB <= 16 ? 4 : 2;  // (registers for their operands)
     static constexpr int kManyRows = 10;  // rows of a wave from which every row's own lanes take all distances
-    static constexpr float kUnit = DSUB <= 32 ? 6.103515625e-5f + 3.814697265625e-6f   // 2^-14 + 2^-18
-                                              : 1.220703125e-4f + 3.814697265625e-6f;  // 2^-13 + 2^-18
+    static_assert(DSUB <= 32, "kUnit and kLost are sums over at most 7 products of 16 places");
+    static constexpr float kUnit = 0x1p-14f + 0x1p-18f;
     static constexpr float kLost = 0x1p-116f;
     struct Shared {
         pq_bf16x8 image[kTiles * kSteps * 64];  // operands in the order of the products
