@@ -40,8 +40,8 @@ def main():
     t_coarse = wall(lambda: idx.ivf_train_coarse_device(x, args.nlist, iters=args.iters, seed=1))
     res = {"workload": "train", "n": args.n, "dim": dim, "m": m, "iters": args.iters,
            "pq_ms_per_iter": round(1e3 * t_pq / args.iters, 3),
-           # per row and sub-quantizer 256 x dsub (subtract, multiply-add)
-           "pq_tflops": round(3.0 * args.n * 256 * dim / (t_pq / args.iters) / 1e12, 2),
+           # bfloat16 products per row and sub-quantizer: 256 x (three per coordinate, three for the norm)
+           "pq_bf16_tflops": round(2.0 * args.n * 256 * (3 * dim + 3 * m) / (t_pq / args.iters) / 1e12, 2),
            "nlist": args.nlist, "coarse_ms_per_iter": round(1e3 * t_coarse / args.iters, 3),
            "coarse_tflops": round(2.0 * args.n * args.nlist * dim / (t_coarse / args.iters) / 1e12, 2)}
     if args.host_iters > 0:
