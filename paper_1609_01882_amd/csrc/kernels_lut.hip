@@ -167,7 +167,7 @@ encode_mfma_kernel(const float *__restrict__ cb, int dim, int m, const float *__
             for (int t = 0; t < DSUB; ++t) v[t] -= sub[t];
         }
         r0 += plain ? 2 * step : step;
-        const int c = plain ? Nearest::all_distances(cbj, v) : Nearest::search(s, cbj, v, plain);
+        const int c = plain ? Nearest::all_distances(cbj, v) : Nearest::search(s, cbj, v, own < nrows, plain);
         if (live) codes[r * m + j] = (uint8_t)c;
     }
 }

@@ -133,7 +133,7 @@ pq_lloyd_mfma_kernel(const float *__restrict__ cb, int dim, int m, const float *
         for (int t = 0; t < DSUB; ++t) v[t] = x[r * dim + j * DSUB + t];
         r0 += plain ? 2 * step : step;
         const bool alone = plain;
-        const int c = plain ? Nearest::all_distances(cbj, v) : Nearest::search(s.nearest, cbj, v, plain);
+        const int c = plain ? Nearest::all_distances(cbj, v) : Nearest::search(s.nearest, cbj, v, live, plain);
         float d = Nearest::distance(v, cbj + c * DSUB);
         if (!(d < __builtin_inff())) d = __builtin_inff();  // (a row that is not a number is at infinity)
         if (!live) continue;

@@ -146,10 +146,11 @@ struct PqNearest {
         return bi;
     }
 
-    // v: the sub-vector of row lane % 32 (both halves of the wave hold it); the whole wave calls.  `many` is set
-    // if many of the rows needed all distances.
+    // v: the sub-vector of row lane % 32 (both halves of the wave hold it); the whole wave calls.  live: whether the
+    // answer is asked for (rows past the end are copies of the last one, and a close call there would be many: 500 rows,
+    // 8 sub-vectors of 8, 24 us where it is 11).  `many` is set if many of the rows needed all distances.
     static __device__ __forceinline__ int search(const Shared &s, const float *__restrict__ cb, const float (&v)[DSUB],
-                                                 bool &many)
+                                                 bool live, bool &many)
     {
         const int lane = (int)(threadIdx.x & 63), half = lane >> 5;
         pq_bf16x8 row[kSteps];
@@ -237,7 +238,7 @@ struct PqNearest {
         const int near = best <= reach ? 1 : 0, deep = !finite || next <= reach ? 2 : 0;
         const int other = __shfl_xor(near | deep, 32, 64), theirs = __shfl_xor(mine, 32, 64);
         int winner = near ? mine : theirs;
-        const bool all = ((deep | other) & 2) != 0, both = near && (other & 1) && !all;
+        const bool all = live && ((deep | other) & 2) != 0, both = near && (other & 1) && !all;
         if (__ballot(both) != 0) {
             const float d = both ? distance(v, cb + mine * DSUB) : 0.f;
             const float o = __shfl_xor(d, 32, 64);
