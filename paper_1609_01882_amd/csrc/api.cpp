@@ -63,9 +63,13 @@ static int sync_codebook_to_device(const psc_index *idx)
     return PSC_OK;
 }
 
-// Device scratch of one training call, released when the call returns.
+// Device scratch of one training call, released when the call returns.  What fits is cut from chunks: an allocation
+// and its release take 2 us, from 2 MB on 45 (1000 rows, one iteration: 13 of them).
 struct DeviceScratch {
+    static constexpr size_t kChunk = ((size_t)2 << 20) - 4096;
     std::vector<void *> owned;
+    char *chunk = nullptr;
+    size_t left = 0;
     ~DeviceScratch()
     {
         for (void *p : owned) (void)hipFree(p);
@@ -73,10 +77,21 @@ struct DeviceScratch {
     template <class T>
     int get(T **out, size_t count)
     {
-        void *p = nullptr;
-        PSC_HIP_TRY(hipMalloc(&p, (count ? count : 1) * sizeof(T)));
-        owned.push_back(p);
-        *out = (T *)p;
+        const size_t bytes = ((count ? count : 1) * sizeof(T) + 255) / 256 * 256;
+        if (bytes > left) {
+            void *p = nullptr;
+            PSC_HIP_TRY(hipMalloc(&p, std::max(bytes, kChunk)));
+            owned.push_back(p);
+            if (bytes >= kChunk) {  // one of its own; the chunk stays
+                *out = (T *)p;
+                return PSC_OK;
+            }
+            chunk = (char *)p;
+            left = kChunk;
+        }
+        *out = (T *)chunk;
+        chunk += bytes;
+        left -= bytes;
         return PSC_OK;
     }
 };
