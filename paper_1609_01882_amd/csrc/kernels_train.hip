@@ -26,9 +26,11 @@ namespace {
 // for every lane, come through the scalar cache: read from LDS, four 16-byte reads per 32 vector
 // instructions, they take as long as the arithmetic.  For sub-vectors of 48 and 64, whose operands and sums do not
 // fit LDS, and of 1, where nearly every row is a close call (1M rows, 16 sub-quantizers 677 / 1600 us an
-// iteration); the others take pq_lloyd_mfma_kernel.
+// iteration); the others take pq_lloyd_mfma_kernel.  Few rows with sub-vectors of 1 do read the centroids from LDS (STAGED):
+// there are not the waves to hide the scalar cache's trips.  An iteration with LDS / scalar cache, us: 8 sub-quantizers,
+// 300 rows 56 / 62, 3000 59 / 62, 30k 98 / 99, 1M 382 / 383; 16, 300 54 / 58, 300k 275 / 274, 1M 691 / 674.
 // ---------------------------------------------------------------------------------------------
-template <int DSUB>
+template <int DSUB, bool STAGED>
 __global__ void __launch_bounds__(256)
 pq_lloyd_step_kernel(const float *__restrict__ cb, int dim, int m, const float *__restrict__ x, int64_t n,
                      uint8_t *__restrict__ cell, float *__restrict__ dmin, double *__restrict__ gsum,
@@ -39,7 +41,11 @@ pq_lloyd_step_kernel(const float *__restrict__ cb, int dim, int m, const float *
     float *sum = smem;                                    // [256][LD]
     uint32_t *cnt = (uint32_t *)(smem + kCentroids * LD);  // [256]
     const int j = blockIdx.y, tid = threadIdx.x;
-    const float *__restrict__ cen = cb + (int64_t)j * kCentroids * DSUB;  // (the same address in every lane)
+    const float *__restrict__ from = cb + (int64_t)j * kCentroids * DSUB;
+    __shared__ float staged[STAGED ? kCentroids * DSUB : 1];
+    if constexpr (STAGED)
+        for (int e = tid; e < kCentroids * DSUB; e += 256) staged[e] = from[e];
+    const float *cen = STAGED ? staged : from;  // (the same address in every lane)
     for (int e = tid; e < kCentroids * LD; e += 256) sum[e] = 0.f;
     cnt[tid] = 0u;
     __syncthreads();
@@ -332,21 +338,31 @@ mean_centroid_kernel(float *__restrict__ cent, int ncent, int dim)
     if (threadIdx.x == 0) cent[(int64_t)ncent * dim + t] = (float)((part[0] + part[1] + part[2] + part[3]) / ncent);
 }
 
-template <int DSUB>
-int run_pq_step(const float *cb, int dim, int m, const float *x, int64_t n, uint8_t *cell, float *dmin,
+template <int DSUB, bool STAGED>
+int run_pq_step_form(const float *cb, int dim, int m, const float *x, int64_t n, uint8_t *cell, float *dmin,
                 double *gsum, uint32_t *gcount, double *gobj, hipStream_t s)
 {
     const size_t lds = (size_t)(kCentroids * (DSUB + 2)) * sizeof(float);
     if (lds > 48 * 1024)
-        PSC_HIP_TRY(hipFuncSetAttribute((const void *)pq_lloyd_step_kernel<DSUB>,
+        PSC_HIP_TRY(hipFuncSetAttribute((const void *)pq_lloyd_step_kernel<DSUB, STAGED>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     // at most 2048 workgroups (8 to a compute unit), all with the same number of turns
     const int64_t want = (n + 255) / 256, cap = 2048 / m, turns = (want + cap - 1) / cap;
     dim3 grid((unsigned)((want + turns - 1) / turns), (unsigned)m);
-    hipLaunchKernelGGL((pq_lloyd_step_kernel<DSUB>), grid, dim3(256), lds, s, cb, dim, m, x, n, cell, dmin,
+    hipLaunchKernelGGL((pq_lloyd_step_kernel<DSUB, STAGED>), grid, dim3(256), lds, s, cb, dim, m, x, n, cell, dmin,
                        gsum, gcount, gobj);
     PSC_HIP_TRY(hipGetLastError());
     return PSC_OK;
+}
+
+template <int DSUB>
+int run_pq_step(const float *cb, int dim, int m, const float *x, int64_t n, uint8_t *cell, float *dmin,
+                double *gsum, uint32_t *gcount, double *gobj, hipStream_t s)
+{
+    // (up to 30k rows ahead, even up to 300k x 16 and 1M x 8)
+    if constexpr (DSUB == 1)
+        if (n * m <= 4'000'000) return run_pq_step_form<1, true>(cb, dim, m, x, n, cell, dmin, gsum, gcount, gobj, s);
+    return run_pq_step_form<DSUB, false>(cb, dim, m, x, n, cell, dmin, gsum, gcount, gobj, s);
 }
 
 }  // namespace

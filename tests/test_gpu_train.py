@@ -116,6 +116,23 @@ def test_pq_lloyd_iteration_of_many_rows(psc, dim, m, n):
         check_update(sub, cb[j], cells[:, j].astype(np.int64), got[j], ref, GAP_PQ, f"sub-quantizer {j}")
 
 
+@pytest.mark.parametrize("m,n", [(8, 256), (16, 3_001), (16, 250_000), (16, 250_001)])
+def test_pq_lloyd_iteration_of_single_coordinates(psc, m, n):
+    """Sub-vectors of 1 read the centroids from LDS up to 4M codes and through the scalar cache past them."""
+    rng = np.random.default_rng(n)
+    x = rng.normal(size=(n, m)).astype(np.float32)
+    cb = np.stack([x[rng.choice(n, 256, replace=False), j:j + 1] for j in range(m)])
+    xd, idx = _dev(x), psc.Index(m, m)
+    idx.set_codebook(cb)
+    cells = idx.encode(xd).cpu().numpy()
+    obj = idx.train_pq_device(xd, iters=1, from_current=True)
+    got = idx.get_codebook()
+    for j in range(0, m, 5):
+        ref, robj = O.kmeans(x[:, j:j + 1], 256, 1, seed=0, start=cb[j])
+        assert np.isclose(obj[0, j], robj[0], rtol=1e-6), (j, obj[0, j], robj[0])
+        check_update(x[:, j:j + 1], cb[j], cells[:, j].astype(np.int64), got[j], ref, GAP_PQ, f"sub-quantizer {j}")
+
+
 def test_pq_seeded_start_and_the_host_training(psc):
     """Seeded start: iteration 1 equals the oracle's from the documented starting rows; over
     several iterations the objective never rises and the result quantizes as well as the host
