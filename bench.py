@@ -43,8 +43,8 @@ OPS_PER_PAIR = {8: 5, 16: 9}
 # its data differently in the same shape has to be measured again.
 # Source: profiles/scan_mfma_kernel_flat64_ht24.md.
 MEASURED_TRAFFIC_BYTES = {
-    ("flat64", 24, "scan_mfma_kernel m=8 tq=16 waves=16 slices=2 tiles=738"): 2.6293e10,
-    ("flat64", 24, "scan_kernel m=8 tq=8 waves=8 slices=2 tiles=1476"): 9.6131e10,
+    ("flat64", 24, "scan_mfma_kernel m=8 tq=16 waves=16 slices=2 tiles=738"): 2.6532e10,
+    ("flat64", 24, "scan_kernel m=8 tq=8 waves=8 slices=2 tiles=1476"): 9.6837e10,
 }
 
 

@@ -94,7 +94,7 @@ int psc_train_pq(psc_index *idx, const float *x_host, int64_t n, int iters, uint
  * objective_out_host (may be NULL) [iters][m] receives, per iteration and sub-quantizer, the sum
  * of squared distances at the assignment step.  The sums are added atomically, so two runs agree
  * to rounding, not bit for bit.  Synchronous on `stream`; allocates and frees 5*n*m bytes of
- * device scratch, and for the sums up to 18 MB (parts of them, one for each workgroup that runs at a time)
+ * device scratch, and for the sums up to 20 MB (parts of them, one for each workgroup that runs at a time)
  * and 8*m*iters bytes.  Replaces the codebook. */
 #define PSC_START_SEEDED 0
 #define PSC_START_CURRENT 1

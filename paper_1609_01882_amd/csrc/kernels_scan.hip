@@ -1736,8 +1736,8 @@ adc_kernel(ScanArgs a)
 // is full, and once at the end, are the k smallest selected, by a radix search over the bits in
 // which the keys differ (keys are distinct, ids being so).  One slice per query needs no merge and nothing set
 // up; the slices of a query (`arrived`: a word per query, kPresetWord before) are put together by the one of its
-// workgroups that ends last: 1 query x 100k codes 31 -> 27 us, 100 x 100k 49 -> 42 (with the tables' arg-min
-// taken where the tables are built), 64 x 1M, k = 100 109 -> 72, where the merge was a launch of its own.
+// workgroups that ends last: 1 query x 100k codes 31 -> 22 us, 100 x 100k 49 -> 35 (with the tables' arg-min
+// taken where the tables are built), where the merge was a launch of its own.
 // A wave whose keys find no place waits in `meet`; every wave comes there sooner or later, full
 // pool or no codes left, and the selection makes room and lowers the bound.
 // DENSE: every code is scored and the Hamming test is taken on those below the bound (pure ADC and
@@ -2040,7 +2040,8 @@ scan_pool_kernel(ScanArgs a, float open, int *status, uint32_t *arrived, int64_t
         }
         // (Each wave waits until its stores are acknowledged, the barrier orders them before thread 0's count, and
         //  that releases them; the last workgroup acquires the others'.  One release per workgroup and one acquire
-        //  per query: 1 query x 100k codes 27.4 us and 27.1 with a relaxed count alone, 100 x 100k 42.2 and 42.2;
+        //  per query (up to 512 keys still searched): 1 query x 100k codes 27.4 us and 27.1 with a relaxed count alone,
+        //  100 x 100k 42.2 and 42.2;
         //  fences from each of the 16 waves 82 us, an acquire by every workgroup up to 2 us more than this.)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
