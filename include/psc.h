@@ -233,7 +233,12 @@ int psc_scan_static(int m, const float *lut_dev, const uint8_t *qcodes_dev, int6
                     float *dists_dev, psc_stream stream);
 
 /* Whole flat search from raw queries q_dev [nq][dim]: psc_build_lut + psc_scan,
- * tables and query codes living in the workspace (psc_search_workspace_bytes). */
+ * tables and query codes living in the workspace (psc_search_workspace_bytes).  Batches of 16 queries and more over
+ * 100 000 codes and more, k <= 256, may take a route of their own, with the same results ("bound_scan_kernel ..." to
+ * psc_last_scan_route): bounds on the distances, from products in 6-bit floating point, decide which pairs are
+ * tested and scored at all.  It is taken by estimates of both routes' times, only while no route is forced
+ * (psc_set_filter_route), and only if the workspace has room for it (psc_search_workspace_bytes says how much where some
+ * threshold takes it); a workspace for tables, query codes and psc_scan_workspace_bytes alone is accepted too. */
 size_t psc_search_workspace_bytes(const psc_index *idx, int64_t nq, int64_t n, int k);
 int psc_search(const psc_index *idx, const float *q_dev, int64_t nq, const uint8_t *codes_dev,
                int64_t n, int ht, int k, int64_t *ids_dev, float *dists_dev, void *workspace_dev,

@@ -41,9 +41,10 @@ static int sync_codebook_to_device(const psc_index *idx)
     std::lock_guard<std::mutex> guard(idx->image_lock);
     if (idx->dev_current) return PSC_OK;
     // device image: the codebook, the codebook centred on each sub-quantizer's mean centroid,
-    // and those means (the last two feed the matrix-core table kernel)
+    // those means (the last two feed the matrix-core table kernel), and the centroids in 6-bit floats
     const size_t n = idx->cb_host.size(), sq = (size_t)kCentroids * idx->dsub;
-    std::vector<float> img(2 * n + (size_t)idx->m * idx->dsub);
+    const size_t bound_at = (2 * n + (size_t)idx->m * idx->dsub + 3) / 4 * 4;
+    std::vector<float> img(bound_at + bound_image_floats(idx->m, idx->dsub));
     std::memcpy(img.data(), idx->cb_host.data(), n * sizeof(float));
     for (int j = 0; j < idx->m; ++j) {
         float *mu = &img[2 * n + (size_t)j * idx->dsub];
@@ -56,6 +57,8 @@ static int sync_codebook_to_device(const psc_index *idx)
             for (int t = 0; t < idx->dsub; ++t)
                 img[n + j * sq + (size_t)c * idx->dsub + t] = idx->cb_host[j * sq + (size_t)c * idx->dsub + t] - mu[t];
     }
+    idx->bound_at = bound_at;
+    build_bound_image(&img[n], idx->m, idx->dsub, img.data() + bound_at, &idx->bound);
     if (!idx->cb_dev) PSC_HIP_TRY(hipMalloc((void **)&idx->cb_dev, img.size() * sizeof(float)));
     else PSC_HIP_TRY(hipDeviceSynchronize());  // kernels enqueued earlier on any stream may still read the old image
     PSC_HIP_TRY(hipMemcpy(idx->cb_dev, img.data(), img.size() * sizeof(float), hipMemcpyHostToDevice));
@@ -403,13 +406,22 @@ int psc_scan_static(int m, const float *lut_dev, const uint8_t *qcodes_dev, int6
 
 static size_t round256(size_t v) { return (v + 255) / 256 * 256; }
 
-size_t psc_search_workspace_bytes(const psc_index *idx, int64_t nq, int64_t n, int k)
+// What a search needs in any case: the scan's scratch, tables, query codes.
+static size_t plain_search_bytes(const psc_index *idx, int64_t nq, int64_t n, int k)
 {
-    if (!idx) return 0;
     const size_t scan_bytes = flat_scan_workspace_bytes(idx->m, nq, n, k);
     if (scan_bytes == 0) return 0;
     return round256(scan_bytes) + round256((size_t)nq * idx->m * kCentroids * sizeof(float)) +
            round256((size_t)nq * idx->m);
+}
+
+size_t psc_search_workspace_bytes(const psc_index *idx, int64_t nq, int64_t n, int k)
+{
+    if (!idx) return 0;
+    const size_t bytes = plain_search_bytes(idx, nq, n, k);
+    if (bytes == 0) return 0;
+    const size_t bound = bound_workspace_bytes(idx->m, idx->dsub, nq, n, k);
+    return bytes + (bound != 0 ? round256((size_t)nq * sizeof(uint32_t)) + bound : 0);
 }
 
 int psc_search(const psc_index *idx, const float *q_dev, int64_t nq, const uint8_t *codes_dev,
@@ -418,13 +430,14 @@ int psc_search(const psc_index *idx, const float *q_dev, int64_t nq, const uint8
 {
     int rc = need_codebook(idx);
     if (rc != PSC_OK) return rc;
-    const size_t need = psc_search_workspace_bytes(idx, nq, n, k);
+    // (a workspace without room for the bounds is taken as well)
+    const size_t need = plain_search_bytes(idx, nq, n, k);
     PSC_REQUIRE(need != 0, "%s", psc_last_error());
     if (nq == 0) return PSC_OK;
     PSC_REQUIRE(workspace_dev && workspace_bytes >= need, "workspace too small: need %zu bytes, got %zu",
                 need, workspace_bytes);
     PSC_REQUIRE(((uintptr_t)workspace_dev & 255) == 0, "workspace must be 256-byte aligned");
-    // layout: [scan workspace (status word first)] [tables] [query codes]
+    // layout: [scan workspace (status word first)] [tables] [query codes] [marks of queries] [the bounds' scratch]
     const size_t scan_bytes = round256(flat_scan_workspace_bytes(idx->m, nq, n, k));
     char *w = (char *)workspace_dev + scan_bytes;
     float *lut = (float *)w;
@@ -434,6 +447,38 @@ int psc_search(const psc_index *idx, const float *q_dev, int64_t nq, const uint8
     rc = build_lut(idx, q_dev, nq, lut, qcodes, (uint32_t *)((char *)workspace_dev + 256),
                    (int)std::min<int64_t>(nq, kPresetQueries), &preset, (hipStream_t)stream);
     if (rc != PSC_OK) return rc;
+    const size_t bound_bytes = bound_workspace_bytes(idx->m, idx->dsub, nq, n, k);
+    if (bound_bytes != 0 && idx->bound.usable && g_filter_route.load(std::memory_order_relaxed) == PSC_ROUTE_AUTO && ht >= 0 && ids_dev &&
+        dists_dev && codes_dev && ((uintptr_t)codes_dev & 15) == 0 && bound_search_pays(idx->m, idx->dsub, nq, n, ht, k, scan_bytes) &&
+        workspace_bytes >= need + round256((size_t)nq * sizeof(uint32_t)) + bound_bytes) {
+        BoundSearch b;
+        b.cb = idx->bound;
+        b.image = idx->cb_dev + idx->bound_at;
+        b.mu = idx->cb_dev + 2 * idx->cb_host.size();
+        b.dim = idx->dim;
+        b.m = idx->m;
+        b.dsub = idx->dsub;
+        b.q = q_dev;
+        b.lut = lut;
+        b.qcodes = qcodes;
+        b.codes = codes_dev;
+        b.nq = nq;
+        b.n = n;
+        b.ht = ht;
+        b.k = k;
+        b.ids = ids_dev;
+        b.dists = dists_dev;
+        b.redo = (uint32_t *)((char *)workspace_dev + need);
+        b.ws = (char *)b.redo + round256((size_t)nq * sizeof(uint32_t));
+        rc = launch_bound_search(b, (hipStream_t)stream);
+        if (rc != PSC_OK) return rc;
+        char route[96];
+        snprintf(route, sizeof route, "%s", psc_last_scan_route());
+        rc = launch_scan(idx->m, lut, qcodes, nq, codes_dev, n, ht, k, -1, true, preset, ids_dev, dists_dev,
+                         workspace_dev, scan_bytes, (hipStream_t)stream, b.redo);
+        note_scan_route(route);
+        return rc;
+    }
     return launch_scan(idx->m, lut, qcodes, nq, codes_dev, n, ht, k, -1, true, preset, ids_dev, dists_dev,
                        workspace_dev, scan_bytes, (hipStream_t)stream);
 }

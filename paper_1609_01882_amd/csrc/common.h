@@ -119,11 +119,48 @@ size_t flat_scan_workspace_bytes(int m, int64_t nq, int64_t n, int k);
 // skip_first >= 0: query q never returns database row skip_first + q (k-NN-graph mode).
 // clear_status: reset the workspace's status word first (false for follow-up chunks of one call).
 // preset: the first min(nq, kPresetQueries) words after the status word's 256 bytes hold kPresetWord already.
+// redo_dev: a word per query; only queries whose word is not zero are answered (nullptr: all).
 constexpr int kPresetQueries = 128;
 int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t nq,
                 const uint8_t *codes_dev, int64_t n, int ht, int k, int64_t skip_first,
                 bool clear_status, bool preset, int64_t *ids_dev, float *dists_dev, void *ws, size_t ws_bytes,
-                hipStream_t s);
+                hipStream_t s, const uint32_t *redo_dev = nullptr);
+// What launch_scan of these sizes takes, in microseconds (an estimate: pool_scan_slices); 0: it would refuse them.
+double estimated_scan_time(int m, int64_t nq, int64_t n, int k, int ht, size_t ws_bytes);
+// Share of random codes within Hamming distance ht of a query's.
+double random_code_survival(int nbits, int ht);
+// ---- flat search by bounds on the matrix cores (kernels_bound.hip)
+// What the index keeps for it: the centroids in 6-bit floats in units of the largest coordinate / 7.5.
+struct BoundCodebook {
+    bool usable = false;
+    float per_unit = 0.f, half_unit = 0.f;  // 1 / u, 1 / (2 u^2)
+    float norm_grid = 0.f;
+    uint32_t scale[2] = {0u, 0u};
+};
+// Floats of its image (0: no kernel for these lengths), and the image from the centred codebook [m][256][dsub];
+// false: coordinates that are not finite, or all alike.
+size_t bound_image_floats(int m, int dsub);
+bool build_bound_image(const float *centred, int m, int dsub, float *image, BoundCodebook *cb);
+constexpr int64_t kBoundMinQueries = 16;      // below these sizes a search never comes this way
+constexpr int64_t kBoundMinCodes = 100'000;
+constexpr int64_t kBoundChunk = 5'120;        // queries whose lists the workspace holds at a time
+// Scratch (0: these sizes never come this way), and whether the search of these sizes is the faster one.
+size_t bound_workspace_bytes(int m, int dsub, int64_t nq, int64_t n, int k);
+bool bound_search_pays(int m, int dsub, int64_t nq, int64_t n, int ht, int k, size_t ws_bytes);
+struct BoundSearch {
+    BoundCodebook cb;
+    const float *image, *mu;
+    int dim, m, dsub;
+    const float *q, *lut;
+    const uint8_t *qcodes, *codes;
+    int64_t nq, n;
+    int ht, k;
+    int64_t *ids;
+    float *dists;
+    uint32_t *redo;  // [nq] out: queries that are left to launch_scan
+    void *ws;
+};
+int launch_bound_search(const BoundSearch &b, hipStream_t s);
 // lut_dev: tables of the queries minus the mean coarse centroid, [nq][m][256]; list_tab_dev:
 // the lists' share of the residual tables (launch_list_tables); job_qcodes_dev: out, the query
 // code of every job, in job order.
@@ -272,7 +309,9 @@ struct psc_index {
     int device = 0;
     bool has_codebook = false;
     std::vector<float> cb_host;  // [m][256][dsub], the master copy
-    mutable float *cb_dev = nullptr;   // [m][256][dsub], then the centred copy, then mu [m][dsub]
+    mutable float *cb_dev = nullptr;   // [m][256][dsub], then the centred copy, then mu [m][dsub], then (16-byte aligned) `bound`'s image
+    mutable size_t bound_at = 0;       // floats before that image
+    mutable psc::BoundCodebook bound;
     mutable bool dev_current = false;  // device copy matches cb_host
     // linear transformation in front of the quantizer (psc_set_rotation): the matrix transposed and
     // zero-padded, [rot_din_pad][rot_dout_pad]; rot_din = 0: none set

@@ -32,6 +32,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "entry.h"
 
 namespace psc {
 namespace {
@@ -107,6 +108,9 @@ struct ScanArgs {
     // >= k codes at or below it: nothing farther than v is in the query's top k.  With one word,
     // pub_r = k and pub_kth = 1 this is the plain exchange of k-th best distances.
     int pub_slots = 1, pub_r = 0, pub_kth = 1;
+    // Flat mode: a word per query, non-zero for those this scan is to answer (nullptr: all of them).  Tiles without
+    // such a query end at once.
+    const uint32_t *redo = nullptr;
 };
 
 // Flat mode: which queries and which part of the database a workgroup works on.  Query tiles
@@ -138,6 +142,13 @@ __device__ __forceinline__ FlatTile flat_tile(const ScanArgs &a, int64_t tile, i
     }
     return t;
 }
+// Whether a tile of up to 64 queries has one that ScanArgs::redo asks for.
+__device__ __forceinline__ bool tile_wanted(const ScanArgs &a, int64_t q0, int nvq)
+{
+    if (a.redo == nullptr) return true;
+    const int lane = (int)(threadIdx.x & 63);
+    return __ballot(lane < nvq && a.redo[q0 + lane] != 0u) != 0ull;
+}
 // Padding for the partial lists a one-piece tile leaves unused (slices 1 .. nslice-1 of its queries).
 __device__ __forceinline__ void pad_unused_slices(const ScanArgs &a, int64_t q0, int nvq, int tid, int nthreads)
 {
@@ -148,16 +159,6 @@ __device__ __forceinline__ void pad_unused_slices(const ScanArgs &a, int64_t q0,
         a.part_d[o] = __builtin_inff();
         a.part_i[o] = (int64_t)-1;
     }
-}
-
-__device__ __forceinline__ uint64_t ballot64(bool p) { return __ballot(p); }
-
-__device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63); }
-
-__device__ __forceinline__ int prefix_count(uint64_t mask)
-{
-    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                          __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
 __device__ __forceinline__ float bcast_f(float v, int lane)
@@ -171,7 +172,6 @@ __device__ __forceinline__ uint32_t bcast_u(uint32_t v, int lane)
 
 // Shared-memory view of one workgroup.  The pointers carry the LDS address space explicitly so
 // that every access is a ds_* instruction.
-#define PSC_LDS __attribute__((address_space(3)))
 typedef PSC_LDS float lds_f32;
 typedef PSC_LDS volatile float lds_vf32;
 typedef PSC_LDS volatile uint32_t lds_vu32;
@@ -182,28 +182,7 @@ typedef PSC_LDS int lds_i32;
 typedef PSC_LDS volatile uint64_t lds_vu64;
 typedef PSC_LDS uint64_t lds_u64;
 
-// One list entry = (sortable distance key, id) packed in 64 bits, key in the high word, so that
-// the unsigned 64-bit order is the (distance, id) order.  The key is the usual order-preserving
-// map of float bits to unsigned (negative values flip all bits, others flip the sign bit);
-// -0 is folded into +0 first so that equal distances get equal keys.
-__device__ __forceinline__ uint32_t dist_key(float d)
-{
-    const uint32_t u = __float_as_uint(d + 0.0f);
-    return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
-}
-__device__ __forceinline__ float key_dist(uint32_t key)
-{
-    return __uint_as_float(key ^ ((key >> 31) ? 0x80000000u : 0xffffffffu));
-}
-constexpr uint32_t kKeyInf = 0xff800000u;  // dist_key(+infinity)
 static_assert(kPresetWord == kKeyInf, "init_scan_kernel presets the words too");
-constexpr uint64_t kNoEntry = ~0ull;       // above every entry
-__device__ __forceinline__ uint64_t pack_entry(float d, uint32_t id)
-{
-    return ((uint64_t)dist_key(d) << 32) | id;
-}
-__device__ __forceinline__ float entry_dist(uint64_t e) { return key_dist((uint32_t)(e >> 32)); }
-__device__ __forceinline__ uint32_t entry_id(uint64_t e) { return (uint32_t)e; }
 
 template <int M, int TQ>
 struct Lds {
@@ -991,6 +970,7 @@ scan_kernel(ScanArgs a)
         whole_db = t.whole;
         q0 = t.q0;
         nvq = (int)((a.nq - q0) < TQ ? (a.nq - q0) : TQ);
+        if (!tile_wanted(a, q0, nvq)) return;
         slice_begin = t.slice_begin;
         valid_begin = slice_begin;
         slice_end = t.slice_end;
@@ -1352,6 +1332,7 @@ scan_mfma_kernel(ScanArgs a)
         slice = ft.slice;
         q0 = ft.q0;
         nvq = (int)((a.nq - q0) < TQ ? (a.nq - q0) : TQ);
+        if (!tile_wanted(a, q0, nvq)) return;
         slice_begin = ft.slice_begin;
         slice_end = ft.slice_end;
     }
@@ -1601,6 +1582,7 @@ adc_kernel(ScanArgs a)
     const int slice = ft.slice;
     const int64_t q0 = ft.q0;
     const int nvq = (int)((a.nq - q0) < TQ ? (a.nq - q0) : TQ);
+    if (!tile_wanted(a, q0, nvq)) return;
     const int64_t slice_begin = ft.slice_begin;
     const int64_t slice_end = ft.slice_end;
 
@@ -2098,10 +2080,11 @@ scan_pool_kernel(ScanArgs a, float open, int *status, uint32_t *arrived, int64_t
 template <int OWN>
 __global__ void __launch_bounds__(64)
 merge_kernel(const float *__restrict__ part_d, const int64_t *__restrict__ part_i, int nslice, int k,
-             int64_t id_base, const int *__restrict__ status, int64_t *__restrict__ ids,
-             float *__restrict__ dists)
+             int64_t id_base, const int *__restrict__ status, const uint32_t *__restrict__ redo,
+             int64_t *__restrict__ ids, float *__restrict__ dists)
 {
     const int64_t q = blockIdx.x;
+    if (redo != nullptr && redo[q] == 0u) return;  // (ScanArgs::redo)
     const int lane = lane_id();
     const float *pd = part_d + q * nslice * k;
     const int64_t *pi = part_i + q * nslice * k;
@@ -2211,8 +2194,10 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
 template <int KPL>
 __global__ void __launch_bounds__(1024)
 merge_select_kernel(const float *__restrict__ part_d, const int64_t *__restrict__ part_i, int nslice, int k,
-                    bool infinite, const int *__restrict__ status, int64_t *__restrict__ ids, float *__restrict__ dists)
+                    bool infinite, const int *__restrict__ status, const uint32_t *__restrict__ redo,
+                    int64_t *__restrict__ ids, float *__restrict__ dists)
 {
+    if (redo != nullptr && redo[blockIdx.x] == 0u) return;  // (ScanArgs::redo)
     __shared__ uint32_t part[2][16];
     __shared__ __align__(16) uint32_t selk[1024];
     __shared__ int64_t seli[1024];
@@ -2412,28 +2397,28 @@ bool merge_selects(int64_t nq, int nlists, int k)
 // One wave per query; the lists are spread over the lanes, OWN to a lane.
 // infinite: codes at distance +infinity are listed by the selecting merge too (the other always does).
 int launch_merge(const float *part_d, const int64_t *part_i, int64_t nq, int nlists, int k, bool infinite,
-                 const int *status, int64_t *ids, float *dists, hipStream_t s)
+                 const int *status, const uint32_t *redo, int64_t *ids, float *dists, hipStream_t s)
 {
     PSC_REQUIRE(nlists >= 1 && nlists <= 1024, "between 1 and 1024 partial lists per query, got %d", nlists);
     const dim3 grid((unsigned)nq), block(64);
     if (merge_selects(nq, nlists, k)) {
         if ((int64_t)nlists * k <= 8 * 1024)
             hipLaunchKernelGGL(merge_select_kernel<8>, grid, dim3(1024), 0, s, part_d, part_i, nlists, k, infinite, status,
-                               ids, dists);
+                               redo, ids, dists);
         else
             hipLaunchKernelGGL(merge_select_kernel<32>, grid, dim3(1024), 0, s, part_d, part_i, nlists, k, infinite, status,
-                               ids, dists);
+                               redo, ids, dists);
         PSC_HIP_TRY(hipGetLastError());
         return PSC_OK;
     }
     if (nlists <= 64)
-        hipLaunchKernelGGL(merge_kernel<1>, grid, block, 0, s, part_d, part_i, nlists, k, (int64_t)0, status, ids, dists);
+        hipLaunchKernelGGL(merge_kernel<1>, grid, block, 0, s, part_d, part_i, nlists, k, (int64_t)0, status, redo, ids, dists);
     else if (nlists <= 128)
-        hipLaunchKernelGGL(merge_kernel<2>, grid, block, 0, s, part_d, part_i, nlists, k, (int64_t)0, status, ids, dists);
+        hipLaunchKernelGGL(merge_kernel<2>, grid, block, 0, s, part_d, part_i, nlists, k, (int64_t)0, status, redo, ids, dists);
     else if (nlists <= 256)
-        hipLaunchKernelGGL(merge_kernel<4>, grid, block, 0, s, part_d, part_i, nlists, k, (int64_t)0, status, ids, dists);
+        hipLaunchKernelGGL(merge_kernel<4>, grid, block, 0, s, part_d, part_i, nlists, k, (int64_t)0, status, redo, ids, dists);
     else
-        hipLaunchKernelGGL(merge_kernel<16>, grid, block, 0, s, part_d, part_i, nlists, k, (int64_t)0, status, ids, dists);
+        hipLaunchKernelGGL(merge_kernel<16>, grid, block, 0, s, part_d, part_i, nlists, k, (int64_t)0, status, redo, ids, dists);
     PSC_HIP_TRY(hipGetLastError());
     return PSC_OK;
 }
@@ -2624,6 +2609,7 @@ int dispatch_adc(int m, int tq, int nwaves, const ScanArgs &a, int64_t ntiles, s
 // Share of uniformly random b-bit codes within Hamming distance ht of a given one: what the
 // launcher goes by when it picks the kernel (real codes differ, but not by enough to matter for
 // a choice between two kernels that both give the same results).
+}  // namespace
 double random_code_survival(int nbits, int ht)
 {
     double c = 1.0, sum = 0.0;  // c = C(nbits, i) / 2^nbits, built up stepwise
@@ -2635,6 +2621,7 @@ double random_code_survival(int nbits, int ht)
     return sum;
 }
 
+namespace {
 // The tile shapes plan_scan hands out (queries per tile x waves per workgroup).
 template <bool IVF, bool SHARE>
 int dispatch_scan(int m, int tq, int nwaves, const ScanArgs &a, int64_t ntiles, size_t lds, hipStream_t s)
@@ -2824,7 +2811,7 @@ int plan_scan(int m, int64_t nq, int64_t n, int k, int kind, ScanPlan *plan)
 int merge_partial_lists(const float *part_d, const int64_t *part_i, int64_t nq, int nlists, int k, const int *status,
                         int64_t *ids, float *dists, hipStream_t s)
 {
-    return launch_merge(part_d, part_i, nq, nlists, k, false, status, ids, dists, s);
+    return launch_merge(part_d, part_i, nq, nlists, k, false, status, nullptr, ids, dists, s);
 }
 
 int shared_threshold_words(int64_t lists_per_query)
@@ -2894,13 +2881,18 @@ static double pool_merge_cost(int64_t slices, int64_t n, int k, bool preset, dou
     if (!pool_merges_itself(slices, n, k, preset)) return launch;
     return (preset ? 3.0 : 5.5) + (keys <= kRankedKeys ? 1.3e-5 * keys * keys : 6.0);
 }
-static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool dense, bool mfma, bool preset, const ScanPlan &p,
-                            size_t ws_bytes)
+// The estimates in microseconds (pool: infinite where it is not taken at all) and the pool's slices.
+struct ScanTimes {
+    double pool = HUGE_VAL, tiled = 0.0;
+    int64_t slices = 0;
+};
+static ScanTimes scan_times(int m, int64_t nq, int64_t n, int k, int ht, bool dense, bool mfma, bool preset, const ScanPlan &p)
 {
+    ScanTimes times;
     // (a workgroup per query: past 4096 queries the tiles are ahead; past the caches every query reads
     //  memory for itself: 50M codes of 64 bits, 1 query 138 / 179 us, 2 queries 205 / 181, 400M 786 / 644)
     const double bytes = (double)n * m;
-    if (nq > 4096 || bytes > (nq == 1 ? 400e6 : 128e6)) return 0;
+    const bool pool_serves = nq <= 4096 && bytes <= (nq == 1 ? 400e6 : 128e6);
     static constexpr ScanCosts kCosts[2][2] = {
         {{1.4, 6.7, 2.3, 0.11, 0.58, 0.0, 24.0, 0.059, 0.0149, 0.45, 0.68, 0.25},
          {2.0, 8.0, 2.2, 0.126, 0.92, 9.0, 11.0, 0.19, 0.035, 0.76, 0.61, 0.25}},
@@ -2914,7 +2906,7 @@ static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool de
     const double kilo = dense ? (m == 8 ? 0.37 : 0.72) : 0.13;
     double best = 1e300;
     int64_t slices = 0;
-    for (int64_t sN = 1; sN <= 256 && (sN == 1 || (sN * nq <= 256 && sN * 8192 <= n)); sN *= 2) {
+    for (int64_t sN = 1; pool_serves && sN <= 256 && (sN == 1 || (sN * nq <= 256 && sN * 8192 <= n)); sN *= 2) {
         if ((n + sN - 1) / sN > (1 << 24)) continue;
         const double t = std::max((double)((nq * sN + 255) / 256) * (10.0 + 1e-3 * kilo * (double)n / (double)sN), memory) +
                          pool_merge_cost(sN, n, k, preset, 10.0 + 1e-3 * (double)(sN * k));
@@ -2923,15 +2915,17 @@ static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool de
             slices = sN;
         }
     }
-    if (slices == 0) return 0;
-    const double codes = (double)n / (double)slices;
-    const double group = c.group + c.select * std::min(1.0, keep * codes / k) + 0.01 * c.kept * std::min(keep * codes, (double)k) +
-                         1e-3 * codes * (c.code + c.survivor * keep);
-    // (where the queries read more than 1.2 GB in all the estimate is low by about what a merge of their own saves:
-    //  58 queries x 1.5M codes of 128 bits 155 / 125 us in tiles, 44 x 4.4M of 64 bits 168 / 133)
-    const double launch_merge = merge_selects(nq, (int)slices, k) ? 17.0 + 2.1e-3 * (double)(slices * k) : 10.0 + 0.31 * k;
-    const double merged = (double)nq * bytes > 1.2e9 && slices > 1 ? launch_merge : pool_merge_cost(slices, n, k, preset, launch_merge);
-    const double pool = 10.5 + std::max((double)((nq * slices + 255) / 256) * group, memory) + merged;
+    if (slices != 0) {
+        const double codes = (double)n / (double)slices;
+        const double group = c.group + c.select * std::min(1.0, keep * codes / k) + 0.01 * c.kept * std::min(keep * codes, (double)k) +
+                             1e-3 * codes * (c.code + c.survivor * keep);
+        // (where the queries read more than 1.2 GB in all the estimate is low by about what a merge of their own saves:
+        //  58 queries x 1.5M codes of 128 bits 155 / 125 us in tiles, 44 x 4.4M of 64 bits 168 / 133)
+        const double launch_merge = merge_selects(nq, (int)slices, k) ? 17.0 + 2.1e-3 * (double)(slices * k) : 10.0 + 0.31 * k;
+        const double merged = (double)nq * bytes > 1.2e9 && slices > 1 ? launch_merge : pool_merge_cost(slices, n, k, preset, launch_merge);
+        times.pool = 10.5 + std::max((double)((nq * slices + 255) / 256) * group, memory) + merged;
+        times.slices = slices;
+    }
     auto tile_time = [&](double len) {
         const double survivors = keep * len, insertions = std::min(survivors, k * (1.0 + std::log(std::max(1.0, survivors / k))));
         return c.tile + c.insertion * insertions +
@@ -2941,25 +2935,34 @@ static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool de
     const double scan = (double)p.tiles_one / at_a_time * tile_time((double)n) +
                         (p.tiles_one > 0 ? sliced : std::max(1.0, sliced)) * tile_time((double)p.slice_len);
     const double merge = merge_selects(nq, p.nslice, k) ? 13.0 + 5e-4 * (double)p.nslice * k : c.merge_k * k;
-    if (pool > 0.95 * (c.launch + std::max(scan, bytes / 5.8e6) + merge)) return 0;
-    const size_t need = 256 + ((size_t)nq * slices * k * sizeof(float) + 255) / 256 * 256 + (size_t)nq * slices * k * sizeof(int64_t);
-    return need <= ws_bytes ? (int)slices : 0;
+    times.tiled = c.launch + std::max(scan, bytes / 5.8e6) + merge;
+    return times;
+}
+static int pool_scan_slices(int m, int64_t nq, int64_t n, int k, int ht, bool dense, bool mfma, bool preset, const ScanPlan &p,
+                            size_t ws_bytes)
+{
+    const ScanTimes t = scan_times(m, nq, n, k, ht, dense, mfma, preset, p);
+    if (t.slices == 0 || t.pool > 0.95 * t.tiled) return 0;
+    const size_t need = 256 + ((size_t)nq * t.slices * k * sizeof(float) + 255) / 256 * 256 + (size_t)nq * t.slices * k * sizeof(int64_t);
+    return need <= ws_bytes ? (int)t.slices : 0;
 }
 
-int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t nq,
-                const uint8_t *codes_dev, int64_t n, int ht, int k, int64_t skip_first,
-                bool clear_status, bool preset, int64_t *ids_dev, float *dists_dev, void *ws, size_t ws_bytes,
-                hipStream_t s)
+// Which kernel serves a flat scan, and its plan.
+struct ScanRoute {
+    bool dense = false, mfma = false;
+    ScanPlan plan;
+};
+static int scan_route(int m, int64_t nq, int64_t n, int k, int ht, size_t ws_bytes, ScanRoute *r)
 {
-    PSC_REQUIRE(ht >= 0, "ht must be >= 0, got %d", ht);
     // survivor share from which scoring every pair is the faster route: the dense kernel takes the
     // same time whatever the threshold (it tests only the pairs that beat the k-th best), the fused
     // one grows with the survivors (10M x 10k random codes, k = 100, fused / dense: 64-bit codes ht = 29:
     // 52.1 / 68.8 ms, 30: 67.2 / 69.0, 31: 83.7 / 69.0; 128-bit codes ht = 61: 124 / 136, 62: 148 / 136)
     const double dense_from = 0.34;
-    const bool dense = ht >= 8 * m || random_code_survival(8 * m, ht) >= dense_from;
-    ScanPlan p;
+    r->dense = ht >= 8 * m || random_code_survival(8 * m, ht) >= dense_from;
+    ScanPlan &p = r->plan;
     int rc = PSC_EINVAL;
+    const bool dense = r->dense;
     // Matrix-core filter: 9 queries or more and k small enough for its tile of 16 (128 bits: 8).  128 bits: ahead
     // at every threshold that is not the dense route's (10M random codes, 2000 queries, k = 100, matrix cores
     // / xor-popcount; ht = 40: 3.0 / 5.4 ms, 48: 3.2 / 5.5, 56: 8.3 / 10.1, 60: 20.7 / 21.0).  64 bits: so
@@ -2968,7 +2971,8 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
     // x 10M ht = 26: 4.5 / 6.5 ms, 28: 8.2 / 10.1, 29: 10.7 / 12.7; 93 x 55k, k = 1, ht = 28: 67 / 41 us).
     // psc_set_filter_route overrides the rule (for measurements).
     const bool enough = nq >= kMfmaMinQueries;
-    bool mfma = !dense && enough && (m == 16 || random_code_survival(64, ht) < 0.10 || (double)nq * (double)n >= 5e8);
+    bool &mfma = r->mfma;
+    mfma = !dense && enough && (m == 16 || random_code_survival(64, ht) < 0.10 || (double)nq * (double)n >= 5e8);
     const int forced = g_filter_route.load(std::memory_order_relaxed);
     if (forced == PSC_ROUTE_POPCOUNT) mfma = false;
     if (forced == PSC_ROUTE_MFMA) mfma = !dense && enough;
@@ -2980,7 +2984,28 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
     }
     if (!mfma)
         rc = plan_scan(m, nq, n, k, !dense ? kScanFused : (ht >= 8 * m ? kScanDense : kScanDenseFiltered), &p);
+    return rc;
+}
+
+double estimated_scan_time(int m, int64_t nq, int64_t n, int k, int ht, size_t ws_bytes)
+{
+    ScanRoute r;
+    if (scan_route(m, nq, n, k, ht, ws_bytes, &r) != PSC_OK) return 0.0;
+    const ScanTimes t = scan_times(m, nq, n, k, ht, r.dense, r.mfma, true, r.plan);
+    return t.pool > 0.95 * t.tiled ? t.tiled : t.pool;
+}
+
+int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t nq,
+                const uint8_t *codes_dev, int64_t n, int ht, int k, int64_t skip_first,
+                bool clear_status, bool preset, int64_t *ids_dev, float *dists_dev, void *ws, size_t ws_bytes,
+                hipStream_t s, const uint32_t *redo_dev)
+{
+    PSC_REQUIRE(ht >= 0, "ht must be >= 0, got %d", ht);
+    ScanRoute route;
+    int rc = scan_route(m, nq, n, k, ht, ws_bytes, &route);
     if (rc != PSC_OK) return rc;
+    const ScanPlan &p = route.plan;
+    const bool dense = route.dense, mfma = route.mfma;
     if (nq == 0) return PSC_OK;
     PSC_REQUIRE(ids_dev && dists_dev, "null result pointer");
     if (n == 0) {
@@ -3017,13 +3042,14 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
     a.status = (int *)ws;
     a.gthr = (uint32_t *)((char *)ws + 256);
     a.job_q = nullptr;
+    a.redo = redo_dev;
     a.part_d = (float *)((char *)ws + 256 + p.gthr_bytes);
     a.part_i = (int64_t *)((char *)a.part_d + (((size_t)nq * p.nslice * k * sizeof(float) + 255) / 256 * 256));
     // which entry the lists of a many-slice query publish, and which of the published values bounds
     // the k-th best: pub_kth words x pub_r entries >= k, with pub_kth about 0.4 of the words (the
     // value then sits near the (1.3 k)-th best of everything scanned so far)
     set_exchange(a, p.pub_slots, k);
-    const int pool_slices = forced == PSC_ROUTE_AUTO && skip_first < 0
+    const int pool_slices = g_filter_route.load(std::memory_order_relaxed) == PSC_ROUTE_AUTO && skip_first < 0 && redo_dev == nullptr
                                 ? pool_scan_slices(m, nq, n, k, ht, dense, mfma, preset, p, ws_bytes)
                                 : 0;
     if (pool_slices > 0) {
@@ -3058,7 +3084,7 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
         if (rc != PSC_OK) return rc;
         note_route(dense ? "scan_pool_kernel+all" : "scan_pool_kernel", m, 1, 16, a.nslice, nq * a.nslice);
         if (a.nslice == 1 || self_merge) return PSC_OK;
-        return launch_merge(a.part_d, a.part_i, nq, a.nslice, k, infinite, a.status, ids_dev, dists_dev, s);
+        return launch_merge(a.part_d, a.part_i, nq, a.nslice, k, infinite, a.status, nullptr, ids_dev, dists_dev, s);
     }
     const int64_t nwords = nq * p.pub_slots;
     hipLaunchKernelGGL(init_scan_kernel, dim3((unsigned)((nwords + 255) / 256)), dim3(256), 0, s, a.gthr, nwords,
@@ -3096,7 +3122,7 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
     if (rc != PSC_OK) return rc;
     note_route(ht >= nbits ? "adc_kernel" : dense ? "adc_kernel+filter" : mfma ? "scan_mfma_kernel" : "scan_kernel",
                m, p.tq, p.nwaves, p.nslice, p.ntiles);
-    return launch_merge(a.part_d, a.part_i, nq, p.nslice, k, false, a.status, ids_dev, dists_dev, s);
+    return launch_merge(a.part_d, a.part_i, nq, p.nslice, k, false, a.status, redo_dev, ids_dev, dists_dev, s);
 }
 
 // Which filter the grouped inverted-file scan takes.  The matrix-core kernel needs 64-bit codes,
@@ -3194,7 +3220,7 @@ int launch_ivf_scan(int m, int tq, int nwaves, int kpad, size_t lds_bytes, const
     note_route(on_matrix_cores ? (list_tab_dev ? "scan_mfma_kernel+lists" : "scan_mfma_kernel+lists+direct-tables")
                                : (list_tab_dev ? "scan_kernel+lists" : "scan_kernel+lists+direct-tables"),
                m, tq, nwaves, 1, max_tiles);
-    return launch_merge(part_d, part_i, nq, nprobe, k, false, status, ids_dev, dists_dev, s);
+    return launch_merge(part_d, part_i, nq, nprobe, k, false, status, nullptr, ids_dev, dists_dev, s);
 }
 
 int launch_hamming_filter(int m, const uint8_t *qcodes_dev, int64_t nq, const uint8_t *codes_dev,

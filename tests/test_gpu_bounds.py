@@ -1,0 +1,187 @@
+"""The flat search by bounds on the matrix cores: the same answer as the kernels it stands in for, to the bit, over the
+sizes, thresholds and data that its rule and its tiles distinguish (needs an MI355X)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import workloads as W
+from gpu_util import assert_topk_matches
+
+pytestmark = pytest.mark.gpu
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _mixture(n, dim, seed, clusters=40):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    centres = torch.rand((clusters, dim), generator=torch.Generator(device="cuda").manual_seed(7), device="cuda") * 100.0
+    comp = torch.randint(0, clusters, (n,), generator=g, device="cuda")
+    return (torch.randn((n, dim), generator=g, device="cuda") * 15.0 + centres[comp]).round_(), comp
+
+
+@pytest.fixture(scope="module")
+def trained():
+    """Indexes by (dim, m), trained once; codes of 400 003 vectors."""
+    import paper_1609_01882_amd as psc
+    made = {}
+
+    def get(dim, m):
+        if (dim, m) not in made:
+            idx = psc.Index(dim, m)
+            idx.train_pq_device(_mixture(8_000, dim, 1)[0], iters=4, seed=1)
+            idx.optimize_index_assignment(n_iter=30_000, seed=2)
+            made[dim, m] = (idx, idx.encode(_mixture(400_003, dim, 2)[0]))
+        return made[dim, m]
+    return get
+
+
+def _both(psc, idx, q, codes, ht, k, ws=None):
+    """(route, ids, dists) taken by the rule, and by the tiled kernels."""
+    out = []
+    for route in ("auto", "mfma"):
+        psc.set_filter_route(route)
+        ids, d = idx.search(q, codes, ht, k, workspace=ws if route == "auto" else None)
+        torch.cuda.synchronize()
+        out.append((psc.last_scan_route().split()[0], ids, d))
+    psc.set_filter_route("auto")
+    return out
+
+
+# every padded length of a sub-vector and step count; queries at the edges of groups of 32 and tiles; codes at the edges
+# of blocks of 128 and turns of 32; k from 1 to the largest the route takes; thresholds from filtering to none
+@pytest.mark.parametrize("dim,m,n,nq,ht,k", [
+    (128, 8, 400_003, 1025, 64, 10), (128, 8, 262_144, 1500, 24, 100), (128, 8, 262_145, 1537, 28, 256),
+    (96, 8, 399_999, 700, 30, 1), (64, 8, 400_000, 801, 29, 37), (48, 8, 300_031, 1000, 64, 100),
+    (256, 8, 400_003, 600, 32, 100), (192, 8, 200_033, 700, 64, 10),
+    (128, 16, 400_003, 999, 56, 100), (96, 16, 262_143, 1500, 128, 200), (64, 16, 300_097, 640, 128, 10),
+    (256, 16, 400_003, 513, 64, 100), (192, 16, 200_001, 700, 128, 37),
+])
+def test_bounds_and_tiled_kernels_agree(trained, force_route, dim, m, n, nq, ht, k):
+    import paper_1609_01882_amd as psc
+    idx, codes = trained(dim, m)
+    q = _mixture(nq, dim, 3)[0]
+    print(f"dim={dim} m={m} n={n} nq={nq} ht={ht} k={k}", flush=True)
+    (route, ids, d), (other, want_ids, want_d) = _both(psc, idx, q, codes[:n].contiguous(), ht, k)
+    assert route == "bound_scan_kernel" and other != route, (route, other)
+    assert torch.equal(ids, want_ids) and torch.equal(d, want_d)
+
+
+@pytest.mark.parametrize("m,ht", [(8, 64), (8, 26), (16, 128)])
+def test_search_by_bounds_matches_oracle(trained, m, ht):
+    import paper_1609_01882_amd as psc
+    idx, codes = trained(128, m)
+    n, nq, k = 200_007, 600, 20
+    c = codes[:n].contiguous()
+    q = _mixture(nq, 128, 4)[0]
+    ids, d = idx.search(q, c, ht, k)
+    assert psc.last_scan_route().startswith("bound_scan_kernel ")
+    lut, qc = idx.build_lut(q[:60].contiguous())
+    torch.cuda.synchronize()
+    lut64, qc_h, c_h = lut.cpu().numpy().astype(np.float64), qc.cpu().numpy(), c.cpu().numpy()
+    ref = O.scan(lut64, qc_h, c_h, ht, k)
+    assert_topk_matches(ids[:60].cpu().numpy(), d[:60].cpu().numpy(), ref, lut64, qc_h, c_h, ht, what=f"bounds m={m} ht={ht}")
+
+
+@pytest.mark.parametrize("data", ["sorted", "few distinct", "one code", "random codes", "far queries", "near the mean"])
+def test_data_that_the_rounds_do_not_expect(trained, force_route, data):
+    """Databases in the order of their clusters, with thousands of equal codes, of one code; codes and numberings
+    that say nothing about distance; queries far from every code, and at the mean: marked or not, the same answer."""
+    import paper_1609_01882_amd as psc
+    idx, codes = trained(128, 8)
+    n, nq, k, ht = 300_007, 600, 50, 24
+    q = _mixture(nq, 128, 5)[0]
+    c = codes[:n]
+    if data == "sorted":
+        c = c[torch.sort(c[:, 0].to(torch.int64) * 256 + c[:, 1].to(torch.int64)).indices]
+    elif data == "few distinct":
+        c = c[:300].repeat((n + 299) // 300, 1)[:n]
+    elif data == "one code":
+        c = c[:1].repeat(n, 1)
+        ht = 64
+    elif data == "random codes":
+        c = _dev(W.random_codes(n, 8, seed=5))
+    elif data == "far queries":
+        q = q * 50.0 + 3000.0
+        ht = 64
+    elif data == "near the mean":
+        q = q * 1e-3 + q.mean(0, keepdim=True)
+        ht = 64
+    print(data, flush=True)
+    (route, ids, d), (_, want_ids, want_d) = _both(psc, idx, q.contiguous(), c.contiguous(), ht, k)
+    assert route == "bound_scan_kernel", route
+    assert torch.equal(ids, want_ids) and torch.equal(d, want_d)
+
+
+def test_queries_that_are_not_finite_are_left_to_the_other_scan(trained, force_route):
+    import paper_1609_01882_amd as psc
+    idx, codes = trained(128, 8)
+    q = _mixture(700, 128, 6)[0]
+    q[3, 5], q[40, 0], q[41, 127], q[699, 64], q[100], q[200] = float("nan"), float("inf"), -float("inf"), 3e38, 1e25, 1e19
+    (route, ids, d), (_, want_ids, want_d) = _both(psc, idx, q, codes[:250_000].contiguous(), 64, 10)
+    assert route == "bound_scan_kernel", route
+    assert torch.equal(ids, want_ids) and torch.equal(d.view(torch.int32), want_d.view(torch.int32))
+
+
+def test_fewer_codes_within_the_threshold_than_asked_for(trained, force_route):
+    """Queries whose own code is far from every other: some have fewer than k codes within the threshold."""
+    import paper_1609_01882_amd as psc
+    idx, codes = trained(128, 16)
+    q = _mixture(1200, 128, 8)[0]
+    q[::3] = 100.0 - q[::3]
+    (route, ids, d), (_, want_ids, want_d) = _both(psc, idx, q, codes[:300_000].contiguous(), 48, 256)
+    assert route == "bound_scan_kernel", route
+    assert torch.equal(ids, want_ids) and torch.equal(d, want_d)
+
+
+def test_workspaces_and_codebooks_without_the_bounds(trained, force_route):
+    """A workspace with room for the plain search only, one full of another call's words, and a codebook that has no
+    scale."""
+    import paper_1609_01882_amd as psc
+    idx, codes = trained(128, 8)
+    n, nq, k, ht = 300_000, 700, 10, 64
+    c, q = codes[:n].contiguous(), _mixture(nq, 128, 9)[0]
+    full = idx.search_workspace_bytes(nq, n, k)
+    plain = (psc.scan_workspace_bytes(8, nq, n, k) + 255) // 256 * 256 + nq * 8 * 1024 + (nq * 8 + 255) // 256 * 256
+    assert plain < full
+    ws = torch.full((full,), 0xa5, dtype=torch.uint8, device="cuda")
+    ids, d = idx.search(q, c, ht, k, workspace=ws)
+    assert psc.last_scan_route().startswith("bound_scan_kernel ")
+    ids2, d2 = idx.search(q, c, ht, k, workspace=ws[:plain])
+    assert not psc.last_scan_route().startswith("bound_scan_kernel ")
+    torch.cuda.synchronize()
+    assert torch.equal(ids, ids2) and torch.equal(d, d2)
+    flat = psc.Index(128, 8)
+    flat.set_codebook(np.zeros((8, 256, 16), np.float32))
+    ids3, d3 = flat.search(q, c, ht, k)
+    torch.cuda.synchronize()
+    assert not psc.last_scan_route().startswith("bound_scan_kernel ")
+    assert torch.equal(ids3.cpu(), torch.arange(k).repeat(nq, 1))
+
+
+def test_replays_of_a_recorded_search_by_bounds(trained):
+    import paper_1609_01882_amd as psc
+    idx, codes = trained(128, 8)
+    n, nq, k, ht = 250_000, 700, 10, 64
+    c, q = codes[:n].contiguous(), _mixture(nq, 128, 10)[0].clone()
+    ws = torch.empty(idx.search_workspace_bytes(nq, n, k), dtype=torch.uint8, device="cuda")
+    out = (torch.empty((nq, k), dtype=torch.int64, device="cuda"), torch.empty((nq, k), dtype=torch.float32, device="cuda"))
+    idx.search(q, c, ht, k, workspace=ws, out=out)
+    assert psc.last_scan_route().startswith("bound_scan_kernel ")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        idx.search(q, c, ht, k, workspace=ws, out=out)
+    for turn in range(4):
+        q.copy_(_mixture(nq, 128, 20 + turn)[0])
+        out[0].fill_(-7)
+        print(f"replay {turn}", flush=True)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = out[0].clone(), out[1].clone()
+        want = idx.search(q, c, ht, k)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), turn
