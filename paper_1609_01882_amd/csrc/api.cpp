@@ -577,17 +577,17 @@ static int sync_coarse_to_device(const psc_index *idx)
         PSC_HIP_TRY(hipFree(idx->coarse_dev));
         idx->coarse_dev = nullptr;
     }
-    const size_t split_bytes = centroid_split_bytes(idx->nlist, idx->dim);
-    const size_t split_at = (img.size() + 63) / 64 * 64;
-    PSC_HIP_TRY(hipMalloc((void **)&idx->coarse_dev, split_at * sizeof(float) + split_bytes));
+    const size_t image_bytes = centroid_image_bytes(idx->nlist, idx->dim);
+    const size_t image_at = (img.size() + 63) / 64 * 64;
+    PSC_HIP_TRY(hipMalloc((void **)&idx->coarse_dev, image_at * sizeof(float) + image_bytes));
     PSC_HIP_TRY(hipMemcpy(idx->coarse_dev, img.data(), bytes, hipMemcpyHostToDevice));
-    idx->coarse_split = 0;
-    if (split_bytes != 0) {
-        int rc = launch_split_centroids(idx->coarse_dev, idx->coarse_dev + nl * dim, idx->nlist, idx->dim,
-                                        idx->coarse_dev + split_at, nullptr);
+    idx->coarse_image = 0;
+    if (image_bytes != 0) {
+        int rc = launch_centroid_image(idx->coarse_dev, idx->coarse_dev + nl * dim, idx->nlist, idx->dim,
+                                        idx->coarse_dev + image_at, nullptr);
         if (rc != PSC_OK) return rc;
         PSC_HIP_TRY(hipStreamSynchronize(nullptr));
-        idx->coarse_split = split_at;
+        idx->coarse_image = image_at;
     }
     idx->coarse_current = true;
     return PSC_OK;
@@ -770,18 +770,19 @@ int psc_ivf_get_coarse(const psc_index *idx, float *centroids_host)
 }
 
 // The assignment step of the coarse quantizer's trainings, by the kernel that adds vectors to lists unless the
-// layout of the new centroids costs more than it saves: an iteration with float32 products / split search
-// takes 145 / 118 us for 1k rows x 1024 lists of 128 dimensions, 199 / 200 for 20k x 512, 96 / 125 for 20k x
-// 512 of 32 dimensions.  cent [nlist + 1][dim], the mean last; split: scratch of centroid_split_bytes.
-static int assign_to_centroids(const float *x_dev, int64_t n, int dim, const float *cent, int nlist, char *split,
+// layout of the new centroids (some 18 us) costs more than it saves: an iteration with float32 products / float16
+// search takes 80 / 76 us for 1k rows x 300 lists of 128 dimensions, 145 / 90 for 2k x 1024, 94 / 95 for 5k x 256,
+// 118 / 130 for 20k x 256 of 64, 92 / 104 for 20k x 512 of 32, 706 / 433 for 100k x 1024 of 128.  cent [nlist + 1][dim],
+// the mean last; image: scratch of centroid_image_bytes.
+static int assign_to_centroids(const float *x_dev, int64_t n, int dim, const float *cent, int nlist, char *image,
                                int32_t *assign, hipStream_t s)
 {
     const float *mean = cent + (size_t)nlist * dim;
-    if (centroid_split_bytes(nlist, dim) == 0 || !split_assignment_pays(n, dim, nlist) ||
-        (n < 10'000 && (int64_t)nlist * dim < 65536))
+    const int64_t values = (int64_t)nlist * dim;
+    if (centroid_image_bytes(nlist, dim) == 0 || (values < 36'000 && n < 1'000'000'000 / values))
         return launch_nearest_centroid(x_dev, n, dim, cent, nlist, mean, assign, s);
-    PSC_TRY(launch_split_centroids(cent, mean, nlist, dim, split, s));
-    return launch_nearest_centroid_split(x_dev, n, dim, cent, nlist, mean, split, assign, s);
+    PSC_TRY(launch_centroid_image(cent, mean, nlist, dim, image, s));
+    return launch_nearest_centroid_half(x_dev, n, dim, cent, nlist, mean, image, assign, s);
 }
 
 // k-means of the coarse quantizer: assignment on the device (the nearest-centroid kernel),
@@ -813,8 +814,8 @@ int psc_ivf_train_coarse(psc_index *idx, const float *x_host, int64_t n, int nli
     PSC_TRY(scratch.get(&x_dev, (size_t)n * dim));
     PSC_TRY(scratch.get(&c_dev, (size_t)(nlist + 1) * dim));  // + the mean centroid
     PSC_TRY(scratch.get(&a_dev, (size_t)n));
-    char *split = nullptr;
-    PSC_TRY(scratch.get(&split, centroid_split_bytes(nlist, dim)));
+    char *image = nullptr;
+    PSC_TRY(scratch.get(&image, centroid_image_bytes(nlist, dim)));
     PSC_HIP_TRY(hipMemcpy(x_dev, x_host, (size_t)n * dim * sizeof(float), hipMemcpyHostToDevice));
     for (int it = 0; it < iters; ++it) {
         PSC_HIP_TRY(hipMemcpy(c_dev, cent.data(), cent.size() * sizeof(float), hipMemcpyHostToDevice));
@@ -826,7 +827,7 @@ int psc_ivf_train_coarse(psc_index *idx, const float *x_host, int64_t n, int nli
             for (int t = 0; t < dim; ++t) mean[(size_t)t] = (float)(acc[(size_t)t] / nlist);
             PSC_HIP_TRY(hipMemcpy(c_dev + (size_t)nlist * dim, mean.data(), (size_t)dim * sizeof(float), hipMemcpyHostToDevice));
         }
-        PSC_TRY(assign_to_centroids(x_dev, n, dim, c_dev, nlist, split, a_dev, nullptr));
+        PSC_TRY(assign_to_centroids(x_dev, n, dim, c_dev, nlist, image, a_dev, nullptr));
         PSC_HIP_TRY(hipMemcpy(assign.data(), a_dev, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost));
         std::fill(sum.begin(), sum.end(), 0.0);
         std::fill(count.begin(), count.end(), (int64_t)0);
@@ -989,8 +990,8 @@ int psc_ivf_train_coarse_device(psc_index *idx, const float *x_dev, int64_t n, i
     int64_t *rows = nullptr;
     PSC_TRY(scratch.get(&cent, (size_t)(nlist + 1) * dim));  // + the mean centroid
     PSC_TRY(scratch.get(&assign, (size_t)n));
-    char *split = nullptr;
-    PSC_TRY(scratch.get(&split, centroid_split_bytes(nlist, dim)));
+    char *image = nullptr;
+    PSC_TRY(scratch.get(&image, centroid_image_bytes(nlist, dim)));
     PSC_TRY(scratch.get(&sum, (size_t)nlist * dim));
     PSC_TRY(scratch.get(&count, (size_t)nlist));
     PSC_TRY(scratch.get(&key, 1));
@@ -1011,7 +1012,7 @@ int psc_ivf_train_coarse_device(psc_index *idx, const float *x_dev, int64_t n, i
     PSC_TRY(launch_gather_rows(x_dev, dim, rows, nlist, cent, s));
     for (int it = 0; it < iters; ++it) {
         PSC_TRY(launch_mean_centroid(cent, nlist, dim, s));
-        PSC_TRY(assign_to_centroids(x_dev, n, dim, cent, nlist, split, assign, s));
+        PSC_TRY(assign_to_centroids(x_dev, n, dim, cent, nlist, image, assign, s));
         PSC_TRY(launch_coarse_accumulate(x_dev, n, dim, assign, nlist, sum, count, s));
         PSC_HIP_TRY(hipMemcpyAsync(hcount.data(), count, (size_t)nlist * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
         PSC_HIP_TRY(hipStreamSynchronize(s));
@@ -1040,9 +1041,9 @@ int psc_ivf_assign_encode(const psc_index *idx, const float *x_dev, int64_t n, i
     if (n == 0) return PSC_OK;
     PSC_REQUIRE(x_dev && list_no_dev, "null pointer");
     const float *mean = idx->coarse_dev + (size_t)idx->nlist * idx->dim;
-    if (idx->coarse_split != 0 && split_assignment_pays(n, idx->dim, idx->nlist))
-        rc = launch_nearest_centroid_split(x_dev, n, idx->dim, idx->coarse_dev, idx->nlist, mean,
-                                           idx->coarse_dev + idx->coarse_split, list_no_dev,
+    if (idx->coarse_image != 0 && half_assignment_pays(n, idx->dim, idx->nlist))
+        rc = launch_nearest_centroid_half(x_dev, n, idx->dim, idx->coarse_dev, idx->nlist, mean,
+                                           idx->coarse_dev + idx->coarse_image, list_no_dev,
                                            (hipStream_t)stream);
     else
         rc = launch_nearest_centroid(x_dev, n, idx->dim, idx->coarse_dev, idx->nlist, mean, list_no_dev, (hipStream_t)stream);

@@ -192,13 +192,13 @@ int launch_select_probes(const float *dist_dev, int64_t n, int nlist, int nprobe
 // Nearest centroid of each row (lowest number on ties) -> assign [n] (int32).
 int launch_nearest_centroid(const float *x_dev, int64_t n, int dim, const float *cent_dev, int nlist,
                             const float *mu_dev, int32_t *assign_dev, hipStream_t s);
-// The same with the search on bfloat16 parts of the centroids laid out beforehand (dimensions 32, 64, 96,
+// The same with the search on float16 operands of the centroids laid out beforehand (dimensions 32, 64, 96,
 // 128): bytes of the layout (0: no such kernel for the dimension), whether the search is the faster one, the
 // layout, the assignment.
-size_t centroid_split_bytes(int nlist, int dim);
-bool split_assignment_pays(int64_t n, int dim, int nlist);
-int launch_split_centroids(const float *cent_dev, const float *mu_dev, int nlist, int dim, void *image_dev, hipStream_t s);
-int launch_nearest_centroid_split(const float *x_dev, int64_t n, int dim, const float *cent_dev, int nlist,
+size_t centroid_image_bytes(int nlist, int dim);
+bool half_assignment_pays(int64_t n, int dim, int nlist);
+int launch_centroid_image(const float *cent_dev, const float *mu_dev, int nlist, int dim, void *image_dev, hipStream_t s);
+int launch_nearest_centroid_half(const float *x_dev, int64_t n, int dim, const float *cent_dev, int nlist,
                                   const float *mu_dev, const void *image_dev, int32_t *assign_dev, hipStream_t s);
 struct IvfJobBuffers {
     int32_t *hist;       // [nblk][2 nlist]
@@ -322,8 +322,8 @@ struct psc_index {
     // inverted file: coarse centroids (owned) and borrowed views of the caller's lists
     int nlist = 0;
     std::vector<float> coarse_host;  // [nlist][dim]
-    mutable float *coarse_dev = nullptr;  // [nlist][dim], their mean [dim], then launch_split_centroids' layout
-    mutable size_t coarse_split = 0;      // floats before the layout; 0: none for this dimension
+    mutable float *coarse_dev = nullptr;  // [nlist][dim], their mean [dim], then launch_centroid_image' layout
+    mutable size_t coarse_image = 0;      // floats before the layout; 0: none for this dimension
     mutable bool coarse_current = false;
     // the lists' share of the residual tables [nlist][m][256] (launch_list_tables); follows the
     // codebook and the coarse centroids

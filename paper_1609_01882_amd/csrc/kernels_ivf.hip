@@ -617,249 +617,375 @@ nearest_centroid_marked_kernel(const float *__restrict__ x, int64_t n, const flo
 }
 
 // ---------------------------------------------------------------------------------------------
-// Nearest centroid with the search on bfloat16 products and the decision in float32.  The float32
-// products above run at 1/16 of the rate of bfloat16 ones.  Every coordinate is split in two
-// bfloat16 parts (x' = x - mu = xh + xl + rest, |rest| <= 2^-18 |x'|), and of
-//     v(c) = || c' ||^2 - 2 x'.c'
-// the three larger products xh ch + xh cl + xl ch are taken (v_mfma_f32_32x32x16_bf16, float32 sums),
-// the factor -2 sitting in x and the norm coming in as three more coordinates.  The result is off by
-// at most u (|| x' ||^2 + || c' ||^2), u = 2^-14 + 2^-(22 - b) (3 * 2^-18 a product from what the split
-// leaves out, a rounding per addition, and the b low bits of the mantissa that carry the tile number).
-// With c1 the centroid of the smallest value and d1 its distance, || x' ||^2 + v(c1) gives
-// d1^2 <= (1 + 3 u) (|| x' ||^2 + v(c1) + 3 u || x' ||^2); the nearest centroid is no farther, so it and c1 are
-// no longer than || x' || + d1, and the nearest one's value is within
-//     2 u (|| x' ||^2 + min(max || c' ||^2, (|| x' || + d1)^2))
-// of the smallest (the bound by the row keeps one long centroid from widening it for all: 1M x 4096 with
-// one centroid 30 times as far from the mean as the others took as long as without it).  Mostly one
-// centroid is; otherwise the distances of those that are (the close calls) are taken by direct
+// Nearest centroid with the search on float16 products and the decision in float32.  The float32
+// products above run at 1/16 of the rate of float16 ones.  With a = s (x - mu), b = s (c - mu) (s a power
+// of two, the longest b between 2^8 and 2^9), rounded to float16 as a = A + e, b = B + f,
+//     v(c) = (|a|^2 - 2 a.e) + (|b|^2 - 2 b.f) - 2 A.B
+// is |a - b|^2 but for 2 (a - b).(e - f) + 2 e.f: what rounding does to a and b along themselves
+// is in the two brackets, and what is left is as small as the distance.  So with d = |a - b|, E = |e| + |f|,
+//     | v - d^2 | <= 2 d E + 2 |e||f| + u (|a|^2 + |b|^2) + w v,
+// u = 2^-16 (the brackets come in as three bfloat16 parts each; a rounding per addition), w = 2^-(22 - b) for
+// the b low bits of the mantissa that carry the tile number.  |e| is each row's own; |f| is at most the
+// largest of all centroids, and at most r (|b| + 2), r the largest |f| / (|b| + 2), with |b| <= |a| + d (so one
+// long centroid does not widen it for all).  With c1 the centroid of the smallest value, this gives
+// D >= d1; the nearest is no farther, and its value is within twice the bound at D of the smallest.  Mostly
+// one centroid is; otherwise the distances of those that are (the close calls) are taken by direct
 // differences in float32 and the smallest wins, lower number on ties.
 //
 // A lane keeps the two smallest v of its columns.  If a lane's second is a close call too, all
 // centroids of that lane are compared; if that happens in more than a few lanes, or too many lanes have a
 // close call, the tiles are gone through again and every value within reach is listed.  That is the
 // dearer the more there are: a workgroup whose rows have more than kManyNear lanes each with a close call
-// after an eighth of the tiles gives up, and so does a row with kMostLanes at the end or with lengths
-// that squares or sums in float32 do not hold; nearest_centroid_marked_kernel takes those.
-// 1M x 4096 at 128 dimensions (10.6 ms by the float32 products alone): 3.1 ms for the mixture of the
-// workloads, 2.9 with one of the centroids 30 times as far out, 3.0 with squared lengths log-normal, 5.5
-// with every centroid twice; clusters of spread 4 / 2 / 1 / 0.3 around 100 centres in 0 .. 100 (2, 7, 26
-// and 41 close calls a row) 3.3 / 5.8 / 10.5 / 10.0.
+// after an eighth of the tiles gives up, and so does a row with kMostLanes at the end, one with a coordinate
+// that float16 does not hold (64 times the longest centroid), or all if the centroids' squared lengths are no
+// float32; nearest_centroid_marked_kernel takes those.
 //
-// The centroids' parts are laid out once per quantizer in operand order (split_centroids_kernel):
-// per tile of 32 centroids DIM / 16 pairs of 1 KB operands (high, low) and one with the norms.
-// One workgroup = 4 waves x 32 rows; the rows' parts sit in registers, tiles go through LDS, two in
-// turn.  Bound by the matrix cores: 3 DIM / 16 + 1 products of 32 cycles per 32 x 32 outputs against 48
-// vector instructions (tile number into the mantissa, minimum, median).
+// The centroids' operands are laid out once per quantizer (centroid_operands_kernel): per tile of 32
+// centroids DIM / 16 of 1 KB and one with the norms.  One workgroup = 4 waves x G groups of 32 rows; the rows'
+// operands sit in registers, tiles go through LDS, two in turn; a wave's operands of the next tile are read and the
+// values of one group looked at while the products of the next group are under way.  DIM / 16 + 1 products of
+// 32 cycles per 32 x 32 outputs stand against 48 vector instructions (tile number into the mantissa, minimum,
+// median) and (DIM / 16 + 1) KB read from LDS, which serve all G groups.  1M x 4096 at 128 dimensions: 1.19 ms
+// (2.64 with three bfloat16 products a coordinate, 10.6 by the float32 products alone); the products alone take
+// 0.68 at the rate registers give (1.73 PFLOP/s); with half of the vector instructions 1.00.  300k rows x 4096:
+// with one of the centroids 30 times as far out 0.40 (before: 0.88), squared lengths log-normal 0.45 (0.90), every
+// centroid twice 0.88 (1.75), clusters of spread 4 / 2 / 1 / 0.3 around 100 centres in 0 .. 100: 0.43 / 0.54 /
+// 0.89 / 3.08 (0.91 / 1.12 / 3.54 / 3.13).
 // ---------------------------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float part_of(float v, float &rest)
+// v in three bfloat16 parts at p[0 .. 2] (2^-24 of it are left out)
+__device__ __forceinline__ void three_parts(float v, __bf16 *p)
 {
-    const __bf16 h = (__bf16)v;  // nearest even
-    rest = v - (float)h;         // (exact)
-    return (float)h;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        p[i] = (__bf16)v;  // nearest even
+        v -= (float)p[i];  // (exact)
+    }
 }
 
-// tile_max2: per tile the largest squared length of its centroids (rounded up; one that is not a number stays
-// on top and leaves every row undecided).
+// Nearest float16, 0 where that is no normal number (whatever the matrix cores make of those).
+__device__ __forceinline__ _Float16 half_of(float v)
+{
+    return __builtin_fabsf(v) < 6.103515625e-5f ? (_Float16)0.f : (_Float16)v;
+}
+
+// Largest of n floats that are not negative, by one wave, as bits: these are ordered as the floats are, one
+// that is not a number above all others.
+__device__ __forceinline__ uint32_t largest_bits(const float *p, int n)
+{
+    uint32_t top = 0u;
+    for (int i = (int)threadIdx.x & 63; i < n; i += 64) top = max(top, __float_as_uint(p[i]));
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) top = max(top, (uint32_t)__shfl_xor((int)top, off, 64));
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)top);
+}
+
+// The power of two s by the bits of the largest squared length: s sqrt(top) in [2^8, 2^9).
+__device__ __forceinline__ float scale_of(uint32_t top)
+{
+    if (top == 0u || top >= 0x7f800000u) return 1.f;
+    const int e = (int)(top >> 23) - 127;  // top < 2^(e + 1)
+    return __uint_as_float((uint32_t)(127 + 9 - ((e + 2) >> 1)) << 23);
+}
+
+// Per tile, rounded up: the largest squared length (before scaling) ...
 template <int DIM>
 __global__ void __launch_bounds__(64)
-split_centroids_kernel(const float *__restrict__ cent, const float *__restrict__ mu, int nlist,
-                       bf16x8 *__restrict__ image, float *__restrict__ tile_max2)
+centroid_lengths_kernel(const float *__restrict__ cent, const float *__restrict__ mu, int nlist,
+                        float *__restrict__ tile_max2)
+{
+    const int lane = threadIdx.x, half = lane >> 5, c = blockIdx.x * 32 + (lane & 31);
+    double norm = 0.0;
+    if (c < nlist) {
+#pragma unroll
+        for (int i = 0; i < DIM / 8; ++i) {
+            const float4 a = *(const float4 *)(cent + (int64_t)c * DIM + 8 * i + 4 * half);
+            const float4 b = *(const float4 *)(mu + 8 * i + 4 * half);
+            const float e[4] = {a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w};
+#pragma unroll
+            for (int p = 0; p < 4; ++p) norm += (double)e[p] * (double)e[p];
+        }
+    }
+    norm += __shfl_xor(norm, 32, 64);
+    uint32_t top = __float_as_uint((float)norm * 1.0001f);
+#pragma unroll
+    for (int off = 16; off >= 1; off >>= 1) top = max(top, (uint32_t)__shfl_xor((int)top, off, 64));
+    if (lane == 0) tile_max2[blockIdx.x] = __uint_as_float(top);
+}
+
+// ... and, scaled, the largest |f| and |f| / (|b| + 2), with the operands.
+template <int DIM>
+__global__ void __launch_bounds__(64)
+centroid_operands_kernel(const float *__restrict__ cent, const float *__restrict__ mu, int nlist,
+                         const float *__restrict__ tile_max2, u32x4 *__restrict__ image,
+                         float *__restrict__ tile_rest, float *__restrict__ tile_ratio)
 {
     constexpr int KS = DIM / 16;
     const int tile = blockIdx.x, lane = threadIdx.x, half = lane >> 5, c = tile * 32 + (lane & 31);
-    bf16x8 *out = image + (int64_t)tile * (2 * KS + 1) * 64;
-    float4 v[2 * KS], m[2 * KS];
+    float4 v[2 * KS], mean[2 * KS];
 #pragma unroll
     for (int i = 0; i < 2 * KS; ++i) {
         const int d = 16 * (i >> 1) + 8 * half + 4 * (i & 1);
         v[i] = c < nlist ? *(const float4 *)(cent + (int64_t)c * DIM + d) : make_float4(0.f, 0.f, 0.f, 0.f);
-        m[i] = c < nlist ? *(const float4 *)(mu + d) : make_float4(0.f, 0.f, 0.f, 0.f);
+        mean[i] = c < nlist ? *(const float4 *)(mu + d) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    double norm = 0.0;
+    const float scale = scale_of(largest_bits(tile_max2, (int)gridDim.x));
+    u32x4 *out = image + (int64_t)tile * (KS + 1) * 64;
+    double norm = 0.0, rest2 = 0.0, along = 0.0;
 #pragma unroll
     for (int t = 0; t < KS; ++t) {
-        bf16x8 h, l;
+        f16x8 h;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const float4 a = v[2 * t + i], b = m[2 * t + i];
-            const float e[4] = {a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w};
+            const float4 a = v[2 * t + i], m = mean[2 * t + i];
+            const float e[4] = {a.x - m.x, a.y - m.y, a.z - m.z, a.w - m.w};
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
-                float r1, r2;
-                h[4 * i + p] = (__bf16)part_of(e[p], r1);
-                l[4 * i + p] = (__bf16)part_of(r1, r2);
-                norm += (double)e[p] * (double)e[p];
+                const float b = e[p] * scale;  // (exact, or below 2^-80)
+                h[4 * i + p] = half_of(b);
+                const float f = b - (float)h[4 * i + p];
+                norm += (double)b * (double)b;
+                rest2 += (double)f * (double)f;
+                along += (double)b * (double)f;
             }
         }
-        out[(2 * t) * 64 + lane] = h;
-        out[(2 * t + 1) * 64 + lane] = l;
+        out[t * 64 + lane] = __builtin_bit_cast(u32x4, h);
     }
     norm += __shfl_xor(norm, 32, 64);
-    bf16x8 n;
+    rest2 += __shfl_xor(rest2, 32, 64);
+    along += __shfl_xor(along, 32, 64);
+    __bf16 n[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) n[i] = (__bf16)0.f;
     if (half == 0) {  // (places past the last centroid: farther than anything finite)
-        float r = c < nlist ? (float)norm : 3.3e38f;
+        three_parts(c < nlist ? (float)(norm - 2.0 * along) : 1e30f, n);
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            float rest;
-            n[i] = (__bf16)part_of(r, rest);
-            r = c < nlist ? rest : 0.f;
-        }
+        for (int i = 3; i < 6; ++i) n[i] = (__bf16)1.f;
     }
-    out[(2 * KS) * 64 + lane] = n;
-    // (bits of floats that are not negative are ordered as the floats are)
-    uint32_t top = c < nlist ? __float_as_uint((float)norm * 1.0001f) : 0u;
+    bf16x8 ops;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ops[i] = n[i];
+    out[KS * 64 + lane] = __builtin_bit_cast(u32x4, ops);
+    const float rest = __builtin_amdgcn_sqrtf((float)rest2) * 1.0001f;
+    uint32_t most = __float_as_uint(rest);
+    uint32_t ratio = __float_as_uint(rest * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf((float)norm) * 0.9999f + 2.f) * 1.0001f);
 #pragma unroll
     for (int off = 16; off >= 1; off >>= 1) {
-        const uint32_t o = (uint32_t)__shfl_xor((int)top, off, 64);
-        top = o > top ? o : top;
+        most = max(most, (uint32_t)__shfl_xor((int)most, off, 64));
+        ratio = max(ratio, (uint32_t)__shfl_xor((int)ratio, off, 64));
     }
-    if (lane == 0) tile_max2[tile] = __uint_as_float(top);
+    if (lane == 0) {
+        tile_rest[tile] = __uint_as_float(most);
+        tile_ratio[tile] = __uint_as_float(ratio);
+    }
 }
 
-constexpr int kSplitWaves = 4;
+constexpr int kHalfWaves = 4;
+// Rows from which a wave takes two groups: below, twice the workgroups weigh more (one group / two, us, 4096
+// lists of 128 dimensions: 20k rows 90 / 107, 50k 122 / 123, 100k 192 / 182, 1M 1341 / 1188; 1024 of 64, 20k 25 / 33,
+// 100k 49 / 47, 500k 164 / 155).
+constexpr int64_t kTwoGroupRows = 100'000;
 constexpr int kPairList = 512;    // pairs a wave lists before it takes their distances
-constexpr int kManyNear = 3;      // (some 25 close calls a row in all: listing them takes as long as the float32
-                                  //  products, 8.7 / 10.0 ms for 1M x 4096, 1.35 / 1.24 for 100k)
+constexpr int kManyNear = 3;      // (some 25 close calls a row in all: listing them takes about as long as the
+                                  //  float32 products)
 constexpr int kMostLanes = 28;    // of 32
 constexpr int kDeepLanes = 16;    // of a workgroup's rows: comparing all centroids of so many lanes takes as long
                                   // as going through the tiles again
-// (Three waves per SIMD hide the ends of the workgroups' turns: two take 3.15 ms for the mixture, 0.43 instead
-//  of 0.33 with 256 centroids.)
-template <int DIM>
-__global__ void __launch_bounds__(kSplitWaves * 64) __attribute__((amdgpu_waves_per_eu(3)))
-nearest_centroid_split_kernel(const float *__restrict__ x, int64_t n, const float *__restrict__ cent,
-                              const float *__restrict__ mu, const bf16x8 *__restrict__ image,
-                              const float *__restrict__ tile_max2, int nlist, int tile_bits,
-                              int32_t *__restrict__ assign)
+template <int DIM, int G>
+__global__ void __launch_bounds__(kHalfWaves * 64) __attribute__((amdgpu_waves_per_eu(G == 1 ? 3 : 2)))
+nearest_centroid_half_kernel(const float *__restrict__ x, int64_t n, const float *__restrict__ cent,
+                             const float *__restrict__ mu, const u32x4 *__restrict__ image,
+                             const float *__restrict__ tile_max2, int nlist, int tile_bits,
+                             int32_t *__restrict__ assign)
 {
     constexpr int KS = DIM / 16;
-    constexpr int kThreads = kSplitWaves * 64;
-    constexpr int kOps = (2 * KS + 1) * 64;  // 16-byte entries of a tile
-    __shared__ __align__(16) u32x4 tile[2][kOps];
-    __shared__ float xnorm[kSplitWaves][32];
-    __shared__ float limit[kSplitWaves][32];        // rows gone through again: what counts as a close call
-    __shared__ unsigned long long nearest[kSplitWaves][32];  // (distance, number) of the best listed pair
-    __shared__ uint32_t pairs[kSplitWaves][kPairList];  // row << 16 | centroid
+    constexpr int kThreads = kHalfWaves * 64;
+    constexpr int kRows = 32 * G;            // of a wave
+    constexpr int kOps = (KS + 1) * 64;      // 16-byte entries of a tile
+    constexpr int kTurns = (kOps + kThreads - 1) / kThreads;
+    __shared__ __align__(16) u32x4 tile[2][kTurns * kThreads];
+    __shared__ float row_norm[kHalfWaves][kRows], row_rest[kHalfWaves][kRows];  // |a|^2, |e|
+    __shared__ float limit[kHalfWaves][kRows];  // what counts as a close call
+    __shared__ unsigned long long nearest[kHalfWaves][kRows];  // (distance, number) of the best listed pair
+    __shared__ uint16_t near_tile[kHalfWaves][kRows][32];      // of the lanes whose smallest value is a close call
+    __shared__ uint32_t pairs[kHalfWaves][kPairList];          // row << 16 | centroid
     __shared__ int tally[2];
     const int tid = (int)threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, col = lane & 31;
-    const int64_t r0 = (int64_t)blockIdx.x * (32 * kSplitWaves) + wave * 32;
+    const int64_t r0 = ((int64_t)blockIdx.x * kHalfWaves + wave) * kRows;
     const int ntiles = (nlist + 31) / 32;
-    uint32_t top = 0u;  // (as in split_centroids_kernel)
-    for (int i = lane; i < ntiles; i += 64) top = max(top, __float_as_uint(tile_max2[i]));
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) top = max(top, (uint32_t)__shfl_xor((int)top, off, 64));
-    const float cmax2 = __uint_as_float(__builtin_amdgcn_readfirstlane((int)top));
-    const float unit = 6.103515625e-5f + __uint_as_float((uint32_t)(127 - 22 + tile_bits) << 23);
+    const uint32_t top = largest_bits(tile_max2, ntiles);
+    const float scale = scale_of(top);
+    // (rest_max is not a number where the centroids' lengths are none: nothing is then within reach)
+    const float cmax2 = __uint_as_float(top) * scale * scale;
+    const float rest_max = top < 0x7f800000u ? __uint_as_float(largest_bits(tile_max2 + ntiles, ntiles)) : __builtin_nanf("");
+    const float ratio = __uint_as_float(largest_bits(tile_max2 + 2 * ntiles, ntiles));
+    constexpr float kSum = 1.52587890625e-5f;
+    const float kTag = __uint_as_float((uint32_t)(127 - 22 + tile_bits) << 23);
 
-    bf16x8 xh[KS], xl[KS], one;
-    {
-        const int64_t r = r0 + col;
+    f16x8 xh[G][KS];
+    bf16x8 one[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const int64_t r = r0 + 32 * g + col;
         const float *xr = x + (r < n ? r : n - 1) * DIM + 8 * half;
-        float norm = 0.f;
+        float norm = 0.f, rest2 = 0.f, along = 0.f;
 #pragma unroll
         for (int t = 0; t < KS; ++t) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const float v = xr[16 * t + i] - mu[16 * t + 8 * half + i];
-                float r1, r2;
+                const float v = (xr[16 * t + i] - mu[16 * t + 8 * half + i]) * scale;
+                xh[g][t][i] = half_of(-2.f * v);
+                const float rest = fmaf(-2.f, v, -(float)xh[g][t][i]);  // (-2 e)
                 norm = fmaf(v, v, norm);
-                xh[t][i] = (__bf16)part_of(-2.f * v, r1);
-                xl[t][i] = (__bf16)part_of(r1, r2);
+                rest2 = fmaf(rest, rest, rest2);
+                along = fmaf(v, rest, along);
             }
         }
         norm += __shfl_xor(norm, 32, 64);
+        rest2 += __shfl_xor(rest2, 32, 64);
+        along += __shfl_xor(along, 32, 64);
+        __bf16 p[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) p[i] = (__bf16)(half == 0 && i < 3 ? 1.f : 0.f);
         if (half == 0) {
-            xnorm[wave][col] = norm;
-            nearest[wave][col] = ~0ull;
-            limit[wave][col] = __builtin_nanf("");  // (no value is within it)
+            three_parts(norm + along, p + 3);
+            row_norm[wave][32 * g + col] = norm;
+            row_rest[wave][32 * g + col] = __builtin_amdgcn_sqrtf(rest2) * 0.5005f;
+            nearest[wave][32 * g + col] = ~0ull;
         }
-        if (tid < 2) tally[tid] = 0;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) one[i] = (__bf16)(half == 0 && i < 3 ? 1.f : 0.f);
+        for (int i = 0; i < 8; ++i) one[g][i] = p[i];
     }
-    constexpr int kPer = 2 * KS * 64 / kThreads;  // whole turns of the workgroup, and one of wave 0 for the norms
-    static_assert(kPer * kThreads == 2 * KS * 64, "operands of a tile");
-    u32x4 hold[kPer], hold_norm = {0u, 0u, 0u, 0u};
+    if (tid < 2) tally[tid] = 0;
+    u32x4 hold[kTurns];
     auto fetch = [&](int t) {
-        const u32x4 *src = (const u32x4 *)image + (int64_t)t * kOps;
 #pragma unroll
-        for (int i = 0; i < kPer; ++i) hold[i] = src[i * kThreads + tid];
-        if (tid < 64) hold_norm = src[kPer * kThreads + tid];
+        for (int i = 0; i < kTurns; ++i)
+            hold[i] = image[(int64_t)t * kOps + min(i * kThreads + tid, kOps - 1)];
     };
     auto put = [&](int buf) {
 #pragma unroll
-        for (int i = 0; i < kPer; ++i) tile[buf][i * kThreads + tid] = hold[i];
-        if (tid < 64) tile[buf][kPer * kThreads + tid] = hold_norm;
+        for (int i = 0; i < kTurns; ++i)
+            tile[buf][i * kThreads + tid] = hold[i];
     };
-    // Tiles [from, to), the first of which waits in LDS, as does tile `to` afterwards: see(t, values).
+    float best[G][16], next[G][16];
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) best[g][v] = next[g][v] = __builtin_inff();
+    // Tiles [from, to): see(t, group, values).  The operands of the first are held and the tile after it waits in
+    // LDS, as do those of `to` and the tile after that at the end.  The values of one group are looked at while
+    // the products of the next are under way.
+    u32x4 op[KS + 1];
     auto sweep = [&](int from, int to, auto &&see) {
+        f32x16 last;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) last[v] = 1e30f;  // (beyond every reach)
         for (int t = from; t < to; ++t) {
-            fetch(t + 1 < ntiles ? t + 1 : t);
-            const bf16x8 *b = (const bf16x8 *)tile[t & 1];
-            f32x16 acc;
+            fetch(min(t + 2, ntiles - 1));
+            const u32x4 *b = tile[(t + 1) & 1];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-            bf16x8 op[2 * KS + 1];  // all operands asked for before the first product
+            for (int g = 0; g < G; ++g) {
+                f32x16 acc;
 #pragma unroll
-            for (int s = 0; s < 2 * KS + 1; ++s) op[s] = b[(s == 0 ? 2 * KS : s - 1) * 64 + lane];
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(one, op[0], acc, 0, 0, 0);
+                for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(one[g], __builtin_bit_cast(bf16x8, op[KS]), acc, 0, 0, 0);
 #pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                const bf16x8 ch = op[1 + 2 * s], cl = op[2 + 2 * s];
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[s], ch, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl[s], ch, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[s], cl, acc, 0, 0, 0);
+                for (int s = 0; s < KS; ++s)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(xh[g][s], __builtin_bit_cast(f16x8, op[s]), acc, 0, 0, 0);
+                if (g == G - 1) {
+                    op[KS] = b[KS * 64 + lane];
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) op[s] = b[s * 64 + lane];
+                }
+                see(g > 0 ? t : max(t - 1, 0), g > 0 ? g - 1 : G - 1, last);
+                asm volatile("" : "+v"(acc));
+                last = acc;
+#pragma unroll
+                for (int s = 0; s < KS + 1; ++s) {
+                    __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                    if (g == G - 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x2, (48 + KS) / (KS + 1), 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
-            see(t, acc);
-            put((t + 1) & 1);  // (after the last tile: a copy nobody reads)
+            put(t & 1);
             __syncthreads();
         }
+        see(to > 0 ? to - 1 : 0, G - 1, last);
     };
     uint32_t keep = ~((1u << tile_bits) - 1u);
     float low = -__builtin_inff();
     asm("" : "+v"(keep), "+v"(low));
-    float best[16], next[16];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) best[v] = next[v] = __builtin_inff();
-    auto two_smallest = [&](int t, const f32x16 &acc) {
+    auto two_smallest = [&](int t, int g, const f32x16 &acc) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const float d = __uint_as_float((__float_as_uint(acc[v]) & keep) | (uint32_t)t);
-            next[v] = __builtin_amdgcn_fmed3f(d, best[v], next[v]);
-            best[v] = __builtin_amdgcn_fmed3f(d, best[v], low);  // (the smaller of the two)
+            next[g][v] = __builtin_amdgcn_fmed3f(d, best[g][v], next[g][v]);
+            best[g][v] = __builtin_amdgcn_fmed3f(d, best[g][v], low);  // (the smaller of the two)
+            asm volatile("" : "+v"(best[g][v]), "+v"(next[g][v]));     // (here, not after the products)
         }
     };
-    // the largest value of a close call for the row of register v, by the smallest value of its 32 lanes
-    auto reach_of = [&](int v, float bv) {
-        float least = bv;
+    // limit[]: the largest value of a close call for each row, by the smallest of its values.  Halving the
+    // registers with every step across the lanes leaves lane (half, c) with the row of register c of its half.
+    auto set_limits = [&]() {
+        float least[16 * G];
 #pragma unroll
-        for (int off = 16; off >= 1; off >>= 1) least = fminf(least, __shfl_xor(least, off, 64));
-        const float x2 = xnorm[wave][8 * (v / 4) + 4 * half + v % 4];
-        const float d2 = (fmaxf(least + x2, 0.f) + 3.f * unit * x2) * (1.f + 3.f * unit);
-        const float len = __builtin_amdgcn_sqrtf(x2) + __builtin_amdgcn_sqrtf(d2);
-        const float reach = least + 2.f * unit * (x2 + fminf(cmax2, 1.001f * len * len));
-        // (below that all values and the places past the last centroid are finite; no number if the row is none)
-        return x2 + cmax2 < 1e37f ? reach : __builtin_nanf("");
+        for (int i = 0; i < 16 * G; ++i) least[i] = best[i >> 4][i & 15];
+#pragma unroll
+        for (int r = 8 * G; r >= 1; r >>= 1)
+#pragma unroll
+            for (int i = 0; i < r; ++i) {
+                const bool up = (lane & r) != 0;
+                const float mine = up ? least[i + r] : least[i], other = up ? least[i] : least[i + r];
+                least[i] = fminf(mine, __shfl_xor(other, r, 64));
+            }
+        if (G == 1) least[0] = fminf(least[0], __shfl_xor(least[0], 16, 64));
+        const int reg = lane & (16 * G - 1), row = 32 * (reg >> 4) + 8 * (reg >> 2 & 3) + 4 * half + (reg & 3);
+        const float x2 = row_norm[wave][row], e = row_rest[wave][row], len = __builtin_amdgcn_sqrtf(x2);
+        const float seen = fmaxf(least[0], 0.f) + kTag * __builtin_fabsf(least[0]);
+        auto farthest = [&](float f, float b2) {  // D from d^2 <= seen + 2 d (e + f) + 2 e f + u (x2 + b2)
+            return (e + f + __builtin_amdgcn_sqrtf((e + f) * (e + f) + seen + 2.f * e * f + kSum * (x2 + b2))) * 1.001f;
+        };
+        const float reach_len = len + farthest(rest_max, cmax2);
+        const float f = fminf(rest_max, ratio * (reach_len + 2.f)), b2 = fminf(cmax2, reach_len * reach_len);
+        const float d = farthest(f, b2);
+        const float reach = least[0] + 2.002f * (2.f * d * (e + f) + 2.f * e * f + kSum * (x2 + b2) + 2.f * kTag * d * d);
+        // (rows that float16 does not hold have an |e| that is no finite number)
+        limit[wave][row] = x2 < 1e20f && e < 1e20f && rest_max < 1e20f ? reach : __builtin_nanf("");
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     };
+    auto row_of = [&](int g, int v) { return 32 * g + 8 * (v / 4) + 4 * half + v % 4; };
 
-    fetch(0);
-    put(0);
-    __syncthreads();
+    auto begin = [&]() {
+        fetch(0);
+        put(0);
+        fetch(min(1, ntiles - 1));
+        put(1);
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < KS + 1; ++s) op[s] = tile[0][s * 64 + lane];
+        __syncthreads();  // (the first turn of a sweep writes there)
+    };
+    begin();
     const int early = ntiles >= 16 ? ntiles / 8 : 0;
     sweep(0, early, two_smallest);
     if (early > 0) {
         int lanes = 0;
+        set_limits();
 #pragma unroll
-        for (int v = 0; v < 16; ++v) lanes += __builtin_popcountll(__ballot(best[v] <= reach_of(v, best[v])));
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                lanes += __builtin_popcountll(__ballot(best[g][v] <= limit[wave][row_of(g, v)]));
         if (lane == 0) atomicAdd(&tally[0], lanes);
         __syncthreads();
-        if (tally[0] > kManyNear * 32 * kSplitWaves) {
-            if (lane < 32 && r0 + lane < n) assign[r0 + lane] = kUndecided;
+        if (tally[0] > kManyNear * kRows * kHalfWaves) {
+            if (lane < kRows && r0 + lane < n) assign[r0 + lane] = kUndecided;
             return;
         }
     }
@@ -907,79 +1033,66 @@ nearest_centroid_split_kernel(const float *__restrict__ x, int64_t n, const floa
         npairs += __builtin_popcountll(m);
     };
 
-    // every row: register v of half h is row 8 (v / 4) + 4 h + v % 4
-    float reaches[16];
+    // Lane r < kRows gathers of row r which lanes' smallest, and second smallest, value is a close call.
+    uint32_t near = 0u, deep = 0u;
+    set_limits();
 #pragma unroll
-    for (int v = 0; v < 16; ++v) reaches[v] = reach_of(v, best[v]);
-    auto each_register = [&](auto &&f) {
-#pragma unroll 1
+    for (int g = 0; g < G; ++g)
+#pragma unroll
         for (int v = 0; v < 16; ++v) {
-            float bv = best[0], nv = next[0], reach = reaches[0];
-#pragma unroll
-            for (int i = 1; i < 16; ++i) {
-                bv = v == i ? best[i] : bv;
-                nv = v == i ? next[i] : nv;
-                reach = v == i ? reaches[i] : reach;
-            }
-            f(v, bv, nv, reach);
+            const int row = row_of(g, v), upper = 32 * g + 8 * (v / 4) + v % 4;
+            const float reach = limit[wave][row];
+            const uint64_t near2 = __ballot(best[g][v] <= reach), deep2 = __ballot(next[g][v] <= reach);
+            if (best[g][v] <= reach) near_tile[wave][row][col] = (uint16_t)(__float_as_uint(best[g][v]) & ~keep);
+            near = lane == upper ? (uint32_t)near2 : lane == upper + 4 ? (uint32_t)(near2 >> 32) : near;
+            deep = lane == upper ? (uint32_t)deep2 : lane == upper + 4 ? (uint32_t)(deep2 >> 32) : deep;
         }
-    };
-    int decided = kUndecided;  // lane l < 32: what is known of row l
-    int deep_lanes = 0;
-    each_register([&](int v, float bv, float nv, float reach) {
-        const uint64_t near2 = __ballot(bv <= reach), deep2 = __ballot(nv <= reach);
-        const int mine = (int)(__float_as_uint(bv) & ~keep) * 32 + col;
-#pragma unroll 1
-        for (int h = 0; h < 2; ++h) {
-            const uint32_t near = (uint32_t)(near2 >> (32 * h)), deep = (uint32_t)(deep2 >> (32 * h));
-            const int row = 8 * (v / 4) + 4 * h + v % 4;
-            if (r0 + row >= n) continue;
-            if (deep != 0u) {
-                if (__builtin_popcount(near) >= kMostLanes) continue;  // (undecided)
-                deep_lanes += __builtin_popcount(deep);
-                if (half == h && col == 0) limit[wave][row] = reach;
-            } else if ((near & (near - 1u)) != 0u) {
-                list_pairs(half == h && (near >> col & 1u) != 0u, row, mine);
-            } else if (near != 0u) {
-                const int winner = __builtin_amdgcn_readlane(mine, 32 * h + __builtin_ctz(near));
-                if (lane == row && winner < nlist) decided = winner;
-            }
-        }
-    });
-    if (deep_lanes != 0 && lane == 0) atomicAdd(&tally[1], deep_lanes);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    int decided = kUndecided;  // lane r: what is known of row r
+    const bool is_row = lane < kRows && r0 + lane < n;
+    const int count = __builtin_popcount(near);
+    const bool again = is_row && deep != 0u && count < kMostLanes;
+    if (is_row && deep == 0u && count == 1) {
+        const int at = __builtin_ctz(near), winner = (int)near_tile[wave][lane][at] * 32 + at;
+        if (winner < nlist) decided = winner;
+    }
+    if (again) atomicAdd(&tally[1], __builtin_popcount(deep));
+    if (lane < kRows && !again) limit[wave][lane] = __builtin_nanf("");  // (no value is within it)
+    for (uint64_t rows = __ballot(is_row && deep == 0u && count > 1); rows != 0; rows &= rows - 1u) {
+        const int row = __builtin_ctzll(rows);
+        const uint32_t lanes = (uint32_t)__builtin_amdgcn_readlane((int)near, row);
+        list_pairs(half == 0 && (lanes >> col & 1u) != 0u, row, (int)near_tile[wave][row][col] * 32 + col);
+    }
     __syncthreads();
-    const int deep_all = tally[1];
-    if (deep_all > kDeepLanes) {
+    if (tally[1] > kDeepLanes) {
         asm("" : "+s"(image));  // (addresses kept from above would go to scratch memory)
-        float lim[16];
+        float lim[G][16];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) lim[v] = limit[wave][8 * (v / 4) + 4 * half + v % 4];
-        fetch(0);
-        put(0);
-        __syncthreads();
-        sweep(0, ntiles, [&](int t, const f32x16 &acc) {
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) lim[g][v] = limit[wave][row_of(g, v)];
+        begin();
+        sweep(0, ntiles, [&](int t, int g, const f32x16 &acc) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const bool close = __uint_as_float((__float_as_uint(acc[v]) & keep) | (uint32_t)t) <= lim[v];
-                if (__ballot(close) != 0) list_pairs(close, 8 * (v / 4) + 4 * half + v % 4, t * 32 + col);
+                const bool close = __uint_as_float((__float_as_uint(acc[v]) & keep) | (uint32_t)t) <= lim[g][v];
+                if (__ballot(close) != 0) list_pairs(close, row_of(g, v), t * 32 + col);
             }
         });
-    } else if (deep_lanes != 0) {
-        each_register([&](int v, float bv, float nv, float) {
-            const int own = 8 * (v / 4) + 4 * half + v % 4;
-            const bool near = bv <= limit[wave][own];
-            uint64_t deep = __ballot(nv <= limit[wave][own]);
-            if (__ballot(near) == 0) return;
-            list_pairs(near && (deep >> lane & 1u) == 0, own, (int)(__float_as_uint(bv) & ~keep) * 32 + col);
-            for (; deep != 0; deep &= deep - 1u) {
-                const int l = __builtin_ctzll(deep);
+    } else {
+        for (uint64_t rows = __ballot(again); rows != 0; rows &= rows - 1u) {
+            const int row = __builtin_ctzll(rows);
+            const uint32_t lanes = (uint32_t)__builtin_amdgcn_readlane((int)near, row);
+            uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)deep, row);
+            list_pairs(half == 0 && ((lanes & ~all) >> col & 1u) != 0u, row, (int)near_tile[wave][row][col] * 32 + col);
+            for (; all != 0u; all &= all - 1u)
                 for (int t = 0; t < ntiles; t += 64)
-                    list_pairs(t + lane < ntiles, 8 * (v / 4) + 4 * (l >> 5) + v % 4, (t + lane) * 32 + (l & 31));
-            }
-        });
+                    list_pairs(t + lane < ntiles, row, (t + lane) * 32 + __builtin_ctz(all));
+        }
     }
     settle();
-    if (lane < 32 && r0 + lane < n)
+    if (is_row)
         assign[r0 + lane] = nearest[wave][lane] != ~0ull ? (int32_t)(uint32_t)nearest[wave][lane] : decided;
 }
 
@@ -1285,62 +1398,74 @@ static int run_nearest_centroid_mfma(const float *x_dev, int64_t n, const float 
     return PSC_OK;
 }
 
-static size_t split_operand_bytes(int nlist, int dim) { return (size_t)((nlist + 31) / 32) * (size_t)(2 * (dim / 16) + 1) * 64 * 16; }
+static size_t centroid_operand_bytes(int nlist, int dim) { return (size_t)((nlist + 31) / 32) * (size_t)(dim / 16 + 1) * 64 * 16; }
 
-size_t centroid_split_bytes(int nlist, int dim)
+size_t centroid_image_bytes(int nlist, int dim)
 {
     if (dim != 32 && dim != 64 && dim != 96 && dim != 128) return 0;
-    return split_operand_bytes(nlist, dim) + (size_t)((nlist + 31) / 32) * sizeof(float);  // (tile_max2)
+    return centroid_operand_bytes(nlist, dim) + (size_t)((nlist + 31) / 32) * 3 * sizeof(float);  // (of the tiles)
 }
 
-int launch_split_centroids(const float *cent_dev, const float *mu_dev, int nlist, int dim, void *image_dev, hipStream_t s)
+int launch_centroid_image(const float *cent_dev, const float *mu_dev, int nlist, int dim, void *image_dev, hipStream_t s)
 {
-    float *tile_max2 = (float *)((char *)image_dev + split_operand_bytes(nlist, dim));
-    const dim3 grid((unsigned)((nlist + 31) / 32)), block(64);
+    float *tile_max2 = (float *)((char *)image_dev + centroid_operand_bytes(nlist, dim));
+    const int ntiles = (nlist + 31) / 32;
+    const dim3 grid((unsigned)ntiles), block(64);
 #define CALL(D)                                                                                                  \
-    hipLaunchKernelGGL((split_centroids_kernel<D>), grid, block, 0, s, cent_dev, mu_dev, nlist, (bf16x8 *)image_dev, \
-                       tile_max2)
+    do {                                                                                                         \
+        hipLaunchKernelGGL((centroid_lengths_kernel<D>), grid, block, 0, s, cent_dev, mu_dev, nlist, tile_max2); \
+        hipLaunchKernelGGL((centroid_operands_kernel<D>), grid, block, 0, s, cent_dev, mu_dev, nlist, tile_max2, \
+                           (u32x4 *)image_dev, tile_max2 + ntiles, tile_max2 + 2 * ntiles);                      \
+    } while (0)
     switch (dim) {
     case 32: CALL(32); break;
     case 64: CALL(64); break;
     case 96: CALL(96); break;
     case 128: CALL(128); break;
-    default: set_error("no split assignment for dimension %d", dim); return PSC_EINVAL;
+    default: set_error("no float16 assignment for dimension %d", dim); return PSC_EINVAL;
     }
 #undef CALL
     PSC_HIP_TRY(hipGetLastError());
     return PSC_OK;
 }
 
-// The float32 products are done sooner where there is little for either to do (float32 / split, us: 32 lists of
-// 32 dimensions, 1k rows 13 / 18, 1M 112 / 161; 128 of 64, 20k rows 21 / 23, 1M 294 / 218; 256 of 64, 26 / 26
-// and 424 / 250); rows of 96 dimensions and more pass through the split search faster in any case (32
-// lists of 128 dimensions, 20k rows 21 / 21, 1M 421 / 221).
-bool split_assignment_pays(int64_t n, int dim, int nlist)
+// The float32 products are done sooner only where there is next to nothing for either to do (float32 / float16, us:
+// 32 lists of 32 dimensions, 1k rows 12 / 13, 20k 13 / 14, 50k 16 / 14, 1M 106 / 83; 128 of 32, 1k rows 16 / 13; 16
+// of 128, 1k rows 20 / 15, 1M 417 / 174; 128 of 128, 28 / 14 and 641 / 194).
+bool half_assignment_pays(int64_t n, int dim, int nlist) { return (int64_t)nlist * dim > 1024 || n >= 50'000; }
+
+template <int DIM, int G>
+static void launch_half(const float *x_dev, int64_t n, const float *cent_dev, int nlist, const float *mu_dev,
+                        const u32x4 *image, const float *tile_max2, int bits, int32_t *assign_dev, hipStream_t s)
 {
-    return (int64_t)nlist * dim >= 16384 || (dim >= 96 && n >= 50'000);
+    constexpr int kRowsPer = 32 * G * kHalfWaves;
+    hipLaunchKernelGGL((nearest_centroid_half_kernel<DIM, G>), dim3((unsigned)((n + kRowsPer - 1) / kRowsPer)),
+                       dim3(kHalfWaves * 64), 0, s, x_dev, n, cent_dev, mu_dev, image, tile_max2, nlist, bits, assign_dev);
 }
 
-int launch_nearest_centroid_split(const float *x_dev, int64_t n, int dim, const float *cent_dev, int nlist,
-                                  const float *mu_dev, const void *image_dev, int32_t *assign_dev, hipStream_t s)
+int launch_nearest_centroid_half(const float *x_dev, int64_t n, int dim, const float *cent_dev, int nlist,
+                                 const float *mu_dev, const void *image_dev, int32_t *assign_dev, hipStream_t s)
 {
     int rc = check_dim(dim, nlist);
     if (rc != PSC_OK) return rc;
     if (n == 0) return PSC_OK;
-    constexpr int kRowsPer = 32 * kSplitWaves;
+    constexpr int kRowsPer = 32 * kHalfWaves;
     PSC_REQUIRE((n + kRowsPer - 1) / kRowsPer <= 0x7fffffffLL, "too many rows");
-    const float *tile_max2 = (const float *)((const char *)image_dev + split_operand_bytes(nlist, dim));
+    const float *tile_max2 = (const float *)((const char *)image_dev + centroid_operand_bytes(nlist, dim));
     int bits = 0;  // of a tile's number
     while ((1 << bits) < (nlist + 31) / 32) ++bits;
-    const dim3 grid((unsigned)((n + kRowsPer - 1) / kRowsPer)), block(kSplitWaves * 64);
     // (512 workgroups of whole turns for the rows left over, once there are as many)
     const int64_t share = (n / 512 + kRowsPer - 1) / kRowsPer * kRowsPer;
     const int chunk = (int)(share < kRowsPer ? kRowsPer : share < kMarkedChunk ? share : kMarkedChunk);
     const dim3 mgrid((unsigned)((n + chunk - 1) / chunk));
+    const bool two = n >= kTwoGroupRows;
 #define CALL(D)                                                                                                      \
     do {                                                                                                             \
-        hipLaunchKernelGGL((nearest_centroid_split_kernel<D>), grid, block, 0, s, x_dev, n, cent_dev, mu_dev,        \
-                           (const bf16x8 *)image_dev, tile_max2, nlist, bits, assign_dev);                           \
+        const u32x4 *image = (const u32x4 *)image_dev;                                                               \
+        if (two)                                                                                                     \
+            launch_half<D, 2>(x_dev, n, cent_dev, nlist, mu_dev, image, tile_max2, bits, assign_dev, s);             \
+        else                                                                                                         \
+            launch_half<D, 1>(x_dev, n, cent_dev, nlist, mu_dev, image, tile_max2, bits, assign_dev, s);             \
         hipLaunchKernelGGL((nearest_centroid_marked_kernel<D>), mgrid, dim3(256), 0, s, x_dev, n, cent_dev, mu_dev,  \
                            nlist, chunk, assign_dev);                                                                \
     } while (0)
@@ -1349,7 +1474,7 @@ int launch_nearest_centroid_split(const float *x_dev, int64_t n, int dim, const 
     case 64: CALL(64); break;
     case 96: CALL(96); break;
     case 128: CALL(128); break;
-    default: set_error("no split assignment for dimension %d", dim); return PSC_EINVAL;
+    default: set_error("no float16 assignment for dimension %d", dim); return PSC_EINVAL;
     }
 #undef CALL
     PSC_HIP_TRY(hipGetLastError());

@@ -561,3 +561,35 @@ def test_ivf_distances_when_coarse_centroids_lie_far_apart(spread, sigma, direct
         # the bit strings are the oracle's own except on near-ties of a table row
         own = O.ivf_search(xq, s["cb"], s["coarse"], s["offsets"], s["lcodes"], s["lids"], nprobe, ht, k, probed_in=probed)
         assert (own["nsurv"] != ref["nsurv"]).sum() <= max(1, 0.1 * nq)
+
+
+@pytest.mark.parametrize("kind", ["tiny", "huge", "far", "long rows"])
+@pytest.mark.parametrize("dim,nlist,n", [(32, 63, 100_001), (64, 17, 129), (96, 33, 127), (128, 1025, 257), (128, 300, 100_130)])
+def test_assignment_searched_on_scaled_float16(kind, dim, nlist, n):
+    """Values far below and above float16's range, a centroid so far out that the others round to few bits, rows
+    that float16 does not hold: no centroid chosen is farther than the nearest by more than the float32
+    rounding of |c'|^2 - 2 x'.c' (dim + 4 operations on values up to |x'|^2 + |c'|^2, twice)."""
+    import paper_1609_01882_amd as psc
+    rng = np.random.default_rng(dim + nlist + n)
+    cent = rng.normal(size=(nlist, dim)).astype(np.float32)
+    x = rng.normal(size=(n, dim)).astype(np.float32)
+    if kind in ("tiny", "huge"):
+        factor = np.float32({"tiny": 1e-17, "huge": 1e15}[kind])
+        cent, x = cent * factor, x * factor
+    elif kind == "far":
+        cent[nlist // 2] *= np.float32(1e4)
+    else:
+        x[::2] *= (10.0 ** rng.uniform(1, 6, size=(len(x[::2]), 1))).astype(np.float32)
+    idx = psc.Index(dim, 8)
+    idx.ivf_set_coarse(cent)
+    got = idx.ivf_assign_encode(_dev(x), want_codes=False)[0].cpu().numpy()
+    assert got.min() >= 0 and got.max() < nlist
+    look = np.unique(np.concatenate([np.arange(min(n, 1000)), np.arange(max(0, n - 300), n)]))
+    c64, x64 = cent.astype(np.float64), x[look].astype(np.float64)
+    mu = c64.mean(axis=0)
+    d = ((x64[:, None, :] - c64[None, :, :]) ** 2).sum(axis=2)
+    best, took = d.argmin(axis=1), got[look]
+    clen = ((c64 - mu) ** 2).sum(axis=1)
+    size = ((x64 - mu) ** 2).sum(axis=1) + np.maximum(clen[took], clen[best])
+    excess = (d[np.arange(len(look)), took] - d.min(axis=1)) / size
+    assert excess.max() <= 4 * (dim + 4) * 2.0 ** -24, excess.max()
