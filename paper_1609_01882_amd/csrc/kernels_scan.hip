@@ -841,7 +841,11 @@ __device__ __forceinline__ void score_remaining(const Lds<M, TQ> &s, const ScanA
 // Inverted-file tile set-up, shared by the fused kernels: the residual tables of the tile's jobs
 // put together in LDS (see ScanArgs::list_tab) and the jobs' query codes taken from them (s.qcw).
 // Called by the whole workgroup (NW waves) after the per-slot state (s.gidx) is written; ends with
-// a barrier.
+// a barrier.  With short lists this is 40 % of the scan, bound by instruction issue and the waits between
+// barriers: whole rows per wave need no division to find their place and give their minimum from registers,
+// the first rows' shares come while the vectors are staged, four coordinates a read spare sterm the bank conflicts
+// of its stride.  10k queries x 64 of 4096 lists over 10M codes, ht = 24, k = 100: 7200 vector instructions a tile
+// before, 6200 now; the search 4.43 -> 4.09 ms with what short lists save in scan_kernel's last turn.
 template <int M, int TQ, int NW>
 __device__ __forceinline__ void stage_list_tables(const Lds<M, TQ> &s, const ScanArgs &a, int tile_list, int64_t q0,
                                                   int nvq)
@@ -853,79 +857,81 @@ __device__ __forceinline__ void stage_list_tables(const Lds<M, TQ> &s, const Sca
     // direct: the jobs' tables were built one by one by direct differences (a.lut holds them in job
     // order); nothing to put together
     const bool direct = a.list_tab == nullptr;
+    // A wave takes whole rows, four entries a lane: rows wave, wave + NW, ...; up to four rows' shares are asked for
+    // at once, the first ahead of everything else here.
+    constexpr int kRows = TQ * M / NW, kChunk = kRows < 4 ? kRows : 4;
+    static_assert(kRows * NW == TQ * M && kRows % kChunk == 0, "rows of a wave");
+    f32x4 xv[kChunk], tv[kChunk];
+    auto ask = [&](int u0) {
+#pragma unroll
+        for (int u = 0; u < kChunk; ++u) {
+            const int row = wave + (u0 + u) * NW, q = row / M, j = row % M;
+            xv[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+            tv[u] = xv[u];
+            if (q < nvq) {
+                const int64_t from = direct ? q0 + q : (int64_t)a.job_q[q0 + q];
+                xv[u] = ((const f32x4 *)(a.lut + (from * M + j) * 256))[lane];
+                if (!direct) tv[u] = ((const f32x4 *)(a.list_tab + ((int64_t)tile_list * M + j) * 256))[lane];
+            }
+        }
+    };
+    ask(0);
     if (!direct) {
         // the list's centroid and the jobs' queries staged where the tables will go (all loads of the
         // workgroup in flight together; (TQ + 1) * dim floats fit: dim <= 1024 = a quarter of one
         // job's tables at M = 8)
         PSC_LDS float *gs = (PSC_LDS float *)s.lut, *xs = gs + a.dim;
-        for (int e = tid; e < (nvq + 1) * a.dim; e += NW * 64) {
-            const int q = e / a.dim - 1, t = e % a.dim;
-            const float *row = q < 0 ? a.coarse + (int64_t)tile_list * a.dim
-                                     : a.queries + (int64_t)a.job_q[q0 + q] * a.dim;
-            gs[e] = row[t];
+        for (int r = wave; r <= nvq; r += NW) {
+            const float *from = r == 0 ? a.coarse + (int64_t)tile_list * a.dim
+                                       : a.queries + (int64_t)a.job_q[q0 + r - 1] * a.dim;
+            for (int t = lane; t < a.dim; t += 64) gs[r * a.dim + t] = from[t];
         }
         __syncthreads();
-        float sterm = 0.f;
         if (tid < TQ * M) {  // the per-job constant || (q - g)_j ||^2, from the raw vectors
             const int q = tid / M, j = tid - q * M;
+            float sterm = 0.f;
             if (q < nvq) {
-                for (int t = j * dsub; t < (j + 1) * dsub; ++t) {
+                int t = j * dsub;
+                if (dsub % 4 == 0) {  // (the same sums in the same order, four coordinates a read)
+                    for (; t < (j + 1) * dsub; t += 4) {
+                        const f32x4 d4 = *(const PSC_LDS f32x4 *)(xs + q * a.dim + t) - *(const PSC_LDS f32x4 *)(gs + t);
+                        sterm = fmaf(d4.x, d4.x, sterm);
+                        sterm = fmaf(d4.y, d4.y, sterm);
+                        sterm = fmaf(d4.z, d4.z, sterm);
+                        sterm = fmaf(d4.w, d4.w, sterm);
+                    }
+                }
+                for (; t < (j + 1) * dsub; ++t) {
                     const float df = xs[q * a.dim + t] - gs[t];
                     sterm = fmaf(df, df, sterm);
                 }
             }
+            s.sterm[tid] = sterm;
         }
         __syncthreads();  // (the staged vectors are read; their place is the tables' from here on)
-        if (tid < TQ * M) s.sterm[tid] = sterm;
-        __syncthreads();
     }
-    {
-        // the jobs' share and the list's share of every table entry, four entries per thread at
-        // a time: their loads first, the sums after
-        constexpr int kTurns = (TQ * M * 64 + NW * 64 - 1) / (NW * 64);
-        constexpr int kChunk = kTurns < 4 ? kTurns : 4;
-        const f32x4 *tab = direct ? nullptr : (const f32x4 *)(a.list_tab + (int64_t)tile_list * (M * 256));
-        PSC_LDS f32x4 *dst = (PSC_LDS f32x4 *)s.lut;
+    PSC_LDS f32x4 *dst = (PSC_LDS f32x4 *)s.lut;
 #pragma unroll 1
-        for (int u0 = 0; u0 < kTurns; u0 += kChunk) {
-            f32x4 xv[kChunk], tv[kChunk];
+    for (int u0 = 0; u0 < kRows; u0 += kChunk) {
+        if (u0 > 0) ask(u0);
 #pragma unroll
-            for (int u = 0; u < kChunk; ++u) {
-                const int e = tid + (u0 + u) * NW * 64;
-                const int q = e / (M * 64), r = e - q * (M * 64);  // r: 16-byte entry of the job's table
-                xv[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-                tv[u] = xv[u];
-                if (e < TQ * (M * 64) && q < nvq) {
-                    xv[u] = ((const f32x4 *)(a.lut + (direct ? q0 + q : (int64_t)s.gidx[q]) * (M * 256)))[r];
-                    if (!direct) tv[u] = tab[r];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kChunk; ++u) {
-                const int e = tid + (u0 + u) * NW * 64;
-                const int q = e / (M * 64), r = e - q * (M * 64);
-                if (e < TQ * (M * 64)) {
-                    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-                    if (q < nvq) v = direct ? xv[u] : (xv[u] + tv[u]) + s.sterm[q * M + (r >> 6)];
-                    dst[e] = v;
-                }
-            }
+        for (int u = 0; u < kChunk; ++u) {
+            const int row = wave + (u0 + u) * NW;
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            if (row / M < nvq) v = direct ? xv[u] : (xv[u] + tv[u]) + s.sterm[row];
+            dst[row * 64 + lane] = v;
+            // arg-min of the row (lowest index on ties)
+            float best = v.x;
+            int bi = 4 * lane;
+            if (v.y < best) { best = v.y; bi = 4 * lane + 1; }
+            if (v.z < best) { best = v.z; bi = 4 * lane + 2; }
+            if (v.w < best) { best = v.w; bi = 4 * lane + 3; }
+            const uint32_t key = dist_key(best);
+            const uint32_t wk = wave_min_u32(key);
+            const int win = __builtin_ctzll(ballot64(key == wk));  // lower lanes hold lower indices
+            const int code = __builtin_amdgcn_readlane(bi, win);
+            if (lane == 0) ((PSC_LDS volatile uint8_t *)s.qcw)[row] = (uint8_t)code;
         }
-    }
-    __syncthreads();
-    // arg-min of every table row (lowest index on ties): one wave per row
-    for (int row = wave; row < TQ * M; row += NW) {
-        const f32x4 v = ((const PSC_LDS f32x4 *)s.lut)[row * 64 + lane];
-        float best = v.x;
-        int bi = 4 * lane;
-        if (v.y < best) { best = v.y; bi = 4 * lane + 1; }
-        if (v.z < best) { best = v.z; bi = 4 * lane + 2; }
-        if (v.w < best) { best = v.w; bi = 4 * lane + 3; }
-        const uint32_t key = dist_key(best);
-        const uint32_t wk = wave_min_u32(key);
-        const int win = __builtin_ctzll(ballot64(key == wk));  // lower lanes hold lower indices
-        const int code = __builtin_amdgcn_readlane(bi, win);
-        if (lane == 0) ((PSC_LDS volatile uint8_t *)s.qcw)[row] = (uint8_t)code;
     }
     __syncthreads();
 }
@@ -1113,6 +1119,12 @@ scan_kernel(ScanArgs a)
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t blk = sb + u * stride;
+            if constexpr (!INSIDE) {
+                if (blk >= slice_end) {  // (short lists: most blocks of their only turn)
+                    svs[u] = 0u;
+                    continue;
+                }
+            }
             uint32_t far = 0u;
 #pragma unroll
             for (int c = CB - 1; c >= 0; --c) {
@@ -1123,13 +1135,11 @@ scan_kernel(ScanArgs a)
             }
             uint32_t valid = qmask_all;
             if constexpr (!INSIDE) {
-                if (!(blk + 64 * CB <= slice_end && blk >= valid_begin)) {  // ragged or absent block
-                    valid = 0u;
-#pragma unroll
-                    for (int c = 0; c < CB; ++c) {
-                        const int64_t p = blk + (int64_t)lane * CB + c;
-                        valid |= (p < slice_end && p >= valid_begin) ? (qmask << (c * TQ)) : 0u;
-                    }
+                if (!(blk + 64 * CB <= slice_end && blk >= valid_begin)) {  // ragged: the lane's codes [skip, left)
+                    const int left = (int)(slice_end - blk < 64 * CB ? slice_end - blk : 64 * CB) - lane * CB;
+                    const int skip = (int)(valid_begin > blk ? valid_begin - blk : 0) - lane * CB;
+                    if (left < CB) valid &= left > 0 ? (1u << (left * TQ)) - 1u : 0u;
+                    if (skip > 0) valid &= skip < CB ? ~0u << (skip * TQ) : 0u;
                 }
             }
             svs[u] = ~far & valid;
