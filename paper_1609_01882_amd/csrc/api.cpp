@@ -474,7 +474,13 @@ int psc_search(const psc_index *idx, const float *q_dev, int64_t nq, const uint8
         if (rc != PSC_OK) return rc;
         char route[96];
         snprintf(route, sizeof route, "%s", psc_last_scan_route());
-        rc = launch_scan(idx->m, lut, qcodes, nq, codes_dev, n, ht, k, -1, true, preset, ids_dev, dists_dev,
+        // (launches of 25 us where nothing is marked: not worth it where the scan of a marked tile is short)
+        bool cleared = false;
+        if (nq >= 256 && estimated_scan_time(idx->m, nq, n, k, ht, scan_bytes) > 2000.0) {
+            rc = launch_few_marked(b, bound_bytes, (int *)workspace_dev, &cleared, (hipStream_t)stream);
+            if (rc != PSC_OK) return rc;
+        }
+        rc = launch_scan(idx->m, lut, qcodes, nq, codes_dev, n, ht, k, -1, !cleared, preset, ids_dev, dists_dev,
                          workspace_dev, scan_bytes, (hipStream_t)stream, b.redo);
         note_scan_route(route);
         return rc;

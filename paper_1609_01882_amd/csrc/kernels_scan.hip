@@ -3008,7 +3008,7 @@ double estimated_scan_time(int m, int64_t nq, int64_t n, int k, int ht, size_t w
 int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t nq,
                 const uint8_t *codes_dev, int64_t n, int ht, int k, int64_t skip_first,
                 bool clear_status, bool preset, int64_t *ids_dev, float *dists_dev, void *ws, size_t ws_bytes,
-                hipStream_t s, const uint32_t *redo_dev)
+                hipStream_t s, const uint32_t *redo_dev, int *status_dev)
 {
     PSC_REQUIRE(ht >= 0, "ht must be >= 0, got %d", ht);
     ScanRoute route;
@@ -3049,7 +3049,7 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
     const int nbits = 8 * m;
     const int ht_eff = ht > nbits ? nbits : ht;
     a.bias = 0x7fffffffu - (uint32_t)ht_eff;
-    a.status = (int *)ws;
+    a.status = status_dev != nullptr ? status_dev : (int *)ws;
     a.gthr = (uint32_t *)((char *)ws + 256);
     a.job_q = nullptr;
     a.redo = redo_dev;

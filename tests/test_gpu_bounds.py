@@ -185,3 +185,23 @@ def test_replays_of_a_recorded_search_by_bounds(trained):
         want = idx.search(q, c, ht, k)
         torch.cuda.synchronize()
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), turn
+
+
+@pytest.mark.parametrize("marked", ["none", "few", "a sixteenth", "one more", "many"])
+def test_marked_queries_side_by_side(trained, force_route, marked):
+    """A search long enough for few marks to be scanned by themselves: none, some scattered ones (the first and
+    the last query among them), as many as are few, one more, and a third of all (marks by queries that are not finite)."""
+    import paper_1609_01882_amd as psc
+    idx, codes = trained(128, 8)
+    codes = codes.repeat(3, 1).contiguous()
+    nq = 3001
+    q = _mixture(nq, 128, 5)[0]
+    few = (nq + 15) // 16
+    rows = {"none": [], "few": [0, 17, 255, 256, 1000, nq - 1], "a sixteenth": list(range(0, nq, 16))[:few],
+            "one more": list(range(0, 7 * (few + 1), 7)), "many": list(range(0, nq, 3))}[marked]
+    if rows:
+        q[torch.tensor(rows, device="cuda"), 5] = float("inf")
+    (route, ids, d), (other, ids2, d2) = _both(psc, idx, q, codes, 64, 20)
+    assert route == "bound_scan_kernel" and other != route, (route, other)
+    assert torch.equal(ids, ids2)
+    assert torch.equal(d.view(torch.int32), d2.view(torch.int32))
