@@ -29,6 +29,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "bound_queue.h"
 #include "common.h"
 #include "entry.h"
 
@@ -57,7 +58,7 @@ struct Shape {
     static constexpr int NS = M * DP / 64;          // steps of 64 coordinates
     static constexpr int ENT = DP == 8 ? 8 : DP == 16 ? 16 : 32;  // bytes of a centroid in LDS
     static constexpr int QG = NS <= 2 ? 8 : 4;      // groups of 32 queries a wave holds
-    static constexpr int QUEUE = QG == 8 ? 64 * 17 : 64 * 10;  // entries of a wave's queue: what waits, and a group's, or what comes between its two drains
+    static constexpr int QUEUE = kQueuePlaces<QG>;  // entries of a wave's queue
 };
 
 template <int M, int DP>
@@ -376,15 +377,8 @@ bound_scan_kernel(BoundArgs a)
                             fill += __builtin_popcountll(m);
                         }
                     };
-#pragma unroll
-                    for (int t = 0; t < 5; ++t) {
-                        if (ballot64(mx[t] >= least[g]) == 0ull) continue;
-#pragma unroll
-                        for (int r = 3 * t; r < 3 * t + 3; ++r) check(r);
-                        if (QG == 4 && t == 2 && fill >= 64) drain(63);
-                    }
-                    check(15);
-                    if (fill >= 64) drain(63);
+                    queue_group<QG>([&](int t) { return ballot64(mx[t] >= least[g]) != 0ull; }, check,
+                                    [&]() { if (fill >= 64) drain(63); });
                 }
             }
 #pragma unroll

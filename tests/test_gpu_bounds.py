@@ -116,6 +116,40 @@ def test_data_that_the_rounds_do_not_expect(trained, force_route, data):
     assert torch.equal(ids, want_ids) and torch.equal(d, want_d)
 
 
+# the shapes whose waves hold four groups of queries (256 dimensions), whose queue is drained in the middle of a group, and one
+# of 8 coordinates a sub-vector; rows of a turn of 32 apart: those of result registers 6 .. 8 far, the others near, and the reverse
+@pytest.mark.parametrize("dim,m,ht", [(256, 8, 64), (256, 8, 30), (256, 16, 128), (256, 16, 60), (64, 8, 64)])
+@pytest.mark.parametrize("data", ["sorted", "few distinct", "one code", "mostly one code", "half one code", "six rows of 32 far",
+                                  "six rows of 32 near"])
+def test_data_that_the_rounds_do_not_expect_at_other_lengths(trained, force_route, dim, m, ht, data):
+    import paper_1609_01882_amd as psc
+    idx, codes = trained(dim, m)
+    n, nq, k = 300_007, 330, 50
+    q = _mixture(nq, dim, 5)[0]
+    c = codes[:n].clone()
+    common = codes[123].clone()
+    six = torch.isin(torch.arange(n, device="cuda") % 32, torch.tensor([10, 11, 14, 15, 16, 20], device="cuda"))
+    if data == "sorted":
+        c = c[torch.sort(c[:, 0].to(torch.int64) * 256 + c[:, 1].to(torch.int64)).indices]
+    elif data == "few distinct":
+        c = c[:300].repeat((n + 299) // 300, 1)[:n]
+    elif data == "one code":
+        c[:] = common
+    else:
+        if data in ("mostly one code", "half one code"):
+            share = 0.7 if data == "mostly one code" else 0.5
+            c[torch.rand((n,), generator=torch.Generator(device="cuda").manual_seed(11), device="cuda") < share] = common
+        else:
+            c[~six if data == "six rows of 32 far" else six] = common
+        # queries at the common code's vector and a little off it, and some of the mixture
+        vector = torch.from_numpy(idx.get_codebook()).cuda()[torch.arange(m, device="cuda"), common.long()].reshape(1, dim)
+        q[:300] = vector + (torch.arange(300, device="cuda") % 5)[:, None] * 0.02 * (q[:300] - vector)
+    print(f"dim={dim} m={m} ht={ht} {data}", flush=True)
+    (route, ids, d), (other, want_ids, want_d) = _both(psc, idx, q.contiguous(), c.contiguous(), ht, k)
+    assert route == "bound_scan_kernel" and other != route, (route, other)
+    assert torch.equal(ids, want_ids) and torch.equal(d, want_d)
+
+
 def test_queries_that_are_not_finite_are_left_to_the_other_scan(trained, force_route):
     import paper_1609_01882_amd as psc
     idx, codes = trained(128, 8)
