@@ -470,18 +470,13 @@ int psc_search(const psc_index *idx, const float *q_dev, int64_t nq, const uint8
         b.dists = dists_dev;
         b.redo = (uint32_t *)((char *)workspace_dev + need);
         b.ws = (char *)b.redo + round256((size_t)nq * sizeof(uint32_t));
-        rc = launch_bound_search(b, (hipStream_t)stream);
+        MarkedQueries marked;
+        rc = launch_bound_search(b, &marked, (hipStream_t)stream);
         if (rc != PSC_OK) return rc;
         char route[96];
         snprintf(route, sizeof route, "%s", psc_last_scan_route());
-        // (launches of 25 us where nothing is marked: not worth it where the scan of a marked tile is short)
-        bool cleared = false;
-        if (nq >= 256 && estimated_scan_time(idx->m, nq, n, k, ht, scan_bytes) > 2000.0) {
-            rc = launch_few_marked(b, bound_bytes, (int *)workspace_dev, &cleared, (hipStream_t)stream);
-            if (rc != PSC_OK) return rc;
-        }
-        rc = launch_scan(idx->m, lut, qcodes, nq, codes_dev, n, ht, k, -1, !cleared, preset, ids_dev, dists_dev,
-                         workspace_dev, scan_bytes, (hipStream_t)stream, b.redo);
+        rc = launch_scan(idx->m, lut, qcodes, nq, codes_dev, n, ht, k, -1, true, preset, ids_dev, dists_dev,
+                         workspace_dev, scan_bytes, (hipStream_t)stream, &marked);
         note_scan_route(route);
         return rc;
     }

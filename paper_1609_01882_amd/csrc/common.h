@@ -119,13 +119,22 @@ size_t flat_scan_workspace_bytes(int m, int64_t nq, int64_t n, int k);
 // skip_first >= 0: query q never returns database row skip_first + q (k-NN-graph mode).
 // clear_status: reset the workspace's status word first (false for follow-up chunks of one call).
 // preset: the first min(nq, kPresetQueries) words after the status word's 256 bytes hold kPresetWord already.
-// redo_dev: a word per query; only queries whose word is not zero are answered (nullptr: all).  status_dev: the status
-// word in place of the workspace's.
+// marked: only the queries of `redo` are answered (null: all).
 constexpr int kPresetQueries = 128;
+// The queries that a search by bounds leaves to the scan, and room to answer a few of them by themselves.
+struct MarkedQueries {
+    uint32_t *redo;           // [nq] not zero: marked
+    const uint32_t *count;    // how many (0: not counted)
+    const int32_t *which;     // the first `few` of them
+    uint32_t *arrived;        // [few] kPresetWord
+    int few;
+    void *scratch;
+    size_t scratch_bytes;
+};
 int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t nq,
                 const uint8_t *codes_dev, int64_t n, int ht, int k, int64_t skip_first,
                 bool clear_status, bool preset, int64_t *ids_dev, float *dists_dev, void *ws, size_t ws_bytes,
-                hipStream_t s, const uint32_t *redo_dev = nullptr, int *status_dev = nullptr);
+                hipStream_t s, const MarkedQueries *marked = nullptr);
 // What launch_scan of these sizes takes, in microseconds (an estimate: pool_scan_slices); 0: it would refuse them.
 double estimated_scan_time(int m, int64_t nq, int64_t n, int k, int ht, size_t ws_bytes);
 // Share of random codes within Hamming distance ht of a query's.
@@ -161,11 +170,7 @@ struct BoundSearch {
     uint32_t *redo;  // [nq] out: queries that are left to launch_scan
     void *ws;
 };
-int launch_bound_search(const BoundSearch &b, hipStream_t s);
-// Up to nq / 16 marks are answered here and cleared, all by themselves in tiles of marked queries only; more
-// stay as they are.  Takes the bounds' scratch (ws_bytes of it); nothing is done if that is too small.  status_dev: the
-// scan's status word, *cleared whether it was cleared.
-int launch_few_marked(const BoundSearch &b, size_t ws_bytes, int *status_dev, bool *cleared, hipStream_t s);
+int launch_bound_search(const BoundSearch &b, MarkedQueries *marked, hipStream_t s);
 // lut_dev: tables of the queries minus the mean coarse centroid, [nq][m][256]; list_tab_dev:
 // the lists' share of the residual tables (launch_list_tables); job_qcodes_dev: out, the query
 // code of every job, in job order.

@@ -47,6 +47,7 @@ constexpr int kBoundMaxK = 256;
 constexpr int kLeastSample = 4096, kMaxSample = 65536;  // codes of the sample
 constexpr int kMostStep = 5;         // a round looks at most at 2^this times as many codes as all before
 constexpr int kSampleKeys = 4096;    // keys of the sample's pool
+constexpr int kMarkWords = 64;       // of `marks`: the count, and from here on `few` words for the scan of each, then which they are
 constexpr float kLeast = -1e29f;     // below every product, above every invalid row's
 constexpr float kInvalid = 1e30f;    // "half square" of a row past the end
 
@@ -460,6 +461,8 @@ struct PrepareArgs {
     uint32_t *redo;
     int dim, dsub, nq;
     uint32_t *unfit;  // set to zero
+    uint32_t *marks;  // (BoundLayout; null: set by an earlier launch of the call)
+    int few;
     // workgroups past those of the queries gather the sample: every stride-th code
     int query_groups;
     const uint8_t *codes;
@@ -488,6 +491,10 @@ bound_prepare_kernel(PrepareArgs a)
         typedef uint32_t words __attribute__((ext_vector_type(M / 4)));
         const int p = ((int)blockIdx.x - a.query_groups) * 256 + tid;
         if (p == 0) *a.unfit = 0u;
+        if (a.marks != nullptr) {
+            if (p == 0) *a.marks = 0u;
+            for (int i = p; i < a.few; i += ((int)gridDim.x - a.query_groups) * 256) a.marks[kMarkWords + i] = kPresetWord;
+        }
         if (p < a.samples) ((words *)a.sample)[p] = ((const words *)a.codes)[(size_t)p * a.stride];
         return;
     }
@@ -911,6 +918,9 @@ struct RankArgs {
     float ratio;    // the next round's codes to this one's
     int64_t *ids;
     float *dists;
+    // of the last round: where its marks are counted and listed (BoundLayout), unless the batch is unfit (all are marked then)
+    uint32_t *marks;
+    int few, first, nq;
 };
 template <int M>
 struct RankLds {
@@ -934,7 +944,15 @@ bound_rank_kernel(RankArgs a)
     PSC_LDS uint64_t *const sel = s.best;
     const int tid = (int)threadIdx.x, lane = tid & 63, k = a.k;
     const int64_t q = blockIdx.x;
-    if (a.redo[q] != 0u) return;  // (uniform)
+    auto list_mark = [&]() {  // (by one thread)
+        if (*a.unfit * 64u > (uint32_t)a.nq) return;
+        const uint32_t at = __hip_atomic_fetch_add(a.marks, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (at < (uint32_t)a.few) a.marks[kMarkWords + a.few + at] = (uint32_t)a.first + (uint32_t)q;
+    };
+    if (a.redo[q] != 0u) {  // (uniform)
+        if (LAST && tid == 0) list_mark();
+        return;
+    }
     const uint64_t wanted = a.thr[q];
     const int group = (int)(q >> 5);
     int tile = (int)((int64_t)group * a.tiles / a.groups);  // (that of tile g0 .. g0 + ng - 1 of bound_item)
@@ -1012,7 +1030,10 @@ bound_rank_kernel(RankArgs a)
     if (tid >= 64) return;
     const int pooled = (int)s.count;
     if (pooled > kBoundPool) {
-        if (lane == 0) a.redo[q] = 1u;
+        if (lane == 0) {
+            a.redo[q] = 1u;
+            if (LAST) list_mark();
+        }
         return;
     }
     const int wants = LAST ? k : a.rank;
@@ -1053,7 +1074,10 @@ bound_rank_kernel(RankArgs a)
     if constexpr (LAST) {
         // The pool holds all there is up to thr: the k best, unless fewer are that near.
         if (kept < k && wanted != kNoEntry) {
-            if (lane == 0) a.redo[q] = 1u;
+            if (lane == 0) {
+                a.redo[q] = 1u;
+                list_mark();
+            }
             return;
         }
         __builtin_amdgcn_wave_barrier();
@@ -1110,60 +1134,16 @@ float round_e2m3(float v, uint8_t *code)
 
 size_t round256(size_t v) { return (v + 255) / 256 * 256; }
 
-// The marked queries side by side, if they are few: which[c] the c-th of them, wanted[c] whether there is one.
-__global__ void __launch_bounds__(1024)
-part_marks_kernel(uint32_t *__restrict__ redo, int nq, int most, int *__restrict__ which, uint32_t *__restrict__ wanted)
-{
-    __shared__ int count, at;
-    if (threadIdx.x == 0) count = at = 0;
-    __syncthreads();
-    int mine = 0;
-    for (int q = (int)threadIdx.x; q < nq; q += 1024) mine += redo[q] != 0u;
-    if (mine != 0) atomicAdd(&count, mine);
-    __syncthreads();
-    const bool few = count <= most;
-    for (int c = (int)threadIdx.x; c < most; c += 1024) wanted[c] = few && c < count;
-    if (!few) return;
-    for (int q = (int)threadIdx.x; q < nq; q += 1024) {
-        if (redo[q] == 0u) continue;
-        which[atomicAdd(&at, 1)] = q;
-        redo[q] = 0u;
-    }
-}
-
-__global__ void __launch_bounds__(256)
-gather_marked_kernel(const int *__restrict__ which, const uint32_t *__restrict__ wanted, int m, const float *__restrict__ lut,
-                     const uint8_t *__restrict__ qcodes, float *__restrict__ lut_few, uint8_t *__restrict__ qcodes_few)
-{
-    const int c = (int)blockIdx.x;
-    if (wanted[c] == 0u) return;
-    const int64_t q = which[c];
-    const int entries = m * kCentroids / 4;
-    for (int e = (int)threadIdx.x; e < entries; e += 256)
-        ((float4 *)lut_few)[(int64_t)c * entries + e] = ((const float4 *)lut)[q * entries + e];
-    if ((int)threadIdx.x < m) qcodes_few[(int64_t)c * m + threadIdx.x] = qcodes[q * m + threadIdx.x];
-}
-
-__global__ void __launch_bounds__(256)
-scatter_marked_kernel(const int *__restrict__ which, const uint32_t *__restrict__ wanted, int k,
-                      const int64_t *__restrict__ ids_few, const float *__restrict__ dists_few, int64_t *__restrict__ ids,
-                      float *__restrict__ dists)
-{
-    const int c = (int)blockIdx.x;
-    if (wanted[c] == 0u) return;
-    const int64_t q = which[c];
-    for (int e = (int)threadIdx.x; e < k; e += 256) {
-        ids[q * k + e] = ids_few[(int64_t)c * k + e];
-        dists[q * k + e] = dists_few[(int64_t)c * k + e];
-    }
-}
-
 struct BoundLayout {
-    size_t unfit, qimg, qscale, s, thr, sample, raw, near, first, total;
+    size_t marks, unfit, qimg, qscale, s, thr, sample, raw, near, first, total;
 };
-BoundLayout bound_layout(int m, int dsub, int64_t nq)
+// How many marked queries are few: scanned by themselves these take less than the tiles that have one (up to 16 queries and
+// the whole database each).
+int few_marked(int64_t nq) { return (int)std::min<int64_t>((nq + 15) / 16, 1024); }
+BoundLayout bound_layout(int m, int dsub, int64_t nq_all)
 {
     const int ns = m * padded_length(m, dsub) / 64;
+    const int64_t nq = std::min(nq_all, kBoundChunk);
     const size_t groups = (size_t)(nq + 31) / 32;
     BoundLayout l;
     size_t o = 0;
@@ -1172,6 +1152,7 @@ BoundLayout bound_layout(int m, int dsub, int64_t nq)
         o += round256(bytes);
         return at;
     };
+    l.marks = take((kMarkWords + 2 * (size_t)few_marked(nq_all)) * 4);
     l.unfit = take(4);
     l.qimg = take(groups * ns * 6 * 64 * 4);
     l.qscale = take(groups * 64 * 4);
@@ -1405,7 +1386,7 @@ size_t bound_workspace_bytes(int m, int dsub, int64_t nq, int64_t n, int k)
     // (the thresholds at which the other kernels take longest: nothing filtered, and the last before the dense route)
     const size_t any = (size_t)1 << 60;
     for (int ht : {8 * m, m == 8 ? 29 : 61})
-        if (bound_search_pays(m, dsub, nq, n, ht, k, any)) return bound_layout(m, dsub, std::min(nq, kBoundChunk)).total;
+        if (bound_search_pays(m, dsub, nq, n, ht, k, any)) return bound_layout(m, dsub, nq).total;
     return 0;
 }
 
@@ -1450,6 +1431,9 @@ int run_bound(const BoundSearch &b, int64_t q_first, int nq, const BoundLayout &
     p.codes = b.codes;
     p.sample = (uint8_t *)(w + l.sample);
     p.unfit = (uint32_t *)(w + l.unfit);
+    p.few = few_marked(b.nq);
+    uint32_t *const marks = (uint32_t *)(w + l.marks);
+    p.marks = q_first == 0 ? marks : nullptr;
     p.stride = plan.stride[0];
     p.samples = (int)((b.n + p.stride - 1) / p.stride);
     hipLaunchKernelGGL((bound_prepare_kernel<M, DP>), dim3((unsigned)(p.query_groups + (p.samples + 255) / 256)), dim3(256), 0, s, p);
@@ -1501,6 +1485,10 @@ int run_bound(const BoundSearch &b, int64_t q_first, int nq, const BoundLayout &
     r.k = b.k;
     r.ids = b.ids + (size_t)q_first * b.k;
     r.dists = b.dists + (size_t)q_first * b.k;
+    r.marks = marks;
+    r.few = p.few;
+    r.first = (int)q_first;
+    r.nq = nq;
     for (int i = 0; i < plan.rounds; ++i) {
         const bool last = i + 1 == plan.rounds;
         a.stride = plan.stride[i + 1];
@@ -1532,49 +1520,24 @@ int run_bound(const BoundSearch &b, int64_t q_first, int nq, const BoundLayout &
 
 }  // namespace
 
-// The marks that a search leaves are mostly scattered: some two hundred of 10k queries x 10M codes, a tile of 16 queries
-// and the whole database each, took 5.5 ms of 16.0.  Side by side they fill a few tiles, each cut into many slices.
-int launch_few_marked(const BoundSearch &b, size_t ws_bytes, int *status_dev, bool *cleared, hipStream_t s)
-{
-    *cleared = false;
-    const int64_t most = (b.nq + 15) / 16;
-    char *w = (char *)b.ws;
-    size_t o = 0;
-    auto take = [&](size_t bytes) {
-        const size_t at = o;
-        o += round256(bytes);
-        return at;
-    };
-    int *which = (int *)(w + take((size_t)most * sizeof(int)));
-    uint32_t *wanted = (uint32_t *)(w + take((size_t)most * sizeof(uint32_t)));
-    float *lut = (float *)(w + take((size_t)most * b.m * kCentroids * sizeof(float)));
-    uint8_t *qcodes = (uint8_t *)(w + take((size_t)most * b.m));
-    int64_t *ids = (int64_t *)(w + take((size_t)most * b.k * sizeof(int64_t)));
-    float *dists = (float *)(w + take((size_t)most * b.k * sizeof(float)));
-    const size_t scan_bytes = flat_scan_workspace_bytes(b.m, most, b.n, b.k);
-    if (scan_bytes == 0 || o + scan_bytes > ws_bytes) return PSC_OK;
-    hipLaunchKernelGGL(part_marks_kernel, dim3(1), dim3(1024), 0, s, b.redo, (int)b.nq, (int)most, which, wanted);
-    hipLaunchKernelGGL(gather_marked_kernel, dim3((unsigned)most), dim3(256), 0, s, which, wanted, b.m, b.lut, b.qcodes, lut, qcodes);
-    PSC_HIP_TRY(hipGetLastError());
-    int rc = launch_scan(b.m, lut, qcodes, most, b.codes, b.n, b.ht, b.k, -1, true, false, ids, dists, w + o, ws_bytes - o, s,
-                         wanted, status_dev);
-    if (rc != PSC_OK) return rc;
-    *cleared = true;
-    hipLaunchKernelGGL(scatter_marked_kernel, dim3((unsigned)most), dim3(256), 0, s, which, wanted, b.k, ids, dists, b.ids, b.dists);
-    PSC_HIP_TRY(hipGetLastError());
-    return PSC_OK;
-}
-
-int launch_bound_search(const BoundSearch &b, hipStream_t s)
+int launch_bound_search(const BoundSearch &b, MarkedQueries *marked, hipStream_t s)
 {
     const int dp = padded_length(b.m, b.dsub);
     const double keep = b.ht >= 8 * b.m ? 1.0 : random_code_survival(8 * b.m, b.ht);
     const BoundRounds plan = plan_rounds(b.n, b.k, keep);
     PSC_REQUIRE(dp != 0 && plan.rounds > 0, "sizes without a bound search");
+    const BoundLayout l = bound_layout(b.m, b.dsub, b.nq);
+    uint32_t *marks = (uint32_t *)((char *)b.ws + l.marks);
+    marked->few = few_marked(b.nq);
+    marked->redo = b.redo;
+    marked->count = marks;
+    marked->arrived = marks + kMarkWords;
+    marked->which = (const int32_t *)(marks + kMarkWords + marked->few);
+    marked->scratch = (char *)b.ws + l.raw;  // (the lists are read by then)
+    marked->scratch_bytes = l.total - l.raw;
     for (int64_t q = 0; q < b.nq; q += kBoundChunk) {
         const int nq = (int)std::min(kBoundChunk, b.nq - q);
-        const BoundLayout l = bound_layout(b.m, b.dsub, std::min(b.nq, kBoundChunk));
-        int rc = PSC_EINVAL;
+                int rc = PSC_EINVAL;
         if (b.m == 8 && dp == 8) rc = run_bound<8, 8>(b, q, nq, l, plan, s);
         if (b.m == 8 && dp == 16) rc = run_bound<8, 16>(b, q, nq, l, plan, s);
         if (b.m == 8 && dp == 32) rc = run_bound<8, 32>(b, q, nq, l, plan, s);

@@ -1735,6 +1735,10 @@ adc_kernel(ScanArgs a)
 // DENSE: every code is scored and the Hamming test is taken on those below the bound (pure ADC and
 // permissive thresholds), instead of queueing the codes that pass the test.
 // `open`: the largest distance that is listed while there are fewer than k.
+// MARKED: the queries are those that a search by bounds has marked, if they are few, each by itself and in slices; they
+// are marked no more then.  The words and the status of the scan that answers more of them are set on the way.  (Marks are
+// scattered: a tile of up to 16 queries that has one takes the whole database for it.  10k queries x 10M codes with some
+// 220 marks 16.0 ms so, 12.3 with their tables gathered for tiles of marked queries only, 11.4 this way.)
 // ---------------------------------------------------------------------------------------------
 constexpr int kSmallPool = 4096;   // keys
 constexpr int kRankedKeys = 512;   // of that many every key's rank is taken sooner than a search among them ends
@@ -1752,10 +1756,10 @@ struct SmallLds {
     float bound;
 };
 
-template <int M, bool DENSE>
+template <int M, bool DENSE, bool MARKED>
 __global__ void __launch_bounds__(1024)
 scan_pool_kernel(ScanArgs a, float open, int *status, uint32_t *arrived, int64_t *__restrict__ ids,
-                 float *__restrict__ dists)
+                 float *__restrict__ dists, MarkedQueries marked, int64_t nwords)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     PSC_LDS SmallLds<M> &s = *(PSC_LDS SmallLds<M> *)smem;
@@ -1764,7 +1768,7 @@ scan_pool_kernel(ScanArgs a, float open, int *status, uint32_t *arrived, int64_t
     typedef uint32_t words __attribute__((ext_vector_type(WPC)));
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t q = blockIdx.x / a.nslice;
+    const int64_t item = blockIdx.x / a.nslice;  // the query, or its place among the marked ones
     const int slice = (int)(blockIdx.x % a.nslice);
     const int64_t begin = (int64_t)slice * a.slice_len;
     const int64_t end = begin + a.slice_len < a.n ? begin + a.slice_len : a.n;
@@ -1772,6 +1776,14 @@ scan_pool_kernel(ScanArgs a, float open, int *status, uint32_t *arrived, int64_t
     const uint8_t *codes = a.codes + begin * M;
     const int k = a.k;
     if (blockIdx.x == 0 && tid == 0 && status) *status = 0;
+    int64_t q = item;
+    if constexpr (MARKED) {
+        for (int64_t e = (int64_t)blockIdx.x * 1024 + tid; e < nwords; e += (int64_t)gridDim.x * 1024) a.gthr[e] = kKeyInf;
+        const uint32_t count = *marked.count;
+        if (count > (uint32_t)marked.few || item >= (int64_t)count) return;  // (uniform)
+        q = __builtin_amdgcn_readfirstlane(marked.which[item]);
+        if (slice == 0 && tid == 0) marked.redo[q] = 0u;
+    }
 
     // codes of the wave's turn `blk`: code blk + 64 l + lane in c[l]; past the end the range check
     // answers zero
@@ -2022,8 +2034,8 @@ scan_pool_kernel(ScanArgs a, float open, int *status, uint32_t *arrived, int64_t
         // several slices, put together by the workgroup of the query that comes last: each leaves its keys where
         // every XCD sees them, counts itself, and all but the last are done
         const int total = a.nslice * k;  // (<= kSmallPool, the launcher sees to it)
-        float *pd = a.part_d + q * total;
-        int64_t *pi = a.part_i + q * total;
+        float *pd = a.part_d + item * total;
+        int64_t *pi = a.part_i + item * total;
         if (tid < k) {
             const uint64_t key = tid < n ? s.pool[tid] : 0ull;
             __hip_atomic_store(pd + slice * k + tid, tid < n ? entry_dist(key) : 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2038,7 +2050,7 @@ scan_pool_kernel(ScanArgs a, float open, int *status, uint32_t *arrived, int64_t
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (tid == 0) {
-            const uint32_t before = __hip_atomic_fetch_add(arrived + q, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t before = __hip_atomic_fetch_add(arrived + item, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
             if (before == kPresetWord + (uint32_t)a.nslice - 1u) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             s.stuck = before;
             s.count = 0u;
@@ -2582,19 +2594,41 @@ int run_adc(const ScanArgs &a, int64_t ntiles, size_t lds, hipStream_t s)
     return PSC_OK;
 }
 
-template <int M, bool DENSE>
-int run_scan_pool(const ScanArgs &a, float open, int *status, uint32_t *arrived, int64_t *ids, float *dists, hipStream_t s)
+template <int M, bool DENSE, bool MARKED>
+int run_scan_pool(const ScanArgs &a, float open, int *status, uint32_t *arrived, int64_t *ids, float *dists,
+                  const MarkedQueries &marked, int64_t nwords, hipStream_t s)
 {
     static std::atomic<bool> configured{false};
     if (!configured.load(std::memory_order_acquire)) {
-        PSC_HIP_TRY(hipFuncSetAttribute((const void *)scan_pool_kernel<M, DENSE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        PSC_HIP_TRY(hipFuncSetAttribute((const void *)scan_pool_kernel<M, DENSE, MARKED>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                         (int)sizeof(SmallLds<M>)));
         configured.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((scan_pool_kernel<M, DENSE>), dim3((unsigned)(a.nq * a.nslice)), dim3(1024), sizeof(SmallLds<M>), s, a,
-                       open, status, arrived, ids, dists);
+    const int64_t queries = MARKED ? marked.few : a.nq;
+    hipLaunchKernelGGL((scan_pool_kernel<M, DENSE, MARKED>), dim3((unsigned)(queries * a.nslice)), dim3(1024), sizeof(SmallLds<M>),
+                       s, a, open, status, arrived, ids, dists, marked, nwords);
     PSC_HIP_TRY(hipGetLastError());
     return PSC_OK;
+}
+template <bool MARKED>
+int dispatch_scan_pool(int m, bool dense, const ScanArgs &a, float open, int *status, uint32_t *arrived, int64_t *ids, float *dists,
+                       const MarkedQueries &marked, int64_t nwords, hipStream_t s)
+{
+    if (m == 8)
+        return dense ? run_scan_pool<8, true, MARKED>(a, open, status, arrived, ids, dists, marked, nwords, s)
+                     : run_scan_pool<8, false, MARKED>(a, open, status, arrived, ids, dists, marked, nwords, s);
+    return dense ? run_scan_pool<16, true, MARKED>(a, open, status, arrived, ids, dists, marked, nwords, s)
+                 : run_scan_pool<16, false, MARKED>(a, open, status, arrived, ids, dists, marked, nwords, s);
+}
+// The slices of a marked query: as many as its last workgroup puts together, up to 16, of 16384 codes and more.  Small
+// ones: where half of all codes are at one distance a query is dear (30 marks of 3000 queries x 200k codes, k = 100, whole
+// search: slices of 8192 codes 731 us, 16384 775, 65536 1063); and few: workgroups that find nothing marked take time too
+// (of that search of 400 us without marks 8, 5 and 4 us).
+int marked_slices(int64_t n, int k)
+{
+    int slices = 16;
+    while (slices > 1 && (slices * k > kSmallPool || n < (int64_t)slices * 16384)) slices /= 2;
+    return slices;
 }
 
 template <bool SHARE, bool FILTER>
@@ -3008,7 +3042,7 @@ double estimated_scan_time(int m, int64_t nq, int64_t n, int k, int ht, size_t w
 int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t nq,
                 const uint8_t *codes_dev, int64_t n, int ht, int k, int64_t skip_first,
                 bool clear_status, bool preset, int64_t *ids_dev, float *dists_dev, void *ws, size_t ws_bytes,
-                hipStream_t s, const uint32_t *redo_dev, int *status_dev)
+                hipStream_t s, const MarkedQueries *marked)
 {
     PSC_REQUIRE(ht >= 0, "ht must be >= 0, got %d", ht);
     ScanRoute route;
@@ -3049,17 +3083,39 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
     const int nbits = 8 * m;
     const int ht_eff = ht > nbits ? nbits : ht;
     a.bias = 0x7fffffffu - (uint32_t)ht_eff;
-    a.status = status_dev != nullptr ? status_dev : (int *)ws;
+    a.status = (int *)ws;
     a.gthr = (uint32_t *)((char *)ws + 256);
     a.job_q = nullptr;
-    a.redo = redo_dev;
+    a.redo = marked != nullptr ? marked->redo : nullptr;
     a.part_d = (float *)((char *)ws + 256 + p.gthr_bytes);
     a.part_i = (int64_t *)((char *)a.part_d + (((size_t)nq * p.nslice * k * sizeof(float) + 255) / 256 * 256));
     // which entry the lists of a many-slice query publish, and which of the published values bounds
     // the k-th best: pub_kth words x pub_r entries >= k, with pub_kth about 0.4 of the words (the
     // value then sits near the (1.3 k)-th best of everything scanned so far)
     set_exchange(a, p.pub_slots, k);
-    const int pool_slices = g_filter_route.load(std::memory_order_relaxed) == PSC_ROUTE_AUTO && skip_first < 0 && redo_dev == nullptr
+    // (codes at distance +infinity are listed where the merge of the tiled kernels' lists would list them, whichever kernel
+    //  answers)
+    const bool infinite = !merge_selects(nq, p.nslice, k);
+    const float open = infinite ? HUGE_VALF : FLT_MAX;
+    const int64_t nwords = nq * p.pub_slots;
+    bool words_set = false;
+    if (marked != nullptr) {
+        ScanArgs few = a;
+        few.nslice = marked_slices(n, k);
+        few.slice_len = ((n + few.nslice - 1) / few.nslice + 63) / 64 * 64;
+        few.nslice = (int)((n + few.slice_len - 1) / few.slice_len);
+        const size_t entries = (size_t)marked->few * few.nslice * k, dist_bytes = (entries * sizeof(float) + 255) / 256 * 256;
+        few.part_d = (float *)marked->scratch;
+        few.part_i = (int64_t *)((char *)marked->scratch + dist_bytes);
+        if (few.slice_len <= (1 << 24) && (few.nslice == 1 || few.nslice * k <= kSmallPool) &&
+            dist_bytes + entries * sizeof(int64_t) <= marked->scratch_bytes) {
+            rc = dispatch_scan_pool<true>(m, dense, few, open, clear_status ? a.status : nullptr, few.nslice > 1 ? marked->arrived : nullptr,
+                                          ids_dev, dists_dev, *marked, nwords, s);
+            if (rc != PSC_OK) return rc;
+            words_set = true;
+        }
+    }
+    const int pool_slices = g_filter_route.load(std::memory_order_relaxed) == PSC_ROUTE_AUTO && skip_first < 0 && marked == nullptr
                                 ? pool_scan_slices(m, nq, n, k, ht, dense, mfma, preset, p, ws_bytes)
                                 : 0;
     if (pool_slices > 0) {
@@ -3082,23 +3138,15 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
             PSC_HIP_TRY(hipGetLastError());
         }
         int *status = clear_status ? a.status : nullptr;
-        // (codes at distance +infinity are listed where the merge of the tiled kernels' lists would list them)
-        const bool infinite = !merge_selects(nq, p.nslice, k);
-        const float open = infinite ? HUGE_VALF : FLT_MAX;
-        if (m == 8)
-            rc = dense ? run_scan_pool<8, true>(a, open, status, arrived, ids_dev, dists_dev, s)
-                       : run_scan_pool<8, false>(a, open, status, arrived, ids_dev, dists_dev, s);
-        else
-            rc = dense ? run_scan_pool<16, true>(a, open, status, arrived, ids_dev, dists_dev, s)
-                       : run_scan_pool<16, false>(a, open, status, arrived, ids_dev, dists_dev, s);
+        rc = dispatch_scan_pool<false>(m, dense, a, open, status, arrived, ids_dev, dists_dev, MarkedQueries{}, 0, s);
         if (rc != PSC_OK) return rc;
         note_route(dense ? "scan_pool_kernel+all" : "scan_pool_kernel", m, 1, 16, a.nslice, nq * a.nslice);
         if (a.nslice == 1 || self_merge) return PSC_OK;
         return launch_merge(a.part_d, a.part_i, nq, a.nslice, k, infinite, a.status, nullptr, ids_dev, dists_dev, s);
     }
-    const int64_t nwords = nq * p.pub_slots;
-    hipLaunchKernelGGL(init_scan_kernel, dim3((unsigned)((nwords + 255) / 256)), dim3(256), 0, s, a.gthr, nwords,
-                       clear_status ? a.status : (int *)nullptr);
+    if (!words_set)
+        hipLaunchKernelGGL(init_scan_kernel, dim3((unsigned)((nwords + 255) / 256)), dim3(256), 0, s, a.gthr, nwords,
+                           clear_status ? a.status : (int *)nullptr);
     // A single query leaves three of the narrowest tile's four query slots empty: they take copies of
     // its tables and code, every wave feeds the list of slot wave % 4, and the four lists are merged
     // when the slice ends -- a list's lock is then shared by 4 waves instead of 16 while the lists
@@ -3132,7 +3180,7 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
     if (rc != PSC_OK) return rc;
     note_route(ht >= nbits ? "adc_kernel" : dense ? "adc_kernel+filter" : mfma ? "scan_mfma_kernel" : "scan_kernel",
                m, p.tq, p.nwaves, p.nslice, p.ntiles);
-    return launch_merge(a.part_d, a.part_i, nq, p.nslice, k, false, a.status, redo_dev, ids_dev, dists_dev, s);
+    return launch_merge(a.part_d, a.part_i, nq, p.nslice, k, false, a.status, a.redo, ids_dev, dists_dev, s);
 }
 
 // Which filter the grouped inverted-file scan takes.  The matrix-core kernel needs 64-bit codes,

@@ -239,3 +239,18 @@ def test_marked_queries_side_by_side(trained, force_route, marked):
     assert route == "bound_scan_kernel" and other != route, (route, other)
     assert torch.equal(ids, ids2)
     assert torch.equal(d.view(torch.int32), d2.view(torch.int32))
+
+
+@pytest.mark.parametrize("m,nq,k", [(8, 400, 100), (16, 300, 64), (8, 520, 256)])
+def test_few_marked_queries_whose_distances_are_infinite(trained, force_route, m, nq, k):
+    """Which codes at distance +infinity are listed goes by the size of the whole batch (the kernel that merges its lists),
+    not by that of the few marked queries that are scanned by themselves."""
+    import paper_1609_01882_amd as psc
+    idx, codes = trained(128, m)
+    codes = codes.repeat(10, 1).contiguous()
+    q = _mixture(nq, 128, 12)[0]
+    q[3, 5], q[77], q[nq - 1, 0], q[nq - 1, 127] = float("inf"), 1e25, 1.5e19, 1.5e19
+    print(f"m={m} nq={nq} k={k}", flush=True)
+    (route, ids, d), (other, want_ids, want_d) = _both(psc, idx, q, codes, 8 * m, k)
+    assert route == "bound_scan_kernel" and other != route, (route, other)
+    assert torch.equal(ids, want_ids) and torch.equal(d.view(torch.int32), want_d.view(torch.int32))
