@@ -108,8 +108,8 @@ struct ScanArgs {
     // >= k codes at or below it: nothing farther than v is in the query's top k.  With one word,
     // pub_r = k and pub_kth = 1 this is the plain exchange of k-th best distances.
     int pub_slots = 1, pub_r = 0, pub_kth = 1;
-    // Flat mode: a word per query, non-zero for those this scan is to answer (nullptr: all of them).  Tiles without
-    // such a query end at once.
+    // Flat mode: a word per query, non-zero for those this scan is to answer (nullptr: all of them).  Tiles (workgroups
+    // of the small scan) without such a query end at once.
     const uint32_t *redo = nullptr;
 };
 
@@ -1783,6 +1783,8 @@ scan_pool_kernel(ScanArgs a, float open, int *status, uint32_t *arrived, int64_t
         if (count > (uint32_t)marked.few || item >= (int64_t)count) return;  // (uniform)
         q = __builtin_amdgcn_readfirstlane(marked.which[item]);
         if (slice == 0 && tid == 0) marked.redo[q] = 0u;
+    } else {
+        if (a.redo != nullptr && a.redo[q] == 0u) return;  // (uniform)
     }
 
     // codes of the wave's turn `blk`: code blk + 64 l + lane in c[l]; past the end the range check
@@ -3115,7 +3117,7 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
             words_set = true;
         }
     }
-    const int pool_slices = g_filter_route.load(std::memory_order_relaxed) == PSC_ROUTE_AUTO && skip_first < 0 && marked == nullptr
+    const int pool_slices = g_filter_route.load(std::memory_order_relaxed) == PSC_ROUTE_AUTO && skip_first < 0
                                 ? pool_scan_slices(m, nq, n, k, ht, dense, mfma, preset, p, ws_bytes)
                                 : 0;
     if (pool_slices > 0) {
@@ -3133,16 +3135,16 @@ int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t 
         uint32_t *arrived = self_merge ? a.gthr : nullptr;
         a.part_d = (float *)((char *)ws + 256 + (self_merge ? words : 0));
         a.part_i = (int64_t *)((char *)a.part_d + dist_bytes);
-        if (self_merge && !preset) {
+        if (self_merge && !preset && !words_set) {
             hipLaunchKernelGGL(init_scan_kernel, dim3((unsigned)((nq + 255) / 256)), dim3(256), 0, s, arrived, nq, (int *)nullptr);
             PSC_HIP_TRY(hipGetLastError());
         }
-        int *status = clear_status ? a.status : nullptr;
+        int *status = clear_status && !words_set ? a.status : nullptr;
         rc = dispatch_scan_pool<false>(m, dense, a, open, status, arrived, ids_dev, dists_dev, MarkedQueries{}, 0, s);
         if (rc != PSC_OK) return rc;
         note_route(dense ? "scan_pool_kernel+all" : "scan_pool_kernel", m, 1, 16, a.nslice, nq * a.nslice);
         if (a.nslice == 1 || self_merge) return PSC_OK;
-        return launch_merge(a.part_d, a.part_i, nq, a.nslice, k, infinite, a.status, nullptr, ids_dev, dists_dev, s);
+        return launch_merge(a.part_d, a.part_i, nq, a.nslice, k, infinite, a.status, a.redo, ids_dev, dists_dev, s);
     }
     if (!words_set)
         hipLaunchKernelGGL(init_scan_kernel, dim3((unsigned)((nwords + 255) / 256)), dim3(256), 0, s, a.gthr, nwords,

@@ -254,3 +254,24 @@ def test_few_marked_queries_whose_distances_are_infinite(trained, force_route, m
     (route, ids, d), (other, want_ids, want_d) = _both(psc, idx, q, codes, 8 * m, k)
     assert route == "bound_scan_kernel" and other != route, (route, other)
     assert torch.equal(ids, want_ids) and torch.equal(d.view(torch.int32), want_d.view(torch.int32))
+
+
+@pytest.mark.parametrize("m,n,nq,ht,k", [(8, 200_003, 3000, 24, 100), (8, 100_003, 2000, 64, 10), (8, 400_003, 100, 64, 10),
+                                         (16, 200_003, 1500, 56, 37), (16, 300_001, 100, 128, 100)])
+@pytest.mark.parametrize("share", [1.0, 0.3])
+def test_batches_that_are_left_to_the_scan(trained, m, n, nq, ht, k, share):
+    """All queries marked, and a third of them: the scan of the former route answers them, the small scan (whose results
+    those of `scan` on ready tables are) where that is its route."""
+    import paper_1609_01882_amd as psc
+    idx, codes = trained(128, m)
+    c = codes[:n].contiguous() if share < 1.0 else _dev(W.random_codes(n, m, seed=6))
+    q = _mixture(nq, 128, 13)[0]
+    if share < 1.0:
+        q[torch.arange(nq, device="cuda") % 10 < 3, 7] = float("inf")
+    print(f"m={m} n={n} nq={nq} ht={ht} k={k} {share}", flush=True)
+    ids, d = idx.search(q, c, ht, k)
+    assert psc.last_scan_route().startswith("bound_scan_kernel ")
+    lut, qc = idx.build_lut(q)
+    want_ids, want_d = psc.scan(lut, qc, c, ht, k)
+    torch.cuda.synchronize()
+    assert torch.equal(ids, want_ids) and torch.equal(d.view(torch.int32), want_d.view(torch.int32))
