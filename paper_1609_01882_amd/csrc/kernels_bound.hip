@@ -213,6 +213,14 @@ bound_scan_kernel(BoundArgs a)
         for (int g = 0; g < QG; ++g) least[g] = ((volatile PSC_LDS float *)s.least)[g * 32 + (lane & 31)];
     };
     load_least();
+    bool any = false;
+#pragma unroll
+    for (int g = 0; g < QG; ++g) any = any || least[g] < __builtin_inff();
+    __syncthreads();  // (the waves have read the same: none has marked a query yet)
+    if (ballot64(any) == 0ull) {  // every query of the tile is marked
+        for (int i = tid; i < 257; i += 256) a.first[(size_t)item * 257 + i] = 0u;
+        return;
+    }
 
     const uint32_t bytes = (uint32_t)a.n * (uint32_t)M;  // (< 2^31)
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.codes, 0, (int)bytes, 0x00020000);

@@ -275,3 +275,17 @@ def test_batches_that_are_left_to_the_scan(trained, m, n, nq, ht, k, share):
     want_ids, want_d = psc.scan(lut, qc, c, ht, k)
     torch.cuda.synchronize()
     assert torch.equal(ids, want_ids) and torch.equal(d.view(torch.int32), want_d.view(torch.int32))
+
+
+@pytest.mark.parametrize("dim,m,n,nq", [(128, 8, 3_200_024, 600), (256, 16, 1_200_009, 300)])
+def test_lists_that_run_over_in_the_first_of_several_rounds(trained, force_route, dim, m, n, nq):
+    """A database of one code but for some rows: every query is marked before the later rounds."""
+    import paper_1609_01882_amd as psc
+    idx, codes = trained(dim, m)
+    c = codes[:1].repeat(n, 1)
+    c[::1001] = codes[1]
+    q = _mixture(nq, dim, 14)[0]
+    print(f"dim={dim} m={m} n={n} nq={nq}", flush=True)
+    (route, ids, d), (other, want_ids, want_d) = _both(psc, idx, q, c, 8 * m, 10)
+    assert route == "bound_scan_kernel" and other != route, (route, other)
+    assert torch.equal(ids, want_ids) and torch.equal(d, want_d)
