@@ -47,6 +47,10 @@ constexpr int kBoundMaxK = 256;
 constexpr int kLeastSample = 4096, kMaxSample = 65536;  // codes of the sample
 constexpr int kMostStep = 5;         // a round looks at most at 2^this times as many codes as all before
 constexpr int kSampleKeys = 4096;    // keys of the sample's pool
+// Rows that a query may list in a round over so many codes.  More are ranked by one workgroup, 2.6 ns a row, in longer than
+// 16 take to scan all codes for a query that is marked (4000 queries x 4M codes, half of them alike, 128 bits, nothing
+// filtered: 5500 us with all of them ranked, 5000 with this; 3000 x 200k 935 and 592).
+inline double most_listed(double codes) { return 2.0 * kNear + codes / 32.0; }
 constexpr int kMarkWords = 64;       // of `marks`: the count, and from here on `few` words for the scan of each, then which they are
 constexpr float kLeast = -1e29f;     // below every product, above every invalid row's
 constexpr float kInvalid = 1e30f;    // "half square" of a row past the end
@@ -656,7 +660,7 @@ bound_prepare_kernel(PrepareArgs a)
 struct SelectScratch {
     uint32_t hist[256];
     uint32_t lo[4], hi[4];
-    uint32_t bin, below, kept;
+    uint32_t bin, below, kept, tied;
 };
 template <int PER>
 __device__ __forceinline__ uint32_t kth_smallest(PSC_LDS SelectScratch &s, const uint32_t (&e)[PER], int regs, uint32_t kk)
@@ -748,8 +752,8 @@ struct SampleLds {
 template <int M>
 __global__ void __launch_bounds__(256)
 bound_sample_kernel(const uint8_t *__restrict__ codes, const uint8_t *__restrict__ qcodes, const float *__restrict__ luts,
-                    int total, uint32_t bias, int rank, int checked, uint32_t most_near, uint32_t *__restrict__ unfit,
-                    const uint32_t *__restrict__ redo, uint64_t *__restrict__ thr)
+                    int total, uint32_t bias, int rank, int checked, uint32_t most_near, uint32_t most_tied, uint32_t most_alone,
+                    uint32_t *__restrict__ unfit, uint32_t *__restrict__ redo, uint64_t *__restrict__ thr)
 {
     constexpr int WPC = M / 4;
     typedef uint32_t words __attribute__((ext_vector_type(WPC)));
@@ -792,20 +796,26 @@ bound_sample_kernel(const uint8_t *__restrict__ codes, const uint8_t *__restrict
         base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
         if (take) s.pool[base + (uint32_t)prefix_count(m)] = key;  // (kSampleRoom places are kept)
     };
-    // the `rank` smallest to the front of the pool's c keys, the largest of them
+    // the `rank` smallest to the front of the pool's c keys, the largest of them; `more`: how many others are as small
+    uint32_t more = 0u;
     auto select = [&](int c) {
         uint32_t e[kSampleKeys / 256];
         const int regs = (c + 255) >> 8;
 #pragma unroll
         for (int i = 0; i < kSampleKeys / 256; ++i) e[i] = tid + 256 * i < c ? s.pool[tid + 256 * i] : ~0u;
         const uint32_t kth = kth_smallest(s.sel, e, regs, (uint32_t)rank);
-        if (tid == 0) s.sel.kept = 0u;
+        if (tid == 0) s.sel.kept = s.sel.tied = 0u;
         __syncthreads();
+        uint32_t same = 0u;
 #pragma unroll
-        for (int i = 0; i < kSampleKeys / 256; ++i)
+        for (int i = 0; i < kSampleKeys / 256; ++i) {
             if (i < regs && e[i] < kth) s.pool[__hip_atomic_fetch_add(&s.sel.kept, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)] = e[i];
+            same += (uint32_t)__builtin_popcountll(ballot64(i < regs && e[i] == kth));
+        }
+        if (lane == 0) __hip_atomic_fetch_add(&s.sel.tied, same, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         __syncthreads();
         const int below = (int)s.sel.kept;
+        more = (kth == bound ? more : 0u) + (uint32_t)below + s.sel.tied - (uint32_t)rank;
         if (tid < rank - below) s.pool[below + tid] = kth;
         if (tid == 0) s.count = (uint32_t)rank;
         return kth;
@@ -840,7 +850,14 @@ bound_sample_kernel(const uint8_t *__restrict__ codes, const uint8_t *__restrict
     __syncthreads();
     uint64_t key = kNoEntry;
     if (have >= rank) key = (uint64_t)select(have) << 32 | 0xffffffffull;
-    if (tid == 0) thr[q] = key;
+    // Equal distances are all listed, and where fewer than `rank` pass the test everything is.  A query that would list a good
+    // share of the codes so is left to the other scan at once; one in eight says so of the batch.
+    const bool alone = have < rank || (uint32_t)rank + more > most_alone;
+    if (tid == 0) {
+        thr[q] = key;
+        if (alone) redo[q] = 1u;
+        if ((q & 7) == 0 && checked == 0 && (uint32_t)rank + more > most_tied) __hip_atomic_fetch_add(unfit, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     if (checked == 0 || (q & 7) != 0) return;
     // How many codes are as near, whether they pass the test or not: those are what the rounds will list.  Where the
     // numbering of the centroids says nothing about distance they are many times those that pass; a batch of which an
@@ -1449,13 +1466,14 @@ int run_bound(const BoundSearch &b, int64_t q_first, int nq, const BoundLayout &
 
     const int ht = std::min(b.ht, 8 * M);
     const uint32_t bias = 0x7fffffffu - (uint32_t)ht;
-    // A query is unfit if three times what a round lists by its rank, times the codes that are as near as those that
-    // pass, is more than its share of the lists.
+    // A query is unfit if three times the codes of the first round that are as near (of which the test lets some through:
+    // counted over part of the sample; without a test they are those at equal distances) are more than its share of the lists.
     const int checked = ht < 8 * M ? std::min(p.samples, 2048) : 0;
-    const double lists = (double)plan.rank[0] * plan.stride[0] / plan.stride[1];
-    const uint32_t most_near = (uint32_t)((double)checked * plan.rank[0] / p.samples * kNear / (3.0 * lists)) + 8u;
+    const double ratio = (double)plan.stride[0] / plan.stride[1], codes_in = (double)b.n / plan.stride[1];
+    const uint32_t most_near = (uint32_t)((double)checked / p.samples * kNear / (3.0 * ratio)) + 8u;
+    const uint32_t most_tied = (uint32_t)(kNear / (3.0 * ratio)) + 8u, most_alone = (uint32_t)(most_listed(codes_in) / ratio);
     hipLaunchKernelGGL((bound_sample_kernel<M>), dim3((unsigned)nq), dim3(256), 0, s, p.sample, qcodes, lut, p.samples,
-                       bias, plan.rank[0], checked, most_near, p.unfit, redo, thr);
+                       bias, plan.rank[0], checked, most_near, most_tied, most_alone, p.unfit, redo, thr);
     PSC_HIP_TRY(hipGetLastError());
 
     BoundArgs a;
