@@ -941,6 +941,7 @@ struct RankArgs {
     uint32_t bias;  // 0x7fffffff - ht
     int k, rank;    // rank: whose distance bounds the next round
     float ratio;    // the next round's codes to this one's
+    uint32_t most;  // rows that are ranked; a query that lists more is marked (most_listed)
     int64_t *ids;
     float *dists;
     // of the last round: where its marks are counted and listed (BoundLayout), unless the batch is unfit (all are marked then)
@@ -1014,6 +1015,7 @@ bound_rank_kernel(RankArgs a)
         const uint32_t total = s.part[0] + s.part[1] + s.part[2] + s.part[3];
         if (total == 0u) break;  // (uniform)
         listed += total;
+        if (listed > a.most) break;  // (uniform)
         for (int w = 0; w < (tid >> 6); ++w) upto += s.part[w];
         const uint32_t *run = a.near + item * a.cap + at;
         uint32_t mine[kRun];
@@ -1054,7 +1056,7 @@ bound_rank_kernel(RankArgs a)
     __syncthreads();
     if (tid >= 64) return;
     const int pooled = (int)s.count;
-    if (pooled > kBoundPool) {
+    if (pooled > kBoundPool || listed > a.most) {
         if (lane == 0) {
             a.redo[q] = 1u;
             if (LAST) list_mark();
@@ -1531,6 +1533,7 @@ int run_bound(const BoundSearch &b, int64_t q_first, int nq, const BoundLayout &
         PSC_HIP_TRY(hipGetLastError());
         r.cap = a.cap;
         r.slices = a.slices;
+        r.most = (uint32_t)most_listed((double)a.codes_in);
         r.rank = last ? 0 : plan.rank[i + 1];
         r.ratio = last ? 1.f : (float)a.stride / (float)plan.stride[i + 2];
         if (last) hipLaunchKernelGGL((bound_rank_kernel<M, true>), dim3((unsigned)nq), dim3(256), 0, s, r);
