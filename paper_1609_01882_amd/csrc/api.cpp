@@ -447,11 +447,11 @@ int psc_search(const psc_index *idx, const float *q_dev, int64_t nq, const uint8
     rc = build_lut(idx, q_dev, nq, lut, qcodes, (uint32_t *)((char *)workspace_dev + 256),
                    (int)std::min<int64_t>(nq, kPresetQueries), &preset, (hipStream_t)stream);
     if (rc != PSC_OK) return rc;
-    const size_t bound_bytes = bound_workspace_bytes(idx->m, idx->dsub, nq, n, k);
-    if (bound_bytes != 0 && idx->bound.usable && g_filter_route.load(std::memory_order_relaxed) == PSC_ROUTE_AUTO && ht >= 0 && ids_dev &&
-        dists_dev && codes_dev && ((uintptr_t)codes_dev & 15) == 0 && bound_search_pays(idx->m, idx->dsub, nq, n, ht, k, scan_bytes) &&
-        workspace_bytes >= need + round256((size_t)nq * sizeof(uint32_t)) + bound_bytes) {
-        BoundSearch b;
+    BoundSearch b;
+    const size_t marks_bytes = round256((size_t)nq * sizeof(uint32_t));
+    if (idx->bound.usable && g_filter_route.load(std::memory_order_relaxed) == PSC_ROUTE_AUTO && ht >= 0 && ids_dev && dists_dev && codes_dev &&
+        ((uintptr_t)codes_dev & 15) == 0 && workspace_bytes >= need + marks_bytes + bound_scratch_bytes(idx->m, idx->dsub, nq) &&
+        bound_search_pays(idx->m, idx->dsub, nq, n, ht, k, scan_bytes, &b.plan)) {
         b.cb = idx->bound;
         b.image = idx->cb_dev + idx->bound_at;
         b.mu = idx->cb_dev + 2 * idx->cb_host.size();
@@ -469,7 +469,7 @@ int psc_search(const psc_index *idx, const float *q_dev, int64_t nq, const uint8
         b.ids = ids_dev;
         b.dists = dists_dev;
         b.redo = (uint32_t *)((char *)workspace_dev + need);
-        b.ws = (char *)b.redo + round256((size_t)nq * sizeof(uint32_t));
+        b.ws = (char *)b.redo + marks_bytes;
         MarkedQueries marked;
         rc = launch_bound_search(b, &marked, (hipStream_t)stream);
         if (rc != PSC_OK) return rc;

@@ -154,11 +154,20 @@ bool build_bound_image(const float *centred, int m, int dsub, float *image, Boun
 constexpr int64_t kBoundMinQueries = 16;      // below these sizes a search never comes this way
 constexpr int64_t kBoundMinCodes = 100'000;
 constexpr int64_t kBoundChunk = 5'120;        // queries whose lists the workspace holds at a time
-// Scratch (0: these sizes never come this way), and whether the search of these sizes is the faster one.
+// The rounds of a search, each over a part of the codes.
+struct BoundRounds {
+    int rounds = 0;   // after the sample
+    int stride[13];   // of the sample, then of each round, in codes (odd: not all in the same few channels of memory; the last 1)
+    int rank[12];     // whose distance bounds the round
+};
+// Scratch (0: no threshold sends these sizes this way), whether the search of these sizes is the faster one, and its rounds
+// if so; the scratch it takes.
 size_t bound_workspace_bytes(int m, int dsub, int64_t nq, int64_t n, int k);
-bool bound_search_pays(int m, int dsub, int64_t nq, int64_t n, int ht, int k, size_t ws_bytes);
+bool bound_search_pays(int m, int dsub, int64_t nq, int64_t n, int ht, int k, size_t ws_bytes, BoundRounds *plan);
+size_t bound_scratch_bytes(int m, int dsub, int64_t nq);
 struct BoundSearch {
     BoundCodebook cb;
+    BoundRounds plan;
     const float *image, *mu;
     int dim, m, dsub;
     const float *q, *lut;

@@ -1203,40 +1203,38 @@ int floor_log2(int64_t v)
     return l;
 }
 
-// Binomial(trials, p) >= r
-double binomial_tail(int trials, double p, int r)
-{
-    double term = std::pow(1.0 - p, trials), below = 0.0;
-    for (int i = 0; i < r; ++i) {
-        below += term;
-        term *= (double)(trials - i) / (double)(i + 1) * (p / (1.0 - p));
-    }
-    return 1.0 - below;
-}
 // The rank whose distance bounds a round over R times as many codes, so that fewer than k of them are as near in less than 1 of
 // 10^7 cases.  After the sample, whose codes need not be among the round's: k - 1 of the round's and all `rank` of the
 // sample's are the nearest of both.  After a round over a part of the next one's codes: at least `rank` of the next one's k
 // best were among them; at most k.
 int rank_after_sample(int k, double ratio)
 {
+    // Binomial(k + r - 1, p) >= r: less with every r by C(k + r - 1, r) p^r (1 - p)^k
     const double p = 1.0 / (1.0 + ratio);
-    int r = 1;
-    while (binomial_tail(k + r - 1, p, r) > 1e-7) ++r;
+    double term = std::pow(1.0 - p, k), tail = 1.0;
+    int r = 0;
+    do {
+        tail -= term;
+        term *= (double)(k + r) / (double)(r + 1) * p;
+        ++r;
+    } while (tail > 1e-7);
     return r;
 }
 int rank_after_round(int k, double ratio)
 {
-    int r = 1;
-    while (r < k && binomial_tail(k, 1.0 / ratio, r) > 1e-7) ++r;
+    // Binomial(k, p) >= r
+    const double p = 1.0 / ratio;
+    double term = std::pow(1.0 - p, k), tail = 1.0;
+    int r = 0;
+    do {
+        tail -= term;
+        term *= (double)(k - r) / (double)(r + 1) * (p / (1.0 - p));
+        ++r;
+    } while (r < k && tail > 1e-7);
     return r;
 }
 
 // Sample and rounds for n codes, of which a share `keep` passes the Hamming test at least.
-struct BoundRounds {
-    int rounds = 0;   // after the sample
-    int stride[13];   // of the sample, then of each round, in codes (odd: not all in the same few channels of memory; the last 1)
-    int rank[12];     // whose distance bounds the round
-};
 BoundRounds plan_rounds(int64_t n, int k, double keep)
 {
     BoundRounds r;
@@ -1397,23 +1395,29 @@ bool sizes_fit(int m, int dsub, int64_t nq, int64_t n, int k)
 // taken where it was slower by more than 5 % in 3 of them, 0.692 of the time before in geometric mean, 0.681 if the
 // faster one were always taken.  Thresholds that let fewer than 1 random pair of 500 through are left to the Hamming
 // filter: the k-th best among so few is far, and many codes are as near.
-bool bound_search_pays(int m, int dsub, int64_t nq, int64_t n, int ht, int k, size_t ws_bytes)
+// (The plan of the rounds comes last: it takes longer than the estimates.)
+bool bound_search_pays(int m, int dsub, int64_t nq, int64_t n, int ht, int k, size_t ws_bytes, BoundRounds *plan)
 {
     if (!sizes_fit(m, dsub, nq, n, k)) return false;
     const double keep = ht >= 8 * m ? 1.0 : random_code_survival(8 * m, ht);
-    if (keep < 0.002 || plan_rounds(n, k, keep).rounds == 0) return false;
+    if (keep < 0.002) return false;
     const double padded = (double)((nq + 31) / 32 * 32), steps = m * padded_length(m, dsub) / 64;
     const double bounds = 65.0 + 9.6 * std::log2((double)n / 1e5) + 0.042 * (double)nq * (1.0 + k / 100.0) +
                           0.5 * steps * 9.75e-8 * padded * (double)n + 0.7 * m;
-    return bounds < 0.9 * (estimated_scan_time(m, nq, n, k, ht, ws_bytes) + 12.0);
+    if (bounds >= 0.9 * (estimated_scan_time(m, nq, n, k, ht, ws_bytes) + 12.0)) return false;
+    *plan = plan_rounds(n, k, keep);
+    return plan->rounds != 0;
 }
+
+size_t bound_scratch_bytes(int m, int dsub, int64_t nq) { return padded_length(m, dsub) != 0 ? bound_layout(m, dsub, nq).total : 0; }
 
 size_t bound_workspace_bytes(int m, int dsub, int64_t nq, int64_t n, int k)
 {
     // (the thresholds at which the other kernels take longest: nothing filtered, and the last before the dense route)
     const size_t any = (size_t)1 << 60;
+    BoundRounds plan;
     for (int ht : {8 * m, m == 8 ? 29 : 61})
-        if (bound_search_pays(m, dsub, nq, n, ht, k, any)) return bound_layout(m, dsub, nq).total;
+        if (bound_search_pays(m, dsub, nq, n, ht, k, any, &plan)) return bound_scratch_bytes(m, dsub, nq);
     return 0;
 }
 
@@ -1552,8 +1556,7 @@ int run_bound(const BoundSearch &b, int64_t q_first, int nq, const BoundLayout &
 int launch_bound_search(const BoundSearch &b, MarkedQueries *marked, hipStream_t s)
 {
     const int dp = padded_length(b.m, b.dsub);
-    const double keep = b.ht >= 8 * b.m ? 1.0 : random_code_survival(8 * b.m, b.ht);
-    const BoundRounds plan = plan_rounds(b.n, b.k, keep);
+    const BoundRounds &plan = b.plan;
     PSC_REQUIRE(dp != 0 && plan.rounds > 0, "sizes without a bound search");
     const BoundLayout l = bound_layout(b.m, b.dsub, b.nq);
     uint32_t *marks = (uint32_t *)((char *)b.ws + l.marks);

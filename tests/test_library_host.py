@@ -235,3 +235,22 @@ def test_scan_workspace_of_large_databases(psc):
         b = psc.scan_workspace_bytes(m, nq, n, k)
         assert b <= 256 + 4 * nq * slices + 12 * nq * k * slices + 1024, (m, n, b)
         assert b <= psc.PSC_STATIC_SCRATCH_BYTES
+
+
+def test_the_route_of_a_search_is_chosen_in_little_host_time(psc):
+    """The sizes for which a search by bounds is weighed against the scans cost the host a few times what others do, not
+    forty times (every search of 16 queries and 100k codes or more pays for it)."""
+    import time
+    idx = psc.Index(128, 8)
+
+    def per_call(nq, k):
+        best = float("inf")
+        for _ in range(20):
+            t = time.perf_counter()
+            for _ in range(50):
+                idx.search_workspace_bytes(nq, 300_000, k)
+            best = min(best, time.perf_counter() - t)
+        return best / 50
+
+    for k in (10, 100, 256):
+        assert per_call(100, k) < 12 * per_call(15, k), (k, per_call(100, k), per_call(15, k))
