@@ -1205,8 +1205,9 @@ int floor_log2(int64_t v)
 
 // The rank whose distance bounds a round over R times as many codes, so that fewer than k of them are as near in less than 1 of
 // 10^7 cases.  After the sample, whose codes need not be among the round's: k - 1 of the round's and all `rank` of the
-// sample's are the nearest of both.  After a round over a part of the next one's codes: at least `rank` of the next one's k
-// best were among them; at most k.
+// sample's are the nearest of both; so too after a round whose stride is no multiple of the next one's (2^a - 1 divides
+// 2^b - 1 where a divides b).  After a round over a part of the next one's codes: at least `rank` of the next one's k best were
+// among them; at most k.
 int rank_after_sample(int k, double ratio)
 {
     // Binomial(k + r - 1, p) >= r: less with every r by C(k + r - 1, r) p^r (1 - p)^k
@@ -1260,7 +1261,7 @@ BoundRounds plan_rounds(int64_t n, int k, double keep)
         left -= (left + r.rounds - i - 1) / (r.rounds - i);  // (the wider steps first)
         r.stride[i + 1] = odd(left);
         const double ratio = (double)r.stride[i] / r.stride[i + 1];
-        r.rank[i] = i == 0 ? rank_after_sample(k, ratio) : rank_after_round(k, ratio);
+        r.rank[i] = i > 0 && r.stride[i] % r.stride[i + 1] == 0 ? rank_after_round(k, ratio) : rank_after_sample(k, ratio);
     }
     return r;
 }
