@@ -46,7 +46,7 @@ constexpr int kBoundPool = 2048;     // those of them that are tested and nearer
 constexpr int kBoundMaxK = 256;
 constexpr int kLeastSample = 4096, kMaxSample = 65536;  // codes of the sample
 constexpr int kMostStep = 5;         // a round looks at most at 2^this times as many codes as all before
-constexpr int kSampleKeys = 4096;    // keys of the sample's pool
+constexpr int kSampleKeys = 2048;    // keys of the sample's pool
 // Rows that a query may list in a round over so many codes.  More are ranked by one workgroup, 2.6 ns a row, in longer than
 // 16 take to scan all codes for a query that is marked (4000 queries x 4M codes, half of them alike, 128 bits, nothing
 // filtered: 5500 us with all of them ranked, 5000 with this; 3000 x 200k 935 and 592).
@@ -738,8 +738,10 @@ __device__ __forceinline__ uint32_t kth_smallest(PSC_LDS SelectScratch &s, const
     }
 }
 
-// The sample, tested and scored; the key of the rank-th best distance bounds what follows.  One workgroup per query, four codes to a thread and turn; codes that pass the test
-// wait in a queue of their wave until there are 64.
+// The sample, tested and scored; the key of the rank-th best distance bounds what follows.  One workgroup per query, four codes
+// to a thread and turn; codes that pass the test wait in a queue of their wave until there are 64.  Bound by the trip to L2 for
+// a turn's codes and by how many workgroups LDS lets run: with codes two turns ahead and a pool of 2048 keys (one turn and
+// 4096) 1000 queries x 15900 codes of 128 bits take 27 us, 86 before, 3000 x 13300 54 and 99.
 constexpr int kSampleRoom = 1024 + 4 * 64;  // keys of a turn: its codes and those that waited
 template <int M>
 struct SampleLds {
@@ -760,8 +762,17 @@ bound_sample_kernel(const uint8_t *__restrict__ codes, const uint8_t *__restrict
     __shared__ __align__(16) SampleLds<M> shared;
     PSC_LDS SampleLds<M> &s = *(PSC_LDS SampleLds<M> *)&shared;
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t q = blockIdx.x;
+    // The queries that are asked come first; once enough of them have said so the others have nothing to do here.
+    const int asked = ((int)gridDim.x + 7) >> 3, other = (int)blockIdx.x - asked;
+    const int64_t q = other < 0 ? (int64_t)blockIdx.x * 8 : other + other / 7 + 1;
     if (redo[q] != 0u) return;  // (uniform)
+    if (other >= 0) {
+        if (tid == 0) s.count = __hip_atomic_load(unfit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        const uint32_t said = s.count;
+        __syncthreads();
+        if (said * 64u > gridDim.x) return;
+    }
     for (int e = tid; e < M * 64; e += 256) ((PSC_LDS v4i *)s.lut)[e] = ((const v4i *)(luts + q * (M * 256)))[e];
     uint32_t qw[WPC];
 #pragma unroll
@@ -775,8 +786,9 @@ bound_sample_kernel(const uint8_t *__restrict__ codes, const uint8_t *__restrict
             c[i] = p < total ? ((const words *)codes)[p] : words(0u);
         }
     };
-    words cur[4];
-    load(0, cur);
+    words cur[2][4];  // (two turns ahead)
+    load(0, cur[0]);
+    load(1024, cur[1]);
     __syncthreads();
     PSC_LDS words *const queue = (PSC_LDS words *)s.queue[wave];
     int fill = 0;
@@ -820,11 +832,11 @@ bound_sample_kernel(const uint8_t *__restrict__ codes, const uint8_t *__restrict
         if (tid == 0) s.count = (uint32_t)rank;
         return kth;
     };
-    for (int t = 0; t < total; t += 1024) {
+    auto turn = [&](int t, words (&next)[4]) {
         words c[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) c[i] = cur[i];
-        load(t + 1024, cur);
+        for (int i = 0; i < 4; ++i) c[i] = next[i];
+        load(t + 2048, next);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             uint32_t h = bias;
@@ -843,6 +855,10 @@ bound_sample_kernel(const uint8_t *__restrict__ codes, const uint8_t *__restrict
             bound = select(have);
             __syncthreads();
         }
+    };
+    for (int t = 0; t < total; t += 2048) {
+        turn(t, cur[0]);
+        if (t + 1024 < total) turn(t + 1024, cur[1]);
     }
     if (fill > 0) score(fill);
     __syncthreads();
@@ -867,6 +883,7 @@ bound_sample_kernel(const uint8_t *__restrict__ codes, const uint8_t *__restrict
     __syncthreads();
     const uint32_t within = (uint32_t)(key >> 32);
     uint32_t near = 0u;
+#pragma unroll 4
     for (int p = tid; p < checked; p += 256) {
         const words c = ((const words *)codes)[p];
         float d = s.lut[c[0] & 0xffu];
