@@ -1408,11 +1408,20 @@ bool sizes_fit(int m, int dsub, int64_t nq, int64_t n, int k)
 }
 }  // namespace
 
-// The time of a search by bounds against that of launch_scan's kernels with the tables' (12 us more), both estimated;
-// in microseconds, fitted to 337 searches (16 .. 1500 queries x 100k .. 3M codes, k = 10 and 100, five thresholds):
-// taken where it was slower by more than 5 % in 3 of them, 0.692 of the time before in geometric mean, 0.681 if the
-// faster one were always taken.  Thresholds that let fewer than 1 random pair of 500 through are left to the Hamming
-// filter: the k-th best among so few is far, and many codes are as near.
+// The time of a search by bounds against that of launch_scan's kernels with the tables' (12 us more), both estimated; in
+// microseconds, fitted to 337 searches (16 .. 1500 queries x 100k .. 3M codes, k = 10 and 100, five thresholds): taken where
+// it was slower by more than 5 % in 3 of them, 0.692 of the time before in geometric mean, 0.681 if the faster one were
+// always taken.  That was on mixtures, and what the data is cannot be told beforehand: Gaussian vectors, of which many codes
+// are as near as those that pass the test, are given up after the sample.
+// Thresholds that let fewer than 1 random pair of 500 through (64 bits: below 21, 128 bits: below 48) are left to the
+// Hamming filter: the k-th best among so few is far, and less is gained where the bounds hold than lost where they do not.
+// With / without the bounds, k = 100, mixture and Gaussian vectors: 3000 queries x 200k 64 bits ht 20 340 / 461 and 500 /
+// 388 us, ht 21 327 / 464 and 489 / 393, ht 24 347 / 606 and 613 / 530; 128 bits ht 47 379 / 467 and 399 / 281, ht 48
+// 358 / 479 and 419 / 318, ht 50 377 / 526 and 510 / 419; 1000 x 1M 128 bits ht 46 307 / 402 and 329 / 256, ht 48 329 /
+// 419 and 364 / 298.
+// Past the sizes of the fit: 4000 x 4M 64 bits ht 24 1.80 / 2.46 ms (Gaussian 2.37 / 2.28), 128 bits ht 48 2.03 / 3.20 (2.71
+// / 2.58), 10k x 10M 9.98 / 14.1 and 10.6 / 25.3; of 64-bit codes more than some 30M have too many at every distance:
+// 3000 x 100M 45.0 / 43.0 ms (ht 24), 206 / 203 (nothing filtered), given up in the rounds.
 // (The plan of the rounds comes last: it takes longer than the estimates.)
 bool bound_search_pays(int m, int dsub, int64_t nq, int64_t n, int ht, int k, size_t ws_bytes, BoundRounds *plan)
 {
@@ -1422,7 +1431,10 @@ bool bound_search_pays(int m, int dsub, int64_t nq, int64_t n, int ht, int k, si
     const double padded = (double)((nq + 31) / 32 * 32), steps = m * padded_length(m, dsub) / 64;
     const double bounds = 65.0 + 9.6 * std::log2((double)n / 1e5) + 0.042 * (double)nq * (1.0 + k / 100.0) +
                           0.5 * steps * 9.75e-8 * padded * (double)n + 0.7 * m;
-    if (bounds >= 0.9 * (estimated_scan_time(m, nq, n, k, ht, ws_bytes) + 12.0)) return false;
+    // (the estimates of filtered scans of 128 bits are a third too long: 600 queries x 300k, k = 10, ht 56 172 us for 138, where
+    //  the bounds take 138 of mixtures and 187 of Gaussian vectors; 3000 x 200k, k = 100, ht 48 622 for 481, and 359)
+    const double share = m == 16 && ht < 128 ? 0.7 : 0.9;
+    if (bounds >= share * (estimated_scan_time(m, nq, n, k, ht, ws_bytes) + 12.0)) return false;
     *plan = plan_rounds(n, k, keep);
     return plan->rounds != 0;
 }
