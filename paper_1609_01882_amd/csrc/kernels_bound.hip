@@ -239,7 +239,8 @@ bound_scan_kernel(BoundArgs a)
     auto load = [&](int base, CodeHalf<M> (&c)[4]) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int at = (int)((uint32_t)(base + 32 * i + (lane & 31)) * step + (uint32_t)(half * (M / 2)));  // (past the end: zeros)
+            // (past the end: zeros, or where 32 bits wrap some row's code; spread() leaves such rows out either way)
+            const int at = (int)((uint32_t)(base + 32 * i + (lane & 31)) * step + (uint32_t)(half * (M / 2)));
             if constexpr (M == 8) {
                 c[i].w[0] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, at, 0, 0);
             } else {

@@ -2652,10 +2652,11 @@ int dispatch_adc(int m, int tq, int nwaves, const ScanArgs &a, int64_t ntiles, s
     return run_adc<16, 4, 16, SHARE, FILTER>(a, ntiles, lds, s);
 }
 
+}  // namespace
+
 // Share of uniformly random b-bit codes within Hamming distance ht of a given one: what the
 // launcher goes by when it picks the kernel (real codes differ, but not by enough to matter for
 // a choice between two kernels that both give the same results).
-}  // namespace
 double random_code_survival(int nbits, int ht)
 {
     double c = 1.0, sum = 0.0;  // c = C(nbits, i) / 2^nbits, built up stepwise
