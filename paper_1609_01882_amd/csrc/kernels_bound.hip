@@ -85,7 +85,7 @@ struct BoundArgs {
     const float *s;           // [nq][kLambdas]
     const uint64_t *thr;      // [nq] codes with keys up to it are wanted (~0: all)
     uint32_t *redo;           // [nq]
-    const uint32_t *unfit;    // of every eighth query of the batch those that would list too much
+    const uint32_t *unfit;    // of every eighth query of the batch those that would list too much (marked ones twice)
     uint32_t *raw;            // [tiles * slices][cap] what passed the bound, as it came
     uint32_t *near;           // [tiles * slices][cap] the rows of those codes, by query
     uint32_t *first;          // [tiles * slices][257] where a query's rows begin
@@ -868,14 +868,17 @@ bound_sample_kernel(const uint8_t *__restrict__ codes, const uint8_t *__restrict
     uint64_t key = kNoEntry;
     if (have >= rank) key = (uint64_t)select(have) << 32 | 0xffffffffull;
     // Equal distances are all listed, and where fewer than `rank` pass the test everything is.  A query that would list a good
-    // share of the codes so is left to the other scan at once; one in eight says so of the batch.
+    // share of the codes so is left to the other scan at once; one in eight says so of the batch.  It counts twice: from a
+    // sixteenth of the queries marked on (few_marked) the other scan goes through all codes for them anyhow (3000 queries x
+    // 200k codes of 1000 kinds, 128 bits, ht 48, a seventh marked: 1015 us where each counted once).
     const bool alone = have < rank || (uint32_t)rank + more > most_alone;
     if (tid == 0) {
         thr[q] = key;
         if (alone) redo[q] = 1u;
-        if ((q & 7) == 0 && checked == 0 && (uint32_t)rank + more > most_tied) __hip_atomic_fetch_add(unfit, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((q & 7) == 0 && (alone || (checked == 0 && (uint32_t)rank + more > most_tied)))
+            __hip_atomic_fetch_add(unfit, alone ? 2u : 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (checked == 0 || (q & 7) != 0) return;
+    if (checked == 0 || alone || (q & 7) != 0) return;
     // How many codes are as near, whether they pass the test or not: those are what the rounds will list.  Where the
     // numbering of the centroids says nothing about distance they are many times those that pass; a batch of which an
     // eighth is so (every eighth query is asked) is left to the other scan before anything is listed (bound_scan_kernel).
@@ -1600,7 +1603,7 @@ int launch_bound_search(const BoundSearch &b, MarkedQueries *marked, hipStream_t
     marked->scratch_bytes = l.total - l.raw;
     for (int64_t q = 0; q < b.nq; q += kBoundChunk) {
         const int nq = (int)std::min(kBoundChunk, b.nq - q);
-                int rc = PSC_EINVAL;
+        int rc = PSC_EINVAL;
         if (b.m == 8 && dp == 8) rc = run_bound<8, 8>(b, q, nq, l, plan, s);
         if (b.m == 8 && dp == 16) rc = run_bound<8, 16>(b, q, nq, l, plan, s);
         if (b.m == 8 && dp == 32) rc = run_bound<8, 32>(b, q, nq, l, plan, s);
