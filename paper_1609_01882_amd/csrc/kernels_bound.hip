@@ -741,8 +741,10 @@ __device__ __forceinline__ uint32_t kth_smallest(PSC_LDS SelectScratch &s, const
 
 // The sample, tested and scored; the key of the rank-th best distance bounds what follows.  One workgroup per query, four codes
 // to a thread and turn; codes that pass the test wait in a queue of their wave until there are 64.  Bound by the trip to L2 for
-// a turn's codes and by how many workgroups LDS lets run: with codes two turns ahead and a pool of 2048 keys (one turn and
-// 4096) 1000 queries x 15900 codes of 128 bits take 27 us, 86 before, 3000 x 13300 54 and 99.
+// a turn's codes and by how many workgroups run at a time, which LDS is to limit: with codes two turns ahead and a pool of 2048
+// keys (one turn and 4096) 1000 queries x 15900 codes of 128 bits take 27 us, 86 before, 3000 x 13300 54 and 99.  Left to
+// itself the compiler takes registers for four workgroups of 64-bit codes where LDS has room for seven: 1200 queries x 200k,
+// ht 28 36 us, 25 so.
 constexpr int kSampleRoom = 1024 + 4 * 64;  // keys of a turn: its codes and those that waited
 template <int M>
 struct SampleLds {
@@ -753,7 +755,7 @@ struct SampleLds {
     uint32_t count;
 };
 template <int M>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(M == 8 ? 7 : 4)))
 bound_sample_kernel(const uint8_t *__restrict__ codes, const uint8_t *__restrict__ qcodes, const float *__restrict__ luts,
                     int total, uint32_t bias, int rank, int checked, uint32_t most_near, uint32_t most_tied, uint32_t most_alone,
                     uint32_t *__restrict__ unfit, uint32_t *__restrict__ redo, uint64_t *__restrict__ thr)
