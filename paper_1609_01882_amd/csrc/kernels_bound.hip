@@ -1425,6 +1425,11 @@ bool sizes_fit(int m, int dsub, int64_t nq, int64_t n, int k)
 // 388 us, ht 21 327 / 464 and 489 / 393, ht 24 347 / 606 and 613 / 530; 128 bits ht 47 379 / 467 and 399 / 281, ht 48
 // 358 / 479 and 419 / 318, ht 50 377 / 526 and 510 / 419; 1000 x 1M 128 bits ht 46 307 / 402 and 329 / 256, ht 48 329 /
 // 419 and 364 / 298.
+// Filtered searches of 128-bit codes have a time of their own beside that of the others, whichever is longer, fitted to 292
+// (20 .. 5000 queries x 100k .. 3.2M, k = 10 .. 200, ht 48, 56, 60): on mixtures 0.45 of the time before in geometric mean,
+// more than 4 % slower in 2; on Gaussian vectors 0.66, more than 8 % slower in 62.  E.g. with / without, mixture and Gaussian:
+// 2500 x 100k, k = 200, ht 60 333 / 531 and 429 / 547 us, 5000 x 1.6M, k = 10, ht 48 1156 / 1497 and 1351 / 1258, both taken;
+// 1200 x 200k, k = 10, ht 48 184 / 207 and 239 / 161, 600 x 200k, k = 200, ht 48 178 / 130 and 415 / 122, neither.
 // Past the sizes of the fit: 4000 x 4M 64 bits ht 24 1.80 / 2.46 ms (Gaussian 2.37 / 2.28), 128 bits ht 48 2.03 / 3.20 (2.71
 // / 2.58), 10k x 10M 9.98 / 14.1 and 10.6 / 25.3; of 64-bit codes more than some 30M have too many at every distance:
 // 3000 x 100M 45.0 / 43.0 ms (ht 24), 206 / 203 (nothing filtered), given up in the rounds.
@@ -1434,13 +1439,11 @@ bool bound_search_pays(int m, int dsub, int64_t nq, int64_t n, int ht, int k, si
     if (!sizes_fit(m, dsub, nq, n, k)) return false;
     const double keep = ht >= 8 * m ? 1.0 : random_code_survival(8 * m, ht);
     if (keep < 0.002) return false;
-    const double padded = (double)((nq + 31) / 32 * 32), steps = m * padded_length(m, dsub) / 64;
-    const double bounds = 65.0 + 9.6 * std::log2((double)n / 1e5) + 0.042 * (double)nq * (1.0 + k / 100.0) +
-                          0.5 * steps * 9.75e-8 * padded * (double)n + 0.7 * m;
-    // (the estimates of filtered scans of 128 bits are a third too long: 600 queries x 300k, k = 10, ht 56 172 us for 138, where
-    //  the bounds take 138 of mixtures and 187 of Gaussian vectors; 3000 x 200k, k = 100, ht 48 622 for 481, and 359)
-    const double share = m == 16 && ht < 128 ? 0.7 : 0.9;
-    if (bounds >= share * (estimated_scan_time(m, nq, n, k, ht, ws_bytes) + 12.0)) return false;
+    const double padded = (double)((nq + 31) / 32 * 32), steps = m * padded_length(m, dsub) / 64, size = std::log2((double)n / 1e5);
+    double bounds = 65.0 + 9.6 * size + 0.042 * (double)nq * (1.0 + k / 100.0) + 0.5 * steps * 9.75e-8 * padded * (double)n + 0.7 * m;
+    if (m == 16 && ht < 128)
+        bounds = std::max(bounds, 65.0 + 11.5 * size + 0.14 * k + (0.058 + 2.2e-4 * k) * (double)nq + 0.5 * steps * 1.13e-7 * padded * (double)n);
+    if (bounds >= 0.9 * (estimated_scan_time(m, nq, n, k, ht, ws_bytes) + 12.0)) return false;
     *plan = plan_rounds(n, k, keep);
     return plan->rounds != 0;
 }

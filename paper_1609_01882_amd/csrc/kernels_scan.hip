@@ -2933,7 +2933,8 @@ struct ScanTimes {
     double pool = HUGE_VAL, tiled = 0.0;
     int64_t slices = 0;
 };
-static ScanTimes scan_times(int m, int64_t nq, int64_t n, int k, int ht, bool dense, bool mfma, bool preset, const ScanPlan &p)
+static ScanTimes scan_times(int m, int64_t nq, int64_t n, int k, int ht, bool dense, bool mfma, bool preset, const ScanPlan &p,
+                            double cached = 1e7)  // bytes a microsecond from the caches
 {
     ScanTimes times;
     // (a workgroup per query: past 4096 queries the tiles are ahead; past the caches every query reads
@@ -2948,7 +2949,7 @@ static ScanTimes scan_times(int m, int64_t nq, int64_t n, int k, int ht, bool de
     const ScanCosts &c = kCosts[dense ? 1 : 0][m == 8 ? 0 : 1];
     const double in_cluster = 0.01 * std::pow((double)ht / (3 * m), 6);
     const double keep = ht >= 8 * m ? 1.0 : std::min(1.0, random_code_survival(8 * m, ht) + in_cluster);
-    const double memory = (double)nq * bytes / (bytes < 128e6 ? 1e7 : 5.8e6);
+    const double memory = (double)nq * bytes / (bytes < 128e6 ? cached : 5.8e6);
     // the slices: a merge against the codes of a workgroup (the plain estimate the fit's slices were chosen by)
     const double kilo = dense ? (m == 8 ? 0.37 : 0.72) : 0.13;
     double best = 1e300;
@@ -3039,7 +3040,11 @@ double estimated_scan_time(int m, int64_t nq, int64_t n, int k, int ht, size_t w
     ScanRoute r;
     if (scan_route(m, nq, n, k, ht, ws_bytes, &r) != PSC_OK) return 0.0;
     const ScanTimes t = scan_times(m, nq, n, k, ht, r.dense, r.mfma, true, r.plan);
-    return t.pool > 0.95 * t.tiled ? t.tiled : t.pool;
+    if (t.pool > 0.95 * t.tiled) return t.tiled;
+    // (two workgroups a compute unit, the caches give the filtered scan of 128-bit codes more than the route's estimate has
+    //  them give: 600 queries x 200k, k = 200, ht 48 192 us by that and 130 in fact, 1200 x 400k 768 and 407)
+    if (m == 16 && !r.dense && nq >= 512) return scan_times(m, nq, n, k, ht, r.dense, r.mfma, true, r.plan, 1.8e7).pool;
+    return t.pool;
 }
 
 int launch_scan(int m, const float *lut_dev, const uint8_t *qcodes_dev, int64_t nq,
