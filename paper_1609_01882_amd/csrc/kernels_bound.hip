@@ -39,7 +39,12 @@ namespace {
 constexpr int kBlock = 128;          // codes of a block: four turns of a wave
 constexpr int kLambdas = 8;
 __device__ const float kLambda[kLambdas] = {1.0f, 1.04f, 1.1f, 1.18f, 1.35f, 1.7f, 2.5f, 5.0f};
-constexpr int kNear = 12288;         // places per query, on the average of a tile, for the codes that pass its bound in a round
+// Places per query, on the average of a tile, for the codes that pass its bound in a round (two words each: 485 MiB from 5120
+// queries on).  Mixtures take as long with 6144 or 24576 (777 x 1M 0.999 and 0.999 of the time, 10k x 10M 1.02 and 0.99, runs
+// differing by as much).  Gaussian vectors in 128-bit codes, 20 .. 5000 queries x 100k .. 3.2M: with 6144 more are given up
+// that need not be, 0.78 of the time without bounds in geometric mean, 0.755 so.  With 24576 batches go on that are given up
+// later: 4000 x 4M 64-bit codes of 1000 kinds, ht 24 7450 us, 3070 so, random ones 3430 and 2400 (but 1000 x 1M 543, 1128 so).
+constexpr int kNear = 12288;
 constexpr int kRun = 8;              // rows a thread of bound_rank_kernel takes of a run at a time
 constexpr int kMaxItems = 4096;      // work items (tile, slice) of a round
 constexpr int kBoundPool = 2048;     // those of them that are tested and nearer than thr
@@ -1188,7 +1193,7 @@ struct BoundLayout {
     size_t marks, unfit, qimg, qscale, s, thr, sample, raw, near, first, total;
 };
 // How many marked queries are few: scanned by themselves these take less than the tiles that have one (up to 16 queries and
-// the whole database each).
+// the whole database each: at a sixteenth, two tiles of three).
 int few_marked(int64_t nq) { return (int)std::min<int64_t>((nq + 15) / 16, 1024); }
 BoundLayout bound_layout(int m, int dsub, int64_t nq_all)
 {
