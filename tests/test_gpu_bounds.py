@@ -289,3 +289,21 @@ def test_lists_that_run_over_in_the_first_of_several_rounds(trained, force_route
     (route, ids, d), (other, want_ids, want_d) = _both(psc, idx, q, c, 8 * m, 10)
     assert route == "bound_scan_kernel" and other != route, (route, other)
     assert torch.equal(ids, want_ids) and torch.equal(d, want_d)
+
+
+@pytest.mark.parametrize("m,ht,kinds", [(16, 48, 1000), (16, 50, 400), (8, 22, 300)])
+def test_batches_of_which_a_part_is_marked_at_the_sample(trained, m, ht, kinds):
+    """Codes of few kinds under a strict threshold: the sample finds no bound for a part of the queries, more than are
+    answered by themselves and fewer than most; the batch is given up or not, the results are those of the scan."""
+    import paper_1609_01882_amd as psc
+    idx, codes = trained(128, m)
+    n, nq, k = 200_003, 3000, 100
+    c = codes[:kinds].repeat((n + kinds - 1) // kinds, 1)[:n].contiguous()
+    q = _mixture(nq, 128, 15)[0]
+    print(f"m={m} ht={ht} kinds={kinds}", flush=True)
+    ids, d = idx.search(q, c, ht, k)
+    assert psc.last_scan_route().startswith("bound_scan_kernel ")
+    lut, qc = idx.build_lut(q)
+    want_ids, want_d = psc.scan(lut, qc, c, ht, k)
+    torch.cuda.synchronize()
+    assert torch.equal(ids, want_ids) and torch.equal(d.view(torch.int32), want_d.view(torch.int32))
